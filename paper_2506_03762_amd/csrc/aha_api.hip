@@ -329,8 +329,9 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     g.rows = rows;
     hipStream_t st = (hipStream_t)stream;
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
-    // the windowed bf16 scores form the value prior inside their row-statistics launch
-    const bool fold_prior = pl.can_fold && p->value_prior && !with_lse && !rows;
+    // the windowed bf16 scores and the fp32 scores form the value prior inside their
+    // row-statistics launch
+    const bool fold_prior = p->value_prior && !with_lse && (p->dtype == AHA_F32 || (pl.can_fold && !rows));
     if ((rc = hip_result(launch_value_prior(g, pl, workspace, scores, lse,
                                             p->value_prior && !fold_prior, st),
                          "value-prior kernel")))

@@ -66,8 +66,8 @@ constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)
 // `lse`, when not null, holds the caller's natural-log row normalisers
 // [batch, Hq, window]; the launch then also writes them, in the log2 domain, where pass 2
 // expects the row statistics (and the score launchers skip pass 1).
-// `prior_here`: this launch forms the value prior (the windowed bf16 scores form it inside
-// their row-statistics launch instead).  Launches nothing when there is nothing to do.
+// `prior_here`: this launch forms the value prior (the windowed bf16 scores and the fp32 scores
+// form it inside their row-statistics launch instead).  Launches nothing when there is nothing to do.
 hipError_t launch_value_prior(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
                               float *scores, const float *lse, bool prior_here, hipStream_t st);
 // score_f32.hip

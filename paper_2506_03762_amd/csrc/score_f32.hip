@@ -2,12 +2,22 @@
 // kernels.  This is the small-problem, high-accuracy path (fp32 Q/K/V); the
 // bf16 path in score_bf16.hip carries the throughput.
 //
-// Pass 1: one workgroup per observed query row finds max_j and log2-sum-exp2
-//         of t_ij = s_i * log2(e) * (Q_i . K_j) over j <= i.
-// Pass 2: one thread per key keeps its K row in registers and sums
-//         exp2(t_ij - L_i) over the observed rows i >= j.
-#include "aha_dev.h"
-#include "aha_host.h"
+// Pass 1: a workgroup finds max_j and log2-sum-exp2 of t_ij = s_i * log2(e) * (Q_i . K_j) over
+//         j <= i for one or four observed query rows; extra workgroups of the same launch form
+//         the value prior.
+// Pass 2: a workgroup sums exp2(t_ij - L_i) over the observed rows i >= j for its 16 or 64 keys,
+//         the rows dealt to its four waves.
+//
+// In both passes FOUR lanes share a dot product: lane p of a quad holds the 16-byte chunks
+// p, p + 4, ... of its key rows (a quad reads 64 contiguous bytes at a time, and a row takes a
+// quarter of the registers of one thread), and two exchanges inside the quad sum the parts.  Four
+// products of a quad then leave one exponential per lane: four rows of one key in pass 1, four
+// keys of one row in pass 2.  The small variants (one row, 16 keys per workgroup) leave that
+// factor unused for four times as many workgroups: the path's own problem (2 heads x 512 keys x
+// 32 rows, head_dim 64) is bound by latency, and one thread per key gave it four workgroups that
+// each walked all rows.  Measured there: pass 2 25.5 -> 5.5 us, pass 1 and the prior (two
+// launches, 7.2 + 4.5 us) -> 5.6 us.
+#include "value_tile.h"
 
 namespace aha {
 
@@ -20,178 +30,259 @@ __device__ __forceinline__ void reref_stat(float m, float M, float &s, float &u)
     u = (u + (m - M) * s) * f;
     s *= f;
 }
+// the statistic of the union of two key sets
+__device__ __forceinline__ void merge_stat(float &m, float &s, float &u, float m2, float s2,
+                                           float u2) {
+    const float M = fmaxf(m, m2);
+    reref_stat(m, M, s, u);
+    reref_stat(m2, M, s2, u2);
+    m = M;
+    s += s2;
+    u += u2;
+}
 
+// Sum over the four lanes of a quad.
+__device__ __forceinline__ float quad_sum(float x) { return reduce_lanes<1, 4>(x, OpSum{}); }
+// x[part] without a dynamically indexed register file.
+__device__ __forceinline__ float pick4(const float (&x)[4], int part) {
+    const float a = part & 1 ? x[1] : x[0], b = part & 1 ? x[3] : x[2];
+    return part & 2 ? b : a;
+}
+
+// A lane's share of a row: chunks part, part + 4, ... of 16 bytes.
+template <int D>
+struct QuadRow {
+    f32x4 c[D / 16];
+    __device__ __forceinline__ void load(const float *row, int part) {
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) c[t] = *(const f32x4 *)(row + 4 * (part + 4 * t));
+    }
+    __device__ __forceinline__ float dot(const QuadRow &o) const {  // this lane's part
+        float w[2] = {0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[t & 1] = fmaf(c[t][e], o.c[t][e], w[t & 1]);
+        return w[0] + w[1];
+    }
+};
+
+// RQ observed rows (1 or 4) per workgroup; workgroups past the row blocks take the value tiles.
 // `lse_out` / `ent_out` (either may be null): natural-log normaliser and entropy of every
 // observed row, dense [batch, Hq, window].
-template <int D>
-__global__ __launch_bounds__(256) void f32_pass1_kernel(ScoreGeom g, float *rowL, float *lse_out,
-                                                        float *ent_out) {
-    const int z = blockIdx.y, rho = blockIdx.x, tid = threadIdx.x;
+template <int D, int RQ>
+__global__ __launch_bounds__(256) void f32_pass1_kernel(ScoreGeom g, int row_blocks, int n_vtiles,
+                                                        float *gamma, float *gblockmax, float *rowL,
+                                                        float *lse_out, float *ent_out) {
+    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if ((int)blockIdx.x >= row_blocks) {  // (workgroup-uniform)
+        value_prior_tile<4>(g, z, (int)blockIdx.x - row_blocks, n_vtiles, gamma, gblockmax, tid);
+        return;
+    }
     const int b = z / g.Hkv, h = z % g.Hkv;
+    const int rho0 = blockIdx.x * RQ, part = tid & 3, kk = tid >> 2;
     const RowMap rm{g.n, g.r, g.R,
                     g.rows ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
-    const int i = rm.pos(rho);
-    const int hq = h * g.G + rm.head(rho);
-    const float *qrow = (const float *)g.q + b * g.qs[0] + hq * g.qs[1] + (int64_t)i * g.qs[2];
     const float *kbase = (const float *)g.k + b * g.ks[0] + h * g.ks[1];
+    __shared__ float s_m[4][RQ], s_s[4][RQ], s_u[4][RQ];
 
-    __shared__ float s_q[D];
-    __shared__ float s_m[4], s_s[4], s_u[4];
-    if (tid < D) s_q[tid] = qrow[tid];
-    __syncthreads();
-    const float lam = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, i + 1,
+    // (rows past the last one stand for the last; their results are dropped)
+    QuadRow<D> q[RQ];
+    int last = 0;  // the largest position of the rows
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) {
+        const int rho = min(rho0 + r, g.R - 1), i = rm.pos(rho);
+        last = max(last, i);
+        q[r].load((const float *)g.q + b * g.qs[0] + (int64_t)(h * g.G + rm.head(rho)) * g.qs[1] +
+                      (int64_t)i * g.qs[2], part);
+    }
+    // the row whose statistic this lane keeps
+    const int my_rho = min(rho0 + (RQ == 4 ? part : 0), g.R - 1), my_i = rm.pos(my_rho);
+    const float lam = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, my_i + 1,
                                      g.budget, g.d);
 
     float m = -INFINITY, s = 0.f, u = 0.f;
-    for (int j = tid; j <= i; j += 256) {
-        const float4 *kr = (const float4 *)(kbase + (int64_t)j * g.ks[2]);
-        float w = 0.f;
-#pragma unroll 8
-        for (int c = 0; c < D / 4; ++c) {
-            const float4 kv = kr[c];
-            w = fmaf(s_q[4 * c + 0], kv.x, w);
-            w = fmaf(s_q[4 * c + 1], kv.y, w);
-            w = fmaf(s_q[4 * c + 2], kv.z, w);
-            w = fmaf(s_q[4 * c + 3], kv.w, w);
+    constexpr int U = RQ == 4 || D == 128 ? 2 : 4;  // keys per quad requested together
+    for (int j0 = 0; j0 <= last; j0 += 64 * U) {
+        QuadRow<D> k[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+            k[t].load(kbase + (int64_t)min(j0 + t * 64 + kk, last) * g.ks[2], part);
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            float w[RQ];
+#pragma unroll
+            for (int r = 0; r < RQ; ++r) w[r] = quad_sum(q[r].dot(k[t]));
+            float x;
+            if constexpr (RQ == 4) x = pick4(w, part);
+            else x = w[0];
+            // (no branch around the quad's exchanges: its lanes may keep rows that end apart)
+            const bool sees = j0 + t * 64 + kk <= my_i;
+            const float tt = x * lam, mn = sees ? fmaxf(m, tt) : m, dt = sees ? tt - mn : 0.f;
+            reref_stat(m, mn, s, u);
+            const float e = sees ? exp2f(dt) : 0.f;
+            s += e;
+            u = fmaf(e, dt, u);
+            m = mn;
         }
-        const float t = w * lam;
-        const float mn = fmaxf(m, t);
-        reref_stat(m, mn, s, u);
-        const float e = exp2f(t - mn);
-        s += e;
-        u = fmaf(e, t - mn, u);
-        m = mn;
     }
-    // combine the per-thread statistics
-    const float wm = wave_max(m);
-    reref_stat(m, wm, s, u);
-    const float ws = wave_sum(s), wu = wave_sum(u);
-    if ((tid & 63) == 0) { s_m[tid >> 6] = wm; s_s[tid >> 6] = ws; s_u[tid >> 6] = wu; }
+    // over the keys of the wave (lanes with the same part), then over the waves
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1)
+        merge_stat(m, s, u, __shfl_xor(m, o), __shfl_xor(s, o), __shfl_xor(u, o));
+    if (lane < RQ) { s_m[wave][lane] = m; s_s[wave][lane] = s; s_u[wave][lane] = u; }
     __syncthreads();
-    if (tid == 0) {
-        const float M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
-        float S = 0.f, U = 0.f;
-        for (int t = 0; t < 4; ++t) {
-            float st = s_s[t], ut = s_u[t];
-            reref_stat(s_m[t], M, st, ut);
-            S += st;
-            U += ut;
-        }
-        const float L = M + log2f(S);
+    const int rho = rho0 + tid;
+    if (tid < RQ && rho < g.R) {
+        m = s_m[0][tid]; s = s_s[0][tid]; u = s_u[0][tid];
+#pragma unroll
+        for (int t = 1; t < 4; ++t) merge_stat(m, s, u, s_m[t][tid], s_s[t][tid], s_u[t][tid]);
+        const float L = m + log2f(s);
         rowL[(int64_t)z * g.R + rho] = L;
-        const int64_t o = ((int64_t)b * g.Hq + hq) * g.r + (rho % g.r);
+        const int64_t o = ((int64_t)b * g.Hq + h * g.G + rm.head(rho)) * g.r + (rho % g.r);
         const float kLn2 = 0.69314718055994531f;
         if (lse_out) lse_out[o] = L * kLn2;
-        if (ent_out) ent_out[o] = fmaxf(0.f, (log2f(S) - U / S) * kLn2);
+        if (ent_out) ent_out[o] = fmaxf(0.f, (log2f(s) - u / s) * kLn2);
     }
 }
 
-constexpr int kF32QRows = 16;  // query rows staged in LDS per step of pass 2
+constexpr int kF32QRows = 64;  // query rows staged in LDS per step of pass 2
 
-template <int D>
+// KPL keys (1 or 4) per quad: 16 KPL keys per workgroup.
+template <int D, int KPL>
 __global__ __launch_bounds__(256) void f32_pass2_kernel(ScoreGeom g, const float *rowL,
                                                         const float *gamma,
                                                         const float *gblockmax, int n_vtiles,
                                                         float *scores) {
-    const int z = blockIdx.y, tid = threadIdx.x;
+    constexpr int KEYS = 16 * KPL;
+    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int part = lane & 3, kk = lane >> 2;
     const int b = z / g.Hkv, h = z % g.Hkv;
-    const int j = blockIdx.x * 256 + tid;
     const RowMap rm{g.n, g.r, g.R,
                     g.rows ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
     const float *kbase = (const float *)g.k + b * g.ks[0] + h * g.ks[1];
 
-    __shared__ float s_q[kF32QRows][D];
-    __shared__ float s_lam[kF32QRows], s_L[kF32QRows];
+    __shared__ __attribute__((aligned(16))) float s_q[kF32QRows][D];
+    __shared__ float s_lam[kF32QRows], s_L[kF32QRows], s_acc[4][KEYS];
     __shared__ int s_pos[kF32QRows];
 
-    float kreg[D];
-    {
-        const int jj = j < g.n ? j : g.n - 1;
-        const float4 *kr = (const float4 *)(kbase + (int64_t)jj * g.ks[2]);
+    const int j_lo = blockIdx.x * KEYS;        // smallest key of this workgroup
+    const int j = j_lo + kk * KPL + (KPL == 4 ? part : 0);  // the key whose sum this lane keeps
+    QuadRow<D> k[KPL];
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-            const float4 kv = kr[c];
-            kreg[4 * c] = kv.x; kreg[4 * c + 1] = kv.y; kreg[4 * c + 2] = kv.z; kreg[4 * c + 3] = kv.w;
-        }
+    for (int t = 0; t < KPL; ++t)
+        k[t].load(kbase + (int64_t)min(j_lo + kk * KPL + t, g.n - 1) * g.ks[2], part);
+    // the prior of this workgroup's keys and the tiles' maxima travel with the keys
+    float gm = 0.f, gam = 1.f;
+    if (g.value_prior) {
+        for (int t = lane; t < n_vtiles; t += 64) gm = fmaxf(gm, gblockmax[z * n_vtiles + t]);
+        gam = gamma[(int64_t)z * g.n + min(j_lo + tid % KEYS, g.n - 1)];
     }
-    const int j_lo = blockIdx.x * 256;  // smallest key of this workgroup
+
     float acc = 0.f;
     for (int r0 = 0; r0 < g.R; r0 += kF32QRows) {
         // rows of this step; skip steps whose rows all lie before the block's keys
         if (rm.max_pos(r0, r0 + kF32QRows) < j_lo) continue;
+        const int rows = min(kF32QRows, g.R - r0);
         __syncthreads();
-        for (int t = tid; t < kF32QRows * D; t += 256) {
-            const int rr = t / D, c = t % D, rho = r0 + rr;
-            float qv = 0.f;
-            if (rho < g.R) {
-                const int hq = h * g.G + rm.head(rho);
-                qv = ((const float *)g.q)[b * g.qs[0] + hq * g.qs[1] +
-                                           (int64_t)rm.pos(rho) * g.qs[2] + c];
-            }
-            s_q[rr][c] = qv;
+        for (int t = tid; t < rows * (D / 4); t += 256) {
+            const int rr = t / (D / 4), c = t % (D / 4), rho = r0 + rr;
+            *(f32x4 *)&s_q[rr][4 * c] =
+                *(const f32x4 *)((const float *)g.q + b * g.qs[0] +
+                                 (int64_t)(h * g.G + rm.head(rho)) * g.qs[1] +
+                                 (int64_t)rm.pos(rho) * g.qs[2] + 4 * c);
         }
-        if (tid < kF32QRows) {
-            const int rho = r0 + tid;
-            const int i = rm.pos(rho);
+        if (tid < rows) {
+            const int rho = r0 + tid, i = rm.pos(rho);
             s_pos[tid] = i;
-            s_lam[tid] = rho < g.R ? row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor,
-                                                   i + 1, g.budget, g.d)
-                                  : 0.f;
-            s_L[tid] = rho < g.R ? rowL[(int64_t)z * g.R + rho] : INFINITY;
+            s_lam[tid] = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, i + 1,
+                                        g.budget, g.d);
+            s_L[tid] = rowL[(int64_t)z * g.R + rho];
         }
         __syncthreads();
-        for (int rr = 0; rr < kF32QRows; ++rr) {
-            float w = 0.f;
+#pragma unroll 2
+        for (int rr = wave; rr < rows; rr += 4) {
+            QuadRow<D> q;
+            q.load(s_q[rr], part);
+            float w[KPL];
 #pragma unroll
-            for (int c = 0; c < D; ++c) w = fmaf(s_q[rr][c], kreg[c], w);
-            const float p = exp2f(fmaf(w, s_lam[rr], -s_L[rr]));
+            for (int t = 0; t < KPL; ++t) w[t] = quad_sum(q.dot(k[t]));
+            float x;
+            if constexpr (KPL == 4) x = pick4(w, part);
+            else x = w[0];
+            const float p = exp2f(fmaf(x, s_lam[rr], -s_L[rr]));
             acc += (j <= s_pos[rr]) ? p : 0.f;
         }
     }
-    if (j < g.n) {
-        float out = acc;
+    // over the waves; one thread per key writes
+    if (KPL == 4) s_acc[wave][lane % KEYS] = acc;
+    else if (part == 0) s_acc[wave][kk % KEYS] = acc;
+    __syncthreads();
+    gm = wave_max(gm);  // (every lane takes part)
+    if (tid < KEYS && j_lo + tid < g.n) {
+        float out = (s_acc[0][tid] + s_acc[1][tid]) + (s_acc[2][tid] + s_acc[3][tid]);
         if (g.value_prior) {
-            float gm = 0.f;
-            for (int t = 0; t < n_vtiles; ++t) gm = fmaxf(gm, gblockmax[z * n_vtiles + t]);
-            out = gm > 0.f ? acc * (gamma[(int64_t)z * g.n + j] / gm) : acc;  // all-zero values: no prior
+            out = gm > 0.f ? out * (gam / gm) : out;  // all-zero values: no prior
         }
-        scores[(int64_t)z * g.n + j] = out;
+        scores[(int64_t)z * g.n + j_lo + tid] = out;
     }
+}
+
+// Four rows / keys per quad once the small variants would put more than about eight workgroups
+// on every CU: from there the vector ALU bounds the passes and the spare factor four counts.
+constexpr int64_t kF32ManyWgs = 2048;
+
+template <int D>
+static void launch_pass1(const ScoreGeom &g, const PrefillPlan &pl, void *ws, bool prior, float *lse,
+                         float *entropy, hipStream_t st) {
+    char *w = (char *)ws;
+    float *gamma = (float *)(w + pl.off_gamma), *gbm = (float *)(w + pl.off_gblockmax);
+    float *rowL = (float *)(w + pl.off_rowL);
+    const int vt = prior ? pl.n_vtiles : 0;
+    if ((int64_t)g.R * pl.Z >= kF32ManyWgs) {
+        const int rb = (g.R + 3) / 4;
+        hipLaunchKernelGGL((f32_pass1_kernel<D, 4>), dim3(rb + vt, pl.Z), dim3(256), 0, st, g, rb,
+                           pl.n_vtiles, gamma, gbm, rowL, lse, entropy);
+    } else {
+        hipLaunchKernelGGL((f32_pass1_kernel<D, 1>), dim3(g.R + vt, pl.Z), dim3(256), 0, st, g, g.R,
+                           pl.n_vtiles, gamma, gbm, rowL, lse, entropy);
+    }
+}
+
+template <int D>
+static void launch_pass2(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores,
+                         hipStream_t st) {
+    char *w = (char *)ws;
+    const float *rowL = (float *)(w + pl.off_rowL);
+    const float *gamma = (const float *)(w + pl.off_gamma);
+    const float *gbm = (const float *)(w + pl.off_gblockmax);
+    if ((int64_t)((g.n + 15) / 16) * pl.Z >= kF32ManyWgs)
+        hipLaunchKernelGGL((f32_pass2_kernel<D, 4>), dim3((g.n + 63) / 64, pl.Z), dim3(256), 0, st,
+                           g, rowL, gamma, gbm, pl.n_vtiles, scores);
+    else
+        hipLaunchKernelGGL((f32_pass2_kernel<D, 1>), dim3((g.n + 15) / 16, pl.Z), dim3(256), 0, st,
+                           g, rowL, gamma, gbm, pl.n_vtiles, scores);
 }
 
 hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores,
                             hipStream_t st, hipEvent_t mid, bool have_lse) {
-    char *w = (char *)ws;
-    float *rowL = (float *)(w + pl.off_rowL);
-    const float *gamma = (const float *)(w + pl.off_gamma);
-    const float *gbm = (const float *)(w + pl.off_gblockmax);
-    dim3 g1(g.R, pl.Z), g2((g.n + 255) / 256, pl.Z);
-    if (g.d == 64) {
-        if (!have_lse)
-            hipLaunchKernelGGL(f32_pass1_kernel<64>, g1, dim3(256), 0, st, g, rowL, (float *)nullptr,
-                               (float *)nullptr);
-        if (mid) (void)hipEventRecord(mid, st);
-        hipLaunchKernelGGL(f32_pass2_kernel<64>, g2, dim3(256), 0, st, g, rowL, gamma, gbm,
-                           pl.n_vtiles, scores);
-    } else {
-        if (!have_lse)
-            hipLaunchKernelGGL(f32_pass1_kernel<128>, g1, dim3(256), 0, st, g, rowL, (float *)nullptr,
-                               (float *)nullptr);
-        if (mid) (void)hipEventRecord(mid, st);
-        hipLaunchKernelGGL(f32_pass2_kernel<128>, g2, dim3(256), 0, st, g, rowL, gamma, gbm,
-                           pl.n_vtiles, scores);
+    // (with the caller's row normalisers the prior comes from launch_value_prior)
+    if (!have_lse) {
+        if (g.d == 64) launch_pass1<64>(g, pl, ws, g.value_prior, nullptr, nullptr, st);
+        else launch_pass1<128>(g, pl, ws, g.value_prior, nullptr, nullptr, st);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
+    if (mid) (void)hipEventRecord(mid, st);
+    if (g.d == 64) launch_pass2<64>(g, pl, ws, scores, st);
+    else launch_pass2<128>(g, pl, ws, scores, st);
     return hipGetLastError();
 }
 
 hipError_t launch_row_stats_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *lse,
                                 float *entropy, hipStream_t st) {
-    float *rowL = (float *)((char *)ws + pl.off_rowL);
-    dim3 g1(g.R, pl.Z);
-    if (g.d == 64)
-        hipLaunchKernelGGL(f32_pass1_kernel<64>, g1, dim3(256), 0, st, g, rowL, lse, entropy);
-    else
-        hipLaunchKernelGGL(f32_pass1_kernel<128>, g1, dim3(256), 0, st, g, rowL, lse, entropy);
+    if (g.d == 64) launch_pass1<64>(g, pl, ws, false, lse, entropy, st);
+    else launch_pass1<128>(g, pl, ws, false, lse, entropy, st);
     return hipGetLastError();
 }
 

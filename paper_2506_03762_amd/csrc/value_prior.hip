@@ -4,11 +4,10 @@
 //
 // HBM-bound: V is read exactly once (plus (pool-1)/2 halo rows per tile).
 // The windowed bf16 scores form the prior inside their row-statistics launch
-// (score_bf16.hip) and do not use this kernel; it serves the fp32 path, full
-// accumulation (where it also zeroes the scores) and the entry point that is
-// handed the rows' normalisers (which it converts for the column-sum pass).
-#include "aha_dev.h"
-#include "aha_host.h"
+// (score_bf16.hip), fp32 inputs as extra workgroups of theirs (score_f32.hip); this
+// kernel serves full accumulation (where it also zeroes the scores) and the entry point that
+// is handed the rows' normalisers (which it converts for the column-sum pass).
+#include "value_tile.h"
 
 namespace aha {
 
@@ -39,33 +38,7 @@ __global__ __launch_bounds__(256) void vprior_kernel(ScoreGeom g, int n_vtiles, 
         if (j < g.n) zero_scores[(int64_t)z * g.n + j] = 0.f;
     }
     if (!g.value_prior || tile >= n_vtiles) return;
-
-    __shared__ float s_nu[kVTileRows + 256];
-    __shared__ float s_max[4];
-    const int b = z / g.Hkv, h = z % g.Hkv;
-    const char *vbase =
-        (const char *)g.v + (int64_t)ESIZE * (b * g.vs[0] + h * g.vs[1]);
-    const int half = (g.pool - 1) / 2;
-    const int t0 = tile * kVTileRows;
-    const int lo = max(0, t0 - half);
-    const int hi = min(g.n, t0 + kVTileRows + half);  // exclusive
-    value_norms_to_lds<ESIZE>(vbase, g.vs[2], g.d, lo, hi, s_nu, tid);
-    __syncthreads();
-
-    const int j = t0 + tid;
-    float gam = 0.f;
-    if (j < g.n) {
-        const int a = max(0, j - half), e = min(g.n - 1, j + half);
-        float s = 0.f;
-        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
-        gam = s / (float)(e - a + 1);
-        gamma[(int64_t)z * g.n + j] = gam;
-    }
-    float m = wave_max(gam);
-    if ((tid & 63) == 0) s_max[tid >> 6] = m;
-    __syncthreads();
-    if (tid == 0)
-        gblockmax[z * n_vtiles + tile] = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    value_prior_tile<ESIZE>(g, z, tile, n_vtiles, gamma, gblockmax, tid);
 }
 
 hipError_t launch_value_prior(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
