@@ -126,16 +126,25 @@ class Params:
     sink: int = 0
     decode_value_prior: int = 0
 
+    def __setattr__(self, name, value):
+        # (strides are kept as tuples: every change of a field then comes through here and drops
+        # the C struct built from the old values)
+        self.__dict__[name] = tuple(value) if name.endswith("_stride") else value
+        self.__dict__.pop("_c", None)
+
+    def __getstate__(self):  # copies and pickles build their own struct
+        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+
     def c(self) -> aha_params:
-        """The C struct (built once per distinct set of field values: calls in a loop reuse it)."""
-        key = (self.batch, self.n_q_heads, self.n_kv_heads, self.head_dim, self.seq_len,
-               self.window, self.budget, self.recent, self.dtype, self.scale_mode,
-               self.fixed_scale, self.lambda_floor, self.value_prior, self.pool_kernel,
-               tuple(self.q_stride), tuple(self.k_stride), tuple(self.v_stride), self.score_pool,
-               self.sink, self.decode_value_prior)
+        """The C struct of these values (a copy: callers may edit theirs)."""
+        return aha_params.from_buffer_copy(self._struct()[0])
+
+    def _struct(self):
+        """(C struct, pointer to it), built once and kept until a field changes: a call in a loop
+        only passes the pointer."""
         cached = self.__dict__.get("_c")
-        if cached is not None and cached[0] == key:
-            return aha_params.from_buffer_copy(cached[1])   # a copy: callers may edit theirs
+        if cached is not None:
+            return cached
         p = aha_params()
         for f in ("batch", "n_q_heads", "n_kv_heads", "head_dim", "seq_len", "window", "budget",
                   "recent", "dtype", "scale_mode", "value_prior", "pool_kernel", "score_pool",
@@ -146,8 +155,8 @@ class Params:
         p.q_stride = (ctypes.c_int64 * 3)(*self.q_stride)
         p.k_stride = (ctypes.c_int64 * 3)(*self.k_stride)
         p.v_stride = (ctypes.c_int64 * 3)(*self.v_stride)
-        self.__dict__["_c"] = (key, bytes(p))
-        return p
+        self.__dict__["_c"] = cached = (p, ctypes.byref(p))
+        return cached
 
     def with_strides(self, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor) -> "Params":
         """Strides (batch, head, token) of [b, h, n, d] views; the d axis must be contiguous."""
@@ -158,12 +167,19 @@ class Params:
                        v_stride=tuple(v.stride()[:3]))
 
 
+# Addresses go to ctypes as plain integers (the argument types convert them): with a c_void_p
+# object per tensor, a torch.cuda.Stream and a copy of the parameter struct per call, a generation
+# step took 8.5 us of host time to enqueue, 5.1 us without them, a prefill step's calls 25 and 15.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _ws(t: Optional[torch.Tensor]):
+    return (None, 0) if t is None else (t.data_ptr(), t.numel())
 
 
 def torch_dtype(dtype: int):
@@ -172,7 +188,7 @@ def torch_dtype(dtype: int):
 
 def workspace_bytes(p: Params) -> int:
     out = ctypes.c_size_t(0)
-    _check(load().aha_workspace_bytes(ctypes.byref(p.c()), ctypes.byref(out)))
+    _check(load().aha_workspace_bytes(p._struct()[1], ctypes.byref(out)))
     return out.value
 
 
@@ -182,90 +198,74 @@ def alloc_workspace(p: Params, device="cuda") -> torch.Tensor:
 
 def aha_prefill_scores(p: Params, q, k, v, scores, workspace):
     """scores[b, Hkv, n] (fp32) <- refined eviction scores of q, k, v ([b, h, n, d] views)."""
-    cp = p.c()
-    _check(load().aha_prefill_scores(ctypes.byref(cp), _ptr(q), _ptr(k), _ptr(v), _ptr(scores),
-                                     _ptr(workspace), workspace.numel() if workspace is not None else 0,
-                                     _stream()))
+    _check((_lib or load()).aha_prefill_scores(
+        p._struct()[1], _ptr(q), _ptr(k), _ptr(v), _ptr(scores), *_ws(workspace), _stream()))
 
 
 def aha_prefill_scores_lse(p: Params, q, k, v, lse, scores, workspace):
     """As aha_prefill_scores, with the rows' natural-log softmax denominators lse[b, Hq, window]
     (fp32) given, e.g. by the attention forward pass: the row-statistics pass is skipped."""
-    cp = p.c()
-    _check(load().aha_prefill_scores_lse(ctypes.byref(cp), _ptr(q), _ptr(k), _ptr(v), _ptr(lse),
-                                         _ptr(scores), _ptr(workspace),
-                                         workspace.numel() if workspace is not None else 0,
-                                         _stream()))
+    _check((_lib or load()).aha_prefill_scores_lse(
+        p._struct()[1], _ptr(q), _ptr(k), _ptr(v), _ptr(lse), _ptr(scores), *_ws(workspace),
+        _stream()))
 
 
 def aha_prefill_scores_rows(p: Params, q, k, v, rows, scores, workspace):
     """As aha_prefill_scores, accumulated over the query rows at positions rows[b, Hq, window]
     (int32) instead of the most recent ones."""
-    cp = p.c()
-    _check(load().aha_prefill_scores_rows(ctypes.byref(cp), _ptr(q), _ptr(k), _ptr(v), _ptr(rows),
-                                          _ptr(scores), _ptr(workspace),
-                                          workspace.numel() if workspace is not None else 0,
-                                          _stream()))
+    _check((_lib or load()).aha_prefill_scores_rows(
+        p._struct()[1], _ptr(q), _ptr(k), _ptr(v), _ptr(rows), _ptr(scores), *_ws(workspace),
+        _stream()))
 
 
 def window_attention_workspace_bytes(p: Params) -> int:
     out = ctypes.c_size_t(0)
-    _check(load().aha_window_attention_workspace_bytes(ctypes.byref(p.c()), ctypes.byref(out)))
+    _check(load().aha_window_attention_workspace_bytes(p._struct()[1], ctypes.byref(out)))
     return out.value
 
 
 def aha_prefill_window_attention(p: Params, q, k, v, out, lse, workspace):
     """out [b, Hq, window, d] <- causal attention output (standard scale) of the observed rows;
     lse [b, Hq, window] fp32 (or None) <- their natural-log softmax denominators."""
-    cp = p.c()
-    _check(load().aha_prefill_window_attention(ctypes.byref(cp), _ptr(q), _ptr(k), _ptr(v),
-                                               _ptr(out), _ptr(lse), _ptr(workspace),
-                                               workspace.numel() if workspace is not None else 0,
-                                               _stream()))
+    _check((_lib or load()).aha_prefill_window_attention(
+        p._struct()[1], _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), *_ws(workspace),
+        _stream()))
 
 
 def aha_prefill_row_stats(p: Params, q, k, lse, entropy, workspace):
     """lse / entropy [b, Hq, window] (fp32, either may be None) <- natural-log normaliser and
     entropy (nats) of the observed softmax rows."""
-    cp = p.c()
-    _check(load().aha_prefill_row_stats(ctypes.byref(cp), _ptr(q), _ptr(k), _ptr(lse),
-                                        _ptr(entropy), _ptr(workspace),
-                                        workspace.numel() if workspace is not None else 0,
-                                        _stream()))
+    _check((_lib or load()).aha_prefill_row_stats(
+        p._struct()[1], _ptr(q), _ptr(k), _ptr(lse), _ptr(entropy), *_ws(workspace), _stream()))
 
 
 def aha_select_topk(p: Params, scores, idx, workspace=None):
     """idx[b, Hkv, budget] (int32) <- ascending retained token positions."""
-    cp = p.c()
-    _check(load().aha_select_topk(ctypes.byref(cp), _ptr(scores), _ptr(idx), _ptr(workspace),
-                                  workspace.numel() if workspace is not None else 0, _stream()))
+    _check((_lib or load()).aha_select_topk(
+        p._struct()[1], _ptr(scores), _ptr(idx), *_ws(workspace), _stream()))
 
 
 def aha_compact_kv(p: Params, k, v, scores, idx, k_cache, v_cache, scores_c, pos_c, free_slot):
-    cp = p.c()
-    _check(load().aha_compact_kv(ctypes.byref(cp), _ptr(k), _ptr(v), _ptr(scores), _ptr(idx),
-                                 _ptr(k_cache), _ptr(v_cache), _ptr(scores_c), _ptr(pos_c),
-                                 _ptr(free_slot), int(k_cache.shape[2]), _stream()))
+    _check((_lib or load()).aha_compact_kv(
+        p._struct()[1], _ptr(k), _ptr(v), _ptr(scores), _ptr(idx), _ptr(k_cache), _ptr(v_cache),
+        _ptr(scores_c), _ptr(pos_c), _ptr(free_slot), k_cache.size(2), _stream()))
 
 
 def aha_decode_step(p: Params, q_new, k_new, v_new, k_cache, v_cache, scores_c, pos_c, free_slot,
                     logical_pos: int, out, workspace=None):
-    cp = p.c()
-    _check(load().aha_decode_step(ctypes.byref(cp), _ptr(q_new), _ptr(k_new), _ptr(v_new),
-                                  _ptr(k_cache), _ptr(v_cache), _ptr(scores_c), _ptr(pos_c),
-                                  _ptr(free_slot), int(k_cache.shape[2]), int(logical_pos),
-                                  _ptr(out), _ptr(workspace),
-                                  workspace.numel() if workspace is not None else 0, _stream()))
+    _check((_lib or load()).aha_decode_step(
+        p._struct()[1], _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
+        _ptr(scores_c), _ptr(pos_c), _ptr(free_slot), k_cache.size(2), int(logical_pos),
+        _ptr(out), *_ws(workspace), _stream()))
 
 
 def aha_decode_step_static(p: Params, q_new, k_new, v_new, k_cache, v_cache, scores_c, pos_c,
                            free_slot, logical_pos: int, out):
     """aha_decode_step on the library's built-in scratch buffer (allocates nothing)."""
-    cp = p.c()
-    _check(load().aha_decode_step_static(ctypes.byref(cp), _ptr(q_new), _ptr(k_new), _ptr(v_new),
-                                         _ptr(k_cache), _ptr(v_cache), _ptr(scores_c),
-                                         _ptr(pos_c), _ptr(free_slot), int(k_cache.shape[2]),
-                                         int(logical_pos), _ptr(out), _stream()))
+    _check((_lib or load()).aha_decode_step_static(
+        p._struct()[1], _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
+        _ptr(scores_c), _ptr(pos_c), _ptr(free_slot), k_cache.size(2), int(logical_pos),
+        _ptr(out), _stream()))
 
 
 def profile_events(events=None):

@@ -242,3 +242,19 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_params_struct_follows_every_change():
+    import copy
+    import pickle
+    p = good()
+    before = bytes(p.c())
+    assert bytes(p._struct()[0]) == before and p._struct() is p._struct()
+    p.seq_len += 8
+    q = copy.deepcopy(p)
+    q.q_stride = [8 * s for s in q.q_stride]
+    assert p._struct()[0].seq_len == p.seq_len and bytes(p.c()) != before
+    assert tuple(q._struct()[0].q_stride) == q.q_stride != p.q_stride
+    assert bytes(pickle.loads(pickle.dumps(q)).c()) == bytes(copy.copy(q).c()) == bytes(q.c())
+    p.c().seq_len = 1                                  # a copy: the caller's own
+    assert p._struct()[0].seq_len == p.seq_len
