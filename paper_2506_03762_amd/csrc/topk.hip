@@ -3,31 +3,36 @@
 // lower position, written as ascending token positions followed by the recent
 // positions.
 //
-// One workgroup of 1024 threads per problem; each thread owns a contiguous
-// range of token positions whose scores, turned into order-preserving 32-bit
-// keys, stay in registers.  The key of the last selected element is found by
+// One workgroup per problem.  Each wave owns a contiguous range of token positions and walks
+// it 64 positions at a time, lane = position: the loads coalesce whatever a row's alignment,
+// and a comparison over a step is one 64-bit mask on the scalar unit - counted with s_bcnt1,
+// turned into output slots with v_mbcnt - so that nothing per key is kept but the key itself
+// (the scores turned into order-preserving 32-bit keys, in registers).  The last selected
+// element is found by
 //   1. the key range [kmin, kmax] of the problem (one block reduction);
-//   2. ONE histogram of 4096 bins that are linear in key - kmin over exactly
-//      that range, so the keys spread over the bins whatever their exponents
-//      (few same-address LDS atomics), and a block-wide suffix scan that finds
-//      the bin holding the threshold;
-//   3. an exact rank among the (typically few dozen) keys of that bin, kept in
-//      LDS; if the bin is crowded (many equal or nearly equal scores) the low
-//      bits are resolved by 8-bit radix rounds instead.
-// An ordered compaction (one block-wide scan) then writes the indices in
-// ascending order.  Sequences too long for the register file (more than 64
-// keys per thread) re-read the scores from memory in every pass.
-#include <type_traits>
-
+//   2. ONE histogram of BINS bins that are linear in key - kmin over exactly that range, so the
+//      keys spread over the bins whatever their exponents (few same-address LDS atomics), and
+//      a block-wide suffix scan that finds the bin holding the threshold;
+//   3. an exact rank among the (typically few dozen) keys of that bin, kept in LDS; if the bin
+//      is crowded (many equal or nearly equal scores) the low bits are resolved by 8-bit radix
+//      rounds instead.
+// Keys above that bin are selected for certain; the ones inside are decided by (key, position)
+// against the last selected element, so the ascending output needs one count per wave and no
+// further scan.  Of sequences with more than 32 keys per thread the rest is re-read from memory
+// in every pass.
+//
+// Bound by the latency of its chain (launch, first loads, six barriers) and, from 8K tokens on,
+// by the one CU that works on a problem.  In-kernel stamps at 8 x 32768 scores (cycles at
+// 2.4 GHz): loads and range 5.4 K, histogram 5.2 K (the LDS atomics' rate), scan 2.0 K, candidates
+// 5.0 K, rank 1.0 K, output 4.5 K.  Against lanes that own consecutive positions (scattered
+// loads, per-lane bit masks, a second scan), back to back: 2 x 512 scores 5.9 -> 3.4 us,
+// 32 x 4096 6.6 -> 4.8, 12 x 5003 9.0 -> 5.4, 8 x 16384 10.0 -> 8.4, 128 x 16384 11.2 -> 9.5,
+// 8 x 32768 16.1 -> 13.2, 8 x 65536 34.8 -> 31.8, 8 x 120000 290 -> 67.
 #include "aha_dev.h"
 #include "aha_host.h"
 
 namespace aha {
 
-constexpr int kTopkThreads = 1024;
-constexpr int kTopkWaves = kTopkThreads / 64;
-constexpr int kBins = 4096;      // first-round bins
-constexpr int kHistCopies = 2;   // waves alternate between copies
 constexpr int kCandMax = 1024;   // keys of the threshold bin ranked directly
 
 __device__ __forceinline__ uint32_t order_key(float f) {
@@ -35,296 +40,274 @@ __device__ __forceinline__ uint32_t order_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+template <int WAVES, int BINS>
 struct TopkSmem {
-    int hist[kHistCopies][kBins];
+    int hist[BINS];
     unsigned long long cand[kCandMax];  // key << 32 | ~position: descending = selection order
-    uint32_t red[2][kTopkWaves];
-    int wsum[kTopkWaves];
-    int scan[2][kTopkWaves];
-    int bin, need, ncand;
-    uint32_t T;
+    uint32_t red[2][WAVES];
+    int wsum[WAVES];   // histogram counts per wave
+    int wcnt[WAVES];   // selected elements per wave
+    int bin, need, nbin, ncand;
+    uint32_t T;        // key and position of the last selected element
+    int posT;
 };
 
+// Inclusive prefix sum over the wave in the vector ALU: within the rows of 16 lanes, then the
+// last lane of a row added to the next row, then the last lane of the first half to the second.
+__device__ __forceinline__ int wave_prefix_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15, rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31, rows 2 and 3
+    return x;
+}
+
+// `first` plus the number of lanes below this one whose bit is set
+__device__ __forceinline__ int mask_rank(unsigned long long m, int first) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, first));
+}
+
 // Block-wide: given per-thread counts `loc` of consecutive, ascending key ranges (thread
-// t covers lower keys than thread t+1), find the thread whose range holds the need-th
-// largest key.  Returns the number of keys in the ranges above this thread's.
+// t covers lower keys than thread t+1), the number of keys in the ranges above this thread's.
+template <int WAVES>
 __device__ __forceinline__ int suffix_above(int loc, int lane, int wave, int *wsum) {
-    int suf = loc;  // inclusive suffix sum within the wave
+    const int incl = wave_prefix_sum(loc);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (lane == 0) wsum[wave] = total;
+    __syncthreads();
+    int above = total - incl;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_down(suf, o);
-        if (lane + o < 64) suf += t;
-    }
-    if (lane == 0) wsum[wave] = suf;
-    __syncthreads();
-    int above = suf - loc;
-    for (int w = wave + 1; w < kTopkWaves; ++w) above += wsum[w];
-    __syncthreads();
+    for (int w = 0; w < WAVES; ++w) above += w > wave ? wsum[w] : 0;
     return above;
 }
 
-// ITEMS > 0: keys of positions [tid*ITEMS, tid*ITEMS+ITEMS) live in registers.
-// ITEMS == 0: keys are re-read (thread tid owns [tid*ipt, tid*ipt+ipt)).
+// A wave owns 64 * ipt positions; the keys of its first ITEMS steps live in registers, one per
+// lane and step.  LONG: there are more steps, whose scores are re-read in every pass.
 // `sink`: positions below it are retained without being ranked (their keys are the padding
-// key 0, which is never counted), like the `recent` last positions.
-template <int ITEMS>
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float *__restrict__ scores,
-                                                            int n, int budget, int recent,
-                                                            int sink, int32_t *__restrict__ idx) {
-    extern __shared__ __attribute__((aligned(16))) char topk_smem[];
-    TopkSmem &sm = *(TopkSmem *)topk_smem;
+// key 0, which lies below every real key and is never counted), like the `recent` last ones.
+template <int WAVES, int ITEMS, int BINS, bool LONG>
+__global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restrict__ scores, int n,
+                                                          int budget, int recent, int sink,
+                                                          int32_t *__restrict__ idx) {
+    constexpr int THREADS = WAVES * 64, BPT = BINS / THREADS;
+    static_assert(BPT % 4 == 0 && THREADS >= 256, "a thread owns whole 16-byte groups of bins");
+    __shared__ __attribute__((aligned(16))) TopkSmem<WAVES, BINS> sm;
 
-    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float *sc = scores + (int64_t)z * n;
     int32_t *out = idx + (int64_t)z * budget + sink;  // the ranked part starts behind the sinks
     const int n_cand = n - recent;
     const int k = budget - recent - sink;
 
-    for (int t = tid; t < sink; t += kTopkThreads) out[t - sink] = t;
-    for (int t = tid; t < recent; t += kTopkThreads) out[k + t] = n_cand + t;
-    if (k == 0) return;
-
-    constexpr int R = ITEMS > 0 ? ITEMS : 1;
-    // one bit per register-resident key
-    using Mask = std::conditional_t<(ITEMS > 32), unsigned long long, unsigned>;
-    auto lowest = [](Mask m) { return sizeof(Mask) == 8 ? __ffsll((unsigned long long)m) - 1 : __ffs((unsigned)m) - 1; };
-    auto popcount = [](Mask m) { return sizeof(Mask) == 8 ? __popcll((unsigned long long)m) : __popc((unsigned)m); };
-    const int ipt = ITEMS > 0 ? ITEMS : (n_cand + kTopkThreads - 1) / kTopkThreads;
-    const int j0 = min(tid * ipt, n_cand), j1 = min(j0 + ipt, n_cand);
-    uint32_t key[R];
-    if (ITEMS > 0) {
-        // a key of 0 sorts below every real key (real keys have a bit set) and is never counted
-        if (ITEMS % 4 == 0 && (((uintptr_t)(sc + j0)) & 15) == 0 && j0 + ITEMS <= n_cand) {
+    const int ipt = LONG ? (n_cand + THREADS - 1) / THREADS : ITEMS;
+    const int base = wave * 64 * ipt;  // the wave's first position
+    // (LONG: batches of eight steps may reach behind the wave's last one)
+    const bool whole = base >= sink && base + 64 * ipt <= n_cand && (!LONG || (ipt - ITEMS) % 8 == 0);
+    // keys of N steps from step t0 on: all requested (clamped to the row) before the first is
+    // used, and only then turned into keys, so that no step waits for another one's round trip
+    auto load = [&](auto &u, int t0) {
+        constexpr int N = sizeof(u) / sizeof(u[0]);
+        const float *row = sc + base;
+        const int last = n - 1 - base;  // (negative for a wave behind the row's end)
 #pragma unroll
-            for (int t = 0; t < R / 4; ++t) {
-                const float4 v = *(const float4 *)(sc + j0 + 4 * t);
-                key[4 * t] = order_key(v.x); key[4 * t + 1] = order_key(v.y);
-                key[4 * t + 2] = order_key(v.z); key[4 * t + 3] = order_key(v.w);
+        for (int t = 0; t < N; ++t) {
+            const int off = (t0 + t) * 64 + lane;
+            u[t] = __float_as_uint(row[whole ? off : min(off, last)]);
+        }
+#pragma unroll
+        for (int t = 0; t < N; ++t) u[t] = order_key(__uint_as_float(u[t]));
+        if (!whole) {
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int j = base + (t0 + t) * 64 + lane;
+                u[t] = ((j >= sink) & (j < n_cand) & (t0 + t < ipt)) ? u[t] : 0u;
             }
-        } else {
-#pragma unroll
-            for (int t = 0; t < R; ++t) key[t] = j0 + t < j1 ? order_key(sc[j0 + t]) : 0u;
-        }
-        if (j0 < sink) {
-#pragma unroll
-            for (int t = 0; t < R; ++t) key[t] = j0 + t < sink ? 0u : key[t];
-        }
-    }
-    // visit every owned key: f(key, position)
-    auto for_keys = [&](auto f) {
-        if (ITEMS > 0) {
-#pragma unroll
-            for (int t = 0; t < R; ++t)
-                if (j0 + t < j1 && j0 + t >= sink) f(key[t], j0 + t);
-        } else {
-            for (int j = max(j0, sink); j < j1; ++j) f(order_key(sc[j]), j);
         }
     };
+    uint32_t key[ITEMS];
+    if (k > 0) load(key, 0);
+    for (int t = tid; t < BINS; t += THREADS) sm.hist[t] = 0;
+    if (tid == 0) sm.ncand = 0;
+    for (int t = tid; t < sink; t += THREADS) out[t - sink] = t;
+    for (int t = tid; t < recent; t += THREADS) out[k + t] = n_cand + t;
+    if (k == 0) return;
+    // every step of the wave in position order: f(keys of the 64 lanes, step)
+    auto for_steps = [&](auto f) {
+#pragma unroll
+        for (int t = 0; t < ITEMS; ++t) f(key[t], t);
+        if (LONG) {
+            for (int t0 = ITEMS; t0 < ipt; t0 += 8) {  // (eight requests in flight; past the last: padding)
+                uint32_t u[8];
+                load(u, t0);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) f(u[t], t0 + t);
+            }
+        }
+    };
+    auto ballot = [](bool p) { return (unsigned long long)__builtin_amdgcn_ballot_w64(p); };
 
-    // 1. range of the keys
+    // 1. range of the keys (padding: 0 - 1 wraps to the top and never is the minimum)
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    for_keys([&](uint32_t u, int) { kmin = min(kmin, u); kmax = max(kmax, u); });
+    for_steps([&](uint32_t u, int) { kmin = min(kmin, u - 1u); kmax = max(kmax, u); });
     kmin = reduce_lanes<1, 64>(kmin, OpMinU{});
     kmax = reduce_lanes<1, 64>(kmax, OpMaxU{});
     if (lane == 0) { sm.red[0][wave] = kmin; sm.red[1][wave] = kmax; }
-    for (int t = tid; t < kHistCopies * kBins; t += kTopkThreads) (&sm.hist[0][0])[t] = 0;
-    if (tid == 0) sm.ncand = 0;
     __syncthreads();
-    kmin = sm.red[0][0]; kmax = sm.red[1][0];
 #pragma unroll
-    for (int w = 1; w < kTopkWaves; ++w) { kmin = min(kmin, sm.red[0][w]); kmax = max(kmax, sm.red[1][w]); }
+    for (int w = 0; w < WAVES; ++w) { kmin = min(kmin, sm.red[0][w]); kmax = max(kmax, sm.red[1][w]); }
+    kmin += 1u;
 
-    uint32_t T = kmax;  // key of the last selected element
-    int need = k;       // how many keys equal to T are selected (lowest positions first)
-    if (kmin != kmax) {
-        // 2. one histogram, linear in key - kmin, over the occupied range only
-        const uint32_t range = kmax - kmin;
-        const int sh = max(0, 32 - __clz(range) - 12);  // (range >> sh) < 4096
-        int *hist = sm.hist[wave & (kHistCopies - 1)];
-        for_keys([&](uint32_t u, int) { atomicAdd(&hist[(u - kmin) >> sh], 1); });
-        __syncthreads();
-        int cb[4], loc = 0;
+    // 2. one histogram, linear in key - kmin, over the occupied range only
+    const uint32_t range = kmax - kmin;
+    constexpr int kBinBits = 31 - __builtin_clz(BINS);
+    const int sh = range ? max(0, 32 - __clz(range) - kBinBits) : 0;  // (range >> sh) < BINS
+    for_steps([&](uint32_t u, int) {
+        if (u >= kmin) atomicAdd(&sm.hist[(u - kmin) >> sh], 1);  // (padding keys are not counted)
+    });
+    __syncthreads();
+    {
+        int cb[BPT], loc = 0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            cb[t] = 0;
-#pragma unroll
-            for (int c = 0; c < kHistCopies; ++c) cb[t] += sm.hist[c][4 * tid + t];
+        for (int t = 0; t < BPT; ++t) {
+            cb[t] = sm.hist[BPT * tid + t];
             loc += cb[t];
         }
-        int above = suffix_above(loc, lane, wave, sm.wsum);
-        if (above < need && need <= above + loc) {
+        int above = suffix_above<WAVES>(loc, lane, wave, sm.wsum);
+        if (above < k && k <= above + loc) {
 #pragma unroll
-            for (int t = 3; t >= 0; --t) {
-                if (above < need && need <= above + cb[t]) {
-                    sm.bin = 4 * tid + t;
-                    sm.need = need - above;
-                    sm.ncand = cb[t];  // keys in the threshold bin
+            for (int t = BPT - 1; t >= 0; --t) {
+                if (above < k && k <= above + cb[t]) {
+                    sm.bin = BPT * tid + t;
+                    sm.need = k - above;
+                    sm.nbin = cb[t];  // keys in the threshold bin
                 }
                 above += cb[t];
             }
         }
-        __syncthreads();
-        const uint32_t bin = (uint32_t)sm.bin;
-        need = sm.need;
-        const int nc = sm.ncand;
-        __syncthreads();
-        if (sh == 0) {
-            T = kmin + bin;  // bins are single keys
-        } else if (nc <= kCandMax) {
-            // 3a. exact rank among the keys of the threshold bin
-            if (tid == 0) sm.ncand = 0;
-            __syncthreads();
-            if (ITEMS > 0) {
-                // mark the thread's keys of that bin, reserve their slots with one atomic
-                Mask cm = 0;
-#pragma unroll
-                for (int t = 0; t < R; ++t)
-                    cm |= (Mask)(key[t] != 0u && ((key[t] - kmin) >> sh) == bin) << t;
-                if (cm) {
-                    int slot = atomicAdd(&sm.ncand, popcount(cm));
-                    while (cm) {
-                        const int t = lowest(cm);
-                        cm &= cm - 1;
-                        uint32_t u = 0;
-#pragma unroll
-                        for (int q = 0; q < R; ++q) u = q == t ? key[q] : u;
-                        sm.cand[slot++] = ((unsigned long long)u << 32) | (uint32_t)(~(j0 + t));
-                    }
-                }
-            } else {
-                for_keys([&](uint32_t u, int j) {
-                    if (((u - kmin) >> sh) == bin) {
-                        const int slot = atomicAdd(&sm.ncand, 1);
-                        sm.cand[slot] = ((unsigned long long)u << 32) | (uint32_t)(~j);
-                    }
-                });
-            }
-            __syncthreads();
-            if (tid < nc) {
-                const unsigned long long mine = sm.cand[tid];
-                int rank = 0;  // number of candidates selected before this one
-                int u = 0;
-                for (; u + 4 <= nc; u += 4)
-                    rank += (sm.cand[u] > mine) + (sm.cand[u + 1] > mine) + (sm.cand[u + 2] > mine) +
-                            (sm.cand[u + 3] > mine);
-                for (; u < nc; ++u) rank += sm.cand[u] > mine;
-                if (rank == need - 1) sm.T = (uint32_t)(mine >> 32);
-            }
-            __syncthreads();
-            T = sm.T;
-            need = -1;  // number of selected keys equal to T: known once the keys above T are counted
-        } else {
-            // 3b. crowded bin: 8-bit radix rounds over the low `sh` bits of key - kmin
-            uint32_t prefix = bin << sh;
-            for (int shift = ((sh - 1) / 8) * 8; shift >= 0; shift -= 8) {
-                __syncthreads();
-                if (tid < 256) { sm.hist[0][tid] = 0; sm.hist[1][tid] = 0; }
-                __syncthreads();
-                const uint32_t hi_mask = 0xffffffffu << min(shift + 8, 31);  // sh <= 20: never 32
-                for_keys([&](uint32_t u, int) {
-                    const uint32_t rel = u - kmin;
-                    if ((rel >> sh) == bin && (rel & hi_mask) == (prefix & hi_mask))
-                        atomicAdd(&hist[(rel >> shift) & 255u], 1);
-                });
-                __syncthreads();
-                int c = 0;
-                if (tid < 256) c = sm.hist[0][tid] + sm.hist[1][tid];
-                const int ab = suffix_above(c, lane, wave, sm.wsum);  // threads >= 256 hold 0
-                if (tid < 256 && ab < need && need <= ab + c) { sm.bin = tid; sm.need = need - ab; }
-                __syncthreads();
-                prefix |= (uint32_t)sm.bin << shift;
-                need = sm.need;
-            }
-            T = kmin + prefix;
-        }
     }
+    __syncthreads();
+    const uint32_t bin = (uint32_t)__builtin_amdgcn_readfirstlane(sm.bin);
+    int need = __builtin_amdgcn_readfirstlane(sm.need);
+    const int nbin = __builtin_amdgcn_readfirstlane(sm.nbin);
 
-    // ordered compaction
-    int gt = 0, eq = 0;
-    Mask gtm = 0, eqm = 0;  // register-resident keys above / equal to T (padding keys are 0 < T)
-    if (ITEMS > 0) {
-#pragma unroll
-        for (int t = 0; t < R; ++t) {
-            gtm |= (Mask)(key[t] > T) << t;
-            eqm |= (Mask)(key[t] == T) << t;
-        }
-        gt = popcount(gtm);
-        eq = popcount(eqm);
-    } else {
-        for_keys([&](uint32_t u, int) { gt += u > T; eq += u == T; });
-    }
-    // inclusive scans over the wave; with keys in registers both counts (at most 64 per
-    // thread, 4096 per wave) share one word
-    int gi = gt, ei = eq;
-    if (ITEMS > 0) {
-        int pk = gt | (eq << 16);
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int a = __shfl_up(pk, o);
-            if (lane >= o) pk += a;
-        }
-        gi = pk & 0xffff;
-        ei = pk >> 16;
-    } else {
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int a = __shfl_up(gi, o), b = __shfl_up(ei, o);
-            if (lane >= o) { gi += a; ei += b; }
-        }
-    }
-    __syncthreads();
-    if (lane == 63) { sm.scan[0][wave] = gi; sm.scan[1][wave] = ei; }
-    __syncthreads();
-    int gbase = 0, ebase = 0, gtotal = 0;
-    for (int w = 0; w < kTopkWaves; ++w) {
-        if (w < wave) { gbase += sm.scan[0][w]; ebase += sm.scan[1][w]; }
-        gtotal += sm.scan[0][w];
-    }
-    if (need < 0) need = k - gtotal;
-    int gtc = gbase + gi - gt, eqc = ebase + ei - eq;  // exclusive prefixes
-    // the k indices are gathered in LDS (the histogram is dead by now) and then written out
-    // with consecutive lanes on consecutive addresses; beyond the staging capacity each
-    // thread writes its own
-    int *stage = &sm.hist[0][0];
-    const bool staged = k <= kHistCopies * kBins;
-    auto emit = [&](auto *dst) {
-        if (ITEMS > 0) {
-            // selected keys of this thread: all above T and, among those equal to T, the
-            // ones within the first `need` of the problem; visited in position order
-            Mask sel = gtm;
-            int quota = need - eqc;
-            for (Mask m = eqm; m != 0 && quota > 0; m &= m - 1, --quota) sel |= m & (~m + 1);
-            int o = gtc + min(eqc, need);
-            while (sel) {
-                dst[o++] = j0 + lowest(sel);
-                sel &= sel - 1;
+    // the last selected element (T, posT): selected are the keys above T, and those equal to T
+    // at positions up to posT
+    const uint32_t lo = kmin + (bin << sh), span = (1u << sh) - 1u;
+    const uint32_t hi = span > ~lo ? ~0u : lo + span;
+    uint32_t T = lo;
+    int posT = n;
+    auto selected = [&](uint32_t u, int t) {
+        return (u > T) | ((u == T) & (base + t * 64 + lane <= posT));
+    };
+    auto count_selected = [&] {
+        int c = 0;
+        for_steps([&](uint32_t u, int t) { c += __popcll(ballot(selected(u, t))); });
+        if (lane == 0) sm.wcnt[wave] = c;
+    };
+    if (nbin <= kCandMax) {
+        // 3a. exact rank among the keys of the threshold bin
+        int above = 0;  // keys of this wave above the bin
+        for_steps([&](uint32_t u, int t) {
+            const bool gt = u > hi, cand = (u >= lo) & !gt;
+            above += __popcll(ballot(gt));
+            const unsigned long long in = ballot(cand);
+            if (in) {
+                int slot = 0;
+                if (lane == 0) slot = atomicAdd(&sm.ncand, __popcll(in));
+                slot = __builtin_amdgcn_readfirstlane(slot);
+                if (cand)
+                    sm.cand[mask_rank(in, slot)] =
+                        ((unsigned long long)u << 32) | (uint32_t)(~(base + t * 64 + lane));
             }
-        } else {
-            for_keys([&](uint32_t u, int j) {
-                if (u > T) {
-                    dst[gtc + min(eqc, need)] = j;
-                    ++gtc;
-                } else if (u == T) {
-                    if (eqc < need) dst[gtc + eqc] = j;
-                    ++eqc;
-                }
+        });
+        if (lane == 0) sm.wcnt[wave] = above;
+        __syncthreads();
+        for (int i = tid; i < nbin; i += THREADS) {
+            const unsigned long long mine = sm.cand[i];
+            int rank = 0;  // number of candidates selected before this one
+            int u = 0;
+            for (; u + 4 <= nbin; u += 4)
+                rank += (sm.cand[u] > mine) + (sm.cand[u + 1] > mine) + (sm.cand[u + 2] > mine) +
+                        (sm.cand[u + 3] > mine);
+            for (; u < nbin; ++u) rank += sm.cand[u] > mine;
+            const int j = (int)~(uint32_t)mine;
+            if (rank < need) atomicAdd(&sm.wcnt[j / (64 * ipt)], 1);
+            if (rank == need - 1) {
+                sm.T = (uint32_t)(mine >> 32);
+                sm.posT = j;
+            }
+        }
+        __syncthreads();
+        T = sm.T;
+        posT = sm.posT;
+    } else {
+        // 3b. crowded bin: 8-bit radix rounds over the low `sh` bits of key - kmin
+        uint32_t prefix = bin << sh;
+        for (int shift = ((sh + 7) / 8 - 1) * 8; shift >= 0; shift -= 8) {
+            __syncthreads();
+            if (tid < 256) sm.hist[tid] = 0;
+            __syncthreads();
+            const uint32_t hi_mask = 0xffffffffu << min(shift + 8, 31);  // sh <= 24: never 32
+            for_steps([&](uint32_t u, int) {
+                const uint32_t rel = u - kmin;
+                if (u != 0u && (rel >> sh) == bin && (rel & hi_mask) == (prefix & hi_mask))
+                    atomicAdd(&sm.hist[(rel >> shift) & 255u], 1);
+            });
+            __syncthreads();
+            const int c = tid < 256 ? sm.hist[tid] : 0;
+            const int ab = suffix_above<WAVES>(c, lane, wave, sm.wsum);  // threads >= 256 hold 0
+            if (tid < 256 && ab < need && need <= ab + c) { sm.bin = tid; sm.need = need - ab; }
+            __syncthreads();
+            prefix |= (uint32_t)sm.bin << shift;
+            need = sm.need;
+        }
+        T = kmin + prefix;
+        // the position of the need-th key that equals T
+        int eq = 0;
+        for_steps([&](uint32_t u, int) { eq += __popcll(ballot(u == T)); });
+        __syncthreads();
+        if (lane == 0) sm.wsum[wave] = eq;
+        __syncthreads();
+        int before = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) before += w < wave ? sm.wsum[w] : 0;
+        if (before < need && need <= before + eq) {
+            for_steps([&](uint32_t u, int t) {
+                const unsigned long long m = ballot(u == T);
+                if (((m >> lane) & 1) && mask_rank(m, before) == need - 1)
+                    sm.posT = base + t * 64 + lane;
+                before += __popcll(m);
             });
         }
-    };
-    if (staged) {
-        emit(stage);
         __syncthreads();
-        for (int t = tid; t < k; t += kTopkThreads) out[t] = stage[t];
-    } else {
-        emit(out);
+        posT = sm.posT;
+        count_selected();
+        __syncthreads();
     }
+    T = (uint32_t)__builtin_amdgcn_readfirstlane((int)T);
+    posT = __builtin_amdgcn_readfirstlane(posT);
+
+    // ascending output: the wave's first slot, then step by step
+    int o = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) o += w < wave ? sm.wcnt[w] : 0;
+    for_steps([&](uint32_t u, int t) {
+        const bool sel = selected(u, t);
+        const unsigned long long m = ballot(sel);
+        if (sel) out[mask_rank(m, o)] = base + t * 64 + lane;
+        o += __popcll(m);
+    });
 }
 
-template <int ITEMS>
+template <int WAVES, int ITEMS, int BINS, bool LONG = false>
 static void launch_items(const float *scores, int Z, int n, int budget, int recent, int sink,
                          int32_t *idx, hipStream_t st) {
-    hipLaunchKernelGGL(topk_kernel<ITEMS>, dim3(Z), dim3(kTopkThreads), sizeof(TopkSmem), st, scores,
-                       n, budget, recent, sink, idx);
+    static_assert(sizeof(TopkSmem<WAVES, BINS>) <= 64 * 1024, "top-k LDS must fit the static limit");
+    hipLaunchKernelGGL((topk_kernel<WAVES, ITEMS, BINS, LONG>), dim3(Z), dim3(WAVES * 64), 0, st, scores, n,
+                       budget, recent, sink, idx);
 }
 
 // Scores smoothed over tokens before the selection (caption of the method's overview
@@ -344,20 +327,24 @@ __global__ __launch_bounds__(256) void pool_scores_kernel(const float *__restric
 
 hipError_t launch_topk(const float *scores, int Z, int n, int budget, int recent, int sink,
                        int pool, float *pooled, int32_t *idx, hipStream_t st) {
-    static_assert(sizeof(TopkSmem) < 64 * 1024, "top-k LDS must fit the default dynamic limit");
     if (pool > 1) {
         hipLaunchKernelGGL(pool_scores_kernel, dim3((n + 255) / 256, Z), dim3(256), 0, st, scores, n,
                            (pool - 1) / 2, pooled);
         scores = pooled;
     }
     const int n_cand = n - recent;
-    const int ipt = (n_cand + kTopkThreads - 1) / kTopkThreads;
-    if (ipt <= 4) launch_items<4>(scores, Z, n, budget, recent, sink, idx, st);
-    else if (ipt <= 8) launch_items<8>(scores, Z, n, budget, recent, sink, idx, st);
-    else if (ipt <= 16) launch_items<16>(scores, Z, n, budget, recent, sink, idx, st);
-    else if (ipt <= 32) launch_items<32>(scores, Z, n, budget, recent, sink, idx, st);
-    else if (ipt <= 64) launch_items<64>(scores, Z, n, budget, recent, sink, idx, st);
-    else launch_items<0>(scores, Z, n, budget, recent, sink, idx, st);
+    auto steps = [&](int waves) { return (n_cand + waves * 64 - 1) / (waves * 64); };
+    // Four waves up to 2048 candidates (32 x 2000: 6.3 -> 4.7 us; barriers and scans of 16 waves
+    // cost more than the keys), then 16; as many keys per thread as the row needs, since a step of
+    // padding costs what a step of keys does (12 x 5003 with eight steps instead of six: 6.3 us
+    // instead of 5.4).  More than 32 registers of keys per thread spill.
+#define AHA_TOPK(W, I, B) \
+    if (steps(W) <= I) { launch_items<W, I, B>(scores, Z, n, budget, recent, sink, idx, st); return hipGetLastError(); }
+    AHA_TOPK(4, 2, 2048) AHA_TOPK(4, 4, 2048) AHA_TOPK(4, 8, 2048)
+    AHA_TOPK(16, 4, 8192) AHA_TOPK(16, 6, 8192) AHA_TOPK(16, 8, 8192) AHA_TOPK(16, 12, 8192)
+    AHA_TOPK(16, 16, 8192) AHA_TOPK(16, 24, 8192) AHA_TOPK(16, 32, 8192)
+#undef AHA_TOPK
+    launch_items<16, 32, 8192, true>(scores, Z, n, budget, recent, sink, idx, st);
     return hipGetLastError();
 }
 

@@ -1,0 +1,27 @@
+"""Selection at the edges of its launch variants: rows that just fill or just exceed the keys a
+workgroup holds in registers, odd rows (no alignment), crowded threshold bins, infinities."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import topk_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_cand", [1, 63, 512, 513, 1025, 2048, 2049, 4096, 4097, 6145, 8193, 12289,
+                                    16385, 24577, 32768, 32769, 41023, 70001])
+@pytest.mark.parametrize("kind", ["random", "few_values", "narrow"])
+def test_topk_at_variant_edges(n_cand, kind):
+    """Indices equal to the oracle's, bit for bit: scores are fp32 on both sides and ties go to
+    the lower position."""
+    rng = np.random.default_rng(n_cand)
+    recent, sink = 5, min(3, n_cand - 1)
+    n = n_cand + recent
+    s = {"random": lambda: np.exp(rng.standard_normal((3, n))),
+         "few_values": lambda: rng.integers(0, 3, (3, n)) * 0.25,  # crowded bin, many ties
+         "narrow": lambda: 1.0 + rng.integers(0, 4 * n, (3, n)) * 2.0 ** -23}[kind]().astype(np.float32)
+    s[0, rng.integers(0, n)] = np.inf       # one key far above the others: all share one bin
+    s[1, rng.integers(0, n)] = -1.0
+    for k in sorted({0, 1, (n_cand - sink) // 5, n_cand - sink}):
+        got, want = topk_both(s[None], k + recent + sink, recent, sink=sink)
+        assert np.array_equal(got, want), (n_cand, kind, k)
