@@ -176,6 +176,8 @@ __device__ __forceinline__ Segment pair_segment(const RowMap &rm, int rows, int 
 }
 
 // ---------------------------------------------------------------- pass 1 --
+constexpr int kNoPrior = 0, kPriorFold = 1, kPriorOneStep = 2;  // value prior inside pass 1 (below)
+
 // Value prior (Sec. 4.3) inside pass 1.  The value rows of the 64 keys a wave multiplies in a
 // step are loaded with the addressing of the key fragments into the register buffer that is
 // idle in the first half of the step (the next key block is requested at mid-step instead of
@@ -242,7 +244,8 @@ struct PriorHalo {
 constexpr int kPriorPiece = 512;
 constexpr int kPriorMaxHalo = 32;  // rows on both sides together
 constexpr size_t kPriorSmem = (kPriorPiece + kPriorMaxHalo + 4) * sizeof(float);
-template <int D>
+// IN_LDS: the range is at most one piece and its norms are in s_nu already.
+template <int D, bool IN_LDS>
 __device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg,
                                                      int kend, const float *nu_g,
                                                      const PriorHalo<D> &halo, float *s_nu,
@@ -254,7 +257,7 @@ __device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, 
     for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
         const int t1 = min(kend, t0 + kPriorPiece);
         const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
-        for (int t = max(lo, kbeg) + tid; t < min(hi, kend); t += 256)
+        for (int t = max(lo, kbeg) + tid; !IN_LDS && t < min(hi, kend); t += 256)
             s_nu[t - lo] = __hip_atomic_load(nu_g + (int64_t)z * g.n + t, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
         // the halo rows that touch this piece (the first piece below, the last one above)
@@ -333,23 +336,29 @@ __device__ __forceinline__ float value_prior_of_range(const ScoreGeom &g, int b,
 //    step to arrive), and the kernel is bound by the key stream: the value rows are streamed
 //    in a phase of their own after the statistics (16K tokens x 128 heads x 64 rows: 183 us
 //    against 215 us interleaved).
+//  - ranges of one step (kPriorOneStep; problems of which every workgroup gets at most 256
+//    keys): the register buffer of the next key block is idle throughout, so the value rows
+//    and the pooling halo are requested in the set-up, right behind the keys, and their norms
+//    never leave LDS.  The kernel waits for memory once: 32 heads x 4096 tokens x 64 rows 18.4
+//    -> 16.9 us, 12 heads x 5003 x 120 rows 13.7 -> 11.6.
 // ENT: the chunk's mean scaled logit under its own probabilities, E_c[t] = m + u / s, is
 // written to `partial_mean` beside the chunk's log2-sum-exp2; entropy_merge_kernel turns the
 // chunks of a row into its entropy.
-template <int D, int NB, bool ENT, bool ROWS = false, bool PRIOR = false, bool LAZY = false>
+template <int D, int NB, bool ENT, bool ROWS = false, int PRIOR = kNoPrior, bool LAZY = false>
 __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_qtiles, int nparts,
                                                             int total_wgs, float *partial,
                                                             float *partial_mean, float *gamma,
                                                             float *gblockmax, float *nu_g) {
     using S = TileSmem<D, NB>;
-    constexpr bool kInterleave = PRIOR && NB == 8;  // value rows under the tile arithmetic
+    constexpr bool kOneStep = PRIOR == kPriorOneStep;
+    constexpr bool kInterleave = PRIOR == kPriorFold && NB == 8;  // value rows under the tile arithmetic
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __bf16 *sQ = (__bf16 *)smem;
     float *sLam = (float *)(smem + S::q_bytes);
     int *sPos = (int *)(sLam + S::ROWS);
     int *sBlk = sPos + 2 * S::ROWS;
     float4 *sRed = (float4 *)smem;  // reuses the query tile after the main loop
-    float *sNu = (float *)(smem + S::bytes);  // kInterleave: kPriorSmem bytes behind the tile
+    float *sNu = (float *)(smem + S::bytes);  // kInterleave, kOneStep: kPriorSmem bytes behind the tile
 
     // logical workgroup index -> (part, tile pair, problem)
     const int wg = logical_wg_index(total_wgs, n_qtiles > 1);
@@ -375,7 +384,7 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                 my_partial[tid] = -INFINITY;
                 if (ENT) partial_mean[my_off + tid] = 0.f;
             }
-            if (PRIOR && tid == 0) gblockmax[z * nparts + part] = 0.f;  // no keys, no prior
+            if (PRIOR != kNoPrior && tid == 0) gblockmax[z * nparts + part] = 0.f;  // no keys, no prior
             continue;
         }
         if (seg) __syncthreads();  // the previous tile (and its reduction buffer) is done with
@@ -394,6 +403,8 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
         // this wave's key block of step i; past the last step: rows clamped to the range's end
         auto kb_of = [&](int i) { return i < nsteps ? k_at0 + i * kdir : key_end; };
         bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block loads while one multiplies
+        PriorHalo<D> halo;
+        const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
         {
             // (the thread index goes through an opaque move: the set-up's addresses are then
             // recomputed per tile instead of being kept across the main loop, where they
@@ -405,6 +416,10 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             const float lam_req = q_tile_scale<D, NB>(g, rm, rho0, tid_s);
             __builtin_amdgcn_sched_barrier(0);  // the key block is requested last
             load_a<D>(kbase, g.ks[2], kb_of(0), key_end, lane, a0);
+            if constexpr (kOneStep) {
+                load_a<D>(vbase, g.vs[2], kb_of(0), key_end, lane, a1);
+                halo.request(g, vbase, key_begin, key_end, tid_s);
+            }
             q_tile_meta<D, NB>(g, rm, rho0, tid_s, lam_req, sLam, sPos, sBlk);
             q_tile_commit<D, NB>(qt_regs, tid_s, sQ);
         }
@@ -459,7 +474,6 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                 load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
                 blocks(a, kb, 0, NB);
             } else {
-                const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
                 load_a<D>(vbase, g.vs[2], kb, key_end, lane, nx);  // the value rows of these keys
                 __builtin_amdgcn_sched_barrier(0);
                 blocks(a, kb, 0, (NB + 1) / 2);
@@ -477,15 +491,26 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                 blocks(a, kb, (NB + 1) / 2, NB);
             }
         };
-        for (int i = 0; i < nsteps; i += 2) {
-            step(a0, a1, kb_of(i), kb_of(i + 1));
-            if (i + 1 >= nsteps) break;
-            step(a1, a0, kb_of(i + 1), kb_of(i + 2));
+        if constexpr (kOneStep) {
+            const int kb = kb_of(0);
+            blocks(a0, kb, 0, NB);
+            __builtin_amdgcn_sched_barrier(0);
+            float nu[kMB];
+            fragment_row_norms<D>(a1, nu);
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb) {
+                const int row = kb + mb * 32 + lane;
+                if (lane < 32 && row < key_end) sNu[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
+            }
+        } else {
+            for (int i = 0; i < nsteps; i += 2) {
+                step(a0, a1, kb_of(i), kb_of(i + 1));
+                if (i + 1 >= nsteps) break;
+                step(a1, a0, kb_of(i + 1), kb_of(i + 2));
+            }
         }
-
-        PriorHalo<D> halo;  // travels while the statistics are reduced
-        if constexpr (kInterleave)
-            halo.request(g, (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1], key_begin, key_end, tid);
+        if constexpr (kInterleave)  // travels while the statistics are reduced
+            halo.request(g, vbase, key_begin, key_end, tid);
         // fold the two half-waves (same query column, different key rows); a statistic
         // (m, s, u) re-referenced to a maximum M >= m is (M, s f, (u + (m - M) s) f), f = 2^(m - M)
         auto reref = [](float m_, float mref, float &s_, float &u_) {
@@ -530,12 +555,12 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             my_partial[tid] = M + log2f(sum);  // -inf for a row that saw no key
             if (ENT) partial_mean[my_off + tid] = sum > 0.f ? mref + mom / sum : 0.f;
         }
-        if constexpr (kInterleave) {
+        if constexpr (kInterleave || kOneStep) {
             // (every wave's norms were written before the barriers of the reduction above)
-            const float gm = pool_norms_of_range<D>(g, z, key_begin, key_end, nu_g, halo, sNu,
-                                                    gamma, tid);
+            const float gm = pool_norms_of_range<D, kOneStep>(g, z, key_begin, key_end, nu_g, halo,
+                                                              sNu, gamma, tid);
             if (tid == 0) gblockmax[z * nparts + part] = gm;
-        } else if constexpr (PRIOR) {
+        } else if constexpr (PRIOR == kPriorFold) {
             __syncthreads();  // the reduction buffer is done with
             const float gm = value_prior_of_range(g, b, h, z, key_begin, key_end, (float *)smem,
                                                   gamma, tid);
@@ -908,9 +933,10 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
     float *nu = (float *)(w + pl.off_nu);
     static DeviceOnce once;
     const hipError_t ea = device_once(once, [] {
-        const void *kernels[8] = {(const void *)bf16_pass1_kernel<D, NB, false>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, false, true>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, true>,
+        const void *kernels[9] = {(const void *)bf16_pass1_kernel<D, NB, false>,
+                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>,
+                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kPriorFold>,
+                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kPriorOneStep>,
                                   (const void *)bf16_pass1_kernel<D, NB, true>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, true>,
                                   (const void *)bf16_pass2_kernel<D, NB, true>,
@@ -935,12 +961,16 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
                                S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial,
                                (float *)nullptr, (float *)nullptr, (float *)nullptr,
                                (float *)nullptr);
+        else if (fold_prior && pl.nchunks == (g.n + kWgKeys - 1) / kWgKeys)  // ranges of one step
+            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kPriorOneStep>), xcd_grid(wgs1),
+                               dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
+                               partial, (float *)nullptr, gamma, gbm, nu);
         else if (fold_prior)
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, true>), xcd_grid(wgs1),
+            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kPriorFold>), xcd_grid(wgs1),
                                dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
                                partial, (float *)nullptr, gamma, gbm, nu);
         else if (pl.n_qtiles > 1)  // full accumulation: block sums against a lazy reference
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, false, true>), xcd_grid(wgs1),
+            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>), xcd_grid(wgs1),
                                dim3(256), S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
                                partial, (float *)nullptr, (float *)nullptr, (float *)nullptr,
                                (float *)nullptr);
