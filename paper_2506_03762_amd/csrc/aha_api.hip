@@ -215,17 +215,42 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
     return pl;
 }
 
+// Whether a step with fewer than 128 (batch, KV head) problems gives every head to one workgroup
+// all the same.  The split path streams the heads' caches with the whole chip but pays a second
+// launch and the partials' round trip; one workgroup streams a head at the rate of its CU, which
+// falls with the group (dots and weighted sums in the vector ALU).  Fitted to steps over 8, 32, 64
+// and 112 heads with 100 to 1500 slots, d = 64 and 128: us saved by the single launch against
+// KB of keys and values per head at `cu` KB/us, with the split path at 6 GB/ms over all heads (bf16,
+// d = 128: 8 heads x 300 slots, G = 1 7.0 us in one launch, 7.7 split; 8 x 1500 13.7 against
+// 9.3; 64 x 700 11.6 against 13.4; G = 4, 64 x 700 18.9 against 15.8).  From 96 heads on the split
+// path's advantage in rate is gone for up to four heads per group (G = 4, 112 x 700: 19.3
+// against 20.8); wider groups always gain from splitting (G = 8, 112 x 300: 19.1 against 16.1).
+static bool decode_one_launch(int dtype, int Z, int G, double head_kb) {
+    if (G > 4) return false;
+    if (Z >= 96) return true;
+    static const double cu[2][4] = {{80, 57, 48, 40}, {105, 62, 48, 36}};       // fp32, bf16; G = 1 .. 4
+    static const double saved[2][4] = {{3.5, 4.0, 4.2, 4.4}, {2.0, 2.3, 2.3, 1.6}};
+    const int t = dtype == AHA_BF16;
+    return head_kb * (1.0 / cu[t][G - 1] - Z / 6000.0) <= saved[t][G - 1];
+}
+
 // Decode: split a head's slots over workgroups when there are too few heads to fill the GPU.
 // A split workgroup keeps group * (slots of its range) dots and 4 * group * head_dim partial
 // outputs in LDS; the number of splits is raised until that fits kDecodeSplitLds (the limit
 // a launch may ask for without an attribute), and `fits` says whether kMaxDecodeSplit
-// splits were enough.
-static DecodePlan plan_decode(const aha_params *p) {
+// splits were enough.  `max_bytes`, when not 0, bounds the scratch: fewer splits are taken then.
+static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
     DecodePlan pl{};
     const int Z = p->batch * p->n_kv_heads, G = p->n_q_heads / p->n_kv_heads;
     const int live = p->budget + 1;
+    // one workgroup per head: dots and output probabilities of all live slots in LDS
+    const bool mfma = p->dtype == AHA_BF16 && G >= kDecodeMfmaGroup;
+    const bool mfma_v = p->dtype == AHA_BF16 && G >= kDecodeMfmaValuesGroup;
+    const size_t w_floats = decode_w_floats(G, live, p->head_dim, mfma, mfma_v);
+    const size_t q_tile = mfma ? kDecodeQTileBytes(p->head_dim) : 0;
+    const bool one_fits = (w_floats + (size_t)G * live) * 4 + q_tile <= kDecodeSingleLds;
     pl.fits = true;
-    int nsplit = 1;
+    int nsplit = 1, min_split = 1;
     if (Z < 128) {
         nsplit = (256 + Z - 1) / Z;
         const int max_by_size = (live + 63) / 64;  // at least 64 slots per workgroup
@@ -237,26 +262,33 @@ static DecodePlan plan_decode(const aha_params *p) {
             const int64_t need = max_sps > 0 ? (live + max_sps - 1) / max_sps : kMaxDecodeSplit + 1;
             if (need > nsplit) nsplit = need > kMaxDecodeSplit ? kMaxDecodeSplit : (int)need;
             if (need > kMaxDecodeSplit) pl.fits = false;
+            min_split = need > 2 ? (int)need : 2;
         }
     }
-    pl.nsplit = nsplit < 1 ? 1 : nsplit;
-    pl.sps = (live + pl.nsplit - 1) / pl.nsplit;
-    pl.nsplit = (live + pl.sps - 1) / pl.sps;
-    if (pl.nsplit > 1) {
+    auto split_into = [&](int parts) {
+        pl.sps = (live + parts - 1) / parts;
+        pl.nsplit = (live + pl.sps - 1) / pl.sps;
         pl.off_part = align_up(sizeof(float) * (size_t)Z * G * live, 256);
-        pl.off_nu = align_up(pl.off_part + sizeof(float) * (size_t)Z * pl.nsplit * G * (p->head_dim + 2), 256);
+        pl.off_nu = align_up(pl.off_part + sizeof(float) * (size_t)Z * pl.nsplit * G * (p->head_dim + kPartStats), 256);
         pl.bytes = pl.off_nu;
-    } else {
-        // one workgroup per head: dots and output probabilities of all live slots in LDS
-        const bool mfma = p->dtype == AHA_BF16 && G >= kDecodeMfmaGroup;
-        const bool mfma_v = p->dtype == AHA_BF16 && G >= kDecodeMfmaValuesGroup;
-        const size_t w_floats = decode_w_floats(G, live, p->head_dim, mfma, mfma_v);
-        const size_t q_tile = mfma ? kDecodeQTileBytes(p->head_dim) : 0;
-        if ((w_floats + (size_t)G * live) * 4 + q_tile > kDecodeSingleLds) pl.fits = false;
+        // value prior inside the loop: the live slots' value norms and their maximum per head
+        if (p->decode_value_prior)
+            pl.bytes = align_up(pl.off_nu + sizeof(float) * ((size_t)Z * live + Z), 256);
+    };
+    split_into(nsplit);
+    // (a static step refuses by this number: with two statistics per partial output, the size that
+    // its limit was stated for)
+    pl.split_bytes = pl.nsplit > 1 ? pl.bytes - align_up(sizeof(float) * 2 * (size_t)Z * pl.nsplit * G, 256) : 0;
+    const double head_kb = 2e-3 * live * p->head_dim * esize(p->dtype);
+    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, head_kb))) {
+        while (max_bytes && pl.bytes > max_bytes && nsplit > min_split) split_into(--nsplit);
+        return pl;
     }
-    // value prior inside the loop: the live slots' value norms and their maximum per head
-    if (p->decode_value_prior)
-        pl.bytes = align_up(pl.off_nu + sizeof(float) * ((size_t)Z * live + Z), 256);
+    if (pl.nsplit <= 1 && !one_fits) pl.fits = false;
+    pl.nsplit = 1;
+    pl.sps = live;
+    pl.off_part = pl.off_nu = pl.bytes = 0;
+    if (p->decode_value_prior) pl.bytes = align_up(sizeof(float) * ((size_t)Z * live + Z), 256);
     return pl;
 }
 
@@ -482,16 +514,18 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
     const int G = p->n_q_heads / p->n_kv_heads;
     if (G > 8)
         return fail(AHA_ERR_UNSUPPORTED, "decode is built for query groups of up to 8 heads, not %d", G);
-    *plan = plan_decode(p);
+    *plan = plan_decode(p, scratch_limit);
     if (!plan->fits)
         return fail(AHA_ERR_UNSUPPORTED,
                     "decode keeps group * (budget + 1) dots in LDS; %d * %d does not fit (%d splits)",
                     G, p->budget + 1, plan->nsplit);
     if (scratch_limit) {
-        if (plan->bytes > scratch_limit)
+        // (the same shapes are refused whichever path would serve them)
+        const size_t need = plan->bytes > plan->split_bytes ? plan->bytes : plan->split_bytes;
+        if (need > scratch_limit)
             return fail(AHA_ERR_UNSUPPORTED,
                         "this shape needs %zu bytes of scratch, the built-in buffer holds %zu: use "
-                        "aha_decode_step with a workspace", plan->bytes, scratch_limit);
+                        "aha_decode_step with a workspace", need, scratch_limit);
         return AHA_OK;
     }
     return check_ws(workspace, workspace_bytes, plan->bytes);

@@ -124,6 +124,8 @@ struct DecodeGeom {
 // With few (batch, KV head) problems the slots of a head are split over nsplit workgroups
 // (two launches, partials in the workspace); otherwise one workgroup handles a head.
 constexpr int kMaxDecodeSplit = 64;  // most workgroups a head's slots are split over
+// a split's partial outputs of a head: d channels, then maximum, output sum, score sum, unused
+constexpr int kPartStats = 4;
 constexpr size_t kDecodeSplitLds = 64 * 1024;    // dynamic LDS of a split workgroup, at most
 constexpr size_t kDecodeSingleLds = 150 * 1024;  // dynamic LDS of the one-workgroup-per-head kernel, at most
 // bf16 caches with at least this many query heads per KV head: the one-workgroup-per-head
@@ -133,6 +135,9 @@ constexpr size_t kDecodeQTileBytes(int d) { return (size_t)32 * (d + 8) * 2; }
 // bf16 caches with at least this many query heads per KV head: the values are weighted on the
 // matrix core as well (16 slots per wave at a time, staged through LDS)
 constexpr int kDecodeMfmaValuesGroup = 4;  // (with 4 heads the dots stay in the vector ALU, with 3 the values too: measured faster)
+// bf16 caches with at least this many query heads per KV head: the split workgroups work on the
+// matrix core
+constexpr int kDecodeSplitMfmaGroup = 4;
 // Floats of the first region of decode_kernel's dynamic LDS (raw dots of all live slots, later
 // the waves' partial outputs [16][G][d]); with the values on the matrix core every wave also
 // stages 16 value rows over the query tile (if any) and this region.
@@ -152,7 +157,8 @@ struct DecodePlan {
     int sps;         // slots per split
     size_t off_part; // partial outputs behind the raw dots
     size_t off_nu;   // ||v||^2 of every live slot behind those (value prior in the loop)
-    size_t bytes;    // workspace bytes (0 when nsplit == 1)
+    size_t bytes;    // workspace bytes
+    size_t split_bytes;  // what the split path needs for this shape, taken or not (0: never split)
     bool fits;       // the LDS the chosen path needs is within its limit
 };
 hipError_t launch_decode(const DecodeGeom &g, const DecodePlan &pl, void *ws, int dtype,

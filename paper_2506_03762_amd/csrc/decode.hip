@@ -402,10 +402,14 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
         __syncthreads();  // every wave is done with its rows: the partial outputs go on top
         if (qn < G) {
 #pragma unroll
+            // (a head's channels permuted by XOR: the heads' rows, a multiple of the banks apart,
+            // would meet in the same banks; G = 8, d = 128: 64 heads x
+            // 100 slots 18.5 -> 17.4 us)
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    s_o[(wave * G + qn) * D + cb * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)] = O[cb][v];
+                for (int v = 0; v < 16; v += 4)
+                    *(f32x4 *)(s_o + (wave * G + qn) * D + ((cb * 32 + 2 * v + 4 * hf) ^ (8 * qn))) =
+                        f32x4{O[cb][v], O[cb][v + 1], O[cb][v + 2], O[cb][v + 3]};
         }
     } else {
     float o[G][CH];
@@ -447,7 +451,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
         const int gi = t / D, c = t % D;
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) v += s_o[(w * G + gi) * D + c];
+        for (int w = 0; w < kDecWaves; ++w) v += s_o[(w * G + gi) * D + (kMfmaValues ? c ^ (8 * gi) : c)];
         const int64_t oi = ((int64_t)(b * g.Hq + h * G + gi)) * D + c;
         if constexpr (ESIZE == 2)
             ((uint16_t *)g.out)[oi] = (uint16_t)f32_to_bf16_rne(v);
@@ -471,32 +475,47 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
 // nu_s = ||v_cache[s]||^2 of every live slot - the new token's row standing in for the free
 // slot - and the largest of them, one workgroup per (batch, KV head).  A launch of its own, so
 // that the decode kernels proper carry nothing of it.
+// (Bound by the latency of its loads: 16 waves with four rows in flight each.  With 4 waves and
+// one row in flight a step of 28 heads x 3785 slots with the prior took 85 us.)
 template <int ESIZE, int D>
-__global__ __launch_bounds__(256) void decode_value_norms_kernel(DecodeGeom g, float *ws_nu,
-                                                                 float *ws_numax) {
-    constexpr int CH = 16 / ESIZE, LPR = D / CH, RP = 256 / LPR, ROWB = D * ESIZE;
-    __shared__ float s_max[4];
+__global__ __launch_bounds__(kDecThreads) void decode_value_norms_kernel(DecodeGeom g, float *ws_nu,
+                                                                         float *ws_numax) {
+    constexpr int CH = 16 / ESIZE, LPR = D / CH, RP = kDecThreads / LPR, ROWB = D * ESIZE, U = 4;
+    __shared__ float s_max[kDecWaves];
     const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int live = g.budget + 1, fs = g.free_slot[z];
     const int rg = tid / LPR, sub = tid % LPR;
     const char *vcz = (const char *)g.vc + (int64_t)z * g.slots * ROWB;
     const u32x4 vnw = *(const u32x4 *)((const char *)g.v_new + (int64_t)z * ROWB + sub * 16);
     float numax = 0.f;
-    for (int s = rg; s < live; s += RP) {
-        const u32x4 vw = s == fs ? vnw : *(const u32x4 *)(vcz + (int64_t)s * ROWB + sub * 16);
-        float vf[CH];
-        unpack<ESIZE>(vw, vf);
-        float nu = 0.f;
+    for (int sb = rg; sb < live; sb += U * RP) {
+        u32x4 vw[U];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) nu = fmaf(vf[c], vf[c], nu);
-        nu = reduce_lanes<1, LPR>(nu, OpSum{});  // over the lanes of the row
-        if (sub == 0) ws_nu[(int64_t)z * live + s] = nu;
-        numax = fmaxf(numax, nu);
+        for (int u = 0; u < U; ++u)
+            vw[u] = *(const u32x4 *)(vcz + (int64_t)min(sb + u * RP, live - 1) * ROWB + sub * 16);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = sb + u * RP;
+            float vf[CH];
+            unpack<ESIZE>(s == fs ? vnw : vw[u], vf);
+            float nu = 0.f;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) nu = fmaf(vf[c], vf[c], nu);
+            nu = reduce_lanes<1, LPR>(nu, OpSum{});  // over the lanes of the row
+            if (s < live) {
+                if (sub == 0) ws_nu[(int64_t)z * live + s] = nu;
+                numax = fmaxf(numax, nu);
+            }
+        }
     }
     numax = wave_max(numax);
     if (lane == 0) s_max[wave] = numax;
     __syncthreads();
-    if (tid == 0) ws_numax[z] = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < kDecWaves; ++w) numax = fmaxf(numax, s_max[w]);
+        ws_numax[z] = numax;
+    }
 }
 
 // ---- few problems: split the slots of a head over several workgroups ----
@@ -511,7 +530,7 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
     extern __shared__ __attribute__((aligned(16))) float dsm[];
     float *s_p = dsm;                 // [G][sps] dots, then unnormalised probabilities
     float *s_o = dsm + G * sps;       // [4 waves][G][D]
-    __shared__ float s_red[4][G];
+    __shared__ float s_red[4][2 * G];
 
     const int split = blockIdx.x, z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = z / g.Hkv, h = z % g.Hkv;
@@ -592,21 +611,27 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
         mx[gi] = fmaxf(fmaxf(s_red[0][gi], s_red[1][gi]), fmaxf(s_red[2][gi], s_red[3][gi]));
     __syncthreads();
     const float c_out = kLog2e * rsqrtf((float)D);
-    float zo[G];
+    const float c_sc = ESIZE == 2 ? row_scale_log2_f32(g.scale_mode, g.fixed_scale, g.lambda_floor,
+                                                       g.logical_pos, g.budget, D)
+                                  : row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor,
+                                                   g.logical_pos, g.budget, D);
+    float zo[G], zs[G];  // sums of the output and of the score softmax over the range
 #pragma unroll
-    for (int gi = 0; gi < G; ++gi) zo[gi] = 0.f;
+    for (int gi = 0; gi < G; ++gi) zo[gi] = zs[gi] = 0.f;
     for (int s = s0 + tid; s < s1; s += 256) {
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
-            const float e = fast_exp2((s_p[gi * sps + s - s0] - mx[gi]) * c_out);
+            const float d = s_p[gi * sps + s - s0] - mx[gi];
+            const float e = fast_exp2(d * c_out);
             s_p[gi * sps + s - s0] = e;
             zo[gi] += e;
+            zs[gi] += fast_exp2(d * c_sc);
         }
     }
 #pragma unroll
     for (int gi = 0; gi < G; ++gi) {
-        const float a = wave_sum(zo[gi]);
-        if (lane == 0) s_red[wave][gi] = a;
+        const float a = wave_sum(zo[gi]), c = wave_sum(zs[gi]);
+        if (lane == 0) { s_red[wave][2 * gi] = a; s_red[wave][2 * gi + 1] = c; }
     }
     __syncthreads();
     float o[G][CH];
@@ -645,144 +670,303 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
             if (lane < LPR) s_o[(wave * G + gi) * D + sub * CH + c] = v;
         }
     __syncthreads();
-    float *part = ws_part + ((int64_t)z * nsplit + split) * G * (D + 2);
+    float *part = ws_part + ((int64_t)z * nsplit + split) * G * (D + kPartStats);
     for (int t = tid; t < G * D; t += 256) {
         const int gi = t / D, c = t % D;
-        part[gi * (D + 2) + c] = s_o[(0 * G + gi) * D + c] + s_o[(1 * G + gi) * D + c] +
+        part[gi * (D + kPartStats) + c] = s_o[(0 * G + gi) * D + c] + s_o[(1 * G + gi) * D + c] +
                                  s_o[(2 * G + gi) * D + c] + s_o[(3 * G + gi) * D + c];
     }
     if (tid < G) {
-        part[tid * (D + 2) + D] = mx[tid];
-        part[tid * (D + 2) + D + 1] = s_red[0][tid] + s_red[1][tid] + s_red[2][tid] + s_red[3][tid];
+        float m = mx[0];
+#pragma unroll
+        for (int gi = 1; gi < G; ++gi) m = tid == gi ? mx[gi] : m;
+        float t[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            t[c] = s_red[0][2 * tid + c] + s_red[1][2 * tid + c] + s_red[2][2 * tid + c] + s_red[3][2 * tid + c];
+        *(f32x4 *)(part + tid * (D + kPartStats) + D) = f32x4{m, t[0], t[1], 0.f};
+    }
+}
+
+// Stage 1 on the matrix core (bf16): with several query heads per KV head the vector-ALU dots
+// and weighted sums above cost more than the key and value streams (whole step
+// at 8 queries per head, d = 128: 8 heads x 100 slots 20.9 -> 10.9 us, 64 x 1500 42.0 -> 22.0).
+// Workgroup = (slot range, batch, KV head) as above; each of its four waves takes blocks of 32
+// slots on its own, and the waves meet once, at the end:
+//   S = K Q^T       v_mfma_f32_32x32x16_bf16, slots on M, the query heads on N (columns past the
+//                   last head repeat it and are never used); key fragments straight from global
+//                   memory, query fragments in registers
+//   softmax         a column's 32 dots sit in lanes l and l + 32: one reference per column, moved
+//                   only when a block's maximum exceeds it, as a raw dot
+//   O^T += V^T P^T  the accumulator layout hands a lane the probabilities of exactly the slots it
+//                   supplies as a B fragment; V^T fragments by transposing reads from the wave's
+//                   copy of the block's value rows in LDS.  A probability goes in as the sum of two
+//                   bf16 numbers (2^-17 relative), so that the output keeps the precision
+//                   of fp32 probabilities.
+// The next block's keys are requested as soon as the dots are formed and its value rows as soon as
+// this block's are in LDS.  The free slot's rows are read like any other; the block that holds
+// it takes the new token's rows instead (kept in LDS by every wave for itself) and writes them to
+// the cache.
+template <int D, int G>
+__global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g, int nsplit, int sps,
+                                                                   float *ws_w, float *ws_part) {
+    constexpr int LPR = D / 8, ROWB = D * 2, KS = D / 16, CB = D / 32, LD = D + 8;
+    constexpr int RPI = 64 / LPR, NI = 32 / RPI;  // value rows per load instruction, loads per block
+    __shared__ __attribute__((aligned(16))) __bf16 s_v[4][32 * LD];  // later the partial outputs
+    __shared__ __attribute__((aligned(16))) __bf16 s_new[4][2 * D];  // the new token's key and value rows
+    __shared__ float s_m[4][G], s_z[4][G], s_zs[4][G];
+    static_assert(4 * 32 * LD * 2 >= 4 * G * D * 4, "the partial outputs fit the value rows' LDS");
+
+    const int split = blockIdx.x, z = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = z / g.Hkv, h = z % g.Hkv;
+    const int live = g.budget + 1;
+    const int s0 = split * sps, s1 = min(live, s0 + sps);
+    const int col = lane & 31, hf = lane >> 5, sub = lane % LPR;
+    char *kcz = (char *)g.kc + (int64_t)z * g.slots * ROWB;
+    char *vcz = (char *)g.vc + (int64_t)z * g.slots * ROWB;
+
+    // everything the first block needs is requested before anything is used
+    bf16x8 qf[KS], a[KS];
+    u32x4 vw[NI];
+    auto request_keys = [&](int b0) {
+        const char *pr = kcz + (int64_t)min(b0 + col, s1 - 1) * ROWB + hf * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) a[ks] = *(const bf16x8 *)(pr + ks * 32);
+    };
+    auto request_values = [&](int b0) {
+#pragma unroll
+        for (int t = 0; t < NI; ++t)
+            vw[t] = *(const u32x4 *)(vcz + (int64_t)min(b0 + t * RPI + lane / LPR, s1 - 1) * ROWB + sub * 16);
+    };
+    const int fs = g.free_slot[z];
+    {
+        const char *pr = (const char *)g.q + ((int64_t)(b * g.Hq + h * G + min(col, G - 1))) * ROWB + hf * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(pr + ks * 32);
+    }
+    const u32x4 knw = *(const u32x4 *)((const char *)g.k_new + (int64_t)z * ROWB + sub * 16);
+    const u32x4 vnw = *(const u32x4 *)((const char *)g.v_new + (int64_t)z * ROWB + sub * 16);
+    request_keys(s0 + wave * 32);
+    request_values(s0 + wave * 32);
+    __bf16 *sv = s_v[wave], *snew = s_new[wave];
+    if (lane < LPR) {
+        *(u32x4 *)(snew + sub * 8) = knw;
+        *(u32x4 *)(snew + D + sub * 8) = vnw;
+    }
+
+    const float c_out = kLog2e * rsqrtf((float)D);
+    const float c_sc = row_scale_log2_f32(g.scale_mode, g.fixed_scale, g.lambda_floor, g.logical_pos,
+                                          g.budget, D);
+    // reference (raw dot), and this lane's sums of the output and the score softmax relative to it
+    float m = -INFINITY, zsum = 0.f, zsc = 0.f;
+    f32x16 O[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) O[cb][v] = 0.f;
+    for (int b0 = s0 + wave * 32; b0 < s1; b0 += 128) {
+        const bool has_new = fs >= b0 && fs < min(b0 + 32, s1);  // (wave-uniform)
+        if (has_new) {
+            if (b0 + col == fs) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) a[ks] = *(const bf16x8 *)(snew + ks * 16 + hf * 8);
+            }
+            if (lane < LPR) *(u32x4 *)(kcz + (int64_t)fs * ROWB + sub * 16) = *(const u32x4 *)(snew + sub * 8);
+        }
+        f32x16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], qf[ks], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        request_keys(min(b0 + 128, s1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        // lane: column col, slots b0 + 8 (v / 4) + 4 hf + v % 4
+        if (col < G) {
+            float *wp = ws_w + ((int64_t)z * live + b0 + 4 * hf) * G + col;  // [head][slot][query]
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + (v & 3);
+                if (b0 + 4 * hf + r < s1) wp[r * G] = acc[v];
+            }
+        }
+        if (b0 + 32 > s1) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (b0 + 4 * hf + 8 * (v >> 2) + (v & 3) >= s1) acc[v] = -INFINITY;
+        }
+        float bm = acc[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) bm = fmaxf(bm, acc[v]);
+        bm = combine_lane_xor<32>(bm, OpMax{});  // (a block has at least one slot: finite for finite dots)
+        const float mn = fmaxf(m, bm), corr = fast_exp2((m - mn) * c_out);
+        const float corr_sc = m == -INFINITY ? 0.f : fast_exp2((m - mn) * c_sc);
+        m = mn;
+        bf16x8 ph[2], pl[2];
+        float sum[2] = {0.f, 0.f}, sumsc[2] = {0.f, 0.f};
+        const bool ragged = b0 + 32 > s1;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = acc[8 * ks + e] - mn;
+                const float pr = fast_exp2(d * c_out);
+                sum[e & 1] += pr;
+                const float ps = fast_exp2(d * c_sc);
+                sumsc[e & 1] += ragged && d == -INFINITY ? 0.f : ps;  // (a scale of 0 times infinity)
+                const __bf16 hi = (__bf16)pr;
+                ph[ks][e] = hi;
+                pl[ks][e] = (__bf16)(pr - (float)hi);
+            }
+        zsum = zsum * corr + (sum[0] + sum[1]);
+        zsc = zsc * corr_sc + (sumsc[0] + sumsc[1]);
+        if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
+        }
+        // the value rows -> the wave's LDS copy (the new row stands in for the free slot's)
+#pragma unroll
+        for (int t = 0; t < NI; ++t) {
+            const int rin = t * RPI + lane / LPR;
+            u32x4 w = vw[t];
+            if (has_new && b0 + rin == fs) {
+                w = *(const u32x4 *)(snew + D + sub * 8);
+                *(u32x4 *)(vcz + (int64_t)fs * ROWB + sub * 16) = w;
+            }
+            *(u32x4 *)(sv + rin * LD + sub * 8) = w;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        request_values(min(b0 + 128, s1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const bf16x8 vf = lds_transposed_fragment(sv, LD, 16 * ks, 8, cb * 32, lane);
+                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph[ks], O[cb], 0, 0, 0);
+                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[ks], O[cb], 0, 0, 0);
+            }
+    }
+    // the waves' partials, each relative to its own reference, meet in LDS
+    zsum = combine_lane_xor<32>(zsum, OpSum{});
+    zsc = combine_lane_xor<32>(zsc, OpSum{});
+    if (lane < G) {
+        s_m[wave][lane] = m;
+        s_z[wave][lane] = zsum;
+        s_zs[wave][lane] = zsc;
+    }
+    __syncthreads();  // every wave is done with its value rows
+    // [4 waves][G][D], a head's channels permuted (XOR) so that the heads' rows, a multiple of the
+    // banks apart, do not meet in the same banks
+    float *s_o = (float *)&s_v[0][0];
+    if (col < G) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4)
+                *(f32x4 *)(s_o + (wave * G + col) * D + ((cb * 32 + 8 * v4 + 4 * hf) ^ (8 * col))) =
+                    f32x4{O[cb][4 * v4], O[cb][4 * v4 + 1], O[cb][4 * v4 + 2], O[cb][4 * v4 + 3]};
+    }
+    __syncthreads();
+    float *part = ws_part + ((int64_t)z * nsplit + split) * G * (D + kPartStats);
+    for (int t = tid; t < G * D; t += 256) {
+        const int gi = t / D, c = t % D;
+        const float M = fmaxf(fmaxf(s_m[0][gi], s_m[1][gi]), fmaxf(s_m[2][gi], s_m[3][gi]));
+        float o = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)  // (a wave without a block has m = -inf: factor 0)
+            o = fmaf(fast_exp2((s_m[w][gi] - M) * c_out), s_o[(w * G + gi) * D + (c ^ (8 * gi))], o);
+        part[gi * (D + kPartStats) + c] = o;
+        if (c == 0) {
+            float zt = 0.f, zst = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float dm = s_m[w][gi] - M;
+                zt = fmaf(fast_exp2(dm * c_out), s_z[w][gi], zt);
+                if (s_z[w][gi] > 0.f)  // (no block: nothing, not a scale of possibly 0 times infinity)
+                    zst = fmaf(fast_exp2(dm * c_sc), s_zs[w][gi], zst);
+            }
+            *(f32x4 *)(part + gi * (D + kPartStats) + D) = f32x4{M, zt, zst, 0.f};
+        }
     }
 }
 
 // Stage 2, two workgroups per (batch, KV head) that share nothing but their inputs: one
 // merges the partial outputs, the other updates the running scores from the stored dots
 // and picks the victim (side by side they take the time of the longer one).
+// Bound by latency: launch, one round trip for everything a thread needs, one barrier behind the
+// fold of the splits' statistics (wave w folds head w, one split per lane), and a second for the
+// victim.  The splits leave both softmax sums relative to their own maxima, so no thread walks
+// its slots twice.  (With the score sums formed here, a pass over all dots and a block
+// reduction more, the dots of eight heads did not fit a thread's registers: 12 us for this launch at G = 8, now
+// 3.6; steps of 8 heads x 100 slots, G = 1 8.9 -> 7.3 us.)
 constexpr int kMergeThreads = 1024;
+
+// N consecutive floats of a slot's dots
+template <int N>
+__device__ __forceinline__ void load_dots(const float *p, float (&w)[N]) {
+    constexpr int V = N % 4 == 0 ? 4 : N % 2 == 0 ? 2 : 1;  // (a slot's N floats are aligned to V)
+    typedef float vec __attribute__((ext_vector_type(V)));
+#pragma unroll
+    for (int i = 0; i < N; i += V) {
+        if constexpr (V == 1) {
+            w[i] = p[i];
+        } else {
+            const vec x = *(const vec *)(p + i);
+#pragma unroll
+            for (int c = 0; c < V; ++c) w[i + c] = x[c];
+        }
+    }
+}
 
 template <int ESIZE, int D, int G>
 __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeGeom g, int nsplit,
-                                                           const float *ws_w,
-                                                           const float *ws_part,
-                                                           const float *ws_nu,
-                                                           const float *ws_numax) {
+                                                                     const float *ws_w,
+                                                                     const float *ws_part,
+                                                                     const float *ws_nu,
+                                                                     const float *ws_numax) {
     static_assert(G * D <= kMergeThreads, "one output element per thread");
-    static_assert(kMaxDecodeSplit * G <= kMergeThreads, "one (split, head) statistic per thread");
-    __shared__ float s_pm[kMaxDecodeSplit][G], s_pz[kMaxDecodeSplit][G];
-    __shared__ float s_red[kMergeThreads / 64][G];
-    __shared__ unsigned long long s_key[kMergeThreads / 64];
-    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(kMaxDecodeSplit <= 64 && G <= kMergeThreads / 64, "wave = head, lane = split");
+    constexpr int NT = kMergeThreads, PS = D + kPartStats;
+    __shared__ float s_f[kMaxDecodeSplit][G];  // output role: weight of a split's partial output
+    __shared__ float s_max[G], s_rz[G];        // score role: maximum and reciprocal sum of a head
+    __shared__ unsigned long long s_key[NT / 64];
+    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = z / g.Hkv, h = z % g.Hkv;
     const int live = g.budget + 1;
-    float *fcz = g.fc + (int64_t)z * g.slots;
-    int32_t *posz = g.pos + (int64_t)z * g.slots;
-    const float *part = ws_part + (int64_t)z * nsplit * G * (D + 2);
-    const float c_out = kLog2e * rsqrtf((float)D);
-    const float c_sc = ESIZE == 2 ? row_scale_log2_f32(g.scale_mode, g.fixed_scale, g.lambda_floor,
-                                                       g.logical_pos, g.budget, D)
-                                  : row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor,
-                                                   g.logical_pos, g.budget, D);
-    // slots per thread and batch fetched together (fewer for wide groups: G dots per slot)
-    // slots per thread and batch (score role); splits whose outputs are requested up front
-    // (output role: fewer for wide groups, where every split's address takes registers)
-    constexpr int NT = kMergeThreads, U = 4, XB = G <= 4 ? 32 : 16;
+    const float *part = ws_part + (int64_t)z * nsplit * G * PS;
 
-    // Latency-bound like stage 1: every first-use load is requested here, before any result
-    // is needed - the free slot, the splits' statistics, the first batch of stored dots with
-    // their scores and positions (the free slot's stale entries are read like any other and
-    // replaced afterwards), and this thread's output element of the first XB splits.
-    const int fs = g.free_slot[z];
-    float my_pm = -INFINITY, my_pz = 0.f;
-    if (tid < nsplit * G) {
-        my_pm = part[tid * (D + 2) + D];  // tid = split * G + head
-        my_pz = part[tid * (D + 2) + D + 1];
-    }
-    // The score role goes through the query heads in groups of at most four (a slot's dots
-    // lie together in the workspace: one 16-byte load per slot and whole group): with more
-    // heads at once the per-head copies of four slots do not fit a thread of this workgroup.
-    constexpr int GH = G < 4 ? G : 4, NG = (G + GH - 1) / GH;
-    float wr[U][GH], fr[U], nur[U];
-    int pr[U];
-    // dots of head group `grp` (heads grp * GH ..; past G: -inf) of this thread's U slots
-    auto fetch_dots = [&](int base, int grp) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int s = base + tid + u * NT;
-            const bool ok = s < live;
-            // (live * G floats of a head start 16-byte aligned when G is a multiple of four:
-            // the workspace is 256-byte aligned)
-            const float *wp = ws_w + ((int64_t)z * live + (ok ? s : 0)) * G + grp * GH;
-            if constexpr (G % 4 == 0) {
-                const f32x4 w4 = *(const f32x4 *)wp;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) wr[u][c] = ok ? w4[c] : -INFINITY;
-            } else {
-#pragma unroll
-                for (int c = 0; c < GH; ++c)
-                    wr[u][c] = ok && grp * GH + c < G ? wp[grp * GH + c < G ? c : 0] : -INFINITY;
-            }
-        }
-    };
-    auto fetch = [&](int base) {  // the first group's dots, the scores, positions, value norms
-        fetch_dots(base, 0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int s = base + tid + u * NT;
-            const bool ok = s < live;
-            fr[u] = ok ? fcz[s] : 0.f;
-            pr[u] = ok ? posz[s] : 0x7fffffff;
-            nur[u] = (ok && g.value_prior) ? ws_nu[(int64_t)z * live + s] : 0.f;
-        }
-    };
-    auto patch_free_slot = [&](int base) {  // the new token: score 0, position logical_pos - 1
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (base + tid + u * NT == fs) {
-                fr[u] = 0.f;
-                pr[u] = g.logical_pos - 1;
-            }
-    };
-    // The splits' statistics go to LDS and every wave folds the maxima by itself (one split
-    // per lane).  (Written out in both roles, so that neither role's registers stay live
-    // through the other's code: together they do not fit a thread of this workgroup.)
-    auto fold_maxima = [&](float (&mx)[G]) {
-        if (tid < nsplit * G) {
-            s_pm[tid / G][tid % G] = my_pm;
-            s_pz[tid / G][tid % G] = my_pz;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) mx[gi] = wave_max(lane < nsplit ? s_pm[lane][gi] : -INFINITY);
-    };
+    // the statistics of this wave's head, one split per lane: (maximum, output sum, score sum)
+    f32x4 st = {-INFINITY, 0.f, 0.f, 0.f};
+    if (wave < G && lane < nsplit) st = *(const f32x4 *)(part + (lane * G + wave) * PS + D);
+
     if (blockIdx.y == 0) {  // (workgroup-uniform) the attention output
+        // splits whose outputs are requested up front (the rest behind the barrier)
+        constexpr int XB = G <= 4 ? 32 : 16;
         const int ogi = tid / D, oc = tid % D;  // this thread's output element (tid < G * D)
         float x[XB];
 #pragma unroll
         for (int u = 0; u < XB; ++u)
-            x[u] = (tid < G * D && u < nsplit) ? part[(u * G + ogi) * (D + 2) + oc] : 0.f;
-        float mx[G];
-        fold_maxima(mx);
+            x[u] = (tid < G * D && u < nsplit) ? part[(u * G + ogi) * PS + oc] : 0.f;
+        if (wave < G) {
+            const float M = wave_max(st[0]);  // (every lane takes part)
+            const float f = lane < nsplit ? fast_exp2((st[0] - M) * (kLog2e * rsqrtf((float)D))) : 0.f;
+            const float den = wave_sum(st[1] * f);
+            s_f[lane][wave] = f / den;
+        }
+        __syncthreads();
         if (tid >= G * D) return;
-        float mxo = mx[0];  // this thread's head
-#pragma unroll
-        for (int gi = 1; gi < G; ++gi) mxo = ogi == gi ? mx[gi] : mxo;
-        float num = 0.f, den = 0.f;
+        float v = 0.f;
 #pragma unroll
         for (int u = 0; u < XB; ++u)
-            if (u < nsplit) {
-                const float sc = fast_exp2((s_pm[u][ogi] - mxo) * c_out);
-                num = fmaf(x[u], sc, num);
-                den = fmaf(s_pz[u][ogi], sc, den);
-            }
+            if (u < nsplit) v = fmaf(x[u], s_f[u][ogi], v);
 #pragma unroll 8
-        for (int sp = XB; sp < nsplit; ++sp) {
-            const float sc = fast_exp2((s_pm[sp][ogi] - mxo) * c_out);
-            num = fmaf(part[(sp * G + ogi) * (D + 2) + oc], sc, num);
-            den = fmaf(s_pz[sp][ogi], sc, den);
-        }
-        const float v = num / den;
+        for (int sp = XB; sp < nsplit; ++sp) v = fmaf(part[(sp * G + ogi) * PS + oc], s_f[sp][ogi], v);
         const int64_t oi = ((int64_t)(b * g.Hq + h * G + ogi)) * D + oc;
         if constexpr (ESIZE == 2)
             ((uint16_t *)g.out)[oi] = (uint16_t)f32_to_bf16_rne(v);
@@ -790,72 +974,63 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeGeom 
             ((float *)g.out)[oi] = v;
         return;
     }
+
+    // the first slots' dots, running scores and positions travel with the statistics (the free
+    // slot's stale entries are read like any other and replaced)
+    constexpr int U = G <= 4 ? 4 : 2;
+    float *fcz = g.fc + (int64_t)z * g.slots;
+    int32_t *posz = g.pos + (int64_t)z * g.slots;
+    const float *wz = ws_w + (int64_t)z * live * G;
+    float w[U][G], fr[U], nur[U];
+    int pr[U];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = min(base + tid + u * NT, live - 1);
+            load_dots<G>(wz + (int64_t)s * G, w[u]);
+            fr[u] = fcz[s];
+            pr[u] = posz[s];
+            nur[u] = g.value_prior ? ws_nu[(int64_t)z * live + s] : 0.f;
+        }
+    };
+    const int fs = g.free_slot[z];
     fetch(0);
-    float mx[G];
-    fold_maxima(mx);
-    // score softmax over all live slots, from the stored raw dots; four slots per thread
-    // and batch are fetched together so that the loads overlap
-    float zs[G];
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi) zs[gi] = 0.f;
-    // one batch and one head group: the values stay in registers for pass two
-    const bool keep = live <= U * NT && NG == 1;
-    for (int base = 0; base < live; base += U * NT) {
-        if (base) fetch(base);
-#pragma unroll
-        for (int grp = 0; grp < NG; ++grp) {
-            if (grp) fetch_dots(base, grp);
-            // (entries past the last slot are skipped, not fed as -inf: a scale of exactly 0
-            // would turn them into 0 * inf)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (base + tid + u * NT < live)
-#pragma unroll
-                    for (int c = 0; c < GH; ++c)
-                        if (grp * GH + c < G)
-                            zs[grp * GH + c] += fast_exp2((wr[u][c] - mx[grp * GH + c]) * c_sc);
+    const float ginv = g.value_prior ? prior_inverse(ws_numax[z]) : 1.f;
+    const float c_sc = ESIZE == 2 ? row_scale_log2_f32(g.scale_mode, g.fixed_scale, g.lambda_floor,
+                                                       g.logical_pos, g.budget, D)
+                                  : row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor,
+                                                   g.logical_pos, g.budget, D);
+    if (wave < G) {
+        const float M = wave_max(st[0]);
+        // (lanes past the last split have no maximum: 0, not a scale of possibly 0 times infinity)
+        const float zt = wave_sum(lane < nsplit ? st[2] * fast_exp2((st[0] - M) * c_sc) : 0.f);
+        if (lane == 0) {
+            s_max[wave] = M;
+            s_rz[wave] = 1.f / zt;
         }
     }
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-        const float a = wave_sum(zs[gi]);
-        if (lane == 0) s_red[wave][gi] = a;
-    }
     __syncthreads();
+    float mx[G], rz[G];
 #pragma unroll
     for (int gi = 0; gi < G; ++gi) {
-        float a = 0.f;
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) a += s_red[w][gi];
-        zs[gi] = 1.f / a;
+        mx[gi] = s_max[gi];
+        rz[gi] = s_rz[gi];
     }
-    const float ginv = g.value_prior ? prior_inverse(ws_numax[z]) : 1.f;
     unsigned long long best = ~0ull;
     int best_slot = -1;
     for (int base = 0; base < live; base += U * NT) {
-        if (!keep) fetch(base);
-        patch_free_slot(base);
-        float add[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) add[u] = 0.f;
-#pragma unroll
-        for (int grp = 0; grp < NG; ++grp) {
-            if (grp) fetch_dots(base, grp);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int c = 0; c < GH; ++c)
-                    if (grp * GH + c < G)
-                        add[u] += fast_exp2((wr[u][c] - mx[grp * GH + c]) * c_sc) * zs[grp * GH + c];
-        }
+        if (base) fetch(base);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int s = base + tid + u * NT;
             if (s >= live) continue;
-            if (g.value_prior) add[u] *= prior_factor(nur[u], ginv);
-            const float f = fr[u] + add[u];
+            float add = 0.f;
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) add = fmaf(fast_exp2((w[u][gi] - mx[gi]) * c_sc), rz[gi], add);
+            if (g.value_prior) add *= prior_factor(nur[u], ginv);
+            const float f = (s == fs ? 0.f : fr[u]) + add;  // the new token starts from 0
             fcz[s] = f;
-            const int ps = pr[u];
+            const int ps = s == fs ? g.logical_pos - 1 : pr[u];
             if (s == fs) posz[s] = ps;
             if (ps < g.logical_pos - g.recent && ps >= g.sink) {
                 const unsigned long long key =
@@ -867,13 +1042,16 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeGeom 
     const unsigned long long wbest = wave_min_key(best);  // every lane takes part
     if (lane == 0) s_key[wave] = wbest;
     __syncthreads();
-    unsigned long long gbest = s_key[0];
+    // positions are unique, so exactly one thread holds the victim: it retires the slot (only
+    // the waves' own candidates look at the other waves' keys)
+    if (best_slot >= 0 && best == wbest) {
+        unsigned long long gbest = s_key[0];
 #pragma unroll
-    for (int w = 1; w < kMergeThreads / 64; ++w) gbest = s_key[w] < gbest ? s_key[w] : gbest;
-    // positions are unique, so exactly one thread holds the victim: it retires the slot
-    if (best_slot >= 0 && best == gbest) {
-        posz[best_slot] = -1;
-        g.free_slot[z] = best_slot;
+        for (int wv = 1; wv < NT / 64; ++wv) gbest = s_key[wv] < gbest ? s_key[wv] : gbest;
+        if (best == gbest) {
+            posz[best_slot] = -1;
+            g.free_slot[z] = best_slot;
+        }
     }
 }
 
@@ -883,8 +1061,8 @@ static hipError_t launch_g(const DecodeGeom &g, const DecodePlan &pl, void *ws, 
     float *ws_nu = (float *)((char *)ws + pl.off_nu);
     float *ws_numax = ws_nu + (size_t)g.batch * g.Hkv * live;
     if (g.value_prior) {
-        hipLaunchKernelGGL((decode_value_norms_kernel<ESIZE, D>), dim3(g.batch * g.Hkv), dim3(256),
-                           0, st, g, ws_nu, ws_numax);
+        hipLaunchKernelGGL((decode_value_norms_kernel<ESIZE, D>), dim3(g.batch * g.Hkv),
+                           dim3(kDecThreads), 0, st, g, ws_nu, ws_numax);
         const hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
     }
@@ -895,8 +1073,12 @@ static hipError_t launch_g(const DecodeGeom &g, const DecodePlan &pl, void *ws, 
         dim3 g1(pl.nsplit, g.batch * g.Hkv), g2(g.batch * g.Hkv, 2);
 #define AHA_DECS(GG)                                                                             \
     {                                                                                            \
-        hipLaunchKernelGGL((decode_split_kernel<ESIZE, D, GG>), g1, dim3(256), smem1, st, g,     \
-                           pl.nsplit, pl.sps, ws_w, ws_part);                                    \
+        if constexpr (ESIZE == 2 && GG >= kDecodeSplitMfmaGroup)                                 \
+            hipLaunchKernelGGL((decode_split_mfma_kernel<D, GG>), g1, dim3(256), 0, st, g,       \
+                               pl.nsplit, pl.sps, ws_w, ws_part);                                \
+        else                                                                                     \
+            hipLaunchKernelGGL((decode_split_kernel<ESIZE, D, GG>), g1, dim3(256), smem1, st, g, \
+                               pl.nsplit, pl.sps, ws_w, ws_part);                                \
         /* the merge rewrites the cache state: never after a refused first launch */             \
         const hipError_t e1 = hipGetLastError();                                                 \
         if (e1 != hipSuccess) return e1;                                                         \

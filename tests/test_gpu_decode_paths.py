@@ -1,0 +1,90 @@
+"""One generation step over the ways a head's slots are divided (one workgroup per head; split on
+the vector ALU; split on the matrix core) at the edges of their tiles: one slot, a last block of
+a few slots, the new token in the first, the last and a middle slot."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(dtype, z, group, d, budget, seed):
+    import torch
+    from paper_2506_03762_amd import binding as B
+    rng = np.random.default_rng(seed)
+    live, n = budget + 1, 5 * budget + 7
+    recent, sink = min(5, budget // 2), 1 if budget > 12 else 0
+    p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0,
+                 budget=budget, recent=recent, sink=sink, dtype=dtype)
+    tdt = torch.float32 if dtype == B.AHA_F32 else torch.bfloat16
+    def dev(*shape):
+        return torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).to(tdt).cuda()
+    c = B.CompactCache.empty(p)
+    c.k.copy_(dev(*c.k.shape))
+    c.v.copy_(dev(*c.v.shape))
+    q, k, v = dev(1, z * group, d), dev(1, z, d), dev(1, z, d)
+    fs = rng.integers(0, live, z)
+    fs[:3] = [0, live - 1, live // 2][:z]
+    pos = np.stack([np.insert(rng.permutation(n - recent)[:budget - recent].tolist() +
+                              list(range(n - recent, n)), f, -1) for f in fs]).astype(np.int32)
+    score = np.exp(rng.standard_normal((z, live))).astype(np.float32)
+    c.pos[0, :, :live] = torch.from_numpy(pos).cuda()
+    c.scores[0, :, :live] = torch.from_numpy(score).cuda()
+    c.free_slot[0] = torch.from_numpy(fs.astype(np.int32)).cuda()
+    # the step in float64
+    K, V, Q = (t.double().cpu().numpy() for t in (c.k[0, :, :live], c.v[0, :, :live],
+                                                  q.reshape(z, group, d)))
+    rows = np.arange(z)
+    K[rows, fs], V[rows, fs] = k[0].double().cpu().numpy(), v[0].double().cpu().numpy()
+    dots = np.einsum("zgd,zsd->zgs", Q, K)
+    def softmax(x):
+        e = np.exp(x - x.max(-1, keepdims=True))
+        return e / e.sum(-1, keepdims=True)
+    lam = max(np.sqrt(2 * max(np.log((n + 1) / budget), 0) / d), d ** -0.5)
+    out = np.einsum("zgs,zsd->zgd", softmax(dots * d ** -0.5), V)
+    f = score.astype(np.float64)
+    f[rows, fs] = 0
+    f += softmax(dots * lam).sum(1)
+    where = pos.copy()
+    where[rows, fs] = n
+    got = torch.full((1, z * group, d), float("nan"), dtype=tdt, device="cuda")
+    ws = torch.full((max(256, B.workspace_bytes(p)),), 0xA5, dtype=torch.uint8, device="cuda")
+    B.aha_decode_step(p, q, k, v, c.k, c.v, c.scores, c.pos, c.free_slot, n + 1, got, ws)
+    got = got.double().cpu().numpy().reshape(z, group, d)
+    assert np.array_equal(c.k[0, :, :live].double().cpu().numpy(), K)
+    assert np.array_equal(c.v[0, :, :live].double().cpu().numpy(), V)
+    gf = c.scores[0, :, :live].double().cpu().numpy()
+    # fp32 sums of products of up to d terms: an absolute 1e-5 on logits of some tens
+    np.testing.assert_allclose(gf, f, rtol=1e-4, atol=1e-6)
+    for i in range(z):
+        free = (where[i] < n + 1 - recent) & (where[i] >= sink)
+        if not free.any():
+            continue
+        order = np.lexsort((-where[i], np.where(free, f[i], np.inf)))
+        victim = int(c.free_slot[0, i])
+        assert f[i, victim] <= f[i, order[0]] * (1 + 1e-4) and free[victim]
+        assert int(c.pos[0, i, victim]) == -1
+    return got, out
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("z,group", [(3, 1), (5, 3), (2, 4), (7, 5), (4, 8), (100, 2), (97, 8),
+                                     (130, 4), (128, 8)])
+@pytest.mark.parametrize("budget", [1, 30, 31, 127, 128, 330, 1030])
+def test_step_against_float64(dtype, d, z, group, budget):
+    from paper_2506_03762_amd import binding as B
+    got, out = _step(B.AHA_F32 if dtype == "f32" else B.AHA_BF16, z, group, d, budget,
+                     z * 1000 + budget + d)
+    rms = np.sqrt((out ** 2).mean(-1, keepdims=True))
+    if dtype == "f32":
+        assert (np.abs(got - out) <= 2e-5 * rms + 1e-5 * np.abs(out)).all()
+        return
+    # half a unit of the rounded output (bf16 has 8 significant bits: half a unit is at most 2^-8
+    # of the value), and the weights: 2^-17
+    # each where a probability is the sum of two bf16 numbers or fp32 (whenever slots are split),
+    # 2^-9 where it is one (one workgroup per head from 4 heads per group on), which averages out
+    # over the slots except when one of them carries the output
+    weights = 2.0 ** -8 if group >= 4 else 2.0 ** -15
+    assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + weights * 3 * rms + 1e-6).all()
+    if group >= 4 and z < 96 and budget > 200:  # split over workgroups: no 2^-9 weights
+        assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
