@@ -194,7 +194,12 @@ static PrefillPlan plan_prefill(const aha_params *p) {
 
 // Attention output of the observed rows: about 512 workgroups over (block of 32 rows, key
 // range, problem); the key ranges' partials go through the workspace.
-static WindowAttnPlan plan_window_attn(const aha_params *p) {
+// `may_widen`: five and more row blocks may share their keys in one workgroup of eight waves (one
+// per CU, so about 256 workgroups), which needs more scratch.  8 KV heads x 16384 keys, d = 128:
+// 6 blocks 48.8 -> 34.4 us, 9 (a second workgroup with one wave at work) 57.8 -> 48.5, 17 81.6 ->
+// 75.8; d = 64, where a step has half the products per byte read from LDS: 6 blocks 30.6 -> 26.8,
+// 11 40.1 -> 37.2, but 17 47.4 -> 59.1.
+static WindowAttnPlan plan_window_attn(const aha_params *p, bool may_widen = true) {
     WindowAttnPlan pl{};
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
     const int64_t Z = (int64_t)p->batch * p->n_kv_heads;
@@ -202,10 +207,11 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
     pl.nparts = 1;
     pl.nq = pl.n_blocks >= 2 ? 2 : 1;  // row blocks per workgroup
     if (p->dtype != AHA_BF16) return pl;  // fp32: one workgroup per row, no partials
-    const int64_t wg_keys = kP2Keys / 2;  // a workgroup step: four waves of 32 keys
+    pl.wide = may_widen && pl.n_blocks >= 5 && (p->head_dim == 128 || pl.n_blocks <= 12);
+    const int64_t wg_keys = pl.wide ? 64 : kP2Keys / 2;  // a workgroup step (four waves of 32 keys)
     const int64_t steps = (p->seq_len + wg_keys - 1) / wg_keys;
-    const int64_t groups = (pl.n_blocks + pl.nq - 1) / pl.nq;
-    int64_t want = (512 + Z * groups - 1) / (Z * groups);
+    const int64_t per_wg = pl.wide ? 8 : pl.nq, groups = (pl.n_blocks + per_wg - 1) / per_wg;
+    int64_t want = ((pl.wide ? 256 : 512) + Z * groups - 1) / (Z * groups);
     if (want > steps) want = steps;
     if (want > 64) want = 64;
     pl.nparts = (int)(want < 1 ? 1 : want);
@@ -419,7 +425,8 @@ int32_t aha_prefill_window_attention(const aha_params *p, const void *q, const v
         (rc = check_ptr("out", out, 16)))
         return rc;
     if (lse && (rc = check_ptr("lse", lse, 4))) return rc;
-    const WindowAttnPlan pl = plan_window_attn(p);
+    WindowAttnPlan pl = plan_window_attn(p);
+    if (pl.wide && workspace_bytes < pl.bytes) pl = plan_window_attn(p, false);
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     const int64_t Z = (int64_t)p->batch * p->n_kv_heads;
     const int64_t wgs = p->dtype == AHA_BF16 ? (Z * pl.nparts + 7) / 8 * 8 * pl.n_blocks

@@ -406,34 +406,254 @@ __global__ __launch_bounds__(256, 2) void window_attn_kernel(ScoreGeom g, int n_
     }
 }
 
+// ---- five and more blocks of rows: the workgroup's waves share the keys ----
+// With many rows per KV head the kernel above re-reads every key and value once per pair of row
+// blocks, and its waves, with two blocks' outputs in registers, have no room to request more than
+// one step ahead: it waits for memory half of the time.  Here a workgroup of eight waves owns
+// eight blocks of 32 rows, one per wave, and a range of keys; all waves work on the same 64
+// keys, whose rows go from global memory straight into LDS, kStages deep, so that each is
+// fetched once per 256 rows and up to three steps ahead.  A wave keeps its query fragments in
+// registers (they are used in every step) and its rows for the whole range, so the waves have
+// nothing to merge.  Per 64 keys a wave reads 32 KB of key and value fragments from LDS for 32
+// products, so LDS is as busy as the matrix core, and the two take turns: at 8 KV heads x 256 rows
+// x 32768 keys, 60.9 -> 50.5 us, of which the loads alone take 30 and the arithmetic on rows
+// already in LDS 46.  (Half of the waves adding their values half a step later, to overlap one
+// half's softmax with the other's products: 53.3.)
+template <int D>
+struct WideAttn {
+    static constexpr int WAVES = 8, KEYS = 64, CPR = D / 8, RPI = 64 / CPR;
+    static constexpr int NI = KEYS / RPI / WAVES;         // load instructions per wave for a step's keys (and values)
+    static constexpr int kStages = D == 128 ? 4 : 6;
+    static constexpr int half = KEYS * D * 2;             // bytes of a step's key rows
+    static constexpr size_t bytes = (size_t)kStages * 2 * half;
+    static_assert(KEYS % (RPI * WAVES) == 0 && bytes <= 160 * 1024, "whole instructions per wave, one CU's LDS");
+};
+
+template <int D>
+__global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, int n_blocks, int nparts,
+                                                                  int units, float *part_o,
+                                                                  float2 *part_ms) {
+    using A = WideAttn<D>;
+    constexpr int KS = D / 16, CB = D / 32, MB = 2, NI = A::NI, S = A::kStages;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+    // (groups of one (problem, key range) on one XCD, as above)
+    const int n_groups = (n_blocks + A::WAVES - 1) / A::WAVES;
+    const int id = (int)blockIdx.x, xcd = id % kXcds, t0 = id / kXcds;
+    const int grp = t0 % n_groups, u = (t0 / n_groups) * kXcds + xcd;
+    if (u >= units) return;
+    const int part = u % nparts, z = u / nparts;
+    const int b = z / g.Hkv, h = z % g.Hkv;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), col = lane & 31, hf = lane >> 5;
+    const RowMap rm{g.n, g.r, g.R, nullptr};
+    const int blk = grp * A::WAVES + wave;  // the wave's block of rows (may not exist)
+    const int rho0 = blk * 32;
+    const int end = rm.max_pos(grp * A::WAVES * 32, (grp + 1) * A::WAVES * 32) + 1;
+    const int steps = (end + A::KEYS - 1) / A::KEYS;
+    const int st0 = (int)((int64_t)part * steps / nparts), st1 = (int)((int64_t)(part + 1) * steps / nparts);
+    const int key_begin = st0 * A::KEYS, key_end = min(end, st1 * A::KEYS), nsteps = st1 - st0;
+    const bool mine = blk < n_blocks;
+    const int64_t pidx = ((int64_t)(z * nparts + part) * n_blocks + blk) * 32;
+    if (nsteps <= 0) {  // more ranges than these rows have key steps: neutral partials
+        if (mine) {
+            for (int i = lane; i < 32 * D; i += 64) part_o[pidx * D + i] = 0.f;
+            if (lane < 32) part_ms[pidx + lane] = make_float2(-INFINITY, 0.f);
+        }
+        return;
+    }
+    const __bf16 *kbase = (const __bf16 *)g.k + b * g.ks[0] + h * g.ks[1];
+    const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
+
+    // The wave's share of a step's rows -> stage st: instruction i = wave + 8 j covers RPI rows, lane
+    // -> row lane / CPR, position lane % CPR; the 16-byte chunks of a row are permuted by XOR on the
+    // way (keys: with row mod 8, so that eight lanes reading one chunk of eight rows meet eight
+    // bank groups; values: as above).  Rows past the range re-read its last one.  The loads
+    // are assembly and the waits for them by hand, for the reason given at ValueRequest; nothing
+    // else loads from global memory inside the loop.
+    const uint32_t lds0 = uniform((int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem);
+    const int lr = lane / A::CPR, lc = lane % A::CPR;
+    auto request = [&](int step, int st) {
+        const int kb = key_begin + step * A::KEYS;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int i = wave + A::WAVES * j, r = i * A::RPI + lr;
+            const int64_t row = min(kb + r, key_end - 1);
+            const __bf16 *ksrc = kbase + row * g.ks[2] + (lc ^ (r & 7)) * 8;
+            const __bf16 *vsrc = vbase + row * g.vs[2] + (lc ^ value_chunk_swizzle<D>(r)) * 8;
+            const uint32_t dst = lds0 + st * (2 * A::half) + i * 1024;
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                         :
+                         : "v"(ksrc), "s"(dst)
+                         : "memory");
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                         :
+                         : "v"(vsrc), "s"(dst + A::half)
+                         : "memory");
+        }
+    };
+    bf16x8 qf[KS];
+    {
+        const int rho = min(rho0 + col, g.R - 1), gi = rho / g.r, ii = rho - gi * g.r;
+        const __bf16 *pq = (const __bf16 *)g.q + b * g.qs[0] + (int64_t)(h * g.G + gi) * g.qs[1] +
+                           (int64_t)(g.n - g.r + ii) * g.qs[2] + hf * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(pq + ks * 16);
+        request(0, 0);
+        // (waited for here, together with the first step's rows, so that the compiler has no load
+        // of its own to wait for in the loop)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
+    }
+    const int pos = rm.pos(rho0 + col);  // -1 for rows past the last one: every key masked
+    const int bmin = rm.min_pos(rho0, rho0 + 32), bmax = mine ? rm.max_pos(rho0, rho0 + 32) : -1;
+    const float c_out = kLog2e * rsqrtf((float)D);
+    constexpr float kRefSlack = 8.f;  // log2 units
+
+    f32x16 O[CB];
+    float m = -INFINITY, s = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) O[cb][v] = 0.f;
+#pragma unroll
+    for (int i = 1; i < S - 1; ++i) request(i, i);
+    int st = 0;
+    for (int i = 0; i < nsteps; ++i, st = st + 1 == S ? 0 : st + 1) {
+        // this wave's loads of step i have landed (those of the S - 2 steps after it may be in
+        // flight); behind the barrier so have all waves', and all waves are done with step i - 1,
+        // whose stage the next request overwrites
+        __builtin_amdgcn_sched_barrier(0);
+        wait_loads<2 * NI * (S - 2)>();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        request(i + S - 1, st == 0 ? S - 1 : st - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int kb = key_begin + i * A::KEYS;
+        if (kb > bmax) continue;  // (wave-uniform)
+        const __bf16 *sK = (const __bf16 *)(smem + st * (2 * A::half));
+        f32x16 acc[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const bf16x8 a = *(const bf16x8 *)(sK + (mb * 32 + col) * D + ((2 * ks + hf) ^ (col & 7)) * 8);
+                acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], acc[mb], 0, 0, 0);
+            }
+        // causal limit and the ragged end of the key range
+        if (kb + A::KEYS - 1 > bmin || kb + A::KEYS > key_end) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int key = acc_key(kb, mb, v, lane);
+                    if (key > pos || key >= key_end) acc[mb][v] = -INFINITY;
+                }
+        }
+        float amax = -INFINITY;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) amax = fmaxf(amax, acc[mb][v]);
+        amax = combine_lane_xor<32>(amax, OpMax{});
+        // (the reference follows the running maximum lazily, as above; without the maximum, a step
+        // summed first and redone if its sum passes 2^kRefSlack, 52.0 us instead of 50.5)
+        const float bm = amax == -INFINITY ? -INFINITY : amax * c_out;
+        const float mn = bm > m + kRefSlack ? bm : m;
+        const float mref = mn == -INFINITY ? 0.f : mn;
+        const float corr = fast_exp2(m - mref);  // 0 while the column has seen no key
+        float sum[2] = {0.f, 0.f};
+        bf16x8 pf[MB][2];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float pr = fast_exp2(fmaf(acc[mb][8 * ks + e], c_out, -mref));
+                    sum[e & 1] += pr;
+                    pf[mb][ks][e] = (__bf16)pr;
+                }
+        s = s * corr + (sum[0] + sum[1]);
+        m = mn;
+        if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
+        }
+        const __bf16 *sV = sK + A::half / 2;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(value_fragment<D>(sV, mb, ks, cb, lane),
+                                                                    pf[mb][ks], O[cb], 0, 0, 0);
+    }
+    wait_loads<0>();  // (the last requests, past the range, write to LDS)
+    if (!mine) return;
+    const float sc = combine_lane_xor<32>(s, OpSum{});  // the column's sum over both half-waves
+    if (lane < 32) part_ms[pidx + col] = make_float2(m, sc);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; v += 4)
+            *(f32x4 *)(part_o + (pidx + col) * D + cb * 32 + 2 * v + 4 * hf) =
+                f32x4{O[cb][v], O[cb][v + 1], O[cb][v + 2], O[cb][v + 3]};
+}
+
 // Second launch: the key ranges' partials of every observed row -> the normalised output in
-// the inputs' dtype and the row's natural-log normaliser.  256 / D rows per workgroup.
+// the inputs' dtype and the row's natural-log normaliser.  A thread takes four channels of a row,
+// 1024 / D rows per workgroup; sixteen ranges' loads in flight at once (bound by their latency:
+// 8 heads x 256 rows, 32 ranges: 10.4 us with one channel per
+// thread and eight ranges in flight, 8.3 so).
 template <int D>
 __global__ __launch_bounds__(256) void window_attn_merge_kernel(ScoreGeom g, int n_blocks,
                                                                 int nparts, const float *part_o,
                                                                 const float2 *part_ms,
                                                                 uint16_t *out, float *lse) {
-    const int z = blockIdx.y, rho = blockIdx.x * (256 / D) + threadIdx.x / D, ch = threadIdx.x % D;
+    constexpr int TPR = D / 4, U = 16;
+    const int z = blockIdx.y, rho = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, ch = threadIdx.x % TPR * 4;
     if (rho >= g.R) return;
     const int b = z / g.Hkv, h = z % g.Hkv;
-    const int nbk = rho / 32, q = rho % 32;
-    // (the loads of several key ranges in flight at once: the launch is bound by their latency)
-    float M = -INFINITY;
-#pragma unroll 8
-    for (int p = 0; p < nparts; ++p)
-        M = fmaxf(M, part_ms[((int64_t)(z * nparts + p) * n_blocks + nbk) * 32 + q].x);
-    float o = 0.f, ssum = 0.f;
-#pragma unroll 8
-    for (int p = 0; p < nparts; ++p) {
-        const int64_t pi = ((int64_t)(z * nparts + p) * n_blocks + nbk) * 32 + q;
-        const float2 ms = part_ms[pi];
-        const float f = exp2f(ms.x - M);  // (every row sees key 0: M is finite)
-        o = fmaf(f, part_o[pi * D + ch], o);
-        ssum = fmaf(f, ms.y, ssum);
+    const int64_t p0 = ((int64_t)z * nparts * n_blocks + rho / 32) * 32 + rho % 32, step = (int64_t)n_blocks * 32;
+    float M = -INFINITY, ssum = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int pb = 0; pb < nparts; pb += U) {
+        f32x4 x[U];
+        float2 ms[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // (past the last range: it again, dropped below)
+            const int64_t pi = p0 + min(pb + u, nparts - 1) * step;
+            ms[u] = part_ms[pi];
+            x[u] = *(const f32x4 *)(part_o + pi * D + ch);
+        }
+        float bm = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u) bm = fmaxf(bm, ms[u].x);
+        const float mref = bm == -INFINITY ? 0.f : bm;  // (ranges without a key for this row)
+        const float f0 = exp2f(M - mref);
+        M = bm;
+        ssum *= f0;
+        o *= f0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float f = pb + u < nparts ? exp2f(ms[u].x - mref) : 0.f;
+            ssum = fmaf(f, ms[u].y, ssum);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = fmaf(f, x[u][c], o[c]);
+        }
     }
     const int gi = rho / g.r, ii = rho - gi * g.r;
     const int64_t row = ((int64_t)b * g.Hq + h * g.G + gi) * g.r + ii;
-    out[row * D + ch] = (uint16_t)f32_to_bf16_rne(o / ssum);
+    const uint2 packed = {pack_bf16(o[0] / ssum, o[1] / ssum), pack_bf16(o[2] / ssum, o[3] / ssum)};
+    *(uint2 *)(out + row * D + ch) = packed;
     if (lse && ch == 0) lse[row] = (M + log2f(ssum)) * 0.69314718055994531f;
 }
 
@@ -507,6 +727,16 @@ __global__ __launch_bounds__(256) void f32_window_attn_kernel(ScoreGeom g, float
 }
 
 // ---------------------------------------------------------------- launch --
+template <int D>
+static hipError_t launch_merge(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
+                               float *lse, hipStream_t st) {
+    const int rows_per_wg = 1024 / D;
+    hipLaunchKernelGGL(window_attn_merge_kernel<D>, dim3((g.R + rows_per_wg - 1) / rows_per_wg, g.batch * g.Hkv),
+                       dim3(256), 0, st, g, pl.n_blocks, pl.nparts, (const float *)ws,
+                       (const float2 *)((char *)ws + pl.off_ms), (uint16_t *)out, lse);
+    return hipGetLastError();
+}
+
 template <int D, int NQ>
 static hipError_t launch_attn_t(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                 float *lse, hipStream_t st) {
@@ -526,16 +756,31 @@ static hipError_t launch_attn_t(const ScoreGeom &g, const WindowAttnPlan &pl, vo
                        g, pl.n_blocks, pl.nparts, units, part_o, part_ms);
     const hipError_t e1 = hipGetLastError();
     if (e1 != hipSuccess) return e1;
-    const int rows_per_wg = 256 / D;
-    hipLaunchKernelGGL(window_attn_merge_kernel<D>, dim3((g.R + rows_per_wg - 1) / rows_per_wg, Z),
-                       dim3(256), 0, st, g, pl.n_blocks, pl.nparts, part_o, part_ms,
-                       (uint16_t *)out, lse);
-    return hipGetLastError();
+    return launch_merge<D>(g, pl, ws, out, lse, st);
+}
+
+template <int D>
+static hipError_t launch_attn_wide(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
+                                   float *lse, hipStream_t st) {
+    using A = WideAttn<D>;
+    static DeviceOnce once;
+    const hipError_t ea = device_once(once, [] {
+        return hipFuncSetAttribute((const void *)window_attn_wide_kernel<D>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)A::bytes);
+    });
+    if (ea != hipSuccess) return ea;
+    const int units = g.batch * g.Hkv * pl.nparts, n_groups = (pl.n_blocks + A::WAVES - 1) / A::WAVES;
+    const int64_t wgs = (int64_t)((units + kXcds - 1) / kXcds) * kXcds * n_groups;
+    hipLaunchKernelGGL(window_attn_wide_kernel<D>, dim3((unsigned)wgs), dim3(512), A::bytes, st, g,
+                       pl.n_blocks, pl.nparts, units, (float *)ws, (float2 *)((char *)ws + pl.off_ms));
+    const hipError_t e1 = hipGetLastError();
+    return e1 != hipSuccess ? e1 : launch_merge<D>(g, pl, ws, out, lse, st);
 }
 
 template <int D>
 static hipError_t launch_attn_d(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                 float *lse, hipStream_t st) {
+    if (pl.wide) return launch_attn_wide<D>(g, pl, ws, out, lse, st);
     return pl.nq == 2 ? launch_attn_t<D, 2>(g, pl, ws, out, lse, st)
                       : launch_attn_t<D, 1>(g, pl, ws, out, lse, st);
 }
