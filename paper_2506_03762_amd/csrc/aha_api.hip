@@ -132,7 +132,7 @@ static ScoreGeom make_geom(const aha_params *p, const void *q, const void *k, co
 }
 
 // Workspace layout of aha_prefill_scores.
-static PrefillPlan plan_prefill(const aha_params *p) {
+static PrefillPlan plan_prefill(const aha_params *p, bool may_f32_mfma = true) {
     PrefillPlan pl{};
     const int G = p->n_q_heads / p->n_kv_heads;
     const int64_t R = (int64_t)G * p->window;
@@ -167,6 +167,18 @@ static PrefillPlan plan_prefill(const aha_params *p) {
         pl.chunk_keys = n;
         pl.nchunks = 1;
         pl.p2_keys = kP2Keys;
+        // The matrix core from this many (row, key) pairs on; below, the vector ALU's smaller
+        // pieces of work are done sooner.  Both passes, d = 64: 262 K pairs (8 heads x 64 rows x
+        // 512 keys) 14.3 us against 14.1, 805 K 15.5 against 28.2, 18 M 112 against 147;
+        // d = 128: 33 K 18.8 against 13.3, 94 K 27.6 against 33.0, 6.3 M 85 against 123.
+        pl.f32_mfma = may_f32_mfma && (double)pl.Z * R * n >= (p->head_dim == 128 ? 9e4 : 4e5);
+        if (pl.f32_mfma) {
+            const int64_t units = pl.Z * ((R + 31) / 32), steps = (n + 127) / 128;
+            int64_t want = (512 + units - 1) / units;
+            if (want > steps) want = steps;
+            if (want > 16) want = 16;  // (every pass-2 wave folds them)
+            pl.nchunks = (int)want;
+        }
     }
     size_t off = 0;
     pl.off_rowL = off;  // fp32 path: log-sum-exp of every observed row
@@ -175,6 +187,8 @@ static PrefillPlan plan_prefill(const aha_params *p) {
     pl.off_partial = off;
     if (p->dtype == AHA_BF16)
         off = align_up(off + sizeof(float) * (size_t)pl.Z * rows * pl.nchunks, 256);
+    else if (pl.f32_mfma)
+        off = align_up(off + 2 * sizeof(float) * (size_t)pl.Z * ((R + 31) / 32 * 32) * pl.nchunks, 256);
     pl.off_partial_mean = off;  // aha_prefill_row_stats: per-chunk mean scaled logit
     if (p->dtype == AHA_BF16)
         off = align_up(off + sizeof(float) * (size_t)pl.Z * rows * pl.nchunks, 256);
@@ -352,7 +366,8 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
         return rc;
     if (with_lse && (rc = check_ptr("lse", lse, 4))) return rc;
     if (p->value_prior && (rc = check_ptr("v", v, 16))) return rc;
-    const PrefillPlan pl = plan_prefill(p);
+    PrefillPlan pl = plan_prefill(p);
+    if (pl.f32_mfma && workspace_bytes < pl.bytes) pl = plan_prefill(p, false);
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     // the bf16 score launches are one-dimensional over all their workgroups
     const int64_t score_wgs = (int64_t)pl.Z * ((pl.n_qtiles + 1) / 2) * pl.nchunks;
@@ -450,7 +465,7 @@ int32_t aha_prefill_row_stats(const aha_params *p, const void *q, const void *k,
     if (!lse && !entropy) return fail(AHA_ERR_INVALID_ARG, "lse and entropy are both null");
     if ((lse && (rc = check_ptr("lse", lse, 4))) || (entropy && (rc = check_ptr("entropy", entropy, 4))))
         return rc;
-    const PrefillPlan pl = plan_prefill(p);
+    const PrefillPlan pl = plan_prefill(p, false);  // (the fp32 statistics stay in the vector ALU)
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     const int64_t score_wgs = (int64_t)pl.Z * ((pl.n_qtiles + 1) / 2) * pl.nchunks;
     if (score_wgs > (int64_t)1 << 30)

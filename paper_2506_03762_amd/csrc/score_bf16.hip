@@ -570,48 +570,6 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
 }
 
 // ---------------------------------------------------------------- pass 2 --
-// Sum of 16 per-lane values over the 32 lanes of each half-wave by recursive
-// halving: after the call lane l holds the total of element
-// v = 8*bit4(l) + 4*bit3(l) + 2*bit2(l) + bit1(l)   (both lanes of a pair hold it).
-__device__ __forceinline__ float fold16_over32(const f32x16 &xv, int lane) {
-    // The elements go through an opaque move first: otherwise the compiler turns
-    // "lane-dependent choice between two elements" into a dynamically indexed
-    // vector access, which costs a 16-way compare/select chain per element.
-    float x[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        x[t] = xv[t];
-        asm volatile("" : "+v"(x[t]));
-    }
-    // lanes ^ 16: v_permlane16_swap exchanges the odd 16-lane rows of its first operand with
-    // the even rows of its second, so the two results are (own, partner's) copies of
-    // element t in the even rows and of element t + 8 in the odd rows
-    float a[8], b4[4], c2[2];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[t]),
-                                                        __float_as_uint(x[t + 8]), false, false);
-        a[t] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    bool hi = lane & 8;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const float send = hi ? a[t] : a[t + 4], keep = hi ? a[t + 4] : a[t];
-        b4[t] = keep + from_lane_xor<8>(send);
-    }
-    hi = lane & 4;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const float send = hi ? b4[t] : b4[t + 2], keep = hi ? b4[t + 2] : b4[t];
-        c2[t] = keep + from_lane_xor<4>(send);
-    }
-    hi = lane & 2;
-    const float send = hi ? c2[0] : c2[1], keep = hi ? c2[1] : c2[0];
-    float d = keep + from_lane_xor<2>(send);
-    d += from_lane_xor<1>(d);
-    return d;
-}
-
 // Log2-sum-exp2 of one query row from the per-chunk log2-sum-exp2 values that pass 1 left.
 // A batch of values is requested at once (request), so that it travels together with the
 // other loads of the tile set-up, and merged later (merge) into the running (M, sum) with

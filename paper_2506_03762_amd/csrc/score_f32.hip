@@ -1,5 +1,5 @@
-// fp32 eviction scores (Sec. 4.1 - 4.3; Alg. 1 Prefill), plain vector-ALU
-// kernels.  This is the small-problem, high-accuracy path (fp32 Q/K/V); the
+// fp32 eviction scores (Sec. 4.1 - 4.3; Alg. 1 Prefill), vector-ALU kernels for small problems and
+// matrix-core kernels for larger ones.  This is the small-problem, high-accuracy path (fp32 Q/K/V); the
 // bf16 path in score_bf16.hip carries the throughput.
 //
 // Pass 1: a workgroup finds max_j and log2-sum-exp2 of t_ij = s_i * log2(e) * (Q_i . K_j) over
@@ -17,6 +17,7 @@
 // 32 rows, head_dim 64) is bound by latency, and one thread per key gave it four workgroups that
 // each walked all rows.  Measured there: pass 2 25.5 -> 5.5 us, pass 1 and the prior (two
 // launches, 7.2 + 4.5 us) -> 5.6 us.
+#include "score_tile.h"
 #include "value_tile.h"
 
 namespace aha {
@@ -228,6 +229,215 @@ __global__ __launch_bounds__(256) void f32_pass2_kernel(ScoreGeom g, const float
     }
 }
 
+// ---- larger problems: the dots on the matrix core ----
+// v_mfma_f32_32x32x2_f32, keys on M and query rows on N as in score_bf16.hip: fp32 products and
+// sums at twice the vector ALU's rate, and none of the quads' exchanges or of their LDS reads per
+// product.  A lane holds the 16-byte chunks 2 i + lane / 32 of its row; element e of chunk i of the
+// two half-waves is one contraction step (channels 8 i + e and 8 i + 4 + e).  The steps are dealt to
+// eight accumulators, so that no sum is a longer chain (D / 8 products) than in the kernels above
+// and the rounding error stays theirs
+// (against float64, 32 heads x 256 rows x 2206 keys, d = 64: 1.5e-7 of the scores' norm, 2.1e-7 there).
+// Both passes of that problem 147 -> 112 us, at d = 128 258 -> 189; 32 heads x 128 rows x 1108
+// keys, d = 128, 110 -> 73.
+template <int D>
+__device__ __forceinline__ f32x16 f32_block_dots(const f32x4 (&a)[D / 8], const float *sq) {
+    f32x16 acc[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+        const f32x4 q = *(const f32x4 *)(sq + 8 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[(4 * i + e) & 7] =
+                __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], q[e], acc[(4 * i + e) & 7], 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        acc[0][v] = ((acc[0][v] + acc[1][v]) + (acc[2][v] + acc[3][v])) +
+                    ((acc[4][v] + acc[5][v]) + (acc[6][v] + acc[7][v]));
+    return acc[0];
+}
+// key rows of a block of 32 from kb on; past the last key: the last one (its results are dropped)
+template <int D>
+__device__ __forceinline__ void f32_load_keys(const float *kbase, int64_t stride, int kb, int last,
+                                              int lane, f32x4 (&a)[D / 8]) {
+    const float *row = kbase + (int64_t)min(kb + (lane & 31), last) * stride + 4 * (lane >> 5);
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) a[i] = *(const f32x4 *)(row + 8 * i);
+}
+constexpr int f32_ld(int d) { return d + 4; }  // padded row of a query block in LDS (floats)
+
+// THREADS lanes bring the 32 query rows from rho0 on (past the last one: the last) to LDS; request
+// and commit apart, so that whatever else the block needs travels with them
+template <int D, int THREADS>
+struct F32QueryBlock {
+    static constexpr int CPR = D / 4, N = 32 * CPR / THREADS;
+    f32x4 w[N];
+    __device__ __forceinline__ void request(const ScoreGeom &g, const RowMap &rm, int b, int h,
+                                            int rho0, int t0) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int t = t0 + u * THREADS, rho = min(rho0 + t / CPR, g.R - 1);
+            w[u] = *(const f32x4 *)((const float *)g.q + b * g.qs[0] +
+                                    (int64_t)(h * g.G + rm.head(rho)) * g.qs[1] +
+                                    (int64_t)rm.pos(rho) * g.qs[2] + 4 * (t % CPR));
+        }
+    }
+    __device__ __forceinline__ void commit(int t0, float *sq) const {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int t = t0 + u * THREADS;
+            *(f32x4 *)(sq + (t / CPR) * f32_ld(D) + 4 * (t % CPR)) = w[u];
+        }
+    }
+};
+
+// Pass 1: a workgroup takes 32 rows and one of nparts key ranges, its waves 32 keys in turn; each
+// row's maximum and sum over the range go to partial[problem][row block][range][row] (as a pair:
+// pass 2 forms exp2(t - maximum) / sum, free of the rounding of a log-sum-exp2 of some tens).
+// Workgroups past row_blocks * nparts take the value tiles.
+template <int D>
+__global__ __launch_bounds__(256, 2) void f32_mfma_pass1_kernel(ScoreGeom g, int row_blocks, int nparts,
+                                                                int n_vtiles, float *gamma,
+                                                                float *gblockmax, float2 *partial) {
+    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    if ((int)blockIdx.x >= row_blocks * nparts) {  // (workgroup-uniform)
+        value_prior_tile<4>(g, z, (int)blockIdx.x - row_blocks * nparts, n_vtiles, gamma, gblockmax, tid);
+        return;
+    }
+    const int b = z / g.Hkv, h = z % g.Hkv, rb = blockIdx.x / nparts, part = blockIdx.x % nparts;
+    const int rho = rb * 32 + (lane & 31);
+    const RowMap rm{g.n, g.r, g.R,
+                    g.rows ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
+    const float *kbase = (const float *)g.k + b * g.ks[0] + h * g.ks[1];
+    __shared__ __attribute__((aligned(16))) float s_q[32 * f32_ld(D)];
+    __shared__ float s_m[4][32], s_s[4][32];
+    F32QueryBlock<D, 256> qb;
+    qb.request(g, rm, b, h, rb * 32, tid);
+    const int pos = rm.pos(rho);  // -1 past the last row
+    const int end = rm.max_pos(rb * 32, rb * 32 + 32) + 1, steps = (end + 127) / 128;
+    const int k0 = (int)((int64_t)part * steps / nparts) * 128;
+    const int k1 = min(end, (int)((int64_t)(part + 1) * steps / nparts) * 128);
+    const float lam = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, max(pos, 0) + 1,
+                                     g.budget, g.d);
+    f32x4 a[D / 8];
+    f32_load_keys<D>(kbase, g.ks[2], k0 + wave * 32, max(k1, 1) - 1, lane, a);
+    qb.commit(tid, s_q);
+    __syncthreads();
+    const float *sq = s_q + (lane & 31) * f32_ld(D) + 4 * (lane >> 5);
+    float m = -INFINITY, s = 0.f;
+    for (int kb = k0 + wave * 32; kb < k1; kb += 128) {
+        if (kb >= k0 + 128) f32_load_keys<D>(kbase, g.ks[2], kb, k1 - 1, lane, a);
+        f32x16 t = f32_block_dots<D>(a, sq);
+        float mx = m;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int key = acc_key(kb, 0, v, lane);
+            t[v] = key <= pos && key < k1 ? t[v] * lam : -INFINITY;
+            mx = fmaxf(mx, t[v]);
+        }
+        const float mref = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[v] = exp2f(t[v] - mref);
+#pragma unroll
+        for (int o = 8; o; o >>= 1)
+#pragma unroll
+            for (int v = 0; v < o; ++v) t[v] += t[v + o];
+        s = fmaf(s, exp2f(m - mref), t[0]);
+        m = mx;
+    }
+    float u = 0.f;
+    merge_stat(m, s, u, __shfl_xor(m, 32), __shfl_xor(s, 32), 0.f);
+    if (lane < 32) { s_m[wave][lane] = m; s_s[wave][lane] = s; }
+    __syncthreads();
+    if (tid < 32) {
+        m = s_m[0][tid]; s = s_s[0][tid];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) merge_stat(m, s, u, s_m[w][tid], s_s[w][tid], 0.f);
+        // (-inf, 0 for a row that saw no key of the range)
+        partial[(((int64_t)z * row_blocks + rb) * nparts + part) * 32 + tid] = make_float2(m, s);
+    }
+}
+
+// Pass 2: a workgroup takes 4 / wpk blocks of 32 keys; wpk waves share one, the blocks of query rows
+// dealt among them.  `rowL`, when not null, holds the rows' normalisers ([problem][row]).
+template <int D>
+__global__ __launch_bounds__(256, 2) void f32_mfma_pass2_kernel(ScoreGeom g, int row_blocks, int nparts,
+                                                                int wpk, const float2 *partial,
+                                                                const float *rowL, const float *gamma,
+                                                                const float *gblockmax, int n_vtiles,
+                                                                float *scores) {
+    extern __shared__ __attribute__((aligned(16))) float s_q[];  // a query block per wave
+    __shared__ float s_acc[4][32];
+    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int b = z / g.Hkv, h = z % g.Hkv, kw = 4 / wpk;
+    const RowMap rm{g.n, g.r, g.R,
+                    g.rows ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
+    const float *kbase = (const float *)g.k + b * g.ks[0] + h * g.ks[1];
+    const int kb = ((int)blockIdx.x * kw + wave / wpk) * 32;
+    f32x4 a[D / 8];
+    f32_load_keys<D>(kbase, g.ks[2], kb, g.n - 1, lane, a);
+    float gm = 0.f;
+    if (g.value_prior)
+        for (int t = lane; t < n_vtiles; t += 64) gm = fmaxf(gm, gblockmax[z * n_vtiles + t]);
+    gm = wave_max(gm);
+    float *sq_wave = s_q + wave * 32 * f32_ld(D);
+    const float *sq = sq_wave + (lane & 31) * f32_ld(D) + 4 * (lane >> 5);
+    f32x16 col;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) col[v] = 0.f;
+    for (int rb = kb < g.n ? wave % wpk : row_blocks; rb < row_blocks; rb += wpk) {
+        if (rm.max_pos(rb * 32, rb * 32 + 32) < kb) continue;  // no row of the block sees these keys
+        F32QueryBlock<D, 64> qb;
+        qb.request(g, rm, b, h, rb * 32, lane);
+        const int rho = rb * 32 + (lane & 31), pos = rm.pos(rho);
+        float M, inv = 1.f;  // the row's reference and the reciprocal of its sum
+        if (rowL) {
+            M = rowL[(int64_t)z * g.R + min(rho, g.R - 1)];
+        } else {
+            const float2 *pl = partial + ((int64_t)z * row_blocks + rb) * nparts * 32 + (lane & 31);
+            M = pl[0].x;
+            float sum = pl[0].y;
+            for (int c = 1; c < nparts; ++c) {
+                const float2 e = pl[c * 32];
+                const float mn = fmaxf(M, e.x);
+                const float mref = mn == -INFINITY ? 0.f : mn;  // (ranges behind the row's last key)
+                sum = fmaf(sum, exp2f(M - mref), e.y * exp2f(e.x - mref));
+                M = mn;
+            }
+            inv = 1.f / sum;
+        }
+        const float lam = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, max(pos, 0) + 1,
+                                         g.budget, g.d);
+        // (the wave's own copy: no other wave reads it, and a wave's LDS accesses stay in order)
+        qb.commit(lane, sq_wave);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        const f32x16 t = f32_block_dots<D>(a, sq);
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float p = exp2f(fmaf(t[v], lam, -M)) * inv;
+            col[v] += acc_key(kb, 0, v, lane) <= pos ? p : 0.f;
+        }
+    }
+    const float tot = fold16_over32(col, lane);
+    const int my_v = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
+    if ((lane & 1) == 0) s_acc[wave][acc_key(0, 0, my_v, lane)] = tot;
+    __syncthreads();
+    const int j = (int)blockIdx.x * kw * 32 + tid;
+    if (tid < kw * 32 && j < g.n) {
+        float out = 0.f;
+        for (int w = 0; w < wpk; ++w) out += s_acc[tid / 32 * wpk + w][tid % 32];
+        if (g.value_prior) out = gm > 0.f ? out * (gamma[(int64_t)z * g.n + j] / gm) : out;  // all-zero values: no prior
+        scores[(int64_t)z * g.n + j] = out;
+    }
+}
+
 // Four rows / keys per quad once the small variants would put more than about eight workgroups
 // on every CU: from there the vector ALU bounds the passes and the spare factor four counts.
 constexpr int64_t kF32ManyWgs = 2048;
@@ -264,8 +474,39 @@ static void launch_pass2(const ScoreGeom &g, const PrefillPlan &pl, void *ws, fl
                            g, rowL, gamma, gbm, pl.n_vtiles, scores);
 }
 
+template <int D>
+static hipError_t launch_mfma(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores,
+                              hipStream_t st, hipEvent_t mid, bool have_lse) {
+    char *w = (char *)ws;
+    float *gamma = (float *)(w + pl.off_gamma), *gbm = (float *)(w + pl.off_gblockmax);
+    float2 *partial = (float2 *)(w + pl.off_partial);
+    constexpr size_t smem = (size_t)4 * 32 * f32_ld(D) * sizeof(float);
+    static DeviceOnce once;
+    const hipError_t ea = device_once(once, [] {
+        return hipFuncSetAttribute((const void *)f32_mfma_pass2_kernel<D>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    });
+    if (ea != hipSuccess) return ea;
+    const int rb = (g.R + 31) / 32;
+    if (!have_lse) {
+        hipLaunchKernelGGL(f32_mfma_pass1_kernel<D>, dim3(rb * pl.nchunks + (g.value_prior ? pl.n_vtiles : 0), pl.Z),
+                           dim3(256), 0, st, g, rb, pl.nchunks, pl.n_vtiles, gamma, gbm, partial);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (mid) (void)hipEventRecord(mid, st);
+    const int wpk = rb >= 4 ? 4 : rb >= 2 ? 2 : 1, keys = 4 / wpk * 32;
+    hipLaunchKernelGGL(f32_mfma_pass2_kernel<D>, dim3((g.n + keys - 1) / keys, pl.Z), dim3(256), smem, st, g,
+                       rb, pl.nchunks, wpk, partial, have_lse ? (const float *)(w + pl.off_rowL) : nullptr,
+                       gamma, gbm, pl.n_vtiles, scores);
+    return hipGetLastError();
+}
+
 hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores,
                             hipStream_t st, hipEvent_t mid, bool have_lse) {
+    if (pl.f32_mfma)
+        return g.d == 64 ? launch_mfma<64>(g, pl, ws, scores, st, mid, have_lse)
+                         : launch_mfma<128>(g, pl, ws, scores, st, mid, have_lse);
     // (with the caller's row normalisers the prior comes from launch_value_prior)
     if (!have_lse) {
         if (g.d == 64) launch_pass1<64>(g, pl, ws, g.value_prior, nullptr, nullptr, st);

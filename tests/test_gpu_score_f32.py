@@ -1,5 +1,6 @@
-"""fp32 scores where a workgroup takes four rows (row statistics) and 64 keys (column sums), the
-variants for problems with many workgroups; the small variants are covered by the tiny workload."""
+"""fp32 scores of problems large enough for the matrix core: ragged key and row blocks, one to many
+row blocks, given row normalisers, scratch too small for the key ranges' statistics (then the
+vector ALU's variants for many workgroups run); the small variants are covered by the tiny workload."""
 import pytest
 
 import oracle
@@ -8,6 +9,35 @@ from tests import harness as H
 from tests.harness import Opts
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("n,group,window", [(1601, 1, 32), (1633, 1, 33), (999, 3, 40), (600, 4, 90)])
+def test_matrix_core(head_dim, n, group, window):
+    """Also with the rows' normalisers given, and against the vector ALU on the same inputs."""
+    import torch
+    from paper_2506_03762_amd import binding as B
+    from paper_2506_03762_amd import workload
+    hkv, batch = 4, 2
+    w = synth.scaled(synth.C1, name="f32_mfma", batch=batch, n_q_heads=hkv * group, n_kv_heads=hkv,
+                     head_dim=head_dim, seq_len=n, window=window, budget=150, recent=20)
+    assert batch * hkv * group * window * n >= 4e5
+    inputs = synth.make_prefill(w)
+    gpu, ref = H.run_prefill_gpu(w, Opts(), inputs), H.run_prefill_oracle(w, Opts(), inputs)
+    H.assert_scores_close(gpu.scores, ref.scores, w, Opts())
+    H.assert_sets_match(gpu.idx, ref.idx, ref.extra["rank_scores"], w)
+    p = H.gpu_params(w)
+    q, k, v = (workload.to_device(x, w.dtype) for x in inputs)
+    p = p.with_strides(q, k, v)
+    lse = torch.empty((batch, hkv * group, window), device="cuda")
+    got = torch.empty((batch, hkv, n), device="cuda")
+    B.aha_prefill_row_stats(p, q, k, lse, None, B.alloc_workspace(p))
+    B.aha_prefill_scores_lse(p, q, k, v, lse, got, B.alloc_workspace(p))
+    H.assert_scores_close(got.double().cpu().numpy(), ref.scores, w, Opts())
+    need = B.workspace_bytes(p)
+    ranges = 2 * 4 * batch * hkv * (-(-group * window // 32) * 32)  # statistics of one key range
+    B.aha_prefill_scores(p, q, k, v, got, torch.empty(need - ranges, dtype=torch.uint8, device="cuda"))
+    H.assert_scores_close(got.double().cpu().numpy(), ref.scores, w, Opts())
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
