@@ -386,17 +386,22 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
             }
             request_block(min(blk + kDecWaves, nvb - 1));
             // probabilities of slots 8 hf .. 8 hf + 7 of the block for query head qn
-            bf16x8 pfrag;
+            // (as the sum of two bf16 numbers, 2^-17 relative: the weights keep the precision they
+            // have in fp32 on the other paths; the second product is free under the stream)
+            bf16x8 pfrag, plow;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int sl = blk * VB + 8 * hf + e;
-                pfrag[e] = (__bf16)((qn < G && sl < live) ? s_p[min(qn, G - 1) * live + min(sl, live - 1)] : 0.f);
+                const float pr = (qn < G && sl < live) ? s_p[min(qn, G - 1) * live + min(sl, live - 1)] : 0.f;
+                pfrag[e] = (__bf16)pr;
+                plow[e] = (__bf16)(pr - (float)pfrag[e]);
             }
             // V^T fragments (slots 8 hf .. 8 hf + 7 of the block) by transposing LDS reads
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
                 const bf16x8 vfrag = lds_transposed_fragment(sVw, LDVS, 4 * hf, 4, cb * 32, lane);
                 O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, pfrag, O[cb], 0, 0, 0);
+                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, plow, O[cb], 0, 0, 0);
             }
         }
         __syncthreads();  // every wave is done with its rows: the partial outputs go on top

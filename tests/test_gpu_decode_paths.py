@@ -80,11 +80,5 @@ def test_step_against_float64(dtype, d, z, group, budget):
         assert (np.abs(got - out) <= 2e-5 * rms + 1e-5 * np.abs(out)).all()
         return
     # half a unit of the rounded output (bf16 has 8 significant bits: half a unit is at most 2^-8
-    # of the value), and the weights: 2^-17
-    # each where a probability is the sum of two bf16 numbers or fp32 (whenever slots are split),
-    # 2^-9 where it is one (one workgroup per head from 4 heads per group on), which averages out
-    # over the slots except when one of them carries the output
-    weights = 2.0 ** -8 if group >= 4 else 2.0 ** -15
-    assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + weights * 3 * rms + 1e-6).all()
-    if group >= 4 and z < 96 and budget > 200:  # split over workgroups: no 2^-9 weights
-        assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
+    # of the value), and the weights: fp32, or the sum of two bf16 numbers, 2^-17 each
+    assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
