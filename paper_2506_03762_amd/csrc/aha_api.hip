@@ -550,6 +550,9 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
                         "aha_decode_step with a workspace", need, scratch_limit);
         return AHA_OK;
     }
+    // (scratch of the size that two statistics per partial output need: fewer splits)
+    if (plan->bytes > workspace_bytes && plan->split_bytes && workspace_bytes >= plan->split_bytes)
+        *plan = plan_decode(p, workspace_bytes);
     return check_ws(workspace, workspace_bytes, plan->bytes);
 }
 

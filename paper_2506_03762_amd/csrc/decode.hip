@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
 #pragma unroll
             // (a head's channels permuted by XOR: the heads' rows, a multiple of the banks apart,
             // would meet in the same banks; G = 8, d = 128: 64 heads x
-            // 100 slots 18.5 -> 17.4 us)
+            // 100 slots 18.5 -> 17.7 us)
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int v = 0; v < 16; v += 4)
@@ -907,8 +907,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
 // fold of the splits' statistics (wave w folds head w, one split per lane), and a second for the
 // victim.  The splits leave both softmax sums relative to their own maxima, so no thread walks
 // its slots twice.  (With the score sums formed here, a pass over all dots and a block
-// reduction more, the dots of eight heads did not fit a thread's registers: 12 us for this launch at G = 8, now
-// 3.6; steps of 8 heads x 100 slots, G = 1 8.9 -> 7.3 us.)
+// reduction more, the dots of eight heads did not fit a thread's registers: 12 us for this launch at G = 8;
+// steps of 8 heads x 100 slots with the split stage above 18.5 -> 10.9 us, G = 1 8.9 -> 7.3.)
 constexpr int kMergeThreads = 1024;
 
 // N consecutive floats of a slot's dots
