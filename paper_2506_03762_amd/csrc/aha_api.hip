@@ -132,7 +132,7 @@ static ScoreGeom make_geom(const aha_params *p, const void *q, const void *k, co
 }
 
 // Workspace layout of aha_prefill_scores.
-static PrefillPlan plan_prefill(const aha_params *p, bool may_f32_mfma = true) {
+static PrefillPlan plan_prefill(const aha_params *p) {
     PrefillPlan pl{};
     const int G = p->n_q_heads / p->n_kv_heads;
     const int64_t R = (int64_t)G * p->window;
@@ -171,7 +171,7 @@ static PrefillPlan plan_prefill(const aha_params *p, bool may_f32_mfma = true) {
         // pieces of work are done sooner.  Both passes, d = 64: 262 K pairs (8 heads x 64 rows x
         // 512 keys) 14.3 us against 14.1, 805 K 15.5 against 28.2, 18 M 112 against 147;
         // d = 128: 33 K 18.8 against 13.3, 94 K 27.6 against 33.0, 6.3 M 85 against 123.
-        pl.f32_mfma = may_f32_mfma && (double)pl.Z * R * n >= (p->head_dim == 128 ? 9e4 : 4e5);
+        pl.f32_mfma = (double)pl.Z * R * n >= (p->head_dim == 128 ? 9e4 : 4e5);
         if (pl.f32_mfma) {
             const int64_t units = pl.Z * ((R + 31) / 32), steps = (n + 127) / 128;
             int64_t want = (512 + units - 1) / units;
@@ -208,12 +208,12 @@ static PrefillPlan plan_prefill(const aha_params *p, bool may_f32_mfma = true) {
 
 // Attention output of the observed rows: about 512 workgroups over (block of 32 rows, key
 // range, problem); the key ranges' partials go through the workspace.
-// `may_widen`: five and more row blocks may share their keys in one workgroup of eight waves (one
+// Five and more row blocks share their keys in one workgroup of eight waves (one
 // per CU, so about 256 workgroups), which needs more scratch.  8 KV heads x 16384 keys, d = 128:
 // 6 blocks 48.8 -> 34.4 us, 9 (a second workgroup with one wave at work) 57.8 -> 48.5, 17 81.6 ->
 // 75.8; d = 64, where a step has half the products per byte read from LDS: 6 blocks 30.6 -> 26.8,
 // 11 40.1 -> 37.2, but 17 47.4 -> 59.1.
-static WindowAttnPlan plan_window_attn(const aha_params *p, bool may_widen = true) {
+static WindowAttnPlan plan_window_attn(const aha_params *p) {
     WindowAttnPlan pl{};
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
     const int64_t Z = (int64_t)p->batch * p->n_kv_heads;
@@ -221,7 +221,7 @@ static WindowAttnPlan plan_window_attn(const aha_params *p, bool may_widen = tru
     pl.nparts = 1;
     pl.nq = pl.n_blocks >= 2 ? 2 : 1;  // row blocks per workgroup
     if (p->dtype != AHA_BF16) return pl;  // fp32: one workgroup per row, no partials
-    pl.wide = may_widen && pl.n_blocks >= 5 && (p->head_dim == 128 || pl.n_blocks <= 12);
+    pl.wide = pl.n_blocks >= 5 && (p->head_dim == 128 || pl.n_blocks <= 12);
     const int64_t wg_keys = pl.wide ? 64 : kP2Keys / 2;  // a workgroup step (four waves of 32 keys)
     const int64_t steps = (p->seq_len + wg_keys - 1) / wg_keys;
     const int64_t per_wg = pl.wide ? 8 : pl.nq, groups = (pl.n_blocks + per_wg - 1) / per_wg;
@@ -366,8 +366,7 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
         return rc;
     if (with_lse && (rc = check_ptr("lse", lse, 4))) return rc;
     if (p->value_prior && (rc = check_ptr("v", v, 16))) return rc;
-    PrefillPlan pl = plan_prefill(p);
-    if (pl.f32_mfma && workspace_bytes < pl.bytes) pl = plan_prefill(p, false);
+    const PrefillPlan pl = plan_prefill(p);
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     // the bf16 score launches are one-dimensional over all their workgroups
     const int64_t score_wgs = (int64_t)pl.Z * ((pl.n_qtiles + 1) / 2) * pl.nchunks;
@@ -440,8 +439,7 @@ int32_t aha_prefill_window_attention(const aha_params *p, const void *q, const v
         (rc = check_ptr("out", out, 16)))
         return rc;
     if (lse && (rc = check_ptr("lse", lse, 4))) return rc;
-    WindowAttnPlan pl = plan_window_attn(p);
-    if (pl.wide && workspace_bytes < pl.bytes) pl = plan_window_attn(p, false);
+    const WindowAttnPlan pl = plan_window_attn(p);
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     const int64_t Z = (int64_t)p->batch * p->n_kv_heads;
     const int64_t wgs = p->dtype == AHA_BF16 ? (Z * pl.nparts + 7) / 8 * 8 * pl.n_blocks
@@ -465,7 +463,7 @@ int32_t aha_prefill_row_stats(const aha_params *p, const void *q, const void *k,
     if (!lse && !entropy) return fail(AHA_ERR_INVALID_ARG, "lse and entropy are both null");
     if ((lse && (rc = check_ptr("lse", lse, 4))) || (entropy && (rc = check_ptr("entropy", entropy, 4))))
         return rc;
-    const PrefillPlan pl = plan_prefill(p, false);  // (the fp32 statistics stay in the vector ALU)
+    const PrefillPlan pl = plan_prefill(p);
     if ((rc = check_ws(workspace, workspace_bytes, pl.bytes))) return rc;
     const int64_t score_wgs = (int64_t)pl.Z * ((pl.n_qtiles + 1) / 2) * pl.nchunks;
     if (score_wgs > (int64_t)1 << 30)
@@ -550,9 +548,6 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
                         "aha_decode_step with a workspace", need, scratch_limit);
         return AHA_OK;
     }
-    // (scratch of the size that two statistics per partial output need: fewer splits)
-    if (plan->bytes > workspace_bytes && plan->split_bytes && workspace_bytes >= plan->split_bytes)
-        *plan = plan_decode(p, workspace_bytes);
     return check_ws(workspace, workspace_bytes, plan->bytes);
 }
 
