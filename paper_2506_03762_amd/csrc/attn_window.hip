@@ -429,7 +429,22 @@ struct WideAttn {
     static_assert(KEYS % (RPI * WAVES) == 0 && bytes <= 160 * 1024, "whole instructions per wave, one CU's LDS");
 };
 
-template <int D>
+// The probabilities go to the matrix core as bf16, each off by up to 2^-8 of itself; a reference
+// that is a key's own logit makes that key's probability, 2^0, exact, and what lies just below a
+// power of two is rounded half as far as what lies just above.  The pairs of row blocks above give
+// each quarter of a range's keys a reference; with one reference per range here, kept within a
+// factor of two of the maximum, the outputs are no further from float64 (0.88 to 0.98 of the error
+// above over 40 shapes of four and more steps per range; within 2^8 up to 1.02, and equal to the
+// maximum 0.85 to 0.97, but 3 % slower at 8 heads x 32768 keys x 256 rows and 8 % at 32 x 48000 x
+// 192).  In short ranges the exact ones count for more (1.01 to 1.08 without the following, up to
+// four steps in sequences of some 2000 keys, up to two in longer ones): there (FINE) a probability
+// goes in as the sum of two bf16 numbers (0.75 to 0.9), which costs little where latency bounds the
+// call (32 heads x 1000 keys x 256 rows 25.9 -> 27.9 us).
+inline bool wide_attn_fine(int n, int nparts) {
+    const int64_t per_range = (int64_t)nparts * WideAttn<128>::KEYS;
+    return n <= 2 * per_range || (n <= 2304 && n <= 4 * per_range);
+}
+template <int D, bool FINE>
 __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, int n_blocks, int nparts,
                                                                   int units, float *part_o,
                                                                   float2 *part_ms) {
@@ -507,7 +522,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
     const int pos = rm.pos(rho0 + col);  // -1 for rows past the last one: every key masked
     const int bmin = rm.min_pos(rho0, rho0 + 32), bmax = mine ? rm.max_pos(rho0, rho0 + 32) : -1;
     const float c_out = kLog2e * rsqrtf((float)D);
-    constexpr float kRefSlack = 8.f;  // log2 units
+    constexpr float kRefSlack = 1.f;  // log2 units
 
     f32x16 O[CB];
     float m = -INFINITY, s = 0.f;
@@ -561,13 +576,13 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
             for (int v = 0; v < 16; ++v) amax = fmaxf(amax, acc[mb][v]);
         amax = combine_lane_xor<32>(amax, OpMax{});
         // (the reference follows the running maximum lazily, as above; without the maximum, a step
-        // summed first and redone if its sum passes 2^kRefSlack, 52.0 us instead of 50.5)
+        // summed first and redone if its sum passes 2^8, 52.0 us instead of 50.5)
         const float bm = amax == -INFINITY ? -INFINITY : amax * c_out;
         const float mn = bm > m + kRefSlack ? bm : m;
         const float mref = mn == -INFINITY ? 0.f : mn;
         const float corr = fast_exp2(m - mref);  // 0 while the column has seen no key
         float sum[2] = {0.f, 0.f};
-        bf16x8 pf[MB][2];
+        bf16x8 pf[MB][2], pl[MB][2];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -577,6 +592,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
                     const float pr = fast_exp2(fmaf(acc[mb][8 * ks + e], c_out, -mref));
                     sum[e & 1] += pr;
                     pf[mb][ks][e] = (__bf16)pr;
+                    if (FINE) pl[mb][ks][e] = (__bf16)(pr - (float)pf[mb][ks][e]);
                 }
         s = s * corr + (sum[0] + sum[1]);
         m = mn;
@@ -592,9 +608,11 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(value_fragment<D>(sV, mb, ks, cb, lane),
-                                                                    pf[mb][ks], O[cb], 0, 0, 0);
+                for (int cb = 0; cb < CB; ++cb) {
+                    const bf16x8 vf = value_fragment<D>(sV, mb, ks, cb, lane);
+                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[mb][ks], O[cb], 0, 0, 0);
+                    if (FINE) O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[mb][ks], O[cb], 0, 0, 0);
+                }
     }
     wait_loads<0>();  // (the last requests, past the range, write to LDS)
     if (!mine) return;
@@ -771,19 +789,19 @@ static hipError_t launch_attn_t(const ScoreGeom &g, const WindowAttnPlan &pl, vo
     return launch_merge<D>(g, pl, ws, out, lse, st);
 }
 
-template <int D>
+template <int D, bool FINE>
 static hipError_t launch_attn_wide(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                    float *lse, hipStream_t st) {
     using A = WideAttn<D>;
     static DeviceOnce once;
     const hipError_t ea = device_once(once, [] {
-        return hipFuncSetAttribute((const void *)window_attn_wide_kernel<D>,
+        return hipFuncSetAttribute((const void *)window_attn_wide_kernel<D, FINE>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)A::bytes);
     });
     if (ea != hipSuccess) return ea;
     const int units = g.batch * g.Hkv * pl.nparts, n_groups = (pl.n_blocks + A::WAVES - 1) / A::WAVES;
     const int64_t wgs = (int64_t)((units + kXcds - 1) / kXcds) * kXcds * n_groups;
-    hipLaunchKernelGGL(window_attn_wide_kernel<D>, dim3((unsigned)wgs), dim3(512), A::bytes, st, g,
+    hipLaunchKernelGGL((window_attn_wide_kernel<D, FINE>), dim3((unsigned)wgs), dim3(512), A::bytes, st, g,
                        pl.n_blocks, pl.nparts, units, (float *)ws, (float2 *)((char *)ws + pl.off_ms));
     const hipError_t e1 = hipGetLastError();
     return e1 != hipSuccess ? e1 : launch_merge<D>(g, pl, ws, out, lse, st);
@@ -792,7 +810,9 @@ static hipError_t launch_attn_wide(const ScoreGeom &g, const WindowAttnPlan &pl,
 template <int D>
 static hipError_t launch_attn_d(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                 float *lse, hipStream_t st) {
-    if (pl.wide) return launch_attn_wide<D>(g, pl, ws, out, lse, st);
+    if (pl.wide)
+        return wide_attn_fine(g.n, pl.nparts) ? launch_attn_wide<D, true>(g, pl, ws, out, lse, st)
+                                              : launch_attn_wide<D, false>(g, pl, ws, out, lse, st);
     return pl.nq == 2 ? launch_attn_t<D, 2>(g, pl, ws, out, lse, st)
                       : launch_attn_t<D, 1>(g, pl, ws, out, lse, st);
 }
