@@ -373,7 +373,14 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
         const int nvb = (live + VB - 1) / VB, qn = lane & 31, hf = lane >> 5;
         for (int blk = wave; blk < nvb; blk += kDecWaves) {
             // this block's rows -> LDS (the new value row stands in for the free slot's and
-            // goes to the cache), the next block's are requested (clamped: never past the last)
+            // goes to the cache; rows past the last slot, whose weights are 0, are zero: what was
+            // read for them may be the free slot's old contents, and 0 times a NaN is one), the
+            // next block's are requested (clamped: never past the last)
+            if (blk == nvb - 1 && nvb * VB != live) {
+#pragma unroll
+                for (int t = 0; t < VNI; ++t)
+                    if (blk * VB + t * VRPI + lane / LPR >= live) vblk[t] = u32x4{0u, 0u, 0u, 0u};
+            }
 #pragma unroll
             for (int t = 0; t < VNI; ++t) {
                 const int rin = t * VRPI + lane / LPR;
@@ -833,7 +840,14 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
 #pragma unroll
                 for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
         }
-        // the value rows -> the wave's LDS copy (the new row stands in for the free slot's)
+        // the value rows -> the wave's LDS copy (the new row stands in for the free slot's; rows past
+        // the range are zero: their weights are 0, but what was read for them may be the free
+        // slot's old contents, and 0 times a NaN is one)
+        if (ragged) {
+#pragma unroll
+            for (int t = 0; t < NI; ++t)
+                if (b0 + t * RPI + lane / LPR >= s1) vw[t] = u32x4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
         for (int t = 0; t < NI; ++t) {
             const int rin = t * RPI + lane / LPR;

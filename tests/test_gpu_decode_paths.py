@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _step(dtype, z, group, d, budget, seed):
+def _step(dtype, z, group, d, budget, seed, stale=None):
     import torch
     from paper_2506_03762_amd import binding as B
     rng = np.random.default_rng(seed)
@@ -34,6 +34,9 @@ def _step(dtype, z, group, d, budget, seed):
     K, V, Q = (t.double().cpu().numpy() for t in (c.k[0, :, :live], c.v[0, :, :live],
                                                   q.reshape(z, group, d)))
     rows = np.arange(z)
+    if stale is not None:  # what the free slot held before the step
+        for t in (c.k, c.v, c.scores):
+            t[0, rows, fs] = stale
     K[rows, fs], V[rows, fs] = k[0].double().cpu().numpy(), v[0].double().cpu().numpy()
     dots = np.einsum("zgd,zsd->zgs", Q, K)
     def softmax(x):
@@ -81,4 +84,16 @@ def test_step_against_float64(dtype, d, z, group, budget):
         return
     # half a unit of the rounded output (bf16 has 8 significant bits: half a unit is at most 2^-8
     # of the value), and the weights: fp32, or the sum of two bf16 numbers, 2^-17 each
+    assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("z,group", [(3, 1), (3, 4), (4, 8), (100, 4), (128, 4), (128, 8)])
+@pytest.mark.parametrize("budget", [30, 100, 330])
+def test_the_free_slots_old_contents_are_not_used(d, z, group, budget):
+    """The slot is overwritten by the step, whatever it held; in the second head it is the last slot,
+    as after a compaction, and the last block of slots is ragged."""
+    from paper_2506_03762_amd import binding as B
+    got, out = _step(B.AHA_BF16, z, group, d, budget, budget + d, stale=float("nan"))
+    rms = np.sqrt((out ** 2).mean(-1, keepdims=True))
     assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
