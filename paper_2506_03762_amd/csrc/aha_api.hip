@@ -271,7 +271,7 @@ static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
     const bool one_fits = (w_floats + (size_t)G * live) * 4 + q_tile <= kDecodeSingleLds;
     pl.fits = true;
     int nsplit = 1, min_split = 1;
-    if (Z < 128) {
+    if (Z < kDecodeSplitHeads) {
         nsplit = (256 + Z - 1) / Z;
         const int max_by_size = (live + 63) / 64;  // at least 64 slots per workgroup
         if (nsplit > max_by_size) nsplit = max_by_size;

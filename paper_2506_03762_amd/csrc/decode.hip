@@ -66,7 +66,21 @@ __device__ __forceinline__ unsigned long long wave_min_key(unsigned long long ke
     return ((unsigned long long)whi << 32) | wlo;
 }
 
-template <int ESIZE, int D, int G>
+// A weight for the matrix core as the sum of N bf16 numbers, whose products with a value are exact
+// and summed in fp32: three hold fp32's 24 bits (each difference is exact), two 2^-17 of the weight.
+template <int N>
+__device__ __forceinline__ void split_weight(float p, bf16x8 (&w)[N], int e) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        w[t][e] = (__bf16)p;
+        p -= (float)w[t][e];
+    }
+}
+
+// WEIGHTS: bf16 numbers per output weight (matrix-core values): three where the split stage would
+// be the alternative, which weights with fp32 numbers, two from 128 heads on (64 x 128 heads x 1537
+// slots, G = 8: 33.1 us with two, 34.8 with three).
+template <int ESIZE, int D, int G, int WEIGHTS>
 __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w_floats,
                                                              const float *ws_nu,
                                                              const float *ws_numax) {
@@ -393,22 +407,20 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
             }
             request_block(min(blk + kDecWaves, nvb - 1));
             // probabilities of slots 8 hf .. 8 hf + 7 of the block for query head qn
-            // (as the sum of two bf16 numbers, 2^-17 relative: the weights keep the precision they
-            // have in fp32 on the other paths; the second product is free under the stream)
-            bf16x8 pfrag, plow;
+            bf16x8 pfrag[WEIGHTS];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int sl = blk * VB + 8 * hf + e;
                 const float pr = (qn < G && sl < live) ? s_p[min(qn, G - 1) * live + min(sl, live - 1)] : 0.f;
-                pfrag[e] = (__bf16)pr;
-                plow[e] = (__bf16)(pr - (float)pfrag[e]);
+                split_weight(pr, pfrag, e);
             }
             // V^T fragments (slots 8 hf .. 8 hf + 7 of the block) by transposing LDS reads
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
                 const bf16x8 vfrag = lds_transposed_fragment(sVw, LDVS, 4 * hf, 4, cb * 32, lane);
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, pfrag, O[cb], 0, 0, 0);
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, plow, O[cb], 0, 0, 0);
+#pragma unroll
+                for (int t = WEIGHTS - 1; t >= 0; --t)
+                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, pfrag[t], O[cb], 0, 0, 0);
             }
         }
         __syncthreads();  // every wave is done with its rows: the partial outputs go on top
@@ -712,9 +724,8 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
 //                   only when a block's maximum exceeds it, as a raw dot
 //   O^T += V^T P^T  the accumulator layout hands a lane the probabilities of exactly the slots it
 //                   supplies as a B fragment; V^T fragments by transposing reads from the wave's
-//                   copy of the block's value rows in LDS.  A probability goes in as the sum of two
-//                   bf16 numbers (2^-17 relative), so that the output keeps the precision
-//                   of fp32 probabilities.
+//                   copy of the block's value rows in LDS.  A probability goes in whole, as the
+//                   sum of three bf16 numbers.
 // The next block's keys are requested as soon as the dots are formed and its value rows as soon as
 // this block's are in LDS.  The free slot's rows are read like any other; the block that holds
 // it takes the new token's rows instead (kept in LDS by every wave for itself) and writes them to
@@ -816,7 +827,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
         const float mn = fmaxf(m, bm), corr = fast_exp2((m - mn) * c_out);
         const float corr_sc = m == -INFINITY ? 0.f : fast_exp2((m - mn) * c_sc);
         m = mn;
-        bf16x8 ph[2], pl[2];
+        bf16x8 pf[2][3];
         float sum[2] = {0.f, 0.f}, sumsc[2] = {0.f, 0.f};
         const bool ragged = b0 + 32 > s1;
 #pragma unroll
@@ -828,9 +839,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
                 sum[e & 1] += pr;
                 const float ps = fast_exp2(d * c_sc);
                 sumsc[e & 1] += ragged && d == -INFINITY ? 0.f : ps;  // (a scale of 0 times infinity)
-                const __bf16 hi = (__bf16)pr;
-                ph[ks][e] = hi;
-                pl[ks][e] = (__bf16)(pr - (float)hi);
+                split_weight(pr, pf[ks], e);
             }
         zsum = zsum * corr + (sum[0] + sum[1]);
         zsc = zsc * corr_sc + (sumsc[0] + sumsc[1]);
@@ -866,8 +875,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
                 const bf16x8 vf = lds_transposed_fragment(sv, LD, 16 * ks, 8, cb * 32, lane);
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph[ks], O[cb], 0, 0, 0);
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[ks], O[cb], 0, 0, 0);
+#pragma unroll
+                for (int t = 2; t >= 0; --t)
+                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks][t], O[cb], 0, 0, 0);
             }
     }
     // the waves' partials, each relative to its own reference, meet in LDS
@@ -1123,31 +1133,37 @@ static hipError_t launch_g(const DecodeGeom &g, const DecodePlan &pl, void *ws, 
     const size_t smem = (size_t)(w_floats + g.G * live) * sizeof(float) +
                         (mfma ? kDecodeQTileBytes(D) : 0);
     dim3 grid(g.batch * g.Hkv);
+    auto launch = [&](DeviceOnce &once, auto *kernel) {
+        // the largest dynamic LDS any accepted shape asks for, set once per device
+        const hipError_t ea = device_once(once, [kernel] {
+            return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kDecodeSingleLds);
+        });
+        if (ea != hipSuccess) return ea;
+        hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), smem, st, g, w_floats, ws_nu, ws_numax);
+        return hipGetLastError();
+    };
 #define AHA_DEC(GG)                                                                              \
     {                                                                                            \
-        /* the largest dynamic LDS any accepted shape asks for, set once per device */          \
+        if constexpr (ESIZE == 2 && GG == kDecodeMfmaValuesGroup)                                \
+            if (g.batch * g.Hkv < kDecodeSplitHeads) {                                           \
+                static DeviceOnce once3;                                                         \
+                return launch(once3, decode_kernel<ESIZE, D, GG, 3>);                            \
+            }                                                                                    \
         static DeviceOnce once;                                                                  \
-        const hipError_t ea = device_once(once, [] {                                             \
-            return hipFuncSetAttribute((const void *)decode_kernel<ESIZE, D, GG>,                \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,               \
-                                       (int)kDecodeSingleLds);                                   \
-        });                                                                                      \
-        if (ea != hipSuccess) return ea;                                                         \
-        hipLaunchKernelGGL((decode_kernel<ESIZE, D, GG>), grid, dim3(kDecThreads), smem, st, g,  \
-                           w_floats, ws_nu, ws_numax);                                           \
+        return launch(once, decode_kernel<ESIZE, D, GG, 2>);                                     \
     }
     switch (g.G) {
-        case 1: AHA_DEC(1) break;
-        case 2: AHA_DEC(2) break;
-        case 3: AHA_DEC(3) break;
-        case 4: AHA_DEC(4) break;
-        case 5: AHA_DEC(5) break;
-        case 6: AHA_DEC(6) break;
-        case 7: AHA_DEC(7) break;
-        default: AHA_DEC(8) break;
+        case 1: AHA_DEC(1)
+        case 2: AHA_DEC(2)
+        case 3: AHA_DEC(3)
+        case 4: AHA_DEC(4)
+        case 5: AHA_DEC(5)
+        case 6: AHA_DEC(6)
+        case 7: AHA_DEC(7)
+        default: AHA_DEC(8)
     }
 #undef AHA_DEC
-    return hipGetLastError();
 }
 
 hipError_t launch_decode(const DecodeGeom &g, const DecodePlan &pl, void *ws, int dtype,

@@ -97,3 +97,46 @@ def test_the_free_slots_old_contents_are_not_used(d, z, group, budget):
     got, out = _step(B.AHA_BF16, z, group, d, budget, budget + d, stale=float("nan"))
     rms = np.sqrt((out ** 2).mean(-1, keepdims=True))
     assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("z,group,budget", [(3, 4, 30), (3, 4, 1030), (5, 5, 330), (4, 8, 100)])
+def test_output_weights_keep_fp32(d, z, group, budget):
+    """Two slots weigh a third or so each, a few 1e-5 apart, and their value rows of 256 cancel: what is
+    left is the error of the weights.  (A third slot, with values of 0, holds the largest dot.)"""
+    import torch
+    from paper_2506_03762_amd import binding as B
+    rng = np.random.default_rng(d + budget)
+    n, recent, live = 5 * budget, 5, budget + 1
+    p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0,
+                 budget=budget, recent=recent, dtype=B.AHA_BF16)
+    c = B.CompactCache.empty(p)
+    c.k.zero_()
+    c.scores.zero_()
+    c.v.copy_(torch.from_numpy(rng.standard_normal(tuple(c.v.shape))))
+    c.pos.copy_(torch.arange(live, device="cuda", dtype=torch.int32).expand_as(c.pos))
+    c.free_slot.fill_(budget)
+    c.k[0, :, :, 0] = -128                                # logits of -11 or -16
+    c.k[0, :, 7:9, 0] = 0                                 # and of 0 and a few 1e-5
+    c.k[0, :, 8, 1:9] = 2.0 ** -13
+    c.k[0, :, 9, 0] = 8
+    c.v[0, :, 9] = 0
+    c.v[0, :, 7] = 256
+    c.v[0, :, 8] = -256
+    q = torch.from_numpy(rng.standard_normal((1, z * group, d))).to(torch.bfloat16).cuda()
+    q[..., 0] = 1
+    new = torch.zeros((1, z, d), dtype=torch.bfloat16, device="cuda")
+    knew = c.k[0, :, 0].clone()
+    K, V, Q = (t.double().cpu().numpy() for t in (c.k[0, :, :live], c.v[0, :, :live], q.reshape(z, group, d)))
+    V[:, budget] = 0
+    s = np.einsum("zgd,zsd->zgs", Q, K) * d ** -0.5
+    w = np.exp(s - s.max(-1, keepdims=True))
+    ref = np.einsum("zgs,zsd->zgd", w / w.sum(-1, keepdims=True), V)
+    out = torch.empty_like(q)
+    ws = torch.empty((max(256, B.workspace_bytes(p)),), dtype=torch.uint8, device="cuda")
+    B.aha_decode_step(p, q, knew, new, c.k, c.v, c.scores, c.pos, c.free_slot, n, out, ws)
+    err = np.abs(out.double().cpu().numpy().reshape(ref.shape) - ref)
+    # half a unit of the output; of 256 times the weights' sum of 1: an exponential's last bit (2^-23),
+    # the normalisation's and the products' roundings (2^-24 each, at most four of them).  (The two
+    # dots are of 1e-4: an error of theirs would show in the weights' difference.)
+    assert (err <= 2.0 ** -8 * 1.01 * np.abs(ref) + 2.0 ** -21 * 256).all(), err.max()
