@@ -35,9 +35,11 @@ namespace aha {
 
 constexpr int kCandMax = 1024;   // keys of the threshold bin ranked directly
 
+// Order-preserving key, never 0: that is the padding key, and the counts that address the output
+// add up only if every real position has another one (the NaN of all ones would be 0).
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return max((u & 0x80000000u) ? ~u : (u | 0x80000000u), 1u);
 }
 
 template <int WAVES, int BINS>

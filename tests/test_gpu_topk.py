@@ -25,3 +25,29 @@ def test_topk_at_variant_edges(n_cand, kind):
     for k in sorted({0, 1, (n_cand - sink) // 5, n_cand - sink}):
         got, want = topk_both(s[None], k + recent + sink, recent, sink=sink)
         assert np.array_equal(got, want), (n_cand, kind, k)
+
+
+@pytest.mark.parametrize("n_cand", [300, 2049, 20000, 40000])
+@pytest.mark.parametrize("sink", [0, 7])
+def test_topk_survives_scores_of_all_ones(n_cand, sink):
+    """A fill of 0xff bytes reads as NaN in every score: such scores rank below all others, ties to the
+    lower position, and the list stays ascending and inside the sequence, also when they have to be
+    selected."""
+    import torch
+    from paper_2506_03762_amd import binding as B
+    rng = np.random.default_rng(n_cand)
+    recent, n = 5, n_cand + 5
+    bits = np.exp(rng.standard_normal((3, n))).astype(np.float32).view(np.uint32)
+    bits[0, rng.random(n) < 0.5] = 0xffffffff
+    bits[1] = 0xffffffff
+    bits[2, rng.random(n) < 0.99] = 0xffffffff
+    rank = np.where(bits == 0xffffffff, np.float32(-1), bits.view(np.float32))
+    for k in (1, (n_cand - sink) // 2 + 9, n_cand - sink):
+        p = B.Params(batch=1, n_q_heads=3, n_kv_heads=3, head_dim=64, seq_len=n, window=1,
+                     budget=k + recent + sink, recent=recent, sink=sink)
+        idx = torch.full((1, 3, p.budget), -7, dtype=torch.int32, device="cuda")
+        B.aha_select_topk(p, torch.from_numpy(bits.view(np.float32)[None]).cuda(), idx)
+        for got, s in zip(idx[0].cpu().numpy(), rank):
+            best = sink + np.lexsort((np.arange(n_cand - sink), -s[sink:n_cand]))[:k]
+            want = np.concatenate([np.arange(sink), np.sort(best), np.arange(n_cand, n)])
+            assert np.array_equal(got, want), (n_cand, sink, k)
