@@ -66,6 +66,10 @@ __device__ __forceinline__ unsigned long long wave_min_key(unsigned long long ke
     return ((unsigned long long)whi << 32) | wlo;
 }
 
+// What the dots of a part of a head's slots are taken relative to: their maximum, or 0 if all of them
+// are -inf, as of slots that a caller masks out; those weigh nothing, and the other slots still do.
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 // A weight for the matrix core as the sum of N bf16 numbers, whose products with a value are exact
 // and summed in fp32: three hold fp32's 24 bits (each difference is exact), two 2^-17 of the weight.
 template <int N>
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
     for (int s = s0 + tid; s < s1; s += 256) {
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
-            const float d = s_p[gi * sps + s - s0] - mx[gi];
+            const float d = s_p[gi * sps + s - s0] - finite_ref(mx[gi]);
             const float e = fast_exp2(d * c_out);
             s_p[gi * sps + s - s0] = e;
             zo[gi] += e;
@@ -823,9 +827,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
         float bm = acc[0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) bm = fmaxf(bm, acc[v]);
-        bm = combine_lane_xor<32>(bm, OpMax{});  // (a block has at least one slot: finite for finite dots)
-        const float mn = fmaxf(m, bm), corr = fast_exp2((m - mn) * c_out);
-        const float corr_sc = m == -INFINITY ? 0.f : fast_exp2((m - mn) * c_sc);
+        bm = combine_lane_xor<32>(bm, OpMax{});
+        const float mn = fmaxf(m, bm), mref = finite_ref(mn), corr = fast_exp2((m - mref) * c_out);
+        const float corr_sc = m == -INFINITY ? 0.f : fast_exp2((m - mref) * c_sc);
         m = mn;
         bf16x8 pf[2][3];
         float sum[2] = {0.f, 0.f}, sumsc[2] = {0.f, 0.f};
@@ -834,7 +838,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float d = acc[8 * ks + e] - mn;
+                const float d = acc[8 * ks + e] - mref;
                 const float pr = fast_exp2(d * c_out);
                 sum[e & 1] += pr;
                 const float ps = fast_exp2(d * c_sc);
@@ -905,16 +909,17 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
     for (int t = tid; t < G * D; t += 256) {
         const int gi = t / D, c = t % D;
         const float M = fmaxf(fmaxf(s_m[0][gi], s_m[1][gi]), fmaxf(s_m[2][gi], s_m[3][gi]));
+        const float mref = finite_ref(M);
         float o = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w)  // (a wave without a block has m = -inf: factor 0)
-            o = fmaf(fast_exp2((s_m[w][gi] - M) * c_out), s_o[(w * G + gi) * D + (c ^ (8 * gi))], o);
+            o = fmaf(fast_exp2((s_m[w][gi] - mref) * c_out), s_o[(w * G + gi) * D + (c ^ (8 * gi))], o);
         part[gi * (D + kPartStats) + c] = o;
         if (c == 0) {
             float zt = 0.f, zst = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const float dm = s_m[w][gi] - M;
+                const float dm = s_m[w][gi] - mref;
                 zt = fmaf(fast_exp2(dm * c_out), s_z[w][gi], zt);
                 if (s_z[w][gi] > 0.f)  // (no block: nothing, not a scale of possibly 0 times infinity)
                     zst = fmaf(fast_exp2(dm * c_sc), s_zs[w][gi], zst);

@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _step(dtype, z, group, d, budget, seed, stale=None):
+def _step(dtype, z, group, d, budget, seed, stale=None, masked=0):
     import torch
     from paper_2506_03762_amd import binding as B
     rng = np.random.default_rng(seed)
@@ -22,6 +22,10 @@ def _step(dtype, z, group, d, budget, seed, stale=None):
     c.k.copy_(dev(*c.k.shape))
     c.v.copy_(dev(*c.v.shape))
     q, k, v = dev(1, z * group, d), dev(1, z, d), dev(1, z, d)
+    if masked:  # dots of -inf in the first slots
+        q[..., 0] = q[..., 0].abs() + 0.5
+        k[..., 0] = 0
+        c.k[0, :, :masked, 0] = float("-inf")
     fs = rng.integers(0, live, z)
     fs[:3] = [0, live - 1, live // 2][:z]
     pos = np.stack([np.insert(rng.permutation(n - recent)[:budget - recent].tolist() +
@@ -140,3 +144,18 @@ def test_output_weights_keep_fp32(d, z, group, budget):
     # the normalisation's and the products' roundings (2^-24 each, at most four of them).  (The two
     # dots are of 1e-4: an error of theirs would show in the weights' difference.)
     assert (err <= 2.0 ** -8 * 1.01 * np.abs(ref) + 2.0 ** -21 * 256).all(), err.max()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("z,group,budget,masked", [
+    (3, 1, 1030, 130), (3, 4, 1030, 40), (3, 4, 1030, 130), (4, 8, 330, 130), (100, 2, 330, 130), (128, 8, 330, 130)])
+def test_slots_with_dots_of_minus_infinity(dtype, z, group, budget, masked):
+    """They weigh nothing, also where a block or a whole range of slots has no others (ranges of 61
+    slots in the cases of 3 heads)."""
+    from paper_2506_03762_amd import binding as B
+    got, out = _step(B.AHA_F32 if dtype == "f32" else B.AHA_BF16, z, group, 128, budget, budget, masked=masked)
+    rms = np.sqrt((out ** 2).mean(-1, keepdims=True))
+    if dtype == "f32":
+        assert (np.abs(got - out) <= 2e-5 * rms + 1e-5 * np.abs(out)).all()
+    else:
+        assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
