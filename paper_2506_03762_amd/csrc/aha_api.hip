@@ -238,20 +238,30 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
 // Whether a step with fewer than 128 (batch, KV head) problems gives every head to one workgroup
 // all the same.  The split path streams the heads' caches with the whole chip but pays a second
 // launch and the partials' round trip; one workgroup streams a head at the rate of its CU, which
-// falls with the group (dots and weighted sums in the vector ALU).  Fitted to steps over 8, 32, 64
-// and 112 heads with 100 to 1500 slots, d = 64 and 128: us saved by the single launch against
-// KB of keys and values per head at `cu` KB/us, with the split path at 6 GB/ms over all heads (bf16,
-// d = 128: 8 heads x 300 slots, G = 1 7.0 us in one launch, 7.7 split; 8 x 1500 13.7 against
-// 9.3; 64 x 700 11.6 against 13.4; G = 4, 64 x 700 18.9 against 15.8).  From 96 heads on the split
-// path's advantage in rate is gone for up to four heads per group (G = 4, 112 x 700: 19.3
-// against 20.8); wider groups always gain from splitting (G = 8, 112 x 300: 19.1 against 16.1).
-static bool decode_one_launch(int dtype, int Z, int G, double head_kb) {
+// falls with the group (dots and weighted sums in the vector ALU).  So a single launch wins up to a
+// size of the head, counted as its keys and values and 64 bytes of other work per slot, and the
+// fewer ways a head would be split, the larger that size.  The table holds, in thousands of these
+// bytes, where the two cross: steps of 2 to 127 heads with 100 to 8000 slots, d = 64 and 128, were timed
+// both ways (us in one launch against split; fp32, d = 128, G = 1: 8 heads x 300 slots 9.4 and
+// 10.2, 80 x 1000 21.0 and 23.3, 80 x 3000 56.1 and 50.9, 112 x 8000 203 and 188; bf16, d = 128,
+// G = 4: 64 x 100 10.8 and 11.6, 64 x 700 19.4 and 15.7, 112 x 1000 25.0 and 26.0).  Wider groups
+// always split (bf16, d = 128, G = 8: 8 x 100 17.8 and 11.9, 112 x 300 19.0 and 16.3).
+static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
     if (G > 4) return false;
-    if (Z >= 96) return true;
-    static const double cu[2][4] = {{80, 57, 48, 40}, {105, 62, 48, 36}};       // fp32, bf16; G = 1 .. 4
-    static const double saved[2][4] = {{3.5, 4.0, 4.2, 4.4}, {2.0, 2.3, 2.3, 1.6}};
-    const int t = dtype == AHA_BF16;
-    return head_kb * (1.0 / cu[t][G - 1] - Z / 6000.0) <= saved[t][G - 1];
+    const int ways = (256 + Z - 1) / Z;  // workgroups per head if split
+    constexpr int kAny = INT32_MAX;
+    static const int limit[2][4][4] = {   // G = 1 .. 4
+        {{330, 290, 220, 200},            // fp32: seven and more ways,
+         {870, 450, 410, 290},            // five and six,
+         {1300, 1160, 870, 410},          // four,
+         {2350, kAny, 3300, 1700}},       // three (86 heads and more)
+        {{330, 224, 120, 64},             // bf16
+         {480, 400, 170, 64},
+         {1200, 800, 320, 96},
+         {2350, kAny, 2350, 580}}};
+    const int row = ways >= 7 ? 0 : ways >= 5 ? 1 : ways == 4 ? 2 : 3;
+    const int64_t size = (int64_t)live * (2 * d * esize(dtype) + 64);
+    return size <= (int64_t)limit[dtype == AHA_BF16][row][G - 1] * 1000;
 }
 
 // Decode: split a head's slots over workgroups when there are too few heads to fill the GPU.
@@ -299,8 +309,7 @@ static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
     // (a static step refuses by this number: with two statistics per partial output, the size that
     // its limit was stated for)
     pl.split_bytes = pl.nsplit > 1 ? pl.bytes - align_up(sizeof(float) * 2 * (size_t)Z * pl.nsplit * G, 256) : 0;
-    const double head_kb = 2e-3 * live * p->head_dim * esize(p->dtype);
-    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, head_kb))) {
+    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live))) {
         while (max_bytes && pl.bytes > max_bytes && nsplit > min_split) split_into(--nsplit);
         return pl;
     }

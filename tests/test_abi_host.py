@@ -258,3 +258,26 @@ def test_params_struct_follows_every_change():
     assert bytes(pickle.loads(pickle.dumps(q)).c()) == bytes(copy.copy(q).c()) == bytes(q.c())
     p.c().seq_len = 1                                  # a copy: the caller's own
     assert p._struct()[0].seq_len == p.seq_len
+
+
+@pytest.mark.parametrize("dtype,z,group,d,live,one", [
+    # one workgroup per head where it was measured faster, a split where that was, on either side of
+    # the crossings (us: one launch, split)
+    (0, 80, 1, 128, 1000, True),     # 21.0, 23.3
+    (0, 80, 1, 128, 3000, False),    # 56.1, 50.9
+    (0, 112, 1, 128, 8000, False),   # 203, 188
+    (0, 112, 2, 128, 4000, True),    # 104, 110
+    (1, 48, 1, 64, 1500, True),      # 10.5, 12.3
+    (1, 48, 1, 64, 4000, False),     # 21.3, 18.9
+    (1, 64, 1, 128, 8000, False),    # 79.1, 63.8
+    (1, 95, 1, 128, 4000, True),     # 40.3, 42.0
+    (1, 64, 3, 64, 1000, True),      # 13.4, 14.1
+    (1, 96, 4, 128, 4000, False),    # 72.5, 58.8
+    (1, 96, 4, 64, 1000, True),      # 16.5, 17.1
+    (1, 8, 8, 128, 100, False),      # 17.8, 11.9
+])
+def test_decode_split_rule(dtype, z, group, d, live, one):
+    """A step without the value prior needs scratch exactly when it splits its heads' slots."""
+    p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0,
+                 budget=live - 1, recent=16, dtype=dtype)
+    assert (B.workspace_bytes(p) == 0) == one
