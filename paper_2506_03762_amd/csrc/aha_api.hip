@@ -206,13 +206,20 @@ static PrefillPlan plan_prefill(const aha_params *p) {
     return pl;
 }
 
-// Attention output of the observed rows: about 512 workgroups over (block of 32 rows, key
-// range, problem); the key ranges' partials go through the workspace.
-// Five and more row blocks share their keys in one workgroup of eight waves (one
-// per CU, so about 256 workgroups), which needs more scratch.  8 KV heads x 16384 keys, d = 128:
-// 6 blocks 48.8 -> 34.4 us, 9 (a second workgroup with one wave at work) 57.8 -> 48.5, 17 81.6 ->
-// 75.8; d = 64, where a step has half the products per byte read from LDS: 6 blocks 30.6 -> 26.8,
-// 11 40.1 -> 37.2, but 17 47.4 -> 59.1.
+// Attention output of the observed rows: workgroups over (group of 32-row blocks, key range,
+// problem); the key ranges' partials go through the workspace.
+// bf16 has two forms: pairs of row blocks (steps of 128 keys, two workgroups per CU, about 512 in
+// all) and, for d = 128 and five or more blocks, eight blocks that share their keys (steps of 64
+// keys, one workgroup per CU).  Either runs in rounds of the whole chip, so its time goes with
+// rounds * (steps of a range + set-up), and each further range costs the merge a little.  The set-ups
+// (four steps and two and a half), the merge's share (a twentieth of a step) and the weight of a step (1 and 0.9) were
+// fitted to both forms' times over 1 to 256 KV heads, 300 to 48000 keys and 5 to 32 blocks (570
+// shapes): taking the form with the smaller sum is 1.149 times as fast as the first form throughout
+// (the better of both, known beforehand, 1.159) and more than 3 % slower in 26 of them, 14 % at worst.
+// us of first and second form, 8 blocks: 1 head x 48000 keys 28.5, 41.3 (64 workgroups), 8 x 16000
+// 38.5, 37.7, 48 x 16000 203, 130; 5 blocks: 24 x 1000 29.6, 21.9.
+// d = 64 always takes the first form: with half the products per byte read from LDS the second was
+// 3 % slower on average over 586 such shapes, 40 % at worst.
 static WindowAttnPlan plan_window_attn(const aha_params *p) {
     WindowAttnPlan pl{};
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -221,14 +228,21 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
     pl.nparts = 1;
     pl.nq = pl.n_blocks >= 2 ? 2 : 1;  // row blocks per workgroup
     if (p->dtype != AHA_BF16) return pl;  // fp32: one workgroup per row, no partials
-    pl.wide = pl.n_blocks >= 5 && (p->head_dim == 128 || pl.n_blocks <= 12);
-    const int64_t wg_keys = pl.wide ? 64 : kP2Keys / 2;  // a workgroup step (four waves of 32 keys)
-    const int64_t steps = (p->seq_len + wg_keys - 1) / wg_keys;
-    const int64_t per_wg = pl.wide ? 8 : pl.nq, groups = (pl.n_blocks + per_wg - 1) / per_wg;
-    int64_t want = ((pl.wide ? 256 : 512) + Z * groups - 1) / (Z * groups);
-    if (want > steps) want = steps;
-    if (want > 64) want = 64;
-    pl.nparts = (int)(want < 1 ? 1 : want);
+    constexpr int64_t kMaxParts = 64;
+    const int64_t groups = (pl.n_blocks + pl.nq - 1) / pl.nq, steps = (p->seq_len + 127) / 128;
+    int64_t parts = (512 + Z * groups - 1) / (Z * groups);
+    if (parts > steps) parts = steps;
+    if (parts > kMaxParts) parts = kMaxParts;
+    pl.nparts = (int)parts;
+    if (p->head_dim == 128 && pl.n_blocks >= 5) {
+        // (in twentieths of a step; two workgroups per CU: half a round per 256)
+        int64_t best = 10 * ((Z * groups * parts + 255) / 256) * ((steps + parts - 1) / parts + 4) + parts;
+        const int64_t wide_groups = (pl.n_blocks + 7) / 8, wide_steps = (p->seq_len + 63) / 64;
+        for (int64_t n = 1; n <= kMaxParts && n <= wide_steps; ++n) {
+            const int64_t sum = 9 * ((Z * wide_groups * n + 255) / 256) * (2 * ((wide_steps + n - 1) / n) + 5) + n;
+            if (sum < best) { best = sum; pl.nparts = (int)n; pl.wide = true; }
+        }
+    }
     const size_t rows = (size_t)Z * pl.nparts * pl.n_blocks * 32;
     pl.off_ms = align_up(sizeof(float) * rows * p->head_dim, 256);
     pl.bytes = align_up(pl.off_ms + 2 * sizeof(float) * rows, 256);

@@ -423,7 +423,7 @@ template <int D>
 struct WideAttn {
     static constexpr int WAVES = 8, KEYS = 64, CPR = D / 8, RPI = 64 / CPR;
     static constexpr int NI = KEYS / RPI / WAVES;         // load instructions per wave for a step's keys (and values)
-    static constexpr int kStages = D == 128 ? 4 : 6;
+    static constexpr int kStages = 4;
     static constexpr int half = KEYS * D * 2;             // bytes of a step's key rows
     static constexpr size_t bytes = (size_t)kStages * 2 * half;
     static_assert(KEYS % (RPI * WAVES) == 0 && bytes <= 160 * 1024, "whole instructions per wave, one CU's LDS");
@@ -436,13 +436,13 @@ struct WideAttn {
 // factor of two of the maximum, the outputs are no further from float64 (0.88 to 0.98 of the error
 // above over 40 shapes of four and more steps per range; within 2^8 up to 1.02, and equal to the
 // maximum 0.85 to 0.97, but 3 % slower at 8 heads x 32768 keys x 256 rows and 8 % at 32 x 48000 x
-// 192).  In short ranges the exact ones count for more (1.01 to 1.08 without the following, up to
-// four steps in sequences of some 2000 keys, up to two in longer ones): there (FINE) a probability
+// 192).  In short ranges the exact ones count for more (1.01 to 1.14 without the following, up to
+// four steps in sequences of some 2000 keys, up to three in longer ones): there (FINE) a probability
 // goes in as the sum of two bf16 numbers (0.75 to 0.9), which costs little where latency bounds the
 // call (32 heads x 1000 keys x 256 rows 25.9 -> 27.9 us).
 inline bool wide_attn_fine(int n, int nparts) {
     const int64_t per_range = (int64_t)nparts * WideAttn<128>::KEYS;
-    return n <= 2 * per_range || (n <= 2304 && n <= 4 * per_range);
+    return n <= 3 * per_range || (n <= 2304 && n <= 4 * per_range);
 }
 template <int D, bool FINE>
 __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, int n_blocks, int nparts,
@@ -628,15 +628,15 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
 
 // Second launch: the key ranges' partials of every observed row -> the normalised output in
 // the inputs' dtype and the row's natural-log normaliser.  A thread takes four channels of a row,
-// 1024 / D rows per workgroup; sixteen ranges' loads in flight at once (bound by their latency:
-// 8 heads x 256 rows, 32 ranges: 10.4 us with one channel per
-// thread and eight ranges in flight, 8.3 so).
-template <int D>
+// 1024 / D rows per workgroup; U ranges' loads in flight at once: sixteen where there are more
+// than eight (bound by their latency: 8 heads x 256 rows, 32 ranges: 10.4 us with one channel per
+// thread and eight ranges in flight, 8.3 so), otherwise hardly more than there are.
+template <int D, int U>
 __global__ __launch_bounds__(256) void window_attn_merge_kernel(ScoreGeom g, int n_blocks,
                                                                 int nparts, const float *part_o,
                                                                 const float2 *part_ms,
                                                                 uint16_t *out, float *lse) {
-    constexpr int TPR = D / 4, U = 16;
+    constexpr int TPR = D / 4;
     const int z = blockIdx.y, rho = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, ch = threadIdx.x % TPR * 4;
     if (rho >= g.R) return;
     const int b = z / g.Hkv, h = z % g.Hkv;
@@ -760,10 +760,16 @@ __global__ __launch_bounds__(256) void f32_window_attn_kernel(ScoreGeom g, float
 template <int D>
 static hipError_t launch_merge(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                float *lse, hipStream_t st) {
-    const int rows_per_wg = 1024 / D;
-    hipLaunchKernelGGL(window_attn_merge_kernel<D>, dim3((g.R + rows_per_wg - 1) / rows_per_wg, g.batch * g.Hkv),
-                       dim3(256), 0, st, g, pl.n_blocks, pl.nparts, (const float *)ws,
-                       (const float2 *)((char *)ws + pl.off_ms), (uint16_t *)out, lse);
+    constexpr int rows_per_wg = 1024 / D;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((g.R + rows_per_wg - 1) / rows_per_wg, g.batch * g.Hkv),
+                           dim3(256), 0, st, g, pl.n_blocks, pl.nparts, (const float *)ws,
+                           (const float2 *)((char *)ws + pl.off_ms), (uint16_t *)out, lse);
+    };
+    if (pl.nparts == 1) launch(window_attn_merge_kernel<D, 1>);
+    else if (pl.nparts <= 4) launch(window_attn_merge_kernel<D, 4>);
+    else if (pl.nparts <= 8) launch(window_attn_merge_kernel<D, 8>);
+    else launch(window_attn_merge_kernel<D, 16>);
     return hipGetLastError();
 }
 
@@ -810,9 +816,11 @@ static hipError_t launch_attn_wide(const ScoreGeom &g, const WindowAttnPlan &pl,
 template <int D>
 static hipError_t launch_attn_d(const ScoreGeom &g, const WindowAttnPlan &pl, void *ws, void *out,
                                 float *lse, hipStream_t st) {
-    if (pl.wide)
-        return wide_attn_fine(g.n, pl.nparts) ? launch_attn_wide<D, true>(g, pl, ws, out, lse, st)
-                                              : launch_attn_wide<D, false>(g, pl, ws, out, lse, st);
+    if constexpr (D == 128)
+        if (pl.wide) {
+            return wide_attn_fine(g.n, pl.nparts) ? launch_attn_wide<D, true>(g, pl, ws, out, lse, st)
+                                                  : launch_attn_wide<D, false>(g, pl, ws, out, lse, st);
+        }
     return pl.nq == 2 ? launch_attn_t<D, 2>(g, pl, ws, out, lse, st)
                       : launch_attn_t<D, 1>(g, pl, ws, out, lse, st);
 }

@@ -281,3 +281,18 @@ def test_decode_split_rule(dtype, z, group, d, live, one):
     p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0,
                  budget=live - 1, recent=16, dtype=dtype)
     assert (B.workspace_bytes(p) == 0) == one
+
+
+@pytest.mark.parametrize("d,z,blocks,n,parts", [
+    (64, 24, 8, 9467, 6),      # pairs of row blocks: 24 * 4 pairs * 6
+    (128, 24, 8, 9467, 10),    # eight blocks together: 240 workgroups, one per CU (11 ranges would leave 8 for a second round)
+    (128, 1, 8, 4000, 32),     # 64 workgroups at most with eight together: pairs
+    (128, 8, 5, 16000, 32),
+    (128, 8, 4, 16000, 32),    # four blocks: pairs
+])
+def test_window_attention_ranges(d, z, blocks, n, parts):
+    """Key ranges of the window attention, from its workspace: partial rows of d channels and two
+    statistics."""
+    p = B.Params(batch=1, n_q_heads=z * blocks, n_kv_heads=z, head_dim=d, seq_len=n, window=32,
+                 budget=40, recent=8)
+    assert B.window_attention_workspace_bytes(p) == z * parts * blocks * 32 * (d + 2) * 4
