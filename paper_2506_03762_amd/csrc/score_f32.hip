@@ -44,9 +44,14 @@ __device__ __forceinline__ void merge_stat(float &m, float &s, float &u, float m
 
 // Sum over the four lanes of a quad.
 __device__ __forceinline__ float quad_sum(float x) { return reduce_lanes<1, 4>(x, OpSum{}); }
-// x[part] without a dynamically indexed register file.
+// x[part] without a dynamically indexed array.  The elements go through an opaque move: otherwise
+// the compiler sees through the choice and keeps the array in memory, indexed - in LDS, at an address
+// formed from the workgroup's size, which is read from the dispatch packet in the host's memory (14
+// us of latency: 64 heads x 32 rows x 40 keys 19.3 us instead of 5), or in scratch.
 __device__ __forceinline__ float pick4(const float (&x)[4], int part) {
-    const float a = part & 1 ? x[1] : x[0], b = part & 1 ? x[3] : x[2];
+    float x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+    asm volatile("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
+    const float a = part & 1 ? x1 : x0, b = part & 1 ? x3 : x2;
     return part & 2 ? b : a;
 }
 
@@ -75,13 +80,22 @@ template <int D, int RQ>
 __global__ __launch_bounds__(256) void f32_pass1_kernel(ScoreGeom g, int row_blocks, int n_vtiles,
                                                         float *gamma, float *gblockmax, float *rowL,
                                                         float *lse_out, float *ent_out) {
-    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if ((int)blockIdx.x >= row_blocks) {  // (workgroup-uniform)
-        value_prior_tile<4>(g, z, (int)blockIdx.x - row_blocks, n_vtiles, gamma, gblockmax, tid);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // Workgroups go to the XCDs in turn: a problem's, which read the same keys, are dealt to one of
+    // them (64 heads x 4 rows x 3000 keys, d = 128: 60 -> 21 us).
+    int z = blockIdx.y, blk = blockIdx.x;
+    if (gridDim.x < 1u << 15) {  // (32-bit indexes)
+        const uint32_t per = gridDim.x * gridDim.y / kXcds, id = blockIdx.y * gridDim.x + blockIdx.x;
+        const uint32_t wg = id < per * kXcds ? id % kXcds * per + id / kXcds : id;
+        z = (int)(wg / gridDim.x);
+        blk = (int)(wg % gridDim.x);
+    }
+    if (blk >= row_blocks) {  // (workgroup-uniform)
+        value_prior_tile<4>(g, z, blk - row_blocks, n_vtiles, gamma, gblockmax, tid);
         return;
     }
     const int b = z / g.Hkv, h = z % g.Hkv;
-    const int rho0 = blockIdx.x * RQ, part = tid & 3, kk = tid >> 2;
+    const int rho0 = blk * RQ, part = tid & 3, kk = tid >> 2;
     const RowMap rm{g.n, g.r, g.R,
                     g.rows ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
     const float *kbase = (const float *)g.k + b * g.ks[0] + h * g.ks[1];
@@ -109,6 +123,7 @@ __global__ __launch_bounds__(256) void f32_pass1_kernel(ScoreGeom g, int row_blo
 #pragma unroll
         for (int t = 0; t < U; ++t)
             k[t].load(kbase + (int64_t)min(j0 + t * 64 + kk, last) * g.ks[2], part);
+        __builtin_amdgcn_sched_barrier(0);  // (all requested before the first is used)
 #pragma unroll
         for (int t = 0; t < U; ++t) {
             float w[RQ];
