@@ -167,11 +167,12 @@ static PrefillPlan plan_prefill(const aha_params *p) {
         pl.chunk_keys = n;
         pl.nchunks = 1;
         pl.p2_keys = kP2Keys;
-        // The matrix core from this many (row, key) pairs on; below, the vector ALU's smaller
-        // pieces of work are done sooner.  Both passes, d = 64: 262 K pairs (8 heads x 64 rows x
-        // 512 keys) 14.3 us against 14.1, 805 K 15.5 against 28.2, 18 M 112 against 147;
-        // d = 128: 33 K 18.8 against 13.3, 94 K 27.6 against 33.0, 6.3 M 85 against 123.
-        pl.f32_mfma = (double)pl.Z * R * n >= (p->head_dim == 128 ? 9e4 : 4e5);
+        // The matrix core from this many (row, key) pairs on, unless its blocks of 32 rows would be
+        // mostly empty; otherwise the vector ALU's smaller pieces of work are done sooner.  Both
+        // passes, us on the vector ALU and the matrix core, d = 64: 131 K pairs (8 heads x 64 rows x 256
+        // keys) 13.4, 13.7, 205 K (400 keys) 14.6, 14.5, 410 K (128 rows x 400) 21.3, 14.8, 1.1 M (128 x
+        // 1100) 30.0, 19.7; 16 rows: 64 heads x 1100 keys 30.9, 33.9; 4 rows: 64 x 2000 25.3, 44.4.
+        pl.f32_mfma = R >= 24 && (double)pl.Z * R * n >= 2e5;
         if (pl.f32_mfma) {
             const int64_t units = pl.Z * ((R + 31) / 32), steps = (n + 127) / 128;
             int64_t want = (512 + units - 1) / units;
