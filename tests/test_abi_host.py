@@ -254,10 +254,19 @@ def test_params_struct_follows_every_change():
     q = copy.deepcopy(p)
     q.q_stride = [8 * s for s in q.q_stride]
     assert p._struct()[0].seq_len == p.seq_len and bytes(p.c()) != before
-    assert tuple(q._struct()[0].q_stride) == q.q_stride != p.q_stride
+    assert list(q._struct()[0].q_stride) == q.q_stride != list(p.q_stride)
     assert bytes(pickle.loads(pickle.dumps(q)).c()) == bytes(copy.copy(q).c()) == bytes(q.c())
     p.c().seq_len = 1                                  # a copy: the caller's own
     assert p._struct()[0].seq_len == p.seq_len
+    q.q_stride[1] += 8                                 # lists stay lists and may be edited
+    assert list(q._struct()[0].q_stride) == q.q_stride
+    vars(p).update(seq_len=p.seq_len + 8)              # past __setattr__
+    assert p._struct()[0].seq_len == p.seq_len
+    # a pickle from when the fields' dict also held the struct's bytes
+    old = good()
+    vars(old)["_c"] = (("key",), bytes(old.c()))
+    old = pickle.loads(pickle.dumps(old))
+    assert B.workspace_bytes(old) == B.workspace_bytes(good())
 
 
 @pytest.mark.parametrize("dtype,z,group,d,live,one", [
