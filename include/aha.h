@@ -297,11 +297,13 @@ int32_t aha_compact_kv(const aha_params *p, const void *k, const void *v,
  * p->seq_len, window, value_prior, pool_kernel and the strides are ignored.
  * Exactly budget + 1 slots must be live on entry (budget occupied + the free
  * one), which aha_compact_kv and every previous step guarantee.
- * The dots of a head's live slots are kept in on-chip memory: with fewer than
- * 128 (batch, KV head) problems the slots are split over up to 64 workgroups
- * (group * slots-per-split * 4 + 16 * group * head_dim bytes each, at most
- * 64 KiB), otherwise one workgroup holds 8 * group * (budget + 1) bytes (at
- * most 150 KiB); larger budgets return AHA_ERR_UNSUPPORTED.
+ * The dots of a head's live slots are kept on chip.  With 128 and more
+ * (batch, KV head) problems one workgroup holds a head: about 8 * group *
+ * (budget + 1) bytes, at most 150 KiB.  With fewer the shape has to fit a split
+ * of the slots over up to 64 workgroups (group * slots-per-split * 4 + 16 *
+ * group * head_dim bytes each, at most 64 KiB; no more than 64 slots: one
+ * workgroup as above), whether it is then split or, where that is faster, served
+ * by one workgroup per head.  Larger budgets return AHA_ERR_UNSUPPORTED.
  */
 int32_t aha_decode_step(const aha_params *p, const void *q_new, const void *k_new,
                         const void *v_new, void *k_cache, void *v_cache,
@@ -314,10 +316,16 @@ int32_t aha_decode_step(const aha_params *p, const void *q_new, const void *k_ne
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, result and errors as aha_decode_step, without
  * the workspace: the scratch of the few-heads path lives in a buffer built
- * into the library (4 MiB per GPU, held until the process ends).  The call
- * allocates and frees nothing.  A shape whose scratch (aha_workspace_bytes
- * with seq_len = 0) exceeds 4 MiB returns AHA_ERR_UNSUPPORTED before anything
- * is launched - e.g. 8 KV heads x 4 query heads x budget 2048 needs 0.8 MiB.
+ * into the library (4.1 MiB per GPU, held until the process ends).  The call
+ * allocates and frees nothing.  The buffer is for shapes whose scratch, split
+ * over workgroups and without the value prior, counts up to 4 MiB: 4 * heads *
+ * group * (budget + 1) bytes of dots and 4 * heads * splits * group *
+ * (head_dim + 2) of partial outputs, each rounded up to 256 (heads = batch *
+ * n_kv_heads < 128, splits as in aha_decode_step; nothing for 128 and more); the
+ * prior adds 4 * heads * (budget + 2).  Other shapes return AHA_ERR_UNSUPPORTED
+ * before anything is launched, whichever way the step would be served and
+ * whatever aha_workspace_bytes says - e.g. 8 KV heads x 4 query heads x budget
+ * 2048 counts 0.8 MiB.
  * All calls on one GPU share the buffer: two calls that may overlap in time
  * (different streams, different threads) race and must be ordered by the
  * caller.  The buffer keeps the previous call's contents; the kernels read

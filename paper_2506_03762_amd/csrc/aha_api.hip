@@ -283,8 +283,8 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
 // A split workgroup keeps group * (slots of its range) dots and 4 * group * head_dim partial
 // outputs in LDS; the number of splits is raised until that fits kDecodeSplitLds (the limit
 // a launch may ask for without an attribute), and `fits` says whether kMaxDecodeSplit
-// splits were enough.  `max_bytes`, when not 0, bounds the scratch: fewer splits are taken then.
-static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
+// splits were enough.
+static DecodePlan plan_decode(const aha_params *p) {
     DecodePlan pl{};
     const int Z = p->batch * p->n_kv_heads, G = p->n_q_heads / p->n_kv_heads;
     const int live = p->budget + 1;
@@ -295,7 +295,7 @@ static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
     const size_t q_tile = mfma ? kDecodeQTileBytes(p->head_dim) : 0;
     const bool one_fits = (w_floats + (size_t)G * live) * 4 + q_tile <= kDecodeSingleLds;
     pl.fits = true;
-    int nsplit = 1, min_split = 1;
+    int nsplit = 1;
     if (Z < kDecodeSplitHeads) {
         nsplit = (256 + Z - 1) / Z;
         const int max_by_size = (live + 63) / 64;  // at least 64 slots per workgroup
@@ -307,32 +307,27 @@ static DecodePlan plan_decode(const aha_params *p, size_t max_bytes = 0) {
             const int64_t need = max_sps > 0 ? (live + max_sps - 1) / max_sps : kMaxDecodeSplit + 1;
             if (need > nsplit) nsplit = need > kMaxDecodeSplit ? kMaxDecodeSplit : (int)need;
             if (need > kMaxDecodeSplit) pl.fits = false;
-            min_split = need > 2 ? (int)need : 2;
         }
     }
-    auto split_into = [&](int parts) {
-        pl.sps = (live + parts - 1) / parts;
-        pl.nsplit = (live + pl.sps - 1) / pl.sps;
-        pl.off_part = align_up(sizeof(float) * (size_t)Z * G * live, 256);
-        pl.off_nu = align_up(pl.off_part + sizeof(float) * (size_t)Z * pl.nsplit * G * (p->head_dim + kPartStats), 256);
-        pl.bytes = pl.off_nu;
-        // value prior inside the loop: the live slots' value norms and their maximum per head
-        if (p->decode_value_prior)
-            pl.bytes = align_up(pl.off_nu + sizeof(float) * ((size_t)Z * live + Z), 256);
+    pl.sps = (live + nsplit - 1) / nsplit;
+    pl.nsplit = (live + pl.sps - 1) / pl.sps;
+    // with `stats` floats behind every partial output; value prior inside the loop: the live slots'
+    // value norms and their maximum per head
+    const size_t norms = p->decode_value_prior ? sizeof(float) * ((size_t)Z * live + Z) : 0;
+    auto layout = [&](int stats) {
+        pl.off_part = pl.nsplit > 1 ? align_up(sizeof(float) * (size_t)Z * G * live, 256) : 0;
+        const size_t partials = sizeof(float) * (size_t)Z * pl.nsplit * G * (p->head_dim + stats);
+        pl.off_nu = pl.nsplit > 1 ? align_up(pl.off_part + partials, 256) : 0;
+        return align_up(pl.off_nu + norms, 256);
     };
-    split_into(nsplit);
-    // (a static step refuses by this number: with two statistics per partial output, the size that
-    // its limit was stated for)
-    pl.split_bytes = pl.nsplit > 1 ? pl.bytes - align_up(sizeof(float) * 2 * (size_t)Z * pl.nsplit * G, 256) : 0;
-    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live))) {
-        while (max_bytes && pl.bytes > max_bytes && nsplit > min_split) split_into(--nsplit);
+    pl.static_bytes = layout(2);
+    pl.bytes = layout(kPartStats);
+    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live)))
         return pl;
-    }
     if (pl.nsplit <= 1 && !one_fits) pl.fits = false;
     pl.nsplit = 1;
     pl.sps = live;
-    pl.off_part = pl.off_nu = pl.bytes = 0;
-    if (p->decode_value_prior) pl.bytes = align_up(sizeof(float) * ((size_t)Z * live + Z), 256);
+    pl.bytes = layout(kPartStats);
     return pl;
 }
 
@@ -558,18 +553,17 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
     const int G = p->n_q_heads / p->n_kv_heads;
     if (G > 8)
         return fail(AHA_ERR_UNSUPPORTED, "decode is built for query groups of up to 8 heads, not %d", G);
-    *plan = plan_decode(p, scratch_limit);
+    *plan = plan_decode(p);
     if (!plan->fits)
         return fail(AHA_ERR_UNSUPPORTED,
                     "decode keeps group * (budget + 1) dots in LDS; %d * %d does not fit (%d splits)",
                     G, p->budget + 1, plan->nsplit);
     if (scratch_limit) {
-        // (the same shapes are refused whichever path would serve them)
-        const size_t need = plan->bytes > plan->split_bytes ? plan->bytes : plan->split_bytes;
-        if (need > scratch_limit)
+        // (the same shapes are refused whichever path serves them)
+        if (plan->static_bytes > scratch_limit)
             return fail(AHA_ERR_UNSUPPORTED,
-                        "this shape needs %zu bytes of scratch, the built-in buffer holds %zu: use "
-                        "aha_decode_step with a workspace", need, scratch_limit);
+                        "split over workgroups this shape's scratch counts %zu bytes, the built-in buffer "
+                        "is for %zu: use aha_decode_step with a workspace", plan->static_bytes, scratch_limit);
         return AHA_OK;
     }
     return check_ws(workspace, workspace_bytes, plan->bytes);
@@ -611,8 +605,11 @@ int32_t aha_decode_step(const aha_params *p, const void *q_new, const void *k_ne
 // that can neither allocate nor carry a workspace.  The array's name is only a host-side
 // stand-in: its device address is asked for once per device (each GPU holds its own copy
 // at its own address) and that pointer is what the kernels get.
-constexpr size_t kScratchBytes = (size_t)4 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchBytes = (size_t)4 << 20;  // of static_bytes
+// A partial output has kPartStats statistics, two more floats than are counted; the count holds
+// fewer than 4 MiB / (4 * 66) of them (at least 64 channels and two statistics each).
+constexpr size_t kScratchMargin = kScratchBytes / (4 * 66) * 4 * (kPartStats - 2) + 256;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchMargin];
 static void *g_scratch_ptr[kMaxDevices];
 static DeviceOnce g_scratch_once;
 

@@ -161,7 +161,8 @@ struct DecodePlan {
     size_t off_part; // partial outputs behind the raw dots
     size_t off_nu;   // ||v||^2 of every live slot behind those (value prior in the loop)
     size_t bytes;    // workspace bytes
-    size_t split_bytes;  // what the split path needs for this shape, taken or not (0: never split)
+    size_t static_bytes; // what aha_decode_step_static refuses by: the split path's need, taken or not, with
+                         // two statistics per partial output
     bool fits;       // the LDS the chosen path needs is within its limit
 };
 hipError_t launch_decode(const DecodeGeom &g, const DecodePlan &pl, void *ws, int dtype,

@@ -58,6 +58,24 @@ def _run_both(w, seed, steps):
         assert not torch.isnan(ob.float()).any()
 
 
+@pytest.mark.parametrize("z,group,d,dtype,budget,prior,served", [
+    # the dots and partial outputs of the split count at most 4 MiB, to the byte ...
+    (9, 8, 64, 0, 12647, 0, True), (9, 8, 64, 0, 12648, 0, False),
+    (122, 1, 128, 1, 8203, 0, True), (122, 1, 128, 1, 8204, 0, False),   # ... also where one launch serves the step
+    (1, 8, 64, 1, 112751, 1, True), (1, 8, 64, 0, 116000, 1, False),
+    (128, 1, 64, 1, 8190, 1, True),                                      # never split: the norms alone
+])
+def test_static_decode_serves_the_shapes_that_its_count_allows(z, group, d, dtype, budget, prior, served):
+    import torch
+    if served and torch.cuda.is_available():
+        pytest.skip("would launch with the dummy pointers")
+    p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0, budget=budget,
+                 recent=4, dtype=dtype, decode_value_prior=prior)
+    rc = B.load().aha_decode_step_static(ctypes.byref(p.c()), *([ctypes.c_void_p(4096)] * 8), budget + 1,
+                                         budget + 1, ctypes.c_void_p(4096), None)
+    assert rc == (B.AHA_ERR_HIP if served else B.AHA_ERR_UNSUPPORTED)
+
+
 @pytest.mark.gpu
 def test_static_scratch_decode_matches_workspace_decode():
     big = synth.scaled(synth.C3, name="static_big", batch=1, n_q_heads=32, n_kv_heads=8,
