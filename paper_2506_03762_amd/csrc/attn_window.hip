@@ -23,6 +23,8 @@
 // The waves' partial outputs (each relative to its own reference) meet in LDS, the key ranges'
 // in the workspace, and a small second launch normalises.
 // fp32 (the small high-accuracy path): plain vector-ALU kernel, one workgroup per row.
+#include <type_traits>
+
 #include "score_tile.h"
 
 namespace aha {
@@ -726,21 +728,26 @@ __global__ __launch_bounds__(256) void f32_window_attn_kernel(ScoreGeom g, float
         const float corr = exp2f(m - mn);  // 0 at the first block
         ssum = ssum * corr + (s_red[0] + s_red[1] + s_red[2] + s_red[3]);
         o *= corr;
-        // (value rows requested sixteen at a time, past the block's last key that one again and
-        // unused: one at a time the loop waits out a round trip per key; 4 heads x 64 rows x
-        // 2900 keys, d = 128, 389 -> 132 us, 16 x 64 x 1468 258 -> 144)
+        // (value rows requested sixteen at a time, the last few four at a time, past the block's last key
+        // that one again and unused: one at a time the loop waits out a round trip per key; 4 heads
+        // x 64 rows x 2900 keys, d = 128, 389 -> 132 us, 16 x 64 x 1468 258 -> 144.  Sixteen for the last
+        // few as well: 8 x 256 rows x 257 keys 52 us instead of 43, and 48 one at a time)
         const int jn = min(256, i + 1 - j0);
-        for (int jj = sl; jj < jn; jj += 16 * SL) {
-            float vv[16], pp[16];
+        auto add = [&](auto count, int jj) {
+            constexpr int U = decltype(count)::value;
+            float vv[U], pp[U];
 #pragma unroll
-            for (int t = 0; t < 16; ++t) {
+            for (int t = 0; t < U; ++t) {
                 const int js = jj + t * SL;
                 vv[t] = vbase[(int64_t)(j0 + min(js, jn - 1)) * g.vs[2] + c];
                 pp[t] = js < jn ? s_p[js] : 0.f;
             }
 #pragma unroll
-            for (int t = 0; t < 16; ++t) o = jj + t * SL < jn ? fmaf(pp[t], vv[t], o) : o;
-        }
+            for (int t = 0; t < U; ++t) o = jj + t * SL < jn ? fmaf(pp[t], vv[t], o) : o;
+        };
+        int jj = sl;
+        for (; jj + 12 * SL < jn; jj += 16 * SL) add(std::integral_constant<int, 16>{}, jj);
+        for (; jj < jn; jj += 4 * SL) add(std::integral_constant<int, 4>{}, jj);
         m = mn;
         __syncthreads();  // s_p and s_red are free again
     }
