@@ -227,7 +227,8 @@ struct RowMap {
     }
     __device__ __forceinline__ int head(int rho) const { return rho / r; }
     // largest / smallest position among rows [lo, hi) (hi > lo, clipped to R); closed forms
-    // for the most recent rows, a scan for chosen rows (used on the small fp32 path only)
+    // for the most recent rows, a scan for chosen rows (fp32 inputs; the bf16 tiles find theirs while
+    // they are loaded)
     __device__ __forceinline__ int max_pos(int lo, int hi) const {
         if (hi > R) hi = R;
         if (lo >= hi) return -1;

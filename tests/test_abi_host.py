@@ -284,6 +284,9 @@ def test_params_struct_follows_every_change():
     (1, 96, 4, 128, 4000, False),    # 72.5, 58.8
     (1, 96, 4, 64, 1000, True),      # 16.5, 17.1
     (1, 8, 8, 128, 100, False),      # 17.8, 11.9
+    # (the states of the tie and value-prior tests)
+    (0, 2, 1, 64, 130, True), (0, 2, 1, 64, 1501, False), (0, 4, 2, 64, 1201, False),
+    (1, 2, 1, 128, 1501, False), (1, 2, 2, 128, 1101, False), (1, 2, 3, 128, 901, False), (1, 2, 4, 128, 301, False),
 ])
 def test_decode_split_rule(dtype, z, group, d, live, one):
     """A step without the value prior needs scratch exactly when it splits its heads' slots."""

@@ -440,10 +440,14 @@ def test_decode_extra_slots_are_ignored():
 
 
 @pytest.mark.parametrize("base,batch,hq,hkv,budget,recent", [
-    (BF, 1, 8, 2, 300, 2),            # few heads: slots split over workgroups, merge launch
+    (BF, 1, 8, 2, 300, 2),            # few heads: slots split over workgroups, matrix core, merge launch
     (BF, 16, 8, 8, 70, 3),            # 128 heads: one workgroup per head
-    (synth.C1, 1, 2, 2, 129, 1),      # fp32, split path
-    (synth.C1, 16, 8, 8, 40, 2),      # fp32, single launch
+    (synth.C1, 1, 2, 2, 129, 1),      # fp32, few heads and slots: one workgroup per head
+    (synth.C1, 16, 8, 8, 40, 2),      # fp32, 128 heads
+    (synth.C1, 1, 2, 2, 1500, 1),     # fp32, split
+    (BF, 1, 2, 2, 1500, 2),           # bf16, split on the vector ALU, one to three heads per group
+    (BF, 1, 4, 2, 1100, 2),
+    (BF, 1, 6, 2, 900, 2),
 ])
 def test_decode_equal_minima_evict_the_highest_position(base, batch, hq, hkv, budget, recent):
     """Tie rule of the generation step on both decode paths.  Scale 0 gives every slot the
@@ -548,9 +552,12 @@ def test_sink_policy_end_to_end_with_decode():
 
 
 @pytest.mark.parametrize("base,batch,hq,hkv,budget", [
-    (BF, 1, 8, 2, 300),            # few heads: split + merge launches
+    (BF, 1, 8, 2, 300),            # few heads: split (matrix core) + merge launches
     (BF, 16, 8, 8, 70),            # one workgroup per head
-    (synth.C1, 2, 4, 2, 129),      # fp32
+    (synth.C1, 2, 4, 2, 129),      # fp32, one workgroup per head
+    (synth.C1, 2, 4, 2, 1200),     # fp32, split
+    (BF, 1, 2, 2, 1500),           # bf16, split on the vector ALU
+    (BF, 1, 6, 2, 900),
 ])
 def test_decode_with_value_prior_in_the_loop(base, batch, hq, hkv, budget):
     """Generation with the value prior applied to what is added to the running scores
