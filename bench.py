@@ -176,6 +176,9 @@ def main():
     # Events on the launch stream bracket every launch; between two launches that were
     # enqueued back to back they measure the kernel plus the dispatch gap before it (2-3 us
     # more than the kernel duration a profiler reports).
+    # (the process's first generation step loads its kernels: not one of the timed ones)
+    B.aha_decode_step(p, qn, kn, vn, cache.k, cache.v, cache.scores, cache.pos, cache.free_slot,
+                      n + 1, out, ws)
     stage_sets, call_sets = [], []
     for _ in range(K_STEPS):
         st = [ev() for _ in range(4)]

@@ -338,12 +338,16 @@ int32_t aha_decode_step_static(const aha_params *p, const void *q_new, const voi
                                void *stream);
 
 /*
- * Optional stage timing for aha_prefill_scores (Sec. 4.1 - 4.3 are computed by
- * three launches: value prior, row statistics, column sums).  `events` is an
- * array of `count` caller-created hipEvent_t handles (HOST array, copied by
- * the call); while set, aha_prefill_scores on this thread records events[0]
- * before its first launch and events[1], [2], [3] after the value-prior,
- * row-statistics and column-sum launches, on the call's stream.  count must
+ * Optional stage timing for aha_prefill_scores (Sec. 4.1 - 4.3: value prior, row
+ * statistics, column sums).  `events` is an array of `count` caller-created
+ * hipEvent_t handles (HOST array, copied by the call); while set,
+ * aha_prefill_scores on this thread records events[0] before its first launch
+ * and events[1], [2], [3] behind the value prior's own launch, the row-statistics
+ * and the column-sum launch, on the call's stream.  The prior has a launch of its
+ * own only for bf16 inputs with more than 256 accumulated rows per KV head (where
+ * that launch also zeroes the scores) or a pool_kernel above 17; otherwise it is
+ * formed in the row-statistics launch, between events[1] and [2], and events[0]
+ * and [1] bracket nothing.  count must
  * be 0 (with events NULL: switch off) or 4.  The library neither creates,
  * waits on nor destroys the events.
  */

@@ -436,9 +436,9 @@ struct WideAttn {
 // power of two is rounded half as far as what lies just above.  The pairs of row blocks above give
 // each quarter of a range's keys a reference; with one reference per range here, kept within a
 // factor of two of the maximum, the outputs are no further from float64 (0.88 to 0.98 of the error
-// above over 40 shapes of four and more steps per range; within 2^8 up to 1.02, and equal to the
-// maximum 0.85 to 0.97, but 3 % slower at 8 heads x 32768 keys x 256 rows and 8 % at 32 x 48000 x
-// 192).  In short ranges the exact ones count for more (1.01 to 1.14 without the following, up to
+// above over 40 shapes of four and more steps per range; within 2^8 up to 1.02; equal to the
+// maximum, and the outputs normalised by the sum of the rounded probabilities, 0.85 to 0.97, but 3 %
+// slower at 8 heads x 32768 keys x 256 rows and 8 % at 32 x 48000 x 192).  In short ranges the exact ones count for more (1.01 to 1.14 without the following, up to
 // four steps in sequences of some 2000 keys, up to three in longer ones): there (FINE) a probability
 // goes in as the sum of two bf16 numbers (0.75 to 0.9), which costs little where latency bounds the
 // call (32 heads x 1000 keys x 256 rows 25.9 -> 27.9 us).

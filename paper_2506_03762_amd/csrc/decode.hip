@@ -1,13 +1,21 @@
 // One generation step with running eviction (Alg. 1 Generation, loop body).
 //
-// One workgroup of 1024 threads per (batch, KV head) streams that head's
+// decode_kernel: one workgroup of 1024 threads per (batch, KV head) streams that head's
 // compact K cache once and its V cache once with 16-byte loads (the lanes of
 // a row adjacent, 64 rows per sweep), so the step is bound by HBM bandwidth;
 // the raw dots of all live slots stay in LDS, from which both the attention
 // output (scale 1/sqrt(d)) and the score update (adaptive scale) are formed.
 // No cross-workgroup exchange is needed: the whole head lives in one CU.
-// With five or more query heads per KV head (bf16) the dots of whole 32-slot
-// blocks come from the matrix core instead of per-query vector-ALU dots.
+// bf16: with four or more query heads per KV head the values, with five or more
+// the dots of whole 32-slot blocks as well, go through the matrix core.
+//
+// Fewer than 128 heads: their slots are split over workgroups unless one per head is
+// faster (decode_one_launch).  decode_split_kernel (vector ALU) or decode_split_mfma_kernel
+// (bf16, four or more query heads per KV head) leaves the raw dots and each range's
+// partial output and softmax sums in the workspace; decode_merge_kernel merges the
+// outputs and updates the running scores.
+//
+// decode_value_norms_kernel: a launch before either, where the value prior is on.
 #include "aha_dev.h"
 #include "aha_host.h"
 
