@@ -485,9 +485,18 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DecodeGeom g, int w
     __syncthreads();
     for (int t = tid; t < G * D; t += kDecThreads) {
         const int gi = t / D, c = t % D;
-        float v = 0.f;
+        // Pairwise, four roundings deep: a chain of sixteen partials made the output's error of
+        // fp32 steps 1.05 times that of the split stage, against 1.01 (60 shapes), at the same
+        // time.  (Two chains per thread above would be 0.8 % less again, and took G = 4 steps
+        // from 10.4 to 13.6 us.)
+        float r[kDecWaves];
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) v += s_o[(w * G + gi) * D + (kMfmaValues ? c ^ (8 * gi) : c)];
+        for (int w = 0; w < kDecWaves; ++w) r[w] = s_o[(w * G + gi) * D + (kMfmaValues ? c ^ (8 * gi) : c)];
+#pragma unroll
+        for (int n = kDecWaves / 2; n >= 1; n /= 2)
+#pragma unroll
+            for (int w = 0; w < n; ++w) r[w] += r[w + n];
+        const float v = r[0];
         const int64_t oi = ((int64_t)(b * g.Hq + h * G + gi)) * D + c;
         if constexpr (ESIZE == 2)
             ((uint16_t *)g.out)[oi] = (uint16_t)f32_to_bf16_rne(v);

@@ -159,3 +159,35 @@ def test_slots_with_dots_of_minus_infinity(dtype, z, group, budget, masked):
         assert (np.abs(got - out) <= 2e-5 * rms + 1e-5 * np.abs(out)).all()
     else:
         assert (np.abs(got - out) <= 2.0 ** -8 * np.abs(out) * 1.01 + 2.0 ** -15 * 3 * rms + 1e-6).all()
+
+
+@pytest.mark.parametrize("d,live", [(64, 64), (128, 32)])
+@pytest.mark.parametrize("group", [1, 4])
+def test_the_waves_small_parts_add_up(d, live, group):
+    """Slots of equal weight, one per group of lanes: the first wave's part of the output is 1, each of
+    the other fifteen's 0.9 of half a unit of that.  Added to it one by one, all of those would be lost."""
+    import torch
+    from paper_2506_03762_amd import binding as B
+    z, budget, n = 3, live - 1, 5 * live
+    rows = live // 16
+    p = B.Params(batch=1, n_q_heads=z * group, n_kv_heads=z, head_dim=d, seq_len=0, window=0,
+                 budget=budget, recent=5, dtype=B.AHA_F32)
+    c = B.CompactCache.empty(p)
+    c.k.zero_()
+    c.scores.zero_()
+    c.v.fill_(0.9 * 2.0 ** -24 * live / rows)
+    new = c.v[0, :, 0].clone().unsqueeze(0)
+    c.v[0, :, 0] = live
+    c.pos.copy_(torch.arange(live, device="cuda", dtype=torch.int32).expand_as(c.pos))
+    c.free_slot.fill_(budget)
+    ref = (c.v[0, :, :budget].double().sum(1) + new[0].double()) / live
+    ref = ref.cpu().numpy()[:, None]
+    q = torch.randn((1, z * group, d), device="cuda")
+    out = torch.empty_like(q)
+    ws = torch.empty((max(256, B.workspace_bytes(p)),), dtype=torch.uint8, device="cuda")
+    B.aha_decode_step(p, q, torch.zeros_like(new), new, c.k, c.v, c.scores, c.pos, c.free_slot, n, out, ws)
+    err = np.abs(out.double().cpu().numpy().reshape(z, group, d) - ref)
+    # half a unit of 1 (2^-24) for each sum that the first row goes through: of the rows of its wave
+    # in pairs, then of sixteen waves in pairs (weights of 1 / live and their products are exact but
+    # for the small parts' last bits); in one chain 13.5 of them are lost
+    assert err.max() <= (np.log2(rows) + 4.1) * 2.0 ** -24, err.max() * 2.0 ** 24
