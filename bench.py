@@ -204,11 +204,10 @@ def main():
     d1 = ev()
     torch.cuda.synchronize()
     decode_b2b_us = d0.elapsed_time(d1) * 1e3 / n_dec
-    # (bf16 windowed scores form the value prior inside the row-statistics launch: the
-    # library records events[0] and [1] back to back and pass 1 is bracketed by [1] and [2])
+    # (the windowed bf16 scores are one launch, bracketed by events[1] and [2]; the library records
+    # events[0] and [1] back to back, and [2] and [3])
     kstats = {
-        "score_pass1": us_stats([(s[1], s[2]) for s in stage_sets]),
-        "score_pass2": us_stats([(s[2], s[3]) for s in stage_sets]),
+        "scores": us_stats([(s[1], s[2]) for s in stage_sets]),
         "topk": us_stats([(c[0], c[1]) for c in call_sets]),
         "compact": us_stats([(c[1], c[2]) for c in call_sets]),
         "decode_step": us_stats([(c[2], c[3]) for c in call_sets]),
@@ -219,8 +218,7 @@ def main():
     kbytes = b * hk * n * d * e
     qbytes = b * hq * w.window * d * e
     alg = {  # algorithmic HBM bytes per launch
-        "score_pass1": 2 * kbytes + qbytes + b * hk * n * 4,   # K, V (value prior), Q rows; gamma out
-        "score_pass2": kbytes + qbytes + b * hk * n * 4,
+        "scores": 2 * kbytes + qbytes + b * hk * n * 4,   # K, V (value prior), Q rows; scores out
         "topk": b * hk * n * 4 + b * hk * w.budget * 4,
         "compact": 4 * b * hk * w.budget * d * e + b * hk * w.budget * 12,
         "decode_step": b * hk * (2 * (w.budget + 1) * d * e + 8 * (w.budget + 1) + 2 * d * e)
@@ -231,9 +229,9 @@ def main():
                       "GBps": alg[name] / (kt[name] * 1e-3) / 1e9 if kt[name] > 1e-6 else None}
                for name in kt}
     score_flops_pass = 2.0 * d * b * hq * (w.window * n - w.window * (w.window - 1) / 2)
-    for name in ("score_pass1", "score_pass2"):
-        kernels[name]["TFLOPs"] = score_flops_pass / (kt[name] * 1e-3) / 1e12
-    dom = max(("score_pass1", "score_pass2", "topk", "compact"), key=lambda nm: kt[nm])
+    # (the kernel of this shape sweeps its keys twice and forms the products in both)
+    kernels["scores"]["TFLOPs"] = 2 * score_flops_pass / (kt["scores"] * 1e-3) / 1e12
+    dom = max(("scores", "topk", "compact"), key=lambda nm: kt[nm])
     # HBM bytes per launch from the committed rocprofv3 counter summary of this workload
     traffic = None
     try:
@@ -248,7 +246,7 @@ def main():
                 "timing": "mean of HIP events around the launch on its stream (kernel + dispatch gap)",
                 "kernel_us": kt[dom] * 1e3, "alg_bytes": alg[dom]}
     # the whole score stage against the bytes the method needs once (K + V + Q window)
-    stage_ms = kt["score_pass1"] + kt["score_pass2"]
+    stage_ms = kt["scores"]
     stage_bytes = 2 * kbytes + qbytes + b * hk * n * 4
     roofline_stage = {"stage": "prefill_scores (all its launches)", "bound": "hbm",
                       "achieved": stage_bytes / (stage_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
@@ -601,14 +599,12 @@ def bench_windowed_layer(torch, B, synth, H, w, steps):
         if it >= 2:
             sets.append((st, e0, e1, e2))
     torch.cuda.synchronize()
-    t = {"score_pass1": avg_ms([(s[0][1], s[0][2]) for s in sets]),
-         "score_pass2": avg_ms([(s[0][2], s[0][3]) for s in sets]),
+    t = {"scores": avg_ms([(s[0][1], s[0][2]) for s in sets]),
          "topk": avg_ms([(s[1], s[2]) for s in sets]),
          "compact": avg_ms([(s[2], s[3]) for s in sets])}
     kb = b * hk * n * d * 2
-    # pass 1 also forms the value prior of its key range: it reads K and V once each
-    alg = {"score_pass1": 2 * kb + b * hq * w.window * d * 2 + b * hk * n * 4,
-           "score_pass2": kb + b * hq * w.window * d * 2 + b * hk * n * 4,
+    # one launch: K and V once each
+    alg = {"scores": 2 * kb + b * hq * w.window * d * 2 + b * hk * n * 4,
            "topk": b * hk * (n + w.budget) * 4,
            "compact": 4 * b * hk * w.budget * d * 2 + b * hk * w.budget * 12}
     e0 = ev()

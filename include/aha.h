@@ -344,14 +344,23 @@ int32_t aha_decode_step_static(const aha_params *p, const void *q_new, const voi
  * aha_prefill_scores on this thread records events[0] before its first launch
  * and events[1], [2], [3] behind the value prior's own launch, the row-statistics
  * and the column-sum launch, on the call's stream.  The prior has a launch of its
- * own only for bf16 inputs with more than 256 accumulated rows per KV head (where
+ * own only for bf16 inputs with more than 512 accumulated rows per KV head (where
  * that launch also zeroes the scores) or a pool_kernel above 17; otherwise it is
- * formed in the row-statistics launch, between events[1] and [2], and events[0]
- * and [1] bracket nothing.  count must
+ * formed with the row statistics, and events[0] and [1] bracket nothing.  Most windowed
+ * bf16 scores are a single launch, between events[1] and [2]; events[2] and [3] then
+ * bracket nothing either.  count must
  * be 0 (with events NULL: switch off) or 4.  The library neither creates,
  * waits on nor destroys the events.
  */
 int32_t aha_profile_events(void *const *events, int32_t count);
+
+/*
+ * How patient the workgroups of a launch that exchange parts of a result inside it are, for the
+ * calls of this thread: a workgroup that has looked `looks` times (about a microsecond each;
+ * 4000 at first) without finding the others' parts does the missing ones itself.  Results do
+ * not depend on it.
+ */
+int32_t aha_exchange_looks(int32_t looks);
 
 /* Thread-local description of the last error returned on this thread. */
 const char *aha_last_error(void);

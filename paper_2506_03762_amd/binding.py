@@ -33,7 +33,7 @@ EXPORTS = ("aha_workspace_bytes", "aha_prefill_scores", "aha_prefill_scores_lse"
            "aha_prefill_row_stats", "aha_window_attention_workspace_bytes",
            "aha_prefill_window_attention", "aha_select_topk",
            "aha_compact_kv", "aha_decode_step", "aha_decode_step_static", "aha_profile_events",
-           "aha_last_error",
+           "aha_exchange_looks", "aha_last_error",
            "aha_version")
 
 
@@ -85,6 +85,7 @@ def load() -> ctypes.CDLL:
     lib.aha_decode_step.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, sz, vp]
     lib.aha_decode_step_static.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, vp, vp]
     lib.aha_profile_events.argtypes = [ctypes.POINTER(vp), i32]
+    lib.aha_exchange_looks.argtypes = [i32]
     for name in EXPORTS[:-2]:
         getattr(lib, name).restype = i32
     lib.aha_last_error.restype = ctypes.c_char_p

@@ -4,6 +4,9 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <atomic>
+#include <chrono>
+
 #include "aha_host.h"
 
 namespace aha {
@@ -15,6 +18,10 @@ static thread_local bool g_stage_on = false;
 static hipError_t stage(int i, hipStream_t st) {
     return g_stage_on ? hipEventRecord(g_stage_ev[i], st) : hipSuccess;
 }
+
+// Looks at the other workgroups' announcements before a workgroup does missing parts itself: about a
+// microsecond each.
+constexpr int32_t kLooks = 4000;
 
 static int32_t fail(int32_t code, const char *fmt, ...) {
     va_list ap;
@@ -131,6 +138,84 @@ static ScoreGeom make_geom(const aha_params *p, const void *q, const void *k, co
     return g;
 }
 
+// Windowed bf16 scores in one launch, in the same bytes as the two-launch layout.  Where, and which
+// kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
+// heads, 400 to 65536 keys, d = 64 and 128): 1.30 times as fast as two launches on average, none
+// more than 3 % slower.  us in two launches, in one:
+//  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
+//    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0.  In
+//    several rounds the exchange is waited for in each: a gain only with enough bytes behind it (64 rows,
+//    d = 128: 64 x 32480 296, 276; 8 x 38147 53.8, 56.7, not taken; 32 rows 32 x 28176 121, 130; 64 rows,
+//    d = 64 16 x 34742 51.2, 60.8; 128 rows 64 x 16164 161, 194).  Every range reads all ranges'
+//    statistics: above 48 ranges of 96 and more rows that is too much (1 x 25019 x 123 22.9, 27.6).
+//  - 65 to 128 rows, d = 64, longer problems, swept twice: 6 x 46683 x 126 52.7, 36.3 (d = 128, bound by its
+//    bytes: 8 x 29221 x 128 48.3, 48.9, not taken).
+//  - 129 to 256 rows, held by eight waves where one workgroup per CU covers the problem (16 x 1117 x 152
+//    32.1, 19.1; 32 x 1502 x 256 30.0, 22.2), else swept twice (24 x 32929 x 160 236, 159; 6 x 29092 x
+//    256 66.7, 52.4; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
+//  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 57.8, 33.0; 8 x 9057 x 504 64.6, 56.0).
+static void plan_window(const aha_params *p, PrefillPlan &pl) {
+    pl.win_nb = 0;
+    const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
+    if (p->dtype != AHA_BF16 || R > 512 || (p->value_prior && p->pool_kernel > 17)) return;
+    const int blocks = (int)((R + 31) / 32);
+    const int64_t steps = (p->seq_len + kP2Keys - 1) / kP2Keys;
+    int64_t parts = 0, keys = 0;
+    int nb = 0, tiles = 1;
+    bool hold = false;
+    if (blocks <= 4) {
+        // the shortest ranges of which two per CU cover the problem, else the longest that can be held
+        nb = blocks;
+        int per = 1;
+        while (2 * per * nb <= 4 && pl.Z * ((steps + per - 1) / per) > 512) per *= 2;
+        parts = (steps + per - 1) / per;
+        keys = per * kP2Keys;
+        hold = pl.Z * parts <= 512 ? nb <= 2 || parts <= 48
+                                   : nb == 2 && p->head_dim == 128 && pl.Z * parts >= 1024;
+        if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < 800)) return;
+        if (!hold) nb = 4;
+    } else if (blocks <= 8) {
+        hold = pl.Z * steps <= 256;
+        nb = hold ? (blocks + 1) / 2 : (blocks + 1) / 2 * 2;
+        tiles = hold ? 2 : 1;
+        parts = steps;
+        keys = kP2Keys;
+    } else {
+        tiles = 2;
+        nb = blocks <= 12 ? 6 : 8;
+    }
+    if (!hold) {
+        // one workgroup per CU, in rounds of the whole chip: the number of ranges with the shortest sum
+        // over the rounds of a range's steps and its set-up and exchange, about as long as a step
+        const int64_t step = 512 / tiles, all = (p->seq_len + step - 1) / step;
+        int64_t best = INT64_MAX;
+        parts = 1;
+        for (int64_t n = 1; n <= all && n <= 256; ++n) {
+            const int64_t sum = (pl.Z * n + 255) / 256 * ((all + n - 1) / n + 1);
+            if (sum < best) best = sum, parts = n;
+        }
+        keys = (all + parts - 1) / parts * step;
+        parts = (p->seq_len + keys - 1) / keys;
+    }
+    if (pl.Z * parts > 1 << 30 || parts >= 1 << 19) return;
+    pl.win_nb = nb;
+    pl.win_tiles = tiles;
+    pl.win_hold = hold;
+    pl.win_parts = (int)parts;
+    pl.win_keys = (int)keys;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
+    pl.off_wstats = take(sizeof(float) * (size_t)pl.Z * parts * tiles * nb * 32);
+    pl.off_wmax = take(8 * sizeof(float) * (size_t)pl.Z * parts);  // per wave
+    pl.off_wtags = take(sizeof(uint64_t) * (size_t)pl.Z * parts);
+    pl.off_wcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
+    if (!hold) {
+        pl.off_wnu = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
+        pl.off_wgamma = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
+    }
+    if (off > pl.bytes) pl.bytes = off;
+}
+
 // Workspace layout of aha_prefill_scores.
 static PrefillPlan plan_prefill(const aha_params *p) {
     PrefillPlan pl{};
@@ -200,10 +285,9 @@ static PrefillPlan plan_prefill(const aha_params *p) {
     off = align_up(off + sizeof(float) * (size_t)pl.Z * n_maxima, 256);
     // windowed bf16 scores: pass 1 forms the value prior itself (the pooling halo it gathers
     // at a range's ends is bounded: pool widths up to 17)
-    pl.can_fold = p->dtype == AHA_BF16 && pl.n_qtiles == 1 && p->pool_kernel <= 17;
-    pl.off_nu = off;  // squared value norms [Z][n], pass 1 -> its own pooling
-    if (pl.can_fold) off = align_up(off + sizeof(float) * (size_t)pl.Z * n, 256);
+    pl.can_fold = p->dtype == AHA_BF16 && pl.n_qtiles == 1 && pl.NB <= 4 && p->pool_kernel <= 17;
     pl.bytes = off;
+    plan_window(p, pl);
     return pl;
 }
 
@@ -374,6 +458,19 @@ int32_t aha_workspace_bytes(const aha_params *p, size_t *out_bytes) {
 
 // Shared by aha_prefill_scores (lse == nullptr), aha_prefill_scores_lse and
 // aha_prefill_scores_rows (rows != nullptr).
+
+// A number that no other call of this process uses, for the exchanges inside a launch: the upper 44
+// bits of a counter that starts anywhere, never zero.
+static uint64_t next_tag() {
+    static std::atomic<uint64_t> next{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() *
+                                      0x9E3779B97F4A7C15u};
+    for (;;) {
+        const uint64_t t = next.fetch_add(1, std::memory_order_relaxed) << 20;
+        if (t) return t;
+    }
+}
+static thread_local int32_t g_looks = kLooks;
+
 static int32_t prefill_scores_impl(const aha_params *p, const void *q, const void *k,
                                    const void *v, const float *lse, bool with_lse,
                                    const int32_t *rows, float *scores, void *workspace,
@@ -400,6 +497,14 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     g.rows = rows;
     hipStream_t st = (hipStream_t)stream;
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
+    if (pl.win_nb && !rows && !with_lse) {
+        if ((rc = hip_result(stage(1, st), "stage event")) ||
+            (rc = hip_result(launch_score_window(g, pl, workspace, next_tag(), g_looks, scores, st),
+                             "windowed score kernel")) ||
+            (rc = hip_result(stage(2, st), "stage event")))
+            return rc;
+        return hip_result(stage(3, st), "stage event");
+    }
     // the windowed bf16 scores and the fp32 scores form the value prior inside their
     // row-statistics launch
     const bool fold_prior = p->value_prior && !with_lse && (p->dtype == AHA_F32 || (pl.can_fold && !rows));
@@ -636,6 +741,12 @@ int32_t aha_decode_step_static(const aha_params *p, const void *q_new, const voi
     // nothing has to start from zero
     return decode_step_launch(p, dpl, q_new, k_new, v_new, k_cache, v_cache, scores_c, pos_c,
                               free_slot, cache_slots, logical_pos, out, g_scratch_ptr[dev], stream);
+}
+
+int32_t aha_exchange_looks(int32_t looks) {
+    if (looks < 0) return fail(AHA_ERR_INVALID_ARG, "looks must be >= 0");
+    g_looks = looks;
+    return AHA_OK;
 }
 
 int32_t aha_profile_events(void *const *events, int32_t count) {

@@ -55,8 +55,14 @@ struct PrefillPlan {
     int p2_keys;     // keys per pass-2 workgroup (a multiple of kP2Keys)
     int n_vtiles;    // value-prior tiles per problem (separate launch)
     bool f32_mfma;   // fp32 scores on the matrix core (pass 1 in nchunks key ranges)
-    bool can_fold;   // windowed bf16 scores: pass 1 can form the value prior per key chunk
-    size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax, off_nu;
+    bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
+    // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
+    // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
+    // prior maxima, announcements and their counts, the value norms and the prior live
+    int win_nb, win_tiles, win_parts, win_keys;
+    bool win_hold;
+    size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma;
+    size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;
 };
 
@@ -81,6 +87,11 @@ hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
 hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
                              float *scores, hipStream_t st, hipEvent_t mid, bool have_lse,
                              bool fold_prior);
+// score_window.hip
+// Windowed scores in one launch (pl.win_nb > 0).  `tag`: a number no other call uses, its low 20 bits
+// zero; `looks`: at the other workgroups' announcements before missing parts are done in place.
+hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+                               float *scores, hipStream_t st);
 // Row statistics of the observed rows out (pass 1 only): natural-log normaliser and entropy,
 // dense [batch, Hq, window]; either pointer may be null.
 hipError_t launch_row_stats_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *lse,

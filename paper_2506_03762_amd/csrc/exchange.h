@@ -1,0 +1,93 @@
+// Exchange between the workgroups of one problem inside one launch: every workgroup leaves its
+// part of a result in the workspace, announces it, and uses the others' parts once all of them
+// are announced.
+//
+// No cache is written back or invalidated for it (a device-scope release does that for the whole
+// L2 of an XCD, microseconds per workgroup): what is exchanged is stored and loaded with relaxed
+// agent-scope accesses, which go past the caches that are not shared, and an announcement is
+// stored once the wave's counter of outstanding accesses says that its data has arrived
+// (announce).  512 workgroups, 16 to 64 to a problem: 1.5 to 3 us from the first store to the last
+// load.
+//
+// An announcement is the call's TAG, a 64-bit number that no other call of the process uses, so
+// the workspace needs no clearing launch (3 us) in front: whatever it holds on entry is not this
+// tag.  A captured graph replays a call with its tag, so the workgroup that is the last of its problem to have
+// seen all announcements clears them.  It is found by a counter that starts itself: its upper
+// bits are the tag's, and an arrival that finds other bits there sets them.
+//
+// Nobody depends on workgroups that may not be running: after `looks` looks at the announcements a
+// workgroup does the missing parts itself, one after the other, and announces them too (a part's
+// result is the same bits whoever forms it).
+#pragma once
+
+#include "aha_dev.h"
+
+namespace aha {
+
+struct Exchange {
+    uint64_t *tags;    // [problem][part]
+    uint64_t *counts;  // [problem]
+    uint64_t tag;      // of this call; the low kCountBits are zero, the rest is not
+    int looks;         // at the announcements before missing parts are done here
+};
+constexpr int kCountBits = 20;  // parts of a problem: fewer than 2^20
+
+template <class T>
+__device__ __forceinline__ void put(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T get(const T *p) {
+    return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every thread's put()s so far belong to part `part` of problem z: wait until they have arrived,
+// then announce the part.  Called by the whole workgroup; one barrier.
+__device__ __forceinline__ void announce(const Exchange &x, int z, int nparts, int part, int tid) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) put(x.tags + (int64_t)z * nparts + part, x.tag);
+}
+
+// The first part of problem z that has not been announced after x.looks looks, nparts if there is
+// none.  Called by one wave (more of them would get in the way of the data's loads); every lane gets
+// the result.
+__device__ __forceinline__ int first_missing(const Exchange &x, int z, int nparts, int lane) {
+    const uint64_t *t = x.tags + (int64_t)z * nparts;
+    int missing = nparts;
+    for (int look = 0;; ++look) {
+        missing = nparts;
+        for (int p = lane; p < nparts; p += kWave)
+            if (get(t + p) != x.tag) missing = min(missing, p);
+        if (__builtin_amdgcn_ballot_w64(missing < nparts) == 0) return nparts;
+        if (look >= x.looks) break;
+        __builtin_amdgcn_s_sleep(4);
+    }
+    return reduce_lanes<1, 64>(missing, OpMinI{});
+}
+
+// The count of a problem's workgroups that have seen all announcements, so that the last one can clear
+// them.  Whoever does part 0 sets it to the tag (unless somebody else has) before announcing that part:
+// nobody counts himself before.  One thread of the workgroup: `look` early, `start` some time
+// before announce(), which waits for it.
+struct Count {
+    uint64_t found;
+    __device__ __forceinline__ void look(const Exchange &x, int z) { found = get(x.counts + z); }
+    __device__ __forceinline__ void start(const Exchange &x, int z) {
+        if ((found ^ x.tag) >> kCountBits)
+            (void)__hip_atomic_compare_exchange_strong(x.counts + z, &found, x.tag, __ATOMIC_RELAXED,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // once per workgroup, when it has seen all announcements
+    __device__ __forceinline__ void arrive(const Exchange &x, int z) {
+        found = __hip_atomic_fetch_add(x.counts + z, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+// By the whole wave of the thread that arrived (its last lane), at the end of the workgroup's work.
+__device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, const Count &c, int lane) {
+    if (__builtin_amdgcn_ballot_w64(lane == kWave - 1 && c.found == x.tag + (uint64_t)(nparts - 1)) == 0) return;
+    for (int p = lane; p < nparts; p += kWave) put(x.tags + (int64_t)z * nparts + p, (uint64_t)0);
+    if (lane == 0) put(x.counts + z, (uint64_t)0);
+}
+
+}  // namespace aha

@@ -20,122 +20,9 @@
 // memory into registers (each K byte is fetched once per tile), so waves run
 // independently between the tile barriers; the A fragments are double-buffered so
 // that the next key block is in flight while the current one multiplies.
-#include "score_tile.h"
+#include "score_block.h"
 
 namespace aha {
-
-
-// Online max / sum-of-exp2 of one 64 x 32 block for this lane's query column.
-// The scale is non-negative, so the maximum of the scaled logits is the scale
-// times the maximum raw dot.
-// With ENT the first moment u = sum of exp2(t - m) * (t - m) is kept beside the sum: the
-// row's entropy is ln 2 * (log2 s - u / s) (Sec. 4.2, entropy of a softmax row).
-template <bool MASK, bool ENT, bool LAZY = false>
-__device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam, int pos, int kb,
-                                             int lane, float &m, float &s, float &u) {
-    if (MASK) asm volatile("" ::: "memory");
-    if constexpr (!MASK && LAZY) {
-        // (LAZY: full accumulation, where this loop is the kernel; in the windowed kernel the
-        // second code path costs registers that spill.)
-        // Unmasked blocks: `m` is a REFERENCE that sum and moment are relative to, not
-        // necessarily the running maximum (the final statistics m + log2 s and u / s do not
-        // depend on it).  As long as every lane has one, the block is summed against it as it
-        // stands - no maximum over the block's 32 elements - and the reference is only moved
-        // (by the exact update below, which also redoes this block) when a block's sum says
-        // that it has fallen more than 40 binades behind: fp32 has room for that, and a
-        // reference never lies above the largest logit seen, so nothing underflows that the
-        // exact update would have kept.
-        if (__builtin_amdgcn_ballot_w64(m == -INFINITY) == 0) {
-            float sum[4] = {0.f, 0.f, 0.f, 0.f}, mom[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float x = fmaf(acc[mb][v], lam, -m);
-                    const float e = fast_exp2(x);
-                    sum[v & 3] += e;
-                    if (ENT) mom[v & 3] = fmaf(e, x, mom[v & 3]);
-                }
-            const float bs = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-            if (__builtin_amdgcn_ballot_w64(!(bs < 0x1p40f)) == 0) {  // (also: not a NaN)
-                s += bs;
-                if (ENT) u += (mom[0] + mom[1]) + (mom[2] + mom[3]);
-                return;
-            }
-        }
-    }
-    float amax = -INFINITY;
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float x = acc[mb][v];
-            if (MASK && acc_key(kb, mb, v, lane) > pos) x = -INFINITY;
-            amax = fmaxf(amax, x);
-        }
-    const float tmax = amax == -INFINITY ? -INFINITY : amax * lam;
-    const float mn = fmaxf(m, tmax);
-    const float mref = mn == -INFINITY ? 0.f : mn;
-    // four partial sums: independent chains, so that the exponentials' result latency is
-    // covered by other work instead of wait states
-    float sum[4] = {0.f, 0.f, 0.f, 0.f}, mom[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float x = fmaf(acc[mb][v], lam, -mref);
-            float e = fast_exp2(x);
-            if (MASK && acc_key(kb, mb, v, lane) > pos) e = 0.f;
-            sum[v & 3] += e;
-            // (e = 0 for masked or far-away keys: 0 * x, x finite, adds nothing)
-            if (ENT) mom[v & 3] = fmaf(e, x, mom[v & 3]);
-        }
-    const float f = fast_exp2(m - mref);  // 0 while the row has seen no key
-    if (ENT) {
-        const float dm = m == -INFINITY ? 0.f : m - mref;
-        u = (u + dm * s) * f + ((mom[0] + mom[1]) + (mom[2] + mom[3]));
-    }
-    s = s * f + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
-    m = mn;
-}
-
-template <bool MASK>
-__device__ __forceinline__ void colsum_update(const f32x16 (&acc)[kMB], float lam, float L,
-                                              int pos, int kb, int lane, f32x16 (&col)[kMB]) {
-    // The empty asm keeps the masked and the unmasked instantiation apart: without it the
-    // compiler merges the two branches and every block pays the per-element compare/select.
-    if (MASK) asm volatile("" ::: "memory");
-    if constexpr (!MASK) {
-        // Four elements at a time - their scaled logits, their exponentials, their sums - and
-        // the instructions kept in that order: scheduled by register pressure alone, every
-        // exponential is followed at once by the addition that needs it, with a wait state
-        // (an issue slot of the wave) in between.
-#pragma unroll
-        for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-            for (int v0 = 0; v0 < 16; v0 += 4) {
-                float t[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = fmaf(acc[mb][v0 + i], lam, -L);
-                asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = fast_exp2(t[i]);
-                asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) col[mb][v0 + i] += t[i];
-            }
-        return;
-    }
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float p = fast_exp2(fmaf(acc[mb][v], lam, -L));
-            if (MASK && acc_key(kb, mb, v, lane) > pos) p = 0.f;
-            col[mb][v] += p;
-        }
-    if (MASK) asm volatile("" ::: "memory");
-}
 
 
 // Work split shared by pass 1 and by pass 2 in full accumulation.  Query tile `pair` is
@@ -178,112 +65,35 @@ __device__ __forceinline__ Segment pair_segment(const RowMap &rm, int rows, int 
 // ---------------------------------------------------------------- pass 1 --
 constexpr int kNoPrior = 0, kPriorFold = 1, kPriorOneStep = 2;  // value prior inside pass 1 (below)
 
-// Value prior (Sec. 4.3) inside pass 1.  The value rows of the 64 keys a wave multiplies in a
-// step are loaded with the addressing of the key fragments into the register buffer that is
-// idle in the first half of the step (the next key block is requested at mid-step instead of
-// at the start): a lane then holds one half (the channels of its half-wave) of two value rows.
-
-// nu = ||V_row||^2 of those rows: squares summed in-lane, one exchange between the half-waves.
-template <int D>
-__device__ __forceinline__ void fragment_row_norms(const bf16x8 (&a)[kMB][D / 16],
-                                                   float (&nu)[kMB]) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            const bf16x8 w = a[mb][ks];
-            const bf16x2 p0 = {w[0], w[1]}, p1 = {w[2], w[3]}, p2 = {w[4], w[5]}, p3 = {w[6], w[7]};
-            s0 = __builtin_amdgcn_fdot2_f32_bf16(p0, p0, s0, false);
-            s1 = __builtin_amdgcn_fdot2_f32_bf16(p1, p1, s1, false);
-            s0 = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, s0, false);
-            s1 = __builtin_amdgcn_fdot2_f32_bf16(p3, p3, s1, false);
-        }
-        const float h = s0 + s1;
-        nu[mb] = combine_lane_xor<32>(h, OpSum{});
-    }
-}
-
-// Pooling halo of a key range [kbeg, kend): the (pool - 1) / 2 value rows below and above it,
-// one per group of d / 8 lanes (at most 256 / (d / 8) rows: the host checks the pool width).
-// Requested right after the main loop, squared when the range is pooled.
-template <int D>
-struct PriorHalo {
-    static constexpr int CPR = D / 8;  // 16-byte chunks per value row
-    u32x4 w;
-    int pos;     // token of this thread's halo row
-    bool valid;  // the row exists (inside the sequence, inside the halo)
-    bool below;
-    __device__ __forceinline__ void request(const ScoreGeom &g, const __bf16 *vbase, int kbeg,
-                                            int kend, int tid) {
-        const int half = (g.pool - 1) / 2, hrow = tid / CPR;
-        below = hrow < half;
-        pos = below ? kbeg - half + hrow : kend + hrow - half;
-        valid = hrow < 2 * half && pos >= 0 && pos < g.n;
-        w = u32x4{0u, 0u, 0u, 0u};
-        if (valid) w = *(const u32x4 *)(vbase + (int64_t)pos * g.vs[2] + (tid % CPR) * 8);
-    }
-    // ||row||^2 in the first lane of the row's group (every lane takes part)
-    __device__ __forceinline__ float norm() const {
-        float hn = 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float x = bf16_lo(w[c]), y = bf16_hi(w[c]);
-            hn = fmaf(x, x, fmaf(y, y, hn));
-        }
-        return reduce_lanes<1, CPR>(hn, OpSum{});
-    }
-};
-
 // gamma = edge-truncated mean of nu over the pool window for the keys [kbeg, kend) of problem
-// z, written to `gamma`; returns (in every thread) the largest gamma of the range.  The norms
-// of the range's own rows were left by the workgroup's waves in `nu_g` (read past the L1:
-// other waves of this workgroup wrote them); the range is worked through in pieces staged in
-// s_nu.  The caller has passed a barrier since the last norm was written.
-constexpr int kPriorPiece = 512;
-constexpr int kPriorMaxHalo = 32;  // rows on both sides together
+// z (at most kPriorPiece), whose norms the workgroup's waves left in s_nu, written to `gamma`;
+// returns (in every thread) the largest gamma of the range.
 constexpr size_t kPriorSmem = (kPriorPiece + kPriorMaxHalo + 4) * sizeof(float);
-// IN_LDS: the range is at most one piece and its norms are in s_nu already.
-template <int D, bool IN_LDS>
-__device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg,
-                                                     int kend, const float *nu_g,
-                                                     const PriorHalo<D> &halo, float *s_nu,
-                                                     float *gamma, int tid) {
-    const int half = (g.pool - 1) / 2;
+template <int D>
+__device__ __forceinline__ float pool_norms_in_lds(const ScoreGeom &g, int z, int kbeg, int kend,
+                                                   const PriorHalo<D> &halo, float *s_nu, float *gamma,
+                                                   int tid) {
+    const int half = (g.pool - 1) / 2, lo = max(0, kbeg - half);
     float *s_max = s_nu + kPriorPiece + kPriorMaxHalo;
     const float hn = halo.norm();
+    if (halo.valid && tid % PriorHalo<D>::CPR == 0) s_nu[halo.pos - lo] = hn;
+    __syncthreads();
     float gmax = 0.f;
-    for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
-        const int t1 = min(kend, t0 + kPriorPiece);
-        const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
-        for (int t = max(lo, kbeg) + tid; !IN_LDS && t < min(hi, kend); t += 256)
-            s_nu[t - lo] = __hip_atomic_load(nu_g + (int64_t)z * g.n + t, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        // the halo rows that touch this piece (the first piece below, the last one above)
-        if (halo.valid && tid % PriorHalo<D>::CPR == 0 && (halo.below ? t0 == kbeg : t1 == kend))
-            s_nu[halo.pos - lo] = hn;
-        __syncthreads();
-        for (int j = t0 + tid; j < t1; j += 256) {
-            const int a = max(0, j - half), e = min(g.n - 1, j + half);
-            float s = 0.f;
-            for (int t = a; t <= e; ++t) s += s_nu[t - lo];
-            const float gam = s / (float)(e - a + 1);
-            gamma[(int64_t)z * g.n + j] = gam;
-            gmax = fmaxf(gmax, gam);
-        }
-        __syncthreads();
+    for (int j = kbeg + tid; j < kend; j += 256) {
+        const int a = max(0, j - half), e = min(g.n - 1, j + half);
+        float s = 0.f;
+        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
+        const float gam = s / (float)(e - a + 1);
+        gamma[(int64_t)z * g.n + j] = gam;
+        gmax = fmaxf(gmax, gam);
     }
     gmax = wave_max(gmax);
     if ((tid & 63) == 0) s_max[tid >> 6] = gmax;
     __syncthreads();
-    gmax = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-    __syncthreads();
-    return gmax;
+    return fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
 }
 
-// The prior of a key range formed AFTER the main loop, for tiles of fewer than 256 rows (see
-// bf16_pass1_kernel): value rows of the keys [kbeg, kend) of problem z are streamed in a phase
+// The prior of a key range formed AFTER the main loop (see bf16_pass1_kernel): value rows of the keys [kbeg, kend) of problem z are streamed in a phase
 // of their own: nu = ||V||^2 of the range and its pooling halo into
 // LDS, gamma = edge-truncated mean over the pool window, written to `gamma`; returns (in
 // every thread) the largest gamma of the range.  Works through the range in pieces of
@@ -322,25 +132,17 @@ __device__ __forceinline__ float value_prior_of_range(const ScoreGeom &g, int b,
     return gmax;
 }
 
-// PRIOR (windowed scores with the value prior): the workgroup also forms the prior of its key
-// range and leaves the range's maximum in gblockmax[z * nparts + part]: one launch less than
-// a value-prior kernel of its own (a launch costs 4 - 5 us, a third of that kernel's time at
-// 8 heads x 32K).  Where in the kernel depends on the tile:
-//  - a full tile (256 rows, NB = 8): a step's arithmetic takes microseconds, long enough to
-//    hide a load, so the value rows stream in under it.  Per step a wave loads the value rows
-//    of its 64 keys into the idle register buffer, squares them at mid-step into `nu_g`
-//    ([problem][token], workspace) and only then requests the next key block into that
-//    buffer; after the main loop the range's norms are pooled (32K tokens x 8 KV heads:
-//    pass 1 43.6 -> 39.5 us against a phase after the loop).
-//  - smaller tiles: the steps are too short for that (the key prefetch would have half a
+// PRIOR (windowed scores of up to four row blocks with the value prior, the sizes that score_window.hip
+// leaves): the workgroup also forms the prior of its key range and leaves the range's maximum in
+// gblockmax[z * nparts + part]: one launch less than a value-prior kernel of its own.
+//  - kPriorFold: the steps are too short to hide value rows under (the key prefetch would have half a
 //    step to arrive), and the kernel is bound by the key stream: the value rows are streamed
 //    in a phase of their own after the statistics (16K tokens x 128 heads x 64 rows: 183 us
 //    against 215 us interleaved).
 //  - ranges of one step (kPriorOneStep; problems of which every workgroup gets at most 256
 //    keys): the register buffer of the next key block is idle throughout, so the value rows
 //    and the pooling halo are requested in the set-up, right behind the keys, and their norms
-//    never leave LDS.  The kernel waits for memory once: 32 heads x 4096 tokens x 64 rows 18.4
-//    -> 16.9 us, 12 heads x 5003 x 120 rows 13.7 -> 11.6.
+//    never leave LDS.  The kernel waits for memory once: 12 heads x 5003 x 120 rows 13.7 -> 11.6 us.
 // ENT: the chunk's mean scaled logit under its own probabilities, E_c[t] = m + u / s, is
 // written to `partial_mean` beside the chunk's log2-sum-exp2; entropy_merge_kernel turns the
 // chunks of a row into its entropy.
@@ -348,17 +150,16 @@ template <int D, int NB, bool ENT, bool ROWS = false, int PRIOR = kNoPrior, bool
 __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_qtiles, int nparts,
                                                             int total_wgs, float *partial,
                                                             float *partial_mean, float *gamma,
-                                                            float *gblockmax, float *nu_g) {
+                                                            float *gblockmax) {
     using S = TileSmem<D, NB>;
     constexpr bool kOneStep = PRIOR == kPriorOneStep;
-    constexpr bool kInterleave = PRIOR == kPriorFold && NB == 8;  // value rows under the tile arithmetic
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __bf16 *sQ = (__bf16 *)smem;
     float *sLam = (float *)(smem + S::q_bytes);
     int *sPos = (int *)(sLam + S::ROWS);
     int *sBlk = sPos + 2 * S::ROWS;
     float4 *sRed = (float4 *)smem;  // reuses the query tile after the main loop
-    float *sNu = (float *)(smem + S::bytes);  // kInterleave, kOneStep: kPriorSmem bytes behind the tile
+    float *sNu = (float *)(smem + S::bytes);  // kOneStep: kPriorSmem bytes behind the tile
 
     // logical workgroup index -> (part, tile pair, problem)
     const int wg = logical_wg_index(total_wgs, n_qtiles > 1);
@@ -470,26 +271,8 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
         // how many loads are in flight and would wait for the prefetch itself.
         auto step = [&](const bf16x8 (&a)[kMB][D / 16], bf16x8 (&nx)[kMB][D / 16], int kb,
                         int kb_next) {
-            if constexpr (!kInterleave) {
-                load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
-                blocks(a, kb, 0, NB);
-            } else {
-                load_a<D>(vbase, g.vs[2], kb, key_end, lane, nx);  // the value rows of these keys
-                __builtin_amdgcn_sched_barrier(0);
-                blocks(a, kb, 0, (NB + 1) / 2);
-                __builtin_amdgcn_sched_barrier(0);
-                float nu[kMB];
-                fragment_row_norms<D>(nx, nu);
-#pragma unroll
-                for (int mb = 0; mb < kMB; ++mb) {
-                    const int row = kb + mb * 32 + lane;
-                    if (lane < 32 && row < key_end) nu_g[(int64_t)z * g.n + row] = nu[mb];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
-                __builtin_amdgcn_sched_barrier(0);
-                blocks(a, kb, (NB + 1) / 2, NB);
-            }
+            load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
+            blocks(a, kb, 0, NB);
         };
         if constexpr (kOneStep) {
             const int kb = kb_of(0);
@@ -509,8 +292,6 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                 step(a1, a0, kb_of(i + 1), kb_of(i + 2));
             }
         }
-        if constexpr (kInterleave)  // travels while the statistics are reduced
-            halo.request(g, vbase, key_begin, key_end, tid);
         // fold the two half-waves (same query column, different key rows); a statistic
         // (m, s, u) re-referenced to a maximum M >= m is (M, s f, (u + (m - M) s) f), f = 2^(m - M)
         auto reref = [](float m_, float mref, float &s_, float &u_) {
@@ -555,10 +336,9 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             my_partial[tid] = M + log2f(sum);  // -inf for a row that saw no key
             if (ENT) partial_mean[my_off + tid] = sum > 0.f ? mref + mom / sum : 0.f;
         }
-        if constexpr (kInterleave || kOneStep) {
+        if constexpr (kOneStep) {
             // (every wave's norms were written before the barriers of the reduction above)
-            const float gm = pool_norms_of_range<D, kOneStep>(g, z, key_begin, key_end, nu_g, halo,
-                                                              sNu, gamma, tid);
+            const float gm = pool_norms_in_lds<D>(g, z, key_begin, key_end, halo, sNu, gamma, tid);
             if (tid == 0) gblockmax[z * nparts + part] = gm;
         } else if constexpr (PRIOR == kPriorFold) {
             __syncthreads();  // the reduction buffer is done with
@@ -888,13 +668,15 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
     float *partial = (float *)(w + pl.off_partial);
     float *gamma = (float *)(w + pl.off_gamma);
     float *gbm = (float *)(w + pl.off_gblockmax);
-    float *nu = (float *)(w + pl.off_nu);
+    // (the prior is formed here for tiles of up to four blocks, in ranges of one step for four: the
+    // other sizes are score_window.hip's)
+    constexpr int kFold = NB <= 4 ? kPriorFold : kNoPrior, kOneStep = NB == 4 ? kPriorOneStep : kFold;
     static DeviceOnce once;
     const hipError_t ea = device_once(once, [] {
         const void *kernels[9] = {(const void *)bf16_pass1_kernel<D, NB, false>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kPriorFold>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kPriorOneStep>,
+                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kFold>,
+                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kOneStep>,
                                   (const void *)bf16_pass1_kernel<D, NB, true>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, true>,
                                   (const void *)bf16_pass2_kernel<D, NB, true>,
@@ -917,26 +699,23 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
         if (g.rows)
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, true>), xcd_grid(wgs1), dim3(256),
                                S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial,
-                               (float *)nullptr, (float *)nullptr, (float *)nullptr,
-                               (float *)nullptr);
+                               (float *)nullptr, (float *)nullptr, (float *)nullptr);
         else if (fold_prior && pl.nchunks == (g.n + kWgKeys - 1) / kWgKeys)  // ranges of one step
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kPriorOneStep>), xcd_grid(wgs1),
+            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kOneStep>), xcd_grid(wgs1),
                                dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
-                               partial, (float *)nullptr, gamma, gbm, nu);
+                               partial, (float *)nullptr, gamma, gbm);
         else if (fold_prior)
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kPriorFold>), xcd_grid(wgs1),
+            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kFold>), xcd_grid(wgs1),
                                dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
-                               partial, (float *)nullptr, gamma, gbm, nu);
+                               partial, (float *)nullptr, gamma, gbm);
         else if (pl.n_qtiles > 1)  // full accumulation: block sums against a lazy reference
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>), xcd_grid(wgs1),
                                dim3(256), S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
-                               partial, (float *)nullptr, (float *)nullptr, (float *)nullptr,
-                               (float *)nullptr);
+                               partial, (float *)nullptr, (float *)nullptr, (float *)nullptr);
         else
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false>), xcd_grid(wgs1), dim3(256),
                                S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial,
-                               (float *)nullptr, (float *)nullptr, (float *)nullptr,
-                               (float *)nullptr);
+                               (float *)nullptr, (float *)nullptr, (float *)nullptr);
     }
     const int stat_chunks = have_lse ? 1 : pl.nchunks;
     // the prior's per-range maxima: one per key chunk when pass 1 formed it, else per tile
@@ -984,7 +763,7 @@ static hipError_t launch_stats_t(const ScoreGeom &g, const PrefillPlan &pl, void
     const int64_t wgs1 = (int64_t)pl.nchunks * ((pl.n_qtiles + 1) / 2) * pl.Z;
     hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, true>), xcd_grid(wgs1), dim3(256), S::bytes, st,
                        g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial, partial_mean,
-                       (float *)nullptr, (float *)nullptr, (float *)nullptr);
+                       (float *)nullptr, (float *)nullptr);
     const hipError_t e1 = hipGetLastError();
     if (e1 != hipSuccess) return e1;
     hipLaunchKernelGGL(row_stats_merge_kernel, dim3((g.R + 255) / 256, pl.Z), dim3(256), 0, st, g,

@@ -152,12 +152,12 @@ __device__ __forceinline__ int tile_min_pos(const int *sBlk) {
 // channels ks*16 + (lane/32)*8 .. +8.  Rows at or past `end` (the end of the
 // workgroup's key range, at most the sequence length) read row end - 1 instead:
 // their results are masked or never written, and a prefetch past the range then
-// costs one row, not a block of somebody else's keys.
-template <int D>
+// costs one row, not a block of somebody else's keys.  M: the first M groups of 32 rows only.
+template <int D, int M = kMB>
 __device__ __forceinline__ void load_a(const __bf16 *kbase, int64_t k_tstride, int kb, int end,
                                        int lane, bf16x8 (&a)[kMB][D / 16]) {
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
+    for (int mb = 0; mb < M; ++mb) {
         const int row = min(kb + mb * 32 + (lane & 31), end - 1);
         const __bf16 *p = kbase + (int64_t)row * k_tstride + (lane >> 5) * 8;
 #pragma unroll

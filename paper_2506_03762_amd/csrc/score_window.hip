@@ -1,0 +1,767 @@
+// Windowed bf16 eviction scores in ONE launch (Sec. 4.1 - 4.3; Alg. 1 Prefill).
+//
+// A score needs the log-sum-exp of every observed row over ALL keys before any key's column can be
+// summed.  The workgroups of a (batch, KV head) problem each own a range of its keys; they exchange
+// their ranges' row statistics and prior maxima (exchange.h) and go on to the column sums of their
+// own range.  Against two launches this saves the second set-up (query tile, first keys) and, in the
+// held form, the second read of the keys and their products.
+//
+// window_hold_kernel (up to four blocks of 32 rows, eight with two tiles): the logits of the range stay
+// in the accumulators while the statistics travel.  32 heads x 4096 keys x 64 rows: 29 -> 22 us; bound by
+// the one burst of loads (9 us to the last wave's keys), then one round trip each for announcing,
+// looking and fetching.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
+// window_stream_kernel (below): more rows or longer ranges, the logits formed twice.  8 heads x 16384 x
+// 512 rows 89 -> 67 us, 8 x 32768 x 256 70 -> 67: bound by the vector ALU and the matrix core taking turns
+// (620 ns per 64 x 32 block and SIMD), the first sweep's first step by its loads.
+#include <type_traits>
+
+#include "exchange.h"
+#include "score_block.h"
+
+namespace aha {
+
+template <int D, int NB, int NT, int KEYS, bool PRIOR>
+struct HoldSmem {
+    static constexpr int TROWS = NB * 32, ROWS = NT * TROWS;
+    static constexpr size_t off_red = NT * TileSmem<D, NB>::bytes;  // float2 [wave][row of its tile], then column sums
+    static constexpr size_t off_nu = off_red + 4 * ROWS * sizeof(float2);
+    static constexpr size_t off_gam = off_nu + (PRIOR ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
+    static constexpr size_t off_misc = off_gam + (PRIOR ? KEYS * sizeof(float) : 0);
+    static constexpr size_t bytes = off_misc + 12 * sizeof(float);
+    static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
+};
+
+// gamma (Sec. 4.3) of the keys [kbeg, kend), whose norms and pooling halo are in s_nu[t - lo],
+// lo = max(0, kbeg - half), into s_gam[key - kbeg]; returns this thread's largest.
+__device__ __forceinline__ float pool_norms(const ScoreGeom &g, int kbeg, int kend, const float *s_nu,
+                                            float *s_gam, int tid, int nthreads) {
+    const int half = (g.pool - 1) / 2, lo = max(0, kbeg - half);
+    float gmax = 0.f;
+    for (int j = kbeg + tid; j < kend; j += nthreads) {
+        const int a = max(0, j - half), e = min(g.n - 1, j + half);
+        float s = 0.f;
+        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
+        const float gam = s / (float)(e - a + 1);
+        s_gam[j - kbeg] = gam;
+        gmax = fmaxf(gmax, gam);
+    }
+    return gmax;
+}
+
+// The pair held by lane ^ 32.
+__device__ __forceinline__ void from_other_half(float M, float s, float &M2, float &s2) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(M), __float_as_uint(M), false, false);
+    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    const bool hi = threadIdx.x & 32;  // the swap leaves (low half's, high half's) in both
+    M2 = __uint_as_float(hi ? a[0] : a[1]);
+    s2 = __uint_as_float(hi ? c[0] : c[1]);
+}
+
+// (max, sum of exp2(value - max)) of (M, s) and (M2, s2)
+__device__ __forceinline__ void merge_stats(float &M, float &s, float M2, float s2) {
+    const float mn = fmaxf(M, M2), ref = mn == -INFINITY ? 0.f : mn;
+    s = s * fast_exp2(M - ref) + s2 * fast_exp2(M2 - ref);
+    M = mn;
+}
+
+// A wave's share of merging the ranges' values of a problem's ROWS rows: parts wave + WAVES * i, lanes
+// over rows (and parts, for fewer than 64 rows), several loads in flight; its (max, sum) pairs into
+// red[wave][row] (`first`: its entry of row 0).  `ld`: floats between parts.
+template <int ROWS, int WAVES>
+__device__ __forceinline__ void merge_parts(const float *src, int ld, int nparts, float2 *first, int wave, int lane) {
+    constexpr int RW = ROWS < 64 ? ROWS : 64, SUBS = 64 / RW, RPL = (ROWS + 63) / 64;
+    constexpr int BATCH = RPL == 1 ? 8 : 4;  // loads of a row in flight
+    const int sub = lane / RW;
+    const float *p0 = src + lane % RW;
+    float M[RPL], s[RPL];
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) M[r] = -INFINITY, s[r] = 0.f;
+    for (int i0 = 0; wave + WAVES * i0 * SUBS < nparts; i0 += BATCH) {
+        float e[RPL][BATCH];
+#pragma unroll
+        for (int h = 0; h < BATCH; h += 4) {
+            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;  // uniform
+#pragma unroll
+            for (int t = h; t < h + 4; ++t)
+#pragma unroll
+                for (int r = 0; r < RPL; ++r)
+                    e[r][t] = get(p0 + (int64_t)min(wave + WAVES * ((i0 + t) * SUBS + sub), nparts - 1) * ld +
+                                  (ROWS % 64 && r ? min(64, ROWS - 1 - lane % RW) : 64 * r));
+        }
+#pragma unroll
+        for (int h = 0; h < BATCH; h += 4) {
+            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                float bm = -INFINITY, bs = 0.f;
+#pragma unroll
+                for (int t = h; t < h + 4; ++t) {
+                    if (wave + WAVES * ((i0 + t) * SUBS + sub) >= nparts) e[r][t] = -INFINITY;
+                    bm = fmaxf(bm, e[r][t]);
+                }
+                const float ref = bm == -INFINITY ? 0.f : bm;
+#pragma unroll
+                for (int t = h; t < h + 4; ++t) bs += fast_exp2(e[r][t] - ref);
+                merge_stats(M[r], s[r], bm, bs);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        if constexpr (SUBS == 2) {
+            float M2, s2;
+            from_other_half(M[r], s[r], M2, s2);
+            merge_stats(M[r], s[r], M2, s2);
+        }
+        const int row = lane % RW + 64 * r;
+        if (sub == 0 && row < ROWS) first[row] = make_float2(M[r], s[r]);
+    }
+}
+
+// STEPS: 256-key steps of a workgroup's range, all of whose logits are held: NB * STEPS <= 4.
+// NT = 2: two tiles of rows, eight waves; waves w and w + 4 take the same keys, one tile each.
+template <int D, int NB, int NT, int STEPS, bool PRIOR>
+__global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, int nparts, Exchange x, float *stats,
+                                                                  float *maxima, float *scores) {
+    using S = TileSmem<D, NB>;
+    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR>;
+    static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
+    constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int wave = uniform((int)threadIdx.x >> 6), tile = NT == 2 ? wave >> 2 : 0, kw = wave & 3;
+    __bf16 *sQ = (__bf16 *)(smem + tile * S::bytes);
+    float *sLam = (float *)(smem + tile * S::bytes + S::q_bytes);
+    int *sPos = (int *)(sLam + S::ROWS);
+    float *sL = (float *)(sPos + S::ROWS);
+    int *sBlk = (int *)(sL + S::ROWS);
+    float2 *sRed = (float2 *)(smem + H::off_red);
+    float *sCol = (float *)sRed;
+    float *sNu = (float *)(smem + H::off_nu), *sGam = (float *)(smem + H::off_gam);
+    float *sMax = (float *)(smem + H::off_misc);
+    int *sMissing = (int *)sMax + 8;
+
+    const int own = (int)blockIdx.x % nparts, z = (int)blockIdx.x / nparts;
+    const int b = z / g.Hkv, h = z % g.Hkv;
+    const RowMap rm{g.n, g.r, g.R, nullptr};
+    const __bf16 *kbase = (const __bf16 *)g.k + b * g.ks[0] + h * g.ks[1];
+    const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
+
+    Count count;
+    f32x16 acc[STEPS][NB][kMB];
+    float lam[NB];
+    int pos[NB], bmin[NB];
+    int key_begin, key_end;
+    for (int part = own;;) {
+        // (the loop nearly always runs once; through an opaque move, what depends on the thread is
+        // formed in it and not kept in registers across it)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, ht = tid & 255;
+        if (part == 0 && tid == THREADS - 1) count.look(x, z);
+        key_begin = part * STEPS * kWgKeys;
+        key_end = min(g.n, key_begin + STEPS * kWgKeys);
+        auto kb_of = [&](int st) { return key_begin + st * kWgKeys + kw * kWaveKeys; };
+        bf16x8 a[kMB][D / 16], w[kMB][D / 16];
+        auto load_values = [&](int st) {
+            load_a<D, VM>(vbase, g.vs[2], kb_of(st) + (NT == 2 ? tile * 32 : 0), key_end, lane, w);
+        };
+        PriorHalo<D> halo;
+        {
+            QTileRegs<D, NB> qt;
+            q_tile_request<D, NB>(g, b, h, tile * H::TROWS, ht, qt);
+            const float lam_req = q_tile_scale<D, NB>(g, rm, tile * H::TROWS, ht);
+            __builtin_amdgcn_sched_barrier(0);  // the keys are requested last
+            load_a<D>(kbase, g.ks[2], kb_of(0), key_end, lane, a);
+            if (PRIOR) {
+                load_values(0);
+                halo.request(g, vbase, key_begin, key_end, tid);
+            }
+            q_tile_meta<D, NB>(g, rm, tile * H::TROWS, ht, lam_req, sLam, sPos, sBlk);
+            q_tile_commit<D, NB>(qt, ht, sQ);
+        }
+        __syncthreads();
+        float m[NB], s[NB], u = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            lam[nb] = sLam[nb * 32 + (lane & 31)];
+            pos[nb] = sPos[nb * 32 + (lane & 31)];
+            bmin[nb] = uniform(sBlk[NB + nb]);
+            m[nb] = -INFINITY;
+            s[nb] = 0.f;
+        }
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int kb = kb_of(st);
+            if constexpr (PRIOR) {  // (first: the value rows' registers are then free for the logits)
+                float nu[kMB];
+                fragment_row_norms<D, VM>(w, nu);
+#pragma unroll
+                for (int mb = 0; mb < VM; ++mb) {
+                    const int row = kb + mb * 32 + lane + (NT == 2 ? tile * 32 : 0);
+                    if (lane < 32 && row < key_end) sNu[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (st + 1 < STEPS) load_values(st + 1);
+            }
+            // (keys at or past n, in the last range, lie behind every row's position)
+            bf16x8 qf = query_fragment<D, NB>(sQ, 0, 0, lane);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                mma_block_stream<D, NB>(a, sQ, nb, nb + 1 < NB ? nb + 1 : 0, lane, qf, acc[st][nb]);
+                if (nb == NB - 1 && st + 1 < STEPS) load_a<D>(kbase, g.ks[2], kb_of(st + 1), key_end, lane, a);
+                if (kb + kWaveKeys - 1 > bmin[nb])
+                    stats_update<true, false>(acc[st][nb], lam[nb], pos[nb], kb, lane, m[nb], s[nb], u);
+                else
+                    stats_update<false, false>(acc[st][nb], lam[nb], 0, kb, lane, m[nb], s[nb], u);
+            }
+        }
+        if (part == 0 && tid == THREADS - 1) count.start(x, z);
+        // fold the half-waves (same query row, other keys), then the waves
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float m2, s2;
+            from_other_half(m[nb], s[nb], m2, s2);
+            merge_stats(m[nb], s[nb], m2, s2);
+            if (lane < 32) sRed[wave * H::TROWS + nb * 32 + lane] = make_float2(m[nb], s[nb]);
+        }
+        if (PRIOR) {
+            const float hn = halo.norm();
+            if (halo.valid && tid % PriorHalo<D>::CPR == 0)
+                sNu[halo.pos - max(0, key_begin - (g.pool - 1) / 2)] = hn;
+        }
+        __syncthreads();
+        if (tid < H::ROWS) {
+            float M = -INFINITY, sum = 0.f;
+            const float2 *src = sRed + (NT == 2 ? tid / H::TROWS * 4 * H::TROWS : 0) + tid % H::TROWS;
+#pragma unroll
+            for (int wv = 0; wv < 4; ++wv) merge_stats(M, sum, src[wv * H::TROWS].x, src[wv * H::TROWS].y);
+            put(stats + ((int64_t)z * nparts + part) * H::ROWS + tid, M + log2f(sum));
+        }
+        if (PRIOR) {
+            const float gm = wave_max(pool_norms(g, key_begin, key_end, sNu, sGam, tid, THREADS));
+            if (lane == 0) put(maxima + ((int64_t)z * nparts + part) * WAVES + wave, gm);
+        }
+        announce(x, z, nparts, part, tid);
+        if (wave == 0) {
+            const int missing = first_missing(x, z, nparts, lane);
+            if (lane == 0) *sMissing = missing;
+        }
+        __syncthreads();
+        const int missing = *sMissing;
+        if (missing == nparts && part == own) break;
+        // somebody is not there: done here (and no more waiting); in the end the own part again, whose
+        // logits the accumulators have to hold
+        part = missing < nparts ? missing : own;
+        x.looks = 0;
+        __syncthreads();
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == THREADS - 1) count.arrive(x, z);
+    merge_parts<H::TROWS, 4>(stats + (int64_t)z * nparts * H::ROWS + tile * H::TROWS, H::ROWS, nparts,
+                             sRed + wave * H::TROWS, kw, lane);
+    if (PRIOR) {
+        float gm = 0.f;
+        for (int p = tid; p < WAVES * nparts; p += THREADS) gm = fmaxf(gm, get(maxima + (int64_t)z * nparts * WAVES + p));
+        gm = wave_max(gm);
+        if (lane == 0) sMax[wave] = gm;
+    }
+    __syncthreads();
+    if (tid < H::ROWS) {
+        float M = -INFINITY, sum = 0.f;
+        const int t = tid / H::TROWS, row = tid % H::TROWS;
+        const float2 *src = sRed + t * 4 * H::TROWS + row;
+#pragma unroll
+        for (int wv = 0; wv < 4; ++wv) merge_stats(M, sum, src[wv * H::TROWS].x, src[wv * H::TROWS].y);
+        // (rows past the last one add nothing)
+        ((float *)(smem + t * S::bytes + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
+    }
+    __syncthreads();
+    float ginv = 1.f, L[NB];
+    if (PRIOR) {
+        float gm = sMax[0];
+#pragma unroll
+        for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
+        ginv = prior_inverse(gm);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) L[nb] = sL[nb * 32 + (lane & 31)];
+    const int my_v = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 +
+                     ((lane >> 1) & 1);
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int kb = key_begin + st * kWgKeys + kw * kWaveKeys;
+        f32x16 col[kMB];
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) col[mb][v] = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            if (kb + kWaveKeys - 1 > bmin[nb])
+                colsum_update<true>(acc[st][nb], lam[nb], L[nb], pos[nb], kb, lane, col);
+            else
+                colsum_update<false>(acc[st][nb], lam[nb], L[nb], 0, kb, lane, col);
+        }
+        float tot[kMB];
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb) tot[mb] = fold16_over32(col[mb], lane);
+        if constexpr (NT == 2) {  // the second tile's sums meet the first's (sRed has been read)
+            if (tile == 1 && (lane & 1) == 0) {
+#pragma unroll
+                for (int mb = 0; mb < kMB; ++mb) sCol[acc_key(kb, mb, my_v, lane) - key_begin] = tot[mb];
+            }
+            __syncthreads();
+            if (tile == 1) break;
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb) tot[mb] += sCol[acc_key(kb, mb, my_v, lane) - key_begin];
+        }
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb) {
+            const int j = acc_key(kb, mb, my_v, lane);
+            if ((lane & 1) == 0 && j < key_end)
+                scores[(int64_t)z * g.n + j] = PRIOR ? tot[mb] * prior_factor(sGam[j - key_begin], ginv) : tot[mb];
+        }
+    }
+    if (wave == WAVES - 1) leave(x, z, nparts, count, lane);
+}
+
+// ---- the logits formed twice --------------------------------------------------------------------
+// window_stream_kernel: more rows than whose logits a wave can hold, or longer ranges.  A workgroup of
+// eight waves owns a CU and a range of keys; the first sweep over the range leaves the rows' statistics, the
+// second, from the last step to the first, starts on keys that are in the caches still and sums columns.
+// NT = 1: one tile of up to 256 rows, the waves take 64 keys each.  NT = 2: two tiles, of up to 512 rows;
+// waves w and w + 4 take the same 64 keys, one tile each, and add their column sums in LDS.
+template <int D, int NB, int NT>
+struct StreamSmem {
+    static constexpr int TROWS = NB * 32, ROWS = NT * TROWS, KW = 8 / NT, STEP = KW * kWaveKeys;
+    static constexpr size_t off_red = NT * TileSmem<D, NB>::bytes;  // float2 [8][TROWS], then norms, then column sums
+    static constexpr size_t red_bytes = 8 * TROWS * sizeof(float2) > (kPriorPiece + kPriorMaxHalo) * sizeof(float)
+                                            ? 8 * TROWS * sizeof(float2)
+                                            : (kPriorPiece + kPriorMaxHalo) * sizeof(float);
+    static constexpr size_t off_misc = (off_red + red_bytes + 15) / 16 * 16;
+    static constexpr size_t off_nu = off_misc + 16 * sizeof(float);
+    // ranges of up to KEYS keys keep their norms and prior in LDS, longer ones go through the workspace
+    static constexpr size_t room = 160 * 1024 - off_nu - kPriorMaxHalo * sizeof(float);
+    static constexpr int KEYS = room >= 2048 * 8 ? 2048 : (int)(room / 8) / 256 * 256;
+    static constexpr size_t off_gam = off_nu + (KEYS ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
+    static constexpr size_t bytes = off_gam + KEYS * sizeof(float);
+    static_assert(2 * 4 * kWaveKeys * sizeof(float) <= red_bytes, "column sums of two steps");
+    static_assert(bytes <= 160 * 1024, "LDS of a CU");
+};
+
+// gamma of the keys [kbeg, kend) from the norms the workgroup's waves left in nu_g, in pieces staged in
+// s_nu, to `gamma`; returns this thread's largest.  The caller has passed a barrier since the last norm
+// was written, and nobody uses s_nu any more.
+template <int D, int THREADS>
+__device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg, int kend,
+                                                     const float *nu_g, const PriorHalo<D> &halo,
+                                                     float *s_nu, float *gamma, int tid) {
+    const int half = (g.pool - 1) / 2;
+    const float hn = halo.norm();
+    float gmax = 0.f;
+    for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
+        const int t1 = min(kend, t0 + kPriorPiece);
+        const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
+        for (int t = max(lo, kbeg) + tid; t < min(hi, kend); t += THREADS) s_nu[t - lo] = nu_g[(int64_t)z * g.n + t];
+        // the halo rows that touch this piece (the first piece below, the last one above)
+        if (halo.valid && tid % PriorHalo<D>::CPR == 0 && (halo.below ? t0 == kbeg : t1 == kend))
+            s_nu[halo.pos - lo] = hn;
+        __syncthreads();
+        for (int j = t0 + tid; j < t1; j += THREADS) {
+            const int a = max(0, j - half), e = min(g.n - 1, j + half);
+            float s = 0.f;
+            for (int t = a; t <= e; ++t) s += s_nu[t - lo];
+            const float gam = s / (float)(e - a + 1);
+            gamma[(int64_t)z * g.n + j] = gam;
+            gmax = fmaxf(gmax, gam);
+        }
+        __syncthreads();
+    }
+    return gmax;
+}
+
+template <int D, int NB, int NT, bool PRIOR>
+__global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
+                                                               float *stats, float *maxima, float *nu_g,
+                                                               float *gamma, float *scores) {
+    using S = TileSmem<D, NB>;
+    using W = StreamSmem<D, NB, NT>;
+    // with two tiles a wave takes 32 of the 64 value rows it shares
+    constexpr int VM = NT == 2 ? 1 : kMB;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int wave = uniform((int)threadIdx.x >> 6), half = wave >> 2;
+    const int tile = NT == 2 ? half : 0, kw = NT == 2 ? wave & 3 : wave;
+    __bf16 *sQ = (__bf16 *)(smem + tile * S::bytes);
+    float *sLam = (float *)(smem + tile * S::bytes + S::q_bytes);
+    int *sPos = (int *)(sLam + S::ROWS);
+    float *sL = (float *)(sPos + S::ROWS);
+    int *sBlk = (int *)(sL + S::ROWS);
+    float2 *sRed = (float2 *)(smem + W::off_red);
+    float *sCol = (float *)sRed, *sNu = (float *)sRed;
+    float *sMax = (float *)(smem + W::off_misc);
+    int *sMissing = (int *)sMax + 8;
+    float *sN = (float *)(smem + W::off_nu), *sGam = (float *)(smem + W::off_gam);
+    const bool in_lds = W::KEYS && part_keys <= W::KEYS;
+
+    const int own = (int)blockIdx.x % nparts, z = (int)blockIdx.x / nparts;
+    const int b = z / g.Hkv, h = z % g.Hkv;
+    const RowMap rm{g.n, g.r, g.R, nullptr};
+    const __bf16 *kbase = (const __bf16 *)g.k + b * g.ks[0] + h * g.ks[1];
+    const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
+    const int tile_min = rm.min_pos(tile * W::TROWS, (tile + 1) * W::TROWS);
+
+    Count count;
+    bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block loads while one multiplies
+    int key_begin, key_end, nsteps;
+    auto kb_of = [&](int i) { return i >= 0 && i < nsteps ? key_begin + i * W::STEP + kw * kWaveKeys : key_end; };
+    auto set_range = [&](int part) {
+        key_begin = part * part_keys;
+        key_end = min(g.n, key_begin + part_keys);
+        nsteps = (key_end - key_begin + W::STEP - 1) / W::STEP;
+    };
+    auto load_values = [&](int kb, int lane, bf16x8 (&w)[kMB][D / 16]) {
+        load_a<D, VM>(vbase, g.vs[2], kb + (NT == 2 ? tile * 32 : 0), key_end, lane, w);
+        if (VM == 1) {  // (never read; an array that is only half written stays in memory)
+#pragma unroll
+            for (int ks = 0; ks < D / 16; ++ks) w[1][ks] = bf16x8{};
+        }
+    };
+    // the query rows and their scales to LDS, the keys of step `first` into a0 (and its value rows into a1)
+    auto set_up = [&](int tid, int first) {
+        constexpr int NBL = NB * NT / 2;  // row blocks that 256 threads load
+        const int ht = tid & 255;
+        QTileRegs<D, NBL> qt;
+        q_tile_request<D, NBL>(g, b, h, half * NBL * 32, ht, qt);
+        const int mt = NT == 2 ? ht : tid;
+        const float lam_req = q_tile_scale<D, NB>(g, rm, tile * W::TROWS, mt);
+        __builtin_amdgcn_sched_barrier(0);  // the keys are requested last
+        load_a<D>(kbase, g.ks[2], kb_of(first), key_end, tid & 63, a0);
+        if (PRIOR) load_values(kb_of(first), tid & 63, a1);
+        q_tile_meta<D, NB>(g, rm, tile * W::TROWS, mt, lam_req, sLam, sPos, sBlk);
+        q_tile_commit<D, NBL>(qt, ht, NT == 2 ? sQ : sQ + half * NBL * 32 * S::LD);
+    };
+    // norms of the wave's value rows of the step at kb, and where they go
+    auto store_norms = [&](const bf16x8 (&w)[kMB][D / 16], int kb, int lane) {
+        float nu[kMB];
+        fragment_row_norms<D, VM>(w, nu);
+#pragma unroll
+        for (int mb = 0; mb < VM; ++mb) {
+            const int row = kb + mb * 32 + lane + (NT == 2 ? tile * 32 : 0);
+            if (lane >= 32 || row >= key_end) continue;
+            if (in_lds) sN[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
+            else nu_g[(int64_t)z * g.n + row] = nu[mb];
+        }
+    };
+    // One step of a sweep: blocks(a, kb, from, to) on the keys in `a` while `nx` receives those of kb_next
+    // (unconditionally: past the range, clamped rows that are never used).  With VALUES the step's
+    // value rows pass through `nx` as well: those of the first step came with its keys, so the next
+    // keys have the whole step to travel; the last step has no next keys, and its value rows the whole
+    // step; in between, value rows travel under the first half and keys under the second.
+    auto sweep_step = [&](auto values, auto &&blocks, const bf16x8 (&a)[kMB][D / 16], bf16x8 (&nx)[kMB][D / 16], int kb,
+                          int kb_next, bool first, bool last) {
+        // (through an opaque move: addresses are formed in each step, not kept and spilled)
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        if constexpr (!decltype(values)::value) {
+            load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
+            blocks(a, kb, 0, NB);
+        } else {
+            constexpr int NB1 = NB / 4;  // (the first keys are there before the first value rows)
+            if (!first) load_values(kb, lane, nx);
+            __builtin_amdgcn_sched_barrier(0);
+            blocks(a, kb, 0, NB1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (first) {
+                store_norms(nx, kb, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            blocks(a, kb, NB1, NB / 2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!first && !last) {
+                store_norms(nx, kb, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            blocks(a, kb, NB / 2, NB);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!first && last) store_norms(nx, kb, lane);
+        }
+    };
+    // the column sums of the range, the last step first, its keys in a0 already
+    auto second_sweep = [&](float ginv) {
+        const int lane = threadIdx.x & 63;
+        // (one base for what a lane reads per block: scale, position, normaliser)
+        int at = lane & 31;
+        asm volatile("" : "+v"(at));
+        const float *meta = sLam + at;
+        auto step = [&](const bf16x8 (&a)[kMB][D / 16], bf16x8 (&nx)[kMB][D / 16], int i) {
+            const int kb = kb_of(i);
+            int ln = threadIdx.x & 63;
+            asm volatile("" : "+v"(ln));
+            const int my_v = ((ln >> 4) & 1) * 8 + ((ln >> 3) & 1) * 4 + ((ln >> 2) & 1) * 2 + ((ln >> 1) & 1);
+            float gam[kMB];
+            if (PRIOR && !in_lds) {
+#pragma unroll
+                for (int mb = 0; mb < kMB; ++mb)
+                    gam[mb] = gamma[(int64_t)z * g.n + min(acc_key(kb, mb, my_v, ln), key_end - 1)];
+            }
+            f32x16 col[kMB];
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) col[mb][v] = 0.f;
+            auto blocks = [&](const bf16x8 (&ak)[kMB][D / 16], int kbb, int nb0, int nb1) {
+                if (kbb >= key_end) return;  // (a wave past the range's ragged end)
+                if (kbb + kWaveKeys - 1 <= tile_min) {
+                    // all rows of the tile see all 64 keys: no masks, no skipped blocks
+                    bf16x8 qf = query_fragment<D, NB>(sQ, nb0, 0, lane);
+#pragma unroll
+                    for (int nb = nb0; nb < nb1; ++nb) {
+                        f32x16 acc[kMB];
+                        // (scale and normaliser of the lane's row from LDS in each block: the registers are needed)
+                        const float lam = meta[nb * 32], L = meta[2 * S::ROWS + nb * 32];
+                        mma_block_stream<D, NB>(ak, sQ, nb, nb + 1 < nb1 ? nb + 1 : nb0, lane, qf, acc);
+                        colsum_update<false>(acc, lam, L, 0, kbb, lane, col);
+                    }
+                    return;
+                }
+#pragma unroll
+                for (int nb = nb0; nb < nb1; ++nb) {
+                    if (uniform(sBlk[nb]) < kbb) continue;
+                    f32x16 acc[kMB];
+                    mma_block<D, NB>(ak, sQ, nb, lane, acc);
+                    const float lam = meta[nb * 32], L = meta[2 * S::ROWS + nb * 32];
+                    if (kbb + kWaveKeys - 1 > uniform(sBlk[NB + nb]))
+                        colsum_update<true>(acc, lam, L, ((const int *)meta)[S::ROWS + nb * 32], kbb, lane, col);
+                    else
+                        colsum_update<false>(acc, lam, L, 0, kbb, lane, col);
+                }
+            };
+            sweep_step(std::false_type{}, blocks, a, nx, kb, kb_of(i - 1), i == nsteps - 1, i == 0);
+            float tot[kMB];
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb) tot[mb] = fold16_over32(col[mb], ln);
+            if constexpr (NT == 2) {
+                // the second tile's sums meet the first's (two steps' places: one barrier a step)
+                float *sc = sCol + (i & 1) * 4 * kWaveKeys + kw * kWaveKeys;
+                if (tile == 1 && (ln & 1) == 0) {
+#pragma unroll
+                    for (int mb = 0; mb < kMB; ++mb) sc[acc_key(0, mb, my_v, ln)] = tot[mb];
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (tile == 0) {
+#pragma unroll
+                    for (int mb = 0; mb < kMB; ++mb) tot[mb] += sc[acc_key(0, mb, my_v, ln)];
+                }
+            }
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb) {
+                const int j = acc_key(kb, mb, my_v, ln);
+                if ((ln & 1) || tile || j >= key_end) continue;
+                const float gm = PRIOR ? (in_lds ? sGam[j - key_begin] : gam[mb]) : 1.f;
+                scores[(int64_t)z * g.n + j] = PRIOR ? tot[mb] * prior_factor(gm, ginv) : tot[mb];
+            }
+        };
+        for (int i = nsteps - 1; i >= 0; i -= 2) {
+            step(a0, a1, i);
+            if (i == 0) break;
+            step(a1, a0, i - 1);
+        }
+    };
+    // the prior of the range from its norms; leaves the part's largest gamma
+    auto pool_range = [&](int part, const PriorHalo<D> &halo, int tid) {
+        float gm;
+        if (in_lds) {
+            const float hn = halo.norm();
+            if (halo.valid && tid % PriorHalo<D>::CPR == 0) sN[halo.pos - max(0, key_begin - (g.pool - 1) / 2)] = hn;
+            __syncthreads();
+            gm = pool_norms(g, key_begin, key_end, sN, sGam, tid, 512);
+        } else {
+            __syncthreads();  // (the statistics' LDS becomes the norms')
+            gm = pool_norms_of_range<D, 512>(g, z, key_begin, key_end, nu_g, halo, sNu, gamma, tid);
+        }
+        gm = wave_max(gm);
+        if ((tid & 63) == 0) put(maxima + ((int64_t)z * nparts + part) * 8 + wave, gm);
+    };
+    // the largest gamma of all parts, to sMax (before a barrier); its first values are requested earlier
+    auto request_maxima = [&](int tid) { return get(maxima + (int64_t)z * nparts * 8 + min(tid, 8 * nparts - 1)); };
+    auto fetch_maxima = [&](int tid, float gm) {
+        for (int p = tid + 512; p < 8 * nparts; p += 512) gm = fmaxf(gm, get(maxima + (int64_t)z * nparts * 8 + p));
+        gm = wave_max(gm);
+        if ((tid & 63) == 0) sMax[wave] = gm;
+    };
+    auto largest = [&]() {
+        return fmaxf(fmaxf(fmaxf(sMax[0], sMax[1]), fmaxf(sMax[2], sMax[3])),
+                     fmaxf(fmaxf(sMax[4], sMax[5]), fmaxf(sMax[6], sMax[7])));
+    };
+    for (int part = own;;) {
+        // (through an opaque move, what depends on the thread is formed in the loop and not kept in
+        // registers across it; it nearly always runs once)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
+        if (part == 0 && tid == 511) count.look(x, z);
+        set_range(part);
+        set_up(tid, 0);
+        __syncthreads();
+        int at = lane & 31;
+        asm volatile("" : "+v"(at));
+        const float *meta = sLam + at;
+        float m[NB], s[NB], u = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            m[nb] = -INFINITY;
+            s[nb] = 0.f;
+        }
+        auto blocks = [&](const bf16x8 (&a)[kMB][D / 16], int kb, int nb0, int nb1) {
+            if (kb >= key_end) return;  // (a wave past the range's ragged end)
+            if (kb + kWaveKeys - 1 <= tile_min) {
+                bf16x8 qf = query_fragment<D, NB>(sQ, nb0, 0, lane);
+#pragma unroll
+                for (int nb = nb0; nb < nb1; ++nb) {
+                    f32x16 acc[kMB];
+                    const float lam = meta[nb * 32];
+                    mma_block_stream<D, NB>(a, sQ, nb, nb + 1 < nb1 ? nb + 1 : nb0, lane, qf, acc);
+                    stats_update<false, false>(acc, lam, 0, kb, lane, m[nb], s[nb], u);
+                }
+                return;
+            }
+#pragma unroll
+            for (int nb = nb0; nb < nb1; ++nb) {
+                if (uniform(sBlk[nb]) < kb) continue;  // nothing of this block sees these keys
+                f32x16 acc[kMB];
+                mma_block<D, NB>(a, sQ, nb, lane, acc);
+                const float lam = meta[nb * 32];
+                if (kb + kWaveKeys - 1 > uniform(sBlk[NB + nb]))
+                    stats_update<true, false>(acc, lam, ((const int *)meta)[S::ROWS + nb * 32], kb, lane, m[nb], s[nb], u);
+                else
+                    stats_update<false, false>(acc, lam, 0, kb, lane, m[nb], s[nb], u);
+            }
+        };
+        for (int i = 0; i < nsteps; i += 2) {
+            sweep_step(std::bool_constant<PRIOR>{}, blocks, a0, a1, kb_of(i), kb_of(i + 1), i == 0, i + 1 == nsteps);
+            if (i + 1 >= nsteps) break;
+            sweep_step(std::bool_constant<PRIOR>{}, blocks, a1, a0, kb_of(i + 1), kb_of(i + 2), false, i + 2 == nsteps);
+        }
+        if (part == 0 && tid == 511) count.start(x, z);
+        PriorHalo<D> halo;
+        if (PRIOR) halo.request(g, vbase, key_begin, key_end, tid);  // travels while the statistics are reduced
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float m2, s2;
+            from_other_half(m[nb], s[nb], m2, s2);
+            merge_stats(m[nb], s[nb], m2, s2);
+            if (lane < 32) sRed[wave * W::TROWS + nb * 32 + lane] = make_float2(m[nb], s[nb]);
+        }
+        __syncthreads();
+        if (tid < W::ROWS) {
+            float M = -INFINITY, sum = 0.f;
+            const float2 *src = sRed + (NT == 2 ? tid / W::TROWS * 4 * W::TROWS : 0) + tid % W::TROWS;
+#pragma unroll
+            for (int wv = 0; wv < W::KW; ++wv) merge_stats(M, sum, src[wv * W::TROWS].x, src[wv * W::TROWS].y);
+            put(stats + ((int64_t)z * nparts + part) * W::ROWS + tid, M + log2f(sum));
+        }
+        if (PRIOR) pool_range(part, halo, tid);
+        announce(x, z, nparts, part, tid);
+        if (wave == 0) {
+            const int missing = first_missing(x, z, nparts, lane);
+            if (lane == 0) *sMissing = missing;
+        }
+        __syncthreads();
+        const int missing = *sMissing;
+        if (missing == nparts && part == own) break;
+        // somebody is not there: done here (and no more waiting); in the end the own part again, whose
+        // prior the LDS has to hold
+        part = missing < nparts ? missing : own;
+        x.looks = 0;
+        __syncthreads();
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 511) count.arrive(x, z);
+    const float my_max = PRIOR ? request_maxima(tid) : 0.f;
+    merge_parts<W::TROWS, W::KW>(stats + (int64_t)z * nparts * W::ROWS + tile * W::TROWS, W::ROWS, nparts,
+                                 sRed + wave * W::TROWS, kw, lane);
+    if (PRIOR) fetch_maxima(tid, my_max);
+    load_a<D>(kbase, g.ks[2], kb_of(nsteps - 1), key_end, lane, a0);
+    __syncthreads();
+    if (tid < W::ROWS) {
+        float M = -INFINITY, sum = 0.f;
+        const int t = tid / W::TROWS, row = tid % W::TROWS;
+        const float2 *src = sRed + (NT == 2 ? t * 4 * W::TROWS : 0) + row;
+#pragma unroll
+        for (int wv = 0; wv < W::KW; ++wv) merge_stats(M, sum, src[wv * W::TROWS].x, src[wv * W::TROWS].y);
+        // (rows past the last one add nothing)
+        ((float *)(smem + t * S::bytes + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
+    }
+    __syncthreads();
+    second_sweep(PRIOR ? prior_inverse(largest()) : 1.f);
+    if (wave == 7) leave(x, z, nparts, count, tid & 63);
+}
+
+// ---------------------------------------------------------------- launch --
+template <int D, int NB, int NT, int STEPS, bool PRIOR>
+static hipError_t launch_hold(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
+                              hipStream_t st) {
+    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR>;
+    const auto kernel = window_hold_kernel<D, NB, NT, STEPS, PRIOR>;
+    if (H::bytes > 64 * 1024) {
+        static DeviceOnce once;
+        const hipError_t e = device_once(once, [kernel] {
+            return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)H::bytes);
+        });
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(256 * NT), H::bytes, st, g, pl.win_parts, x,
+                       (float *)(w + pl.off_wstats), (float *)(w + pl.off_wmax), scores);
+    return hipGetLastError();
+}
+
+template <int D, int NB, int NT, bool PRIOR>
+static hipError_t launch_stream(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
+                                hipStream_t st) {
+    using W = StreamSmem<D, NB, NT>;
+    const auto kernel = window_stream_kernel<D, NB, NT, PRIOR>;
+    static DeviceOnce once;
+    const hipError_t e = device_once(once, [kernel] {
+        return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)W::bytes);
+    });
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(512), W::bytes, st, g, pl.win_parts,
+                       pl.win_keys, x, (float *)(w + pl.off_wstats), (float *)(w + pl.off_wmax),
+                       (float *)(w + pl.off_wnu), (float *)(w + pl.off_wgamma), scores);
+    return hipGetLastError();
+}
+
+template <int D, bool PRIOR>
+static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
+                           hipStream_t st) {
+    const int steps = pl.win_keys / kWgKeys;
+#define AHA_HOLD(NB, NT, STEPS)                                                                 \
+    if (pl.win_hold && pl.win_nb == NB && pl.win_tiles == NT && steps == STEPS) \
+        return launch_hold<D, NB, NT, STEPS, PRIOR>(g, pl, x, w, scores, st);
+#define AHA_STREAM(NB, NT)                                            \
+    if (!pl.win_hold && pl.win_nb == NB && pl.win_tiles == NT) \
+        return launch_stream<D, NB, NT, PRIOR>(g, pl, x, w, scores, st);
+    AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(1, 1, 4) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
+    AHA_HOLD(4, 1, 1) AHA_HOLD(3, 2, 1) AHA_HOLD(4, 2, 1)
+    AHA_STREAM(4, 1) AHA_STREAM(6, 1) AHA_STREAM(8, 1) AHA_STREAM(6, 2) AHA_STREAM(8, 2)
+#undef AHA_HOLD
+#undef AHA_STREAM
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+                               float *scores, hipStream_t st) {
+    char *w = (char *)ws;
+    const Exchange x{(uint64_t *)(w + pl.off_wtags), (uint64_t *)(w + pl.off_wcounts), tag, looks};
+    if (g.d == 64)
+        return g.value_prior ? launch_d<64, true>(g, pl, x, w, scores, st) : launch_d<64, false>(g, pl, x, w, scores, st);
+    return g.value_prior ? launch_d<128, true>(g, pl, x, w, scores, st) : launch_d<128, false>(g, pl, x, w, scores, st);
+}
+
+}  // namespace aha
