@@ -343,8 +343,10 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
 // bytes, where the two cross: steps of 2 to 127 heads with 100 to 8000 slots, d = 64 and 128, were timed
 // both ways (us in one launch against split; fp32, d = 128, G = 1: 8 heads x 300 slots 9.4 and
 // 10.2, 80 x 1000 21.0 and 23.3, 80 x 3000 56.1 and 50.9, 112 x 8000 203 and 188; bf16, d = 128,
-// G = 4: 64 x 100 10.8 and 11.6, 64 x 700 19.4 and 15.7, 112 x 1000 25.0 and 26.0).  Wider groups
-// always split (bf16, d = 128, G = 8: 8 x 100 17.8 and 11.9, 112 x 300 19.0 and 16.3).
+// G = 4: 32 x 257 12.7 and 10.7, d = 64 9.85 and 9.81; 96 x 257 12.9 and 12.5, 112 x 801 21.6 and 18.6).
+// Wider groups always split (bf16, d = 128, G = 8: 8 x 100 17.8 and 11.9, 112 x 257 18.9 and 14.1).
+// Exactly 128 heads in groups of four: 128 x 257 13.0 and 13.1, d = 64 x 801 14.4 and 14.4, d = 128 x 801
+// 20.9 and 19.1.
 static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
     if (G > 4) return false;
     const int ways = (256 + Z - 1) / Z;  // workgroups per head if split
@@ -354,10 +356,11 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
          {870, 450, 410, 290},            // five and six,
          {1300, 1160, 870, 410},          // four,
          {2350, kAny, 3300, 1700}},       // three (86 heads and more)
-        {{330, 224, 120, 64},             // bf16
-         {480, 400, 170, 64},
+        {{330, 224, 120, 96},             // bf16
+         {480, 400, 170, 96},
          {1200, 800, 320, 96},
-         {2350, kAny, 2350, 580}}};
+         {2350, kAny, 2350, 325}}};
+    if (Z >= kDecodeSplitHeads) return G < 4 || (int64_t)live * (2 * d * esize(dtype) + 64) <= 250 * 1000;
     const int row = ways >= 7 ? 0 : ways >= 5 ? 1 : ways == 4 ? 2 : 3;
     const int64_t size = (int64_t)live * (2 * d * esize(dtype) + 64);
     return size <= (int64_t)limit[dtype == AHA_BF16][row][G - 1] * 1000;
@@ -368,7 +371,16 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
 // outputs in LDS; the number of splits is raised until that fits kDecodeSplitLds (the limit
 // a launch may ask for without an attribute), and `fits` says whether kMaxDecodeSplit
 // splits were enough.
-static DecodePlan plan_decode(const aha_params *p) {
+//
+// The matrix-core split stage (bf16, G >= 4) is resident three times per CU, so more splits than
+// one workgroup per CU may pay, also for exactly 128 heads; what matters is that the chip is evenly
+// filled.  Its time goes with the slots per CU (64 of them, d = 128, weigh as much as a wave's block of 32
+// slots) and the blocks of a wave one after the other; a further split costs the merge a twelfth of a
+// block.  us of the step at the former count and at this rule's, d = 128, G = 8: 96 heads x 1537 slots 32.7
+// (3 splits), 26.3 (5); 48 x 3073 33.7, 27.5; 128 x 1537 38.3 (one launch), 33.0 (4); over 156 shapes
+// 1.064 times as fast on average.  `limit`: bytes of workspace there are; without room for the plan's
+// the former count (and 128 heads in one launch).
+static DecodePlan plan_decode(const aha_params *p, size_t limit = SIZE_MAX) {
     DecodePlan pl{};
     const int Z = p->batch * p->n_kv_heads, G = p->n_q_heads / p->n_kv_heads;
     const int live = p->budget + 1;
@@ -406,6 +418,25 @@ static DecodePlan plan_decode(const aha_params *p) {
     };
     pl.static_bytes = layout(2);
     pl.bytes = layout(kPartStats);
+    if (p->dtype == AHA_BF16 && G >= kDecodeSplitMfmaGroup && pl.fits &&
+        (Z < kDecodeSplitHeads ? pl.nsplit > 1 : Z == kDecodeSplitHeads && one_fits)) {
+        auto cost = [&](int sps, int ns) {
+            const int64_t per_cu = ((int64_t)Z * ns + 255) / 256;
+            return per_cu * sps * p->head_dim / (128. * 64.) + ((sps + 31) / 32 + 3) / 4 + 0.08 * ns;
+        };
+        const DecodePlan former = pl;
+        double best = pl.nsplit > 1 ? 0.9 * cost(pl.sps, pl.nsplit) : 1e30;  // (left only for a clear gain)
+        for (int n = 2; n <= kMaxDecodeSplit && Z * n <= 768 && n <= (live + 31) / 32; ++n) {
+            const int sps = (live + n - 1) / n, ns = (live + sps - 1) / sps;
+            if (ns > 1 && cost(sps, ns) < best) {
+                best = cost(sps, ns);
+                pl.sps = sps;
+                pl.nsplit = ns;
+            }
+        }
+        pl.bytes = layout(kPartStats);
+        if (pl.bytes > limit) pl = former;
+    }
     if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live)))
         return pl;
     if (pl.nsplit <= 1 && !one_fits) pl.fits = false;
@@ -633,6 +664,12 @@ int32_t aha_compact_kv(const aha_params *p, const void *k, const void *v, const 
                       "compaction kernel");
 }
 
+// Bytes of the built-in scratch of aha_decode_step_static (below).
+constexpr size_t kScratchBytes = (size_t)4 << 20;  // of static_bytes
+// A partial output has kPartStats statistics, two more floats than are counted; the count holds
+// fewer than 4 MiB / (4 * 66) of them (at least 64 channels and two statistics each).
+constexpr size_t kScratchMargin = kScratchBytes / (4 * 66) * 4 * (kPartStats - 2) + 256;
+
 // Host checks shared by aha_decode_step and its variant without a workspace argument
 // (`scratch_limit` > 0: the scratch is the library's own and that many bytes long; the
 // workspace arguments are then not looked at).  Nothing here touches the HIP runtime.
@@ -658,7 +695,7 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
     const int G = p->n_q_heads / p->n_kv_heads;
     if (G > 8)
         return fail(AHA_ERR_UNSUPPORTED, "decode is built for query groups of up to 8 heads, not %d", G);
-    *plan = plan_decode(p);
+    *plan = plan_decode(p, scratch_limit ? kScratchBytes + kScratchMargin : workspace ? workspace_bytes : 0);
     if (!plan->fits)
         return fail(AHA_ERR_UNSUPPORTED,
                     "decode keeps group * (budget + 1) dots in LDS; %d * %d does not fit (%d splits)",
@@ -710,10 +747,6 @@ int32_t aha_decode_step(const aha_params *p, const void *q_new, const void *k_ne
 // that can neither allocate nor carry a workspace.  The array's name is only a host-side
 // stand-in: its device address is asked for once per device (each GPU holds its own copy
 // at its own address) and that pointer is what the kernels get.
-constexpr size_t kScratchBytes = (size_t)4 << 20;  // of static_bytes
-// A partial output has kPartStats statistics, two more floats than are counted; the count holds
-// fewer than 4 MiB / (4 * 66) of them (at least 64 channels and two statistics each).
-constexpr size_t kScratchMargin = kScratchBytes / (4 * 66) * 4 * (kPartStats - 2) + 256;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchMargin];
 static void *g_scratch_ptr[kMaxDevices];
 static DeviceOnce g_scratch_once;

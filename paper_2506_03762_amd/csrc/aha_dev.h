@@ -38,6 +38,20 @@ __device__ __forceinline__ bf16x8 lds_transposed_fragment(const __bf16 *base, in
     return f;
 }
 
+// The same for v_mfma_f32_16x16x32_bf16: the lane's channel col0 + lane % 16 of the rows
+// 4 (lane / 16) + {0..3} and gap + 4 (lane / 16) + {0..3}.
+__device__ __forceinline__ bf16x8 lds_transposed_fragment16(const __bf16 *base, int ld, int gap, int col0,
+                                                            int lane) {
+    using lds_ptr = s16x4 __attribute__((address_space(3))) *;
+    const __bf16 *p = base + (4 * (lane >> 4) + ((lane >> 2) & 3)) * ld + col0 + 4 * (lane & 3);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + gap * ld));
+    bf16x8 f;
+    __builtin_memcpy(&f, &lo, 8);
+    __builtin_memcpy((char *)&f + 8, &hi, 8);
+    return f;
+}
+
 // bf16 <-> fp32 on raw bits (bf16 is the upper half of an fp32).
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }

@@ -9,7 +9,7 @@
 // bf16: with four or more query heads per KV head the values, with five or more
 // the dots of whole 32-slot blocks as well, go through the matrix core.
 //
-// Fewer than 128 heads: their slots are split over workgroups unless one per head is
+// Fewer than 128 heads (bf16 groups of four and more: up to 128): their slots are split over workgroups unless one per head is
 // faster (decode_one_launch).  decode_split_kernel (vector ALU) or decode_split_mfma_kernel
 // (bf16, four or more query heads per KV head) leaves the raw dots and each range's
 // partial output and softmax sums in the workspace; decode_merge_kernel merges the
@@ -736,12 +736,17 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
 // Stage 1 on the matrix core (bf16): with several query heads per KV head the vector-ALU dots
 // and weighted sums above cost more than the key and value streams (whole step
 // at 8 queries per head, d = 128: 8 heads x 100 slots 20.9 -> 10.9 us, 64 x 1500 42.0 -> 22.0).
+// Tiles of 16 columns: with 32, three quarters of the products, exponentials and weight conversions and
+// half of the registers were for columns past the last head (246 registers -> 168, three workgroups per CU
+// instead of two; 64 heads x 1537 slots 24.4 -> 21.2 us, 96 x 1537 37.3 -> 26.3, 8 x 2049 with G = 4
+// 12.9 -> 11.9).  Bound by latency for few heads, else by the loads a CU has in flight (128 heads x 1537: 101
+// MB in 25 us).
 // Workgroup = (slot range, batch, KV head) as above; each of its four waves takes blocks of 32
 // slots on its own, and the waves meet once, at the end:
-//   S = K Q^T       v_mfma_f32_32x32x16_bf16, slots on M, the query heads on N (columns past the
+//   S = K Q^T       v_mfma_f32_16x16x32_bf16, slots on M, the query heads on N (columns past the
 //                   last head repeat it and are never used); key fragments straight from global
 //                   memory, query fragments in registers
-//   softmax         a column's 32 dots sit in lanes l and l + 32: one reference per column, moved
+//   softmax         a column's 32 dots sit in four lanes 16 apart: one reference per column, moved
 //                   only when a block's maximum exceeds it, as a raw dot
 //   O^T += V^T P^T  the accumulator layout hands a lane the probabilities of exactly the slots it
 //                   supplies as a B fragment; V^T fragments by transposing reads from the wave's
@@ -752,9 +757,9 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
 // it takes the new token's rows instead (kept in LDS by every wave for itself) and writes them to
 // the cache.
 template <int D, int G>
-__global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g, int nsplit, int sps,
+__global__ __launch_bounds__(256, 3) void decode_split_mfma_kernel(DecodeGeom g, int nsplit, int sps,
                                                                    float *ws_w, float *ws_part) {
-    constexpr int LPR = D / 8, ROWB = D * 2, KS = D / 16, CB = D / 32, LD = D + 8;
+    constexpr int LPR = D / 8, ROWB = D * 2, KS = D / 32, CB = D / 16, LD = D + 8;
     constexpr int RPI = 64 / LPR, NI = 32 / RPI;  // value rows per load instruction, loads per block
     __shared__ __attribute__((aligned(16))) __bf16 s_v[4][32 * LD];  // later the partial outputs
     __shared__ __attribute__((aligned(16))) __bf16 s_new[4][2 * D];  // the new token's key and value rows
@@ -766,17 +771,20 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
     const int b = z / g.Hkv, h = z % g.Hkv;
     const int live = g.budget + 1;
     const int s0 = split * sps, s1 = min(live, s0 + sps);
-    const int col = lane & 31, hf = lane >> 5, sub = lane % LPR;
+    const int col = lane & 15, q4 = lane >> 4, sub = lane % LPR;
     char *kcz = (char *)g.kc + (int64_t)z * g.slots * ROWB;
     char *vcz = (char *)g.vc + (int64_t)z * g.slots * ROWB;
 
     // everything the first block needs is requested before anything is used
-    bf16x8 qf[KS], a[KS];
+    bf16x8 qf[KS], a[2][KS];
     u32x4 vw[NI];
     auto request_keys = [&](int b0) {
-        const char *pr = kcz + (int64_t)min(b0 + col, s1 - 1) * ROWB + hf * 16;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) a[ks] = *(const bf16x8 *)(pr + ks * 32);
+        for (int t = 0; t < 2; ++t) {
+            const char *pr = kcz + (int64_t)min(b0 + 16 * t + col, s1 - 1) * ROWB + q4 * 16;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) a[t][ks] = *(const bf16x8 *)(pr + ks * 64);
+        }
     };
     auto request_values = [&](int b0) {
 #pragma unroll
@@ -785,9 +793,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
     };
     const int fs = g.free_slot[z];
     {
-        const char *pr = (const char *)g.q + ((int64_t)(b * g.Hq + h * G + min(col, G - 1))) * ROWB + hf * 16;
+        const char *pr = (const char *)g.q + ((int64_t)(b * g.Hq + h * G + min(col, G - 1))) * ROWB + q4 * 16;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(pr + ks * 32);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(pr + ks * 64);
     }
     const u32x4 knw = *(const u32x4 *)((const char *)g.k_new + (int64_t)z * ROWB + sub * 16);
     const u32x4 vnw = *(const u32x4 *)((const char *)g.v_new + (int64_t)z * ROWB + sub * 16);
@@ -804,76 +812,74 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
                                           g.budget, D);
     // reference (raw dot), and this lane's sums of the output and the score softmax relative to it
     float m = -INFINITY, zsum = 0.f, zsc = 0.f;
-    f32x16 O[CB];
+    f32x4 O[CB];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) O[cb][v] = 0.f;
+    for (int cb = 0; cb < CB; ++cb) O[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int b0 = s0 + wave * 32; b0 < s1; b0 += 128) {
         const bool has_new = fs >= b0 && fs < min(b0 + 32, s1);  // (wave-uniform)
         if (has_new) {
-            if (b0 + col == fs) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) a[ks] = *(const bf16x8 *)(snew + ks * 16 + hf * 8);
-            }
+            for (int t = 0; t < 2; ++t)
+                if (b0 + 16 * t + col == fs) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) a[t][ks] = *(const bf16x8 *)(snew + ks * 32 + q4 * 8);
+                }
             if (lane < LPR) *(u32x4 *)(kcz + (int64_t)fs * ROWB + sub * 16) = *(const u32x4 *)(snew + sub * 8);
         }
-        f32x16 acc, odd;  // (two chains of sums: against float64 the scores are as close as with
-                          // the vector ALU's dots, in one chain 4 % further off over 60 shapes)
+        // (two chains of sums: against float64 the scores are as close as with the vector ALU's dots)
+        f32x4 acc[2], odd[2];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = odd[v] = 0.f;
+        for (int t = 0; t < 2; ++t) acc[t] = odd[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ks += 2) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], qf[ks], acc, 0, 0, 0);
-            odd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks + 1], qf[ks + 1], odd, 0, 0, 0);
-        }
+        for (int ks = 0; ks < KS; ks += 2)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] += odd[v];
+            for (int t = 0; t < 2; ++t) {
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][ks], qf[ks], acc[t], 0, 0, 0);
+                odd[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][ks + 1], qf[ks + 1], odd[t], 0, 0, 0);
+            }
+        float w[8];  // lane: column col, slots b0 + 16 (e / 4) + 4 q4 + e % 4
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = acc[e >> 2][e & 3] + odd[e >> 2][e & 3];
         __builtin_amdgcn_sched_barrier(0);
         request_keys(min(b0 + 128, s1 - 1));
         __builtin_amdgcn_sched_barrier(0);
-        // lane: column col, slots b0 + 8 (v / 4) + 4 hf + v % 4
+        const bool ragged = b0 + 32 > s1;
         if (col < G) {
-            float *wp = ws_w + ((int64_t)z * live + b0 + 4 * hf) * G + col;  // [head][slot][query]
+            float *wp = ws_w + ((int64_t)z * live + b0 + 4 * q4) * G + col;  // [head][slot][query]
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 8 * (v >> 2) + (v & 3);
-                if (b0 + 4 * hf + r < s1) wp[r * G] = acc[v];
+            for (int e = 0; e < 8; ++e) {
+                const int r = 16 * (e >> 2) + (e & 3);
+                if (b0 + 4 * q4 + r < s1) wp[r * G] = w[e];
             }
         }
-        if (b0 + 32 > s1) {
+        if (ragged) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (b0 + 4 * hf + 8 * (v >> 2) + (v & 3) >= s1) acc[v] = -INFINITY;
+            for (int e = 0; e < 8; ++e)
+                if (b0 + 4 * q4 + 16 * (e >> 2) + (e & 3) >= s1) w[e] = -INFINITY;
         }
-        float bm = acc[0];
+        float bm = w[0];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) bm = fmaxf(bm, acc[v]);
-        bm = combine_lane_xor<32>(bm, OpMax{});
+        for (int e = 1; e < 8; ++e) bm = fmaxf(bm, w[e]);
+        bm = reduce_lanes<16, 64>(bm, OpMax{});
         const float mn = fmaxf(m, bm), mref = finite_ref(mn), corr = fast_exp2((m - mref) * c_out);
         const float corr_sc = m == -INFINITY ? 0.f : fast_exp2((m - mref) * c_sc);
         m = mn;
-        bf16x8 pf[2][3];
+        bf16x8 pf[3];
         float sum[2] = {0.f, 0.f}, sumsc[2] = {0.f, 0.f};
-        const bool ragged = b0 + 32 > s1;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = acc[8 * ks + e] - mref;
-                const float pr = fast_exp2(d * c_out);
-                sum[e & 1] += pr;
-                const float ps = fast_exp2(d * c_sc);
-                sumsc[e & 1] += ragged && d == -INFINITY ? 0.f : ps;  // (a scale of 0 times infinity)
-                split_weight(pr, pf[ks], e);
-            }
+        for (int e = 0; e < 8; ++e) {
+            const float d = w[e] - mref;
+            const float pr = fast_exp2(d * c_out);
+            sum[e & 1] += pr;
+            const float ps = fast_exp2(d * c_sc);
+            sumsc[e & 1] += ragged && d == -INFINITY ? 0.f : ps;  // (a scale of 0 times infinity)
+            split_weight(pr, pf, e);
+        }
         zsum = zsum * corr + (sum[0] + sum[1]);
         zsc = zsc * corr_sc + (sumsc[0] + sumsc[1]);
         if (__builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
+            for (int cb = 0; cb < CB; ++cb) O[cb] *= corr;
         }
         // the value rows -> the wave's LDS copy (the new row stands in for the free slot's; rows past
         // the range are zero: their weights are 0, but what was read for them may be the free
@@ -886,29 +892,27 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
 #pragma unroll
         for (int t = 0; t < NI; ++t) {
             const int rin = t * RPI + lane / LPR;
-            u32x4 w = vw[t];
+            u32x4 v = vw[t];
             if (has_new && b0 + rin == fs) {
-                w = *(const u32x4 *)(snew + D + sub * 8);
-                *(u32x4 *)(vcz + (int64_t)fs * ROWB + sub * 16) = w;
+                v = *(const u32x4 *)(snew + D + sub * 8);
+                *(u32x4 *)(vcz + (int64_t)fs * ROWB + sub * 16) = v;
             }
-            *(u32x4 *)(sv + rin * LD + sub * 8) = w;
+            *(u32x4 *)(sv + rin * LD + sub * 8) = v;
         }
         __builtin_amdgcn_sched_barrier(0);
         request_values(min(b0 + 128, s1 - 1));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int cb = 0; cb < CB; ++cb) {
+            const bf16x8 vf = lds_transposed_fragment16(sv, LD, 16, cb * 16, lane);
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                const bf16x8 vf = lds_transposed_fragment(sv, LD, 16 * ks, 8, cb * 32, lane);
-#pragma unroll
-                for (int t = 2; t >= 0; --t)
-                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks][t], O[cb], 0, 0, 0);
-            }
+            for (int t = 2; t >= 0; --t)
+                O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[t], O[cb], 0, 0, 0);
+        }
     }
     // the waves' partials, each relative to its own reference, meet in LDS
-    zsum = combine_lane_xor<32>(zsum, OpSum{});
-    zsc = combine_lane_xor<32>(zsc, OpSum{});
+    zsum = reduce_lanes<16, 64>(zsum, OpSum{});
+    zsc = reduce_lanes<16, 64>(zsc, OpSum{});
     if (lane < G) {
         s_m[wave][lane] = m;
         s_z[wave][lane] = zsum;
@@ -921,10 +925,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(DecodeGeom g,
     if (col < G) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4)
-                *(f32x4 *)(s_o + (wave * G + col) * D + ((cb * 32 + 8 * v4 + 4 * hf) ^ (8 * col))) =
-                    f32x4{O[cb][4 * v4], O[cb][4 * v4 + 1], O[cb][4 * v4 + 2], O[cb][4 * v4 + 3]};
+            *(f32x4 *)(s_o + (wave * G + col) * D + ((cb * 16 + 4 * q4) ^ (8 * col))) = O[cb];
     }
     __syncthreads();
     float *part = ws_part + ((int64_t)z * nsplit + split) * G * (D + kPartStats);
