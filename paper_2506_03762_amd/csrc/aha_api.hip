@@ -138,6 +138,23 @@ static ScoreGeom make_geom(const aha_params *p, const void *q, const void *k, co
     return g;
 }
 
+// Key ranges of a problem for workgroups of which the chip holds `resident` at once: in rounds of the whole
+// chip, the number of ranges with the shortest sum over the rounds of a range's steps (of `step` keys) and
+// its set-up and exchange, about as long as a step.  Ranges have at most `most_keys`, a multiple of `step`.
+static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, int64_t most_keys, int64_t &parts,
+                        int64_t &keys) {
+    const int64_t all = (n + step - 1) / step;
+    int64_t best = INT64_MAX;
+    const int64_t least = (n + most_keys - 1) / most_keys;
+    parts = least;
+    for (int64_t c = least; c <= all && c <= 256; ++c) {
+        const int64_t sum = (Z * c + resident - 1) / resident * ((all + c - 1) / c + 1);
+        if (sum < best) best = sum, parts = c;
+    }
+    keys = (all + parts - 1) / parts * step;
+    parts = (n + keys - 1) / keys;
+}
+
 // Windowed bf16 scores in one launch, in the same bytes as the two-launch layout.  Where, and which
 // kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
 // heads, 400 to 65536 keys, d = 64 and 128): 1.30 times as fast as two launches on average, none
@@ -184,19 +201,7 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
         tiles = 2;
         nb = blocks <= 12 ? 6 : 8;
     }
-    if (!hold) {
-        // one workgroup per CU, in rounds of the whole chip: the number of ranges with the shortest sum
-        // over the rounds of a range's steps and its set-up and exchange, about as long as a step
-        const int64_t step = 512 / tiles, all = (p->seq_len + step - 1) / step;
-        int64_t best = INT64_MAX;
-        parts = 1;
-        for (int64_t n = 1; n <= all && n <= 256; ++n) {
-            const int64_t sum = (pl.Z * n + 255) / 256 * ((all + n - 1) / n + 1);
-            if (sum < best) best = sum, parts = n;
-        }
-        keys = (all + parts - 1) / parts * step;
-        parts = (p->seq_len + keys - 1) / keys;
-    }
+    if (!hold) best_ranges(pl.Z, p->seq_len, 512 / tiles, 256, INT64_MAX / 2, parts, keys);
     if (pl.Z * parts > 1 << 30 || parts >= 1 << 19) return;
     pl.win_nb = nb;
     pl.win_tiles = tiles;
@@ -212,6 +217,36 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
     if (!hold) {
         pl.off_wnu = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
         pl.off_wgamma = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
+    }
+    if (off > pl.bytes) pl.bytes = off;
+}
+
+// Windowed bf16 scores from given normalisers in one launch (score_given.hip), in the same bytes: one query
+// tile, and a prior whose pooling halo a workgroup holds.  Against two launches 1.15 times as fast on average
+// over 110 shapes (1 to 256 rows, 2 to 128 KV heads, 250 to 61000 keys), us in two, in one: 8 heads x 32768 keys x
+// 256 rows 46.3, 39.7; 128 x 16384 x 64 198, 172; 32 x 4096 x 64 19.7, 19.1; 2 x 512 x 32 8.3, 7.2.  Not taken
+// where it was the slower one: few heads in many ranges of a step or two, where the exchange is most of the time (8 x
+// 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), and without a prior, of which a
+// second launch would have to be saved, many steps of the larger tiles (32 x 31856 x 256 79.3, 82.3).
+static void plan_given(const aha_params *p, PrefillPlan &pl) {
+    pl.given_nb = 0;
+    const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
+    if (p->dtype != AHA_BF16 || R > 256 || (p->value_prior && p->pool_kernel > 17)) return;
+    const int blocks = (int)((R + 31) / 32);
+    const int nb = blocks <= 2 ? blocks : (blocks + 1) / 2 * 2, resident = nb <= 4 ? 512 : 256;
+    int64_t parts, keys;
+    best_ranges(pl.Z, p->seq_len, nb <= 4 ? 256 : 512, resident, p->value_prior ? given_keys(p->head_dim, nb) : INT64_MAX / 2,
+                parts, keys);
+    if (pl.Z * parts > 1 << 30 || parts > resident) return;  // (all of a problem's workgroups have to run at once)
+    if (p->value_prior ? nb <= 4 && pl.Z <= 8 && parts > (nb <= 2 ? 24 : 50) : nb > 4 && (int64_t)pl.Z * p->seq_len > 1 << 19) return;
+    pl.given_nb = nb;
+    pl.given_parts = (int)parts;
+    pl.given_keys = (int)keys;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
+    if (p->value_prior) {
+        pl.off_gtags = take(2 * sizeof(uint64_t) * (size_t)pl.Z * parts);
+        pl.off_gcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
     }
     if (off > pl.bytes) pl.bytes = off;
 }
@@ -288,6 +323,7 @@ static PrefillPlan plan_prefill(const aha_params *p) {
     pl.can_fold = p->dtype == AHA_BF16 && pl.n_qtiles == 1 && pl.NB <= 4 && p->pool_kernel <= 17;
     pl.bytes = off;
     plan_window(p, pl);
+    plan_given(p, pl);
     return pl;
 }
 
@@ -528,9 +564,10 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     g.rows = rows;
     hipStream_t st = (hipStream_t)stream;
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
-    if (pl.win_nb && !rows && !with_lse) {
+    if (with_lse ? pl.given_nb > 0 : pl.win_nb && !rows) {
         if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(launch_score_window(g, pl, workspace, next_tag(), g_looks, scores, st),
+            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), g_looks, lse, scores, st)
+                                      : launch_score_window(g, pl, workspace, next_tag(), g_looks, scores, st),
                              "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;

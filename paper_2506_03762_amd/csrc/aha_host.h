@@ -62,6 +62,9 @@ struct PrefillPlan {
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold;
     size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma;
+    // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
+    int given_nb, given_parts, given_keys;
+    size_t off_gtags, off_gcounts;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;
 };
@@ -92,6 +95,16 @@ hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws
 // zero; `looks`: at the other workgroups' announcements before missing parts are done in place.
 hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                                float *scores, hipStream_t st);
+// score_given.hip
+// Keys of a range whose norms, prior and column sums (12 bytes) fit beside a tile of nb blocks of query
+// rows (and 1 KB of other values) with two workgroups per CU (up to four blocks) or one.
+constexpr int given_keys(int d, int nb) {
+    const int room = ((nb <= 4 ? 80 : 160) - 1) * 1024 - nb * (32 * (2 * (d + 8) + 12) + 8);
+    return room / 12 / 512 * 512;
+}
+// The same from the caller's row normalisers `lse` (pl.given_nb > 0).
+hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+                              const float *lse, float *scores, hipStream_t st);
 // Row statistics of the observed rows out (pass 1 only): natural-log normaliser and entropy,
 // dense [batch, Hq, window]; either pointer may be null.
 hipError_t launch_row_stats_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *lse,

@@ -25,7 +25,7 @@
 namespace aha {
 
 struct Exchange {
-    uint64_t *tags;    // [problem][part]
+    uint64_t *tags;    // [problem][part], or [problem][part][2] (announce_value)
     uint64_t *counts;  // [problem]
     uint64_t tag;      // of this call; the low kCountBits are zero, the rest is not
     int looks;         // at the announcements before missing parts are done here
@@ -66,6 +66,45 @@ __device__ __forceinline__ int first_missing(const Exchange &x, int z, int npart
     return reduce_lanes<1, 64>(missing, OpMinI{});
 }
 
+// Where all that a part leaves is one float, the announcement carries it: two words per part, the tag with
+// one half of the value in its low bits each, both of which a reader has to find.  One trip to memory
+// each way instead of two, and nothing to wait for in between.
+__device__ __forceinline__ void announce_value(const Exchange &x, int z, int nparts, int part, float value, int tid) {
+    if (tid >= 2) return;
+    const uint32_t bits = __float_as_uint(value);
+    put(x.tags + ((int64_t)z * nparts + part) * 2 + tid, x.tag | (tid ? bits >> 16 : bits & 0xffffu));
+}
+// first_missing() of such parts; the largest value (none is below 0) if there is none missing.  Two parts per
+// lane at a time, and only by lanes that still miss one: waiting workgroups then stay out of the way
+// of those that announce.
+__device__ __forceinline__ int largest_value(const Exchange &x, int z, int nparts, int lane, float &largest) {
+    const uint64_t *t = x.tags + (int64_t)z * nparts * 2;
+    largest = 0.f;
+    for (int p0 = 0; p0 < nparts; p0 += 2 * kWave) {
+        int missing = p0 + lane;  // of this lane's parts
+        for (int look = 0;; ++look) {
+            if (missing < nparts) {
+                const int p1 = min(p0 + kWave + lane, nparts - 1);
+                const uint64_t lo0 = get(t + 2 * (p0 + lane)), hi0 = get(t + 2 * (p0 + lane) + 1);
+                const uint64_t lo1 = get(t + 2 * p1), hi1 = get(t + 2 * p1 + 1);
+                const bool there0 = ((lo0 ^ x.tag) | (hi0 ^ x.tag)) >> kCountBits == 0;
+                const bool there1 = ((lo1 ^ x.tag) | (hi1 ^ x.tag)) >> kCountBits == 0;
+                if (there0 && there1) {
+                    const float a = __uint_as_float((uint32_t)(lo0 & 0xffffu) | (uint32_t)(hi0 & 0xffffu) << 16);
+                    const float b = __uint_as_float((uint32_t)(lo1 & 0xffffu) | (uint32_t)(hi1 & 0xffffu) << 16);
+                    largest = fmaxf(largest, fmaxf(a, b));
+                }
+                missing = there0 ? (there1 ? nparts : p1) : p0 + lane;
+            }
+            if (__builtin_amdgcn_ballot_w64(missing < nparts) == 0) break;
+            if (look >= x.looks) return reduce_lanes<1, 64>(missing, OpMinI{});
+            __builtin_amdgcn_s_sleep(4);
+        }
+    }
+    largest = wave_max(largest);
+    return nparts;
+}
+
 // The count of a problem's workgroups that have seen all announcements, so that the last one can clear
 // them.  Whoever does part 0 sets it to the tag (unless somebody else has) before announcing that part:
 // nobody counts himself before.  One thread of the workgroup: `look` early, `start` some time
@@ -83,10 +122,12 @@ struct Count {
         found = __hip_atomic_fetch_add(x.counts + z, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
-// By the whole wave of the thread that arrived (its last lane), at the end of the workgroup's work.
+// By the whole wave of the thread that arrived (its last lane), at the end of the workgroup's work.  WORDS: of
+// an announcement.
+template <int WORDS = 1>
 __device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, const Count &c, int lane) {
     if (__builtin_amdgcn_ballot_w64(lane == kWave - 1 && c.found == x.tag + (uint64_t)(nparts - 1)) == 0) return;
-    for (int p = lane; p < nparts; p += kWave) put(x.tags + (int64_t)z * nparts + p, (uint64_t)0);
+    for (int p = lane; p < WORDS * nparts; p += kWave) put(x.tags + (int64_t)z * nparts * WORDS + p, (uint64_t)0);
     if (lane == 0) put(x.counts + z, (uint64_t)0);
 }
 

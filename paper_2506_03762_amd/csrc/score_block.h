@@ -146,6 +146,67 @@ __device__ __forceinline__ void fragment_row_norms(const bf16x8 (&a)[kMB][D / 16
     }
 }
 
+// The same for value rows that a wave loads as they lie in memory, D / 8 lanes to a row and 512 / D rows to
+// an instruction.
+template <int D>
+__device__ __forceinline__ void load_rows(const __bf16 *vbase, int64_t v_tstride, int kb, int end, int lane,
+                                          bf16x8 (&w)[kMB][D / 16]) {
+    constexpr int CPR = D / 8, RPI = 64 / CPR;
+    int row = kb + lane / CPR;
+    const __bf16 *p = vbase + (int64_t)min(row, end - 1) * v_tstride + (lane % CPR) * 8;
+#pragma unroll
+    for (int u = 0; u < kMB * D / 16; ++u) {
+        w[u / (D / 16)][u % (D / 16)] = __builtin_nontemporal_load((const bf16x8 *)p);
+        row += RPI;
+        if (row < end) p += RPI * v_tstride;  // (past the end: a row that is there once more)
+    }
+}
+// Recursive halving over M, M / 2, .. 1: of N per-lane values the sums over those lanes, one value in each; `u`: which.
+template <int M, int N>
+__device__ __forceinline__ float fold_rows(float (&x)[N], int lane, int &u) {
+    const bool hi = lane & M;
+    if constexpr (N > 1) {
+        float y[N / 2];
+#pragma unroll
+        for (int t = 0; t < N / 2; ++t) {
+            const float send = hi ? x[t] : x[t + N / 2], keep = hi ? x[t + N / 2] : x[t];
+            y[t] = keep + from_lane_xor<M>(send);
+        }
+        u += hi ? N / 2 : 0;
+        if constexpr (M > 1) return fold_rows<M / 2>(y, lane, u);
+        else return y[0];
+    } else {
+        const float y = x[0] + from_lane_xor<M>(x[0]);
+        if constexpr (M > 1) {
+            float z[1] = {y};
+            return fold_rows<M / 2>(z, lane, u);
+        } else return y;
+    }
+}
+// ||V_row||^2 of one of those rows, in each lane another one: row kb + `row`.
+template <int D>
+__device__ __forceinline__ float loaded_row_norm(const bf16x8 (&w)[kMB][D / 16], int lane, int &row) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    constexpr int CPR = D / 8, RPI = 64 / CPR, U = kMB * D / 16;
+    static_assert(U == CPR, "a row for every lane");
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bf16x8 v = w[u / (D / 16)][u % (D / 16)];
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) {
+            const bf16x2 pr = {v[c], v[c + 1]};
+            s = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, s, false);
+        }
+        x[u] = s;
+    }
+    int u = 0;
+    const float nu = fold_rows<CPR / 2>(x, lane, u);
+    row = u * RPI + lane / CPR;
+    return nu;
+}
+
 constexpr int kPriorPiece = 512;   // keys whose norms are staged for pooling at a time
 constexpr int kPriorMaxHalo = 32;  // rows on both sides together
 // Pooling halo of a key range [kbeg, kend): the (pool - 1) / 2 value rows below and above it,
@@ -178,5 +239,53 @@ struct PriorHalo {
         return reduce_lanes<1, CPR>(hn, OpSum{});
     }
 };
+
+// gamma (Sec. 4.3) of the keys [kbeg, kend), whose norms and pooling halo are in s_nu[t - lo],
+// lo = max(0, kbeg - half), into s_gam[key - kbeg]; returns this thread's largest.
+__device__ __forceinline__ float pool_norms(const ScoreGeom &g, int kbeg, int kend, const float *s_nu,
+                                            float *s_gam, int tid, int nthreads) {
+    const int half = (g.pool - 1) / 2, lo = max(0, kbeg - half);
+    float gmax = 0.f;
+    for (int j = kbeg + tid; j < kend; j += nthreads) {
+        const int a = max(0, j - half), e = min(g.n - 1, j + half);
+        float s = 0.f;
+        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
+        const float gam = s / (float)(e - a + 1);
+        s_gam[j - kbeg] = gam;
+        gmax = fmaxf(gmax, gam);
+    }
+    return gmax;
+}
+
+// gamma of the keys [kbeg, kend) from the norms the workgroup's waves left in nu_g, in pieces staged in
+// s_nu, to `gamma`; returns this thread's largest.  The caller has passed a barrier since the last norm
+// was written, and nobody uses s_nu any more.
+template <int D, int THREADS>
+__device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg, int kend,
+                                                     const float *nu_g, const PriorHalo<D> &halo,
+                                                     float *s_nu, float *gamma, int tid) {
+    const int half = (g.pool - 1) / 2;
+    const float hn = halo.norm();
+    float gmax = 0.f;
+    for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
+        const int t1 = min(kend, t0 + kPriorPiece);
+        const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
+        for (int t = max(lo, kbeg) + tid; t < min(hi, kend); t += THREADS) s_nu[t - lo] = nu_g[(int64_t)z * g.n + t];
+        // the halo rows that touch this piece (the first piece below, the last one above)
+        if (halo.valid && tid % PriorHalo<D>::CPR == 0 && (halo.below ? t0 == kbeg : t1 == kend))
+            s_nu[halo.pos - lo] = hn;
+        __syncthreads();
+        for (int j = t0 + tid; j < t1; j += THREADS) {
+            const int a = max(0, j - half), e = min(g.n - 1, j + half);
+            float s = 0.f;
+            for (int t = a; t <= e; ++t) s += s_nu[t - lo];
+            const float gam = s / (float)(e - a + 1);
+            gamma[(int64_t)z * g.n + j] = gam;
+            gmax = fmaxf(gmax, gam);
+        }
+        __syncthreads();
+    }
+    return gmax;
+}
 
 }  // namespace aha

@@ -31,23 +31,6 @@ struct HoldSmem {
     static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
 };
 
-// gamma (Sec. 4.3) of the keys [kbeg, kend), whose norms and pooling halo are in s_nu[t - lo],
-// lo = max(0, kbeg - half), into s_gam[key - kbeg]; returns this thread's largest.
-__device__ __forceinline__ float pool_norms(const ScoreGeom &g, int kbeg, int kend, const float *s_nu,
-                                            float *s_gam, int tid, int nthreads) {
-    const int half = (g.pool - 1) / 2, lo = max(0, kbeg - half);
-    float gmax = 0.f;
-    for (int j = kbeg + tid; j < kend; j += nthreads) {
-        const int a = max(0, j - half), e = min(g.n - 1, j + half);
-        float s = 0.f;
-        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
-        const float gam = s / (float)(e - a + 1);
-        s_gam[j - kbeg] = gam;
-        gmax = fmaxf(gmax, gam);
-    }
-    return gmax;
-}
-
 // The pair held by lane ^ 32.
 __device__ __forceinline__ void from_other_half(float M, float s, float &M2, float &s2) {
     const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(M), __float_as_uint(M), false, false);
@@ -348,37 +331,6 @@ struct StreamSmem {
     static_assert(2 * 4 * kWaveKeys * sizeof(float) <= red_bytes, "column sums of two steps");
     static_assert(bytes <= 160 * 1024, "LDS of a CU");
 };
-
-// gamma of the keys [kbeg, kend) from the norms the workgroup's waves left in nu_g, in pieces staged in
-// s_nu, to `gamma`; returns this thread's largest.  The caller has passed a barrier since the last norm
-// was written, and nobody uses s_nu any more.
-template <int D, int THREADS>
-__device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg, int kend,
-                                                     const float *nu_g, const PriorHalo<D> &halo,
-                                                     float *s_nu, float *gamma, int tid) {
-    const int half = (g.pool - 1) / 2;
-    const float hn = halo.norm();
-    float gmax = 0.f;
-    for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
-        const int t1 = min(kend, t0 + kPriorPiece);
-        const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
-        for (int t = max(lo, kbeg) + tid; t < min(hi, kend); t += THREADS) s_nu[t - lo] = nu_g[(int64_t)z * g.n + t];
-        // the halo rows that touch this piece (the first piece below, the last one above)
-        if (halo.valid && tid % PriorHalo<D>::CPR == 0 && (halo.below ? t0 == kbeg : t1 == kend))
-            s_nu[halo.pos - lo] = hn;
-        __syncthreads();
-        for (int j = t0 + tid; j < t1; j += THREADS) {
-            const int a = max(0, j - half), e = min(g.n - 1, j + half);
-            float s = 0.f;
-            for (int t = a; t <= e; ++t) s += s_nu[t - lo];
-            const float gam = s / (float)(e - a + 1);
-            gamma[(int64_t)z * g.n + j] = gam;
-            gmax = fmaxf(gmax, gam);
-        }
-        __syncthreads();
-    }
-    return gmax;
-}
 
 template <int D, int NB, int NT, bool PRIOR>
 __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
