@@ -538,6 +538,15 @@ static uint64_t next_tag() {
 }
 static thread_local int32_t g_looks = kLooks;
 
+// Whether the one-launch scores read the value rows past the caches, given the bytes of K and V.  Kept
+// there they serve the gather of the retained rows, as long as the last-level cache (256 MB) has room for
+// them; read past it they are faster.  us, through the caches and past them: 32 heads x 4096 keys (67 MB), the
+// whole step 29.9, 31.0; 48 x 6846 (84 MB), scores 56.1, 47.5; 8 x 32768 (134 MB), step 89.9, 85.8; 128 x 16384
+// (1.07 GB), step 347, 340.  With given normalisers the attention has just read them: 8 x 32768, step 118.7, 121.4.
+static bool values_once(int64_t bytes, bool after_attention) {
+    return bytes > (after_attention ? 200 * 1000 * 1000 : 80 * 1000 * 1000);
+}
+
 static int32_t prefill_scores_impl(const aha_params *p, const void *q, const void *k,
                                    const void *v, const float *lse, bool with_lse,
                                    const int32_t *rows, float *scores, void *workspace,
@@ -562,6 +571,7 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
                     (p->n_q_heads / p->n_kv_heads) * p->window);
     ScoreGeom g = make_geom(p, q, k, v);
     g.rows = rows;
+    g.v_once = values_once((int64_t)4 * pl.Z * g.n * g.d, with_lse);
     hipStream_t st = (hipStream_t)stream;
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
     if (with_lse ? pl.given_nb > 0 : pl.win_nb && !rows) {

@@ -42,6 +42,7 @@ struct ScoreGeom {
     float fixed_scale, lambda_floor;
     int value_prior, pool;
     int dtype;   // AHA_F32 | AHA_BF16
+    bool v_once;  // windowed bf16 scores: value rows are read past the caches
 };
 
 // Where things live in the caller's workspace during aha_prefill_scores.

@@ -146,17 +146,21 @@ __device__ __forceinline__ void fragment_row_norms(const bf16x8 (&a)[kMB][D / 16
     }
 }
 
+// Value prior of the one-launch kernels, a template argument: none, value rows through the caches, past them.
+constexpr int kNoValues = 0, kValuesCached = 1, kValuesOnce = 2;
 // The same for value rows that a wave loads as they lie in memory, D / 8 lanes to a row and 512 / D rows to
-// an instruction.
-template <int D>
+// an instruction.  M: 32 rows each.  ONCE: past the caches.
+template <int D, bool ONCE, int M = kMB>
 __device__ __forceinline__ void load_rows(const __bf16 *vbase, int64_t v_tstride, int kb, int end, int lane,
                                           bf16x8 (&w)[kMB][D / 16]) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;
     int row = kb + lane / CPR;
     const __bf16 *p = vbase + (int64_t)min(row, end - 1) * v_tstride + (lane % CPR) * 8;
 #pragma unroll
-    for (int u = 0; u < kMB * D / 16; ++u) {
-        w[u / (D / 16)][u % (D / 16)] = __builtin_nontemporal_load((const bf16x8 *)p);
+    for (int u = 0; u < M * D / 16; ++u) {
+        bf16x8 &x = w[u / (D / 16)][u % (D / 16)];
+        if constexpr (ONCE) x = __builtin_nontemporal_load((const bf16x8 *)p);
+        else x = *(const bf16x8 *)p;
         row += RPI;
         if (row < end) p += RPI * v_tstride;  // (past the end: a row that is there once more)
     }
@@ -183,12 +187,12 @@ __device__ __forceinline__ float fold_rows(float (&x)[N], int lane, int &u) {
         } else return y;
     }
 }
-// ||V_row||^2 of one of those rows, in each lane another one: row kb + `row`.
-template <int D>
+// ||V_row||^2 of one of those rows, row kb + `row`: in each lane (M = 1: pair of lanes) another one.
+template <int D, int M = kMB>
 __device__ __forceinline__ float loaded_row_norm(const bf16x8 (&w)[kMB][D / 16], int lane, int &row) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    constexpr int CPR = D / 8, RPI = 64 / CPR, U = kMB * D / 16;
-    static_assert(U == CPR, "a row for every lane");
+    constexpr int CPR = D / 8, RPI = 64 / CPR, U = M * D / 16;
+    static_assert(U <= CPR, "no more rows than lanes");
     float x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {

@@ -11,6 +11,8 @@
 // Value rows are loaded as they lie in memory (load_rows) and not with the key fragments' addressing, 32 rows
 // x 32 bytes to an instruction: 128 x 16384 x 64 233 -> 212 us.  Ranges are as long as the LDS keeps their
 // norms, prior and sums; through the workspace instead the same took 212 us, now 174.
+#include <type_traits>
+
 #include "exchange.h"
 #include "score_block.h"
 
@@ -50,11 +52,11 @@ __device__ __forceinline__ void masked_colsum(const f32x16 (&acc)[kMB], float la
 }
 
 // WAVES: 4 with up to four row blocks (two workgroups per CU), 8 with more (one).
-template <int D, int NB, int WAVES, bool PRIOR>
+template <int D, int NB, int WAVES, int PRIOR>
 __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
                                                                      const float *lse, float *scores) {
     using S = TileSmem<D, NB>;
-    using W = GivenSmem<D, NB, PRIOR>;
+    using W = GivenSmem<D, NB, PRIOR != 0>;
     constexpr int THREADS = 64 * WAVES, STEP = WAVES * kWaveKeys, HALVES = WAVES / 4;
     // With few row blocks a step is too short to pass value rows and next keys through one buffer: the
     // value rows then have a buffer of their own and are a whole step ahead, as the keys' own next
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         __builtin_amdgcn_sched_barrier(0);  // the keys are requested last
         load_a<D>(kbase, g.ks[2], kb_of(0), key_end, tid & 63, a0);
         if (PRIOR) {
-            load_rows<D>(vbase, g.vs[2], kb_of(0), key_end, tid & 63, a1);
+            load_rows<D, PRIOR == kValuesOnce>(vbase, g.vs[2], kb_of(0), key_end, tid & 63, a1);
         }
         if (tid < S::ROWS) sL[tid] = L;
         q_tile_meta<D, NB>(g, rm, 0, tid, lam_req, sLam, sPos, sBlk);
@@ -172,13 +174,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             __builtin_amdgcn_sched_barrier(0);
             store_norms(nx, kb, lane);
             __builtin_amdgcn_sched_barrier(0);
-            load_rows<D>(vbase, g.vs[2], kb_next, key_end, lane, nx);
+            load_rows<D, PRIOR == kValuesOnce>(vbase, g.vs[2], kb_next, key_end, lane, nx);
         } else {
             // the first step's value rows came with its keys, so the next keys have most of the step to
             // travel; the last step has no next keys, and its value rows the whole step; in between,
             // value rows travel under the first half and keys under the second
             constexpr int NB1 = NB / 4;
-            if (!first) load_rows<D>(vbase, g.vs[2], kb, key_end, lane, nx);
+            if (!first) load_rows<D, PRIOR == kValuesOnce>(vbase, g.vs[2], kb, key_end, lane, nx);
             __builtin_amdgcn_sched_barrier(0);
             blocks(a, kb, 0, NB1, col, nothing);
             __builtin_amdgcn_sched_barrier(0);
@@ -255,7 +257,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             set_range(part);
             halo.request(g, vbase, key_begin, key_end, tid);
             for (int i = 0; i < nsteps; ++i) {
-                load_rows<D>(vbase, g.vs[2], kb_of(i), key_end, lane, a0);
+                load_rows<D, PRIOR == kValuesOnce>(vbase, g.vs[2], kb_of(i), key_end, lane, a0);
                 store_norms(a0, kb_of(i), lane);
             }
             store_halo(halo, tid);
@@ -270,10 +272,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
 }
 
 // ---------------------------------------------------------------- launch --
-template <int D, int NB, int WAVES, bool PRIOR>
+template <int D, int NB, int WAVES, int PRIOR>
 static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, const float *lse,
                            float *scores, hipStream_t st) {
-    using W = GivenSmem<D, NB, PRIOR>;
+    using W = GivenSmem<D, NB, PRIOR != 0>;
     const auto kernel = window_given_kernel<D, NB, WAVES, PRIOR>;
     if (W::bytes > 64 * 1024) {
         static DeviceOnce once;
@@ -287,7 +289,7 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     return hipGetLastError();
 }
 
-template <int D, bool PRIOR>
+template <int D, int PRIOR>
 static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, const float *lse,
                            float *scores, hipStream_t st) {
     switch (pl.given_nb) {
@@ -304,11 +306,13 @@ hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *w
                               const float *lse, float *scores, hipStream_t st) {
     char *w = (char *)ws;
     const Exchange x{(uint64_t *)(w + pl.off_gtags), (uint64_t *)(w + pl.off_gcounts), tag, looks};
-    if (g.d == 64)
-        return g.value_prior ? launch_d<64, true>(g, pl, x, w, lse, scores, st)
-                             : launch_d<64, false>(g, pl, x, w, lse, scores, st);
-    return g.value_prior ? launch_d<128, true>(g, pl, x, w, lse, scores, st)
-                         : launch_d<128, false>(g, pl, x, w, lse, scores, st);
+    auto launch = [&](auto prior) {
+        constexpr int PRIOR = decltype(prior)::value;
+        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, w, lse, scores, st)
+                         : launch_d<128, PRIOR>(g, pl, x, w, lse, scores, st);
+    };
+    if (!g.value_prior) return launch(std::integral_constant<int, kNoValues>{});
+    return g.v_once ? launch(std::integral_constant<int, kValuesOnce>{}) : launch(std::integral_constant<int, kValuesCached>{});
 }
 
 }  // namespace aha

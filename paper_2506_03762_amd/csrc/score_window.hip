@@ -13,6 +13,13 @@
 // window_stream_kernel (below): more rows or longer ranges, the logits formed twice.  8 heads x 16384 x
 // 512 rows 89 -> 67 us, 8 x 32768 x 256 70 -> 67: bound by the vector ALU and the matrix core taking turns
 // (620 ns per 64 x 32 block and SIMD), the first sweep's first step by its loads.
+//
+// Value rows are loaded as they lie in memory (load_rows); with the key fragments' addressing an instruction
+// reads 32 bytes of 32 rows.  Where the last-level cache would not keep them anyway they go past the caches.  us
+// of the score stage before and after: 48 heads x 6846 keys x 64 rows 59.0, 47.3; 12 x 59081 x 64 108, 92.8; 128 x
+// 16384 x 64 259, 252; 8 x 32768 x 256 70.4, 67.1.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
+// Two tiles share their value rows, 32 each, and load them like keys: as memory lies was slower
+// (8 x 16384 x 512, the whole step, 77.8 and 74.7).
 #include <type_traits>
 
 #include "exchange.h"
@@ -103,11 +110,11 @@ __device__ __forceinline__ void merge_parts(const float *src, int ld, int nparts
 
 // STEPS: 256-key steps of a workgroup's range, all of whose logits are held: NB * STEPS <= 4.
 // NT = 2: two tiles of rows, eight waves; waves w and w + 4 take the same keys, one tile each.
-template <int D, int NB, int NT, int STEPS, bool PRIOR>
+template <int D, int NB, int NT, int STEPS, int PRIOR>
 __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, int nparts, Exchange x, float *stats,
                                                                   float *maxima, float *scores) {
     using S = TileSmem<D, NB>;
-    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR>;
+    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
     static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
     constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         auto kb_of = [&](int st) { return key_begin + st * kWgKeys + kw * kWaveKeys; };
         bf16x8 a[kMB][D / 16], w[kMB][D / 16];
         auto load_values = [&](int st) {
-            load_a<D, VM>(vbase, g.vs[2], kb_of(st) + (NT == 2 ? tile * 32 : 0), key_end, lane, w);
+            load_rows<D, PRIOR == kValuesOnce, VM>(vbase, g.vs[2], kb_of(st) + (NT == 2 ? tile * 32 : 0), key_end, lane, w);
         };
         PriorHalo<D> halo;
         {
@@ -176,13 +183,10 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         for (int st = 0; st < STEPS; ++st) {
             const int kb = kb_of(st);
             if constexpr (PRIOR) {  // (first: the value rows' registers are then free for the logits)
-                float nu[kMB];
-                fragment_row_norms<D, VM>(w, nu);
-#pragma unroll
-                for (int mb = 0; mb < VM; ++mb) {
-                    const int row = kb + mb * 32 + lane + (NT == 2 ? tile * 32 : 0);
-                    if (lane < 32 && row < key_end) sNu[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
-                }
+                int row;
+                const float nu = loaded_row_norm<D, VM>(w, lane, row);
+                row += kb + (NT == 2 ? tile * 32 : 0);
+                if (row < key_end) sNu[row - max(0, key_begin - (g.pool - 1) / 2)] = nu;
                 __builtin_amdgcn_sched_barrier(0);
                 if (st + 1 < STEPS) load_values(st + 1);
             }
@@ -332,7 +336,7 @@ struct StreamSmem {
     static_assert(bytes <= 160 * 1024, "LDS of a CU");
 };
 
-template <int D, int NB, int NT, bool PRIOR>
+template <int D, int NB, int NT, int PRIOR>
 __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
                                                                float *stats, float *maxima, float *nu_g,
                                                                float *gamma, float *scores) {
@@ -372,7 +376,8 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
         nsteps = (key_end - key_begin + W::STEP - 1) / W::STEP;
     };
     auto load_values = [&](int kb, int lane, bf16x8 (&w)[kMB][D / 16]) {
-        load_a<D, VM>(vbase, g.vs[2], kb + (NT == 2 ? tile * 32 : 0), key_end, lane, w);
+        if (NT == 2) load_a<D, VM>(vbase, g.vs[2], kb + tile * 32, key_end, lane, w);
+        else load_rows<D, PRIOR == kValuesOnce>(vbase, g.vs[2], kb, key_end, lane, w);
         if (VM == 1) {  // (never read; an array that is only half written stays in memory)
 #pragma unroll
             for (int ks = 0; ks < D / 16; ++ks) w[1][ks] = bf16x8{};
@@ -394,15 +399,20 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     };
     // norms of the wave's value rows of the step at kb, and where they go
     auto store_norms = [&](const bf16x8 (&w)[kMB][D / 16], int kb, int lane) {
-        float nu[kMB];
-        fragment_row_norms<D, VM>(w, nu);
-#pragma unroll
-        for (int mb = 0; mb < VM; ++mb) {
-            const int row = kb + mb * 32 + lane + (NT == 2 ? tile * 32 : 0);
-            if (lane >= 32 || row >= key_end) continue;
-            if (in_lds) sN[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
-            else nu_g[(int64_t)z * g.n + row] = nu[mb];
+        int row;
+        float nu;
+        if constexpr (NT == 2) {
+            float x[kMB];
+            fragment_row_norms<D, VM>(w, x);
+            nu = x[0];
+            row = lane < 32 ? kb + tile * 32 + lane : key_end;
+        } else {
+            nu = loaded_row_norm<D>(w, lane, row);
+            row += kb;
         }
+        if (row >= key_end) return;
+        if (in_lds) sN[row - max(0, key_begin - (g.pool - 1) / 2)] = nu;
+        else nu_g[(int64_t)z * g.n + row] = nu;
     };
     // One step of a sweep: blocks(a, kb, from, to) on the keys in `a` while `nx` receives those of kb_next
     // (unconditionally: past the range, clamped rows that are never used).  With VALUES the step's
@@ -596,9 +606,9 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             }
         };
         for (int i = 0; i < nsteps; i += 2) {
-            sweep_step(std::bool_constant<PRIOR>{}, blocks, a0, a1, kb_of(i), kb_of(i + 1), i == 0, i + 1 == nsteps);
+            sweep_step(std::bool_constant<PRIOR != 0>{}, blocks, a0, a1, kb_of(i), kb_of(i + 1), i == 0, i + 1 == nsteps);
             if (i + 1 >= nsteps) break;
-            sweep_step(std::bool_constant<PRIOR>{}, blocks, a1, a0, kb_of(i + 1), kb_of(i + 2), false, i + 2 == nsteps);
+            sweep_step(std::bool_constant<PRIOR != 0>{}, blocks, a1, a0, kb_of(i + 1), kb_of(i + 2), false, i + 2 == nsteps);
         }
         if (part == 0 && tid == 511) count.start(x, z);
         PriorHalo<D> halo;
@@ -656,10 +666,10 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
 }
 
 // ---------------------------------------------------------------- launch --
-template <int D, int NB, int NT, int STEPS, bool PRIOR>
+template <int D, int NB, int NT, int STEPS, int PRIOR>
 static hipError_t launch_hold(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
                               hipStream_t st) {
-    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR>;
+    using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
     const auto kernel = window_hold_kernel<D, NB, NT, STEPS, PRIOR>;
     if (H::bytes > 64 * 1024) {
         static DeviceOnce once;
@@ -673,7 +683,7 @@ static hipError_t launch_hold(const ScoreGeom &g, const PrefillPlan &pl, const E
     return hipGetLastError();
 }
 
-template <int D, int NB, int NT, bool PRIOR>
+template <int D, int NB, int NT, int PRIOR>
 static hipError_t launch_stream(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
                                 hipStream_t st) {
     using W = StreamSmem<D, NB, NT>;
@@ -689,7 +699,7 @@ static hipError_t launch_stream(const ScoreGeom &g, const PrefillPlan &pl, const
     return hipGetLastError();
 }
 
-template <int D, bool PRIOR>
+template <int D, int PRIOR>
 static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, float *scores,
                            hipStream_t st) {
     const int steps = pl.win_keys / kWgKeys;
@@ -698,7 +708,7 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
         return launch_hold<D, NB, NT, STEPS, PRIOR>(g, pl, x, w, scores, st);
 #define AHA_STREAM(NB, NT)                                            \
     if (!pl.win_hold && pl.win_nb == NB && pl.win_tiles == NT) \
-        return launch_stream<D, NB, NT, PRIOR>(g, pl, x, w, scores, st);
+        return launch_stream<D, NB, NT, NT == 2 && PRIOR ? kValuesCached : PRIOR>(g, pl, x, w, scores, st);
     AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(1, 1, 4) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
     AHA_HOLD(4, 1, 1) AHA_HOLD(3, 2, 1) AHA_HOLD(4, 2, 1)
     AHA_STREAM(4, 1) AHA_STREAM(6, 1) AHA_STREAM(8, 1) AHA_STREAM(6, 2) AHA_STREAM(8, 2)
@@ -711,9 +721,12 @@ hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *
                                float *scores, hipStream_t st) {
     char *w = (char *)ws;
     const Exchange x{(uint64_t *)(w + pl.off_wtags), (uint64_t *)(w + pl.off_wcounts), tag, looks};
-    if (g.d == 64)
-        return g.value_prior ? launch_d<64, true>(g, pl, x, w, scores, st) : launch_d<64, false>(g, pl, x, w, scores, st);
-    return g.value_prior ? launch_d<128, true>(g, pl, x, w, scores, st) : launch_d<128, false>(g, pl, x, w, scores, st);
+    auto launch = [&](auto prior) {
+        constexpr int PRIOR = decltype(prior)::value;
+        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, w, scores, st) : launch_d<128, PRIOR>(g, pl, x, w, scores, st);
+    };
+    if (!g.value_prior) return launch(std::integral_constant<int, kNoValues>{});
+    return g.v_once ? launch(std::integral_constant<int, kValuesOnce>{}) : launch(std::integral_constant<int, kValuesCached>{});
 }
 
 }  // namespace aha
