@@ -163,7 +163,8 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 //    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0.  In
 //    several rounds the exchange is waited for in each: a gain only with enough bytes behind it (64 rows,
 //    d = 128: 64 x 32480 296, 276; 8 x 38147 53.8, 56.7, not taken; 32 rows 32 x 28176 121, 130; 64 rows,
-//    d = 64 16 x 34742 51.2, 60.8; 128 rows 64 x 16164 161, 194).  Every range reads all ranges'
+//    d = 64 16 x 34742 51.2, 60.8; 128 rows 64 x 16164 161, 194) and while a round still holds several problems
+//    whole (held_in_rounds).  Every range reads all ranges'
 //    statistics: above 48 ranges of 96 and more rows that is too much (1 x 25019 x 123 22.9, 27.6).
 //  - 65 to 128 rows, d = 64, longer problems, swept twice: 6 x 46683 x 126 52.7, 36.3 (d = 128, bound by its
 //    bytes: 8 x 29221 x 128 48.3, 48.9, not taken).
@@ -171,6 +172,20 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 //    32.1, 19.1; 32 x 1502 x 256 30.0, 22.2), else swept twice (24 x 32929 x 160 236, 159; 6 x 29092 x
 //    256 66.7, 52.4; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
 //  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 57.8, 33.0; 8 x 9057 x 504 64.6, 56.0).
+//
+// Workgroups of which the chip holds two per CU at once.  A problem never has more ranges than that: those that
+// run would wait for those that cannot start (8 x 300000 x 64 rows, 586 ranges: 56 ms).
+constexpr int64_t kHeldAtOnce = 512;
+// Logits held in several rounds of the whole chip, 33 to 64 rows, d = 128: up to which number of ranges that is the
+// faster one.  The workgroups of a problem that begins at the end of a round wait for the next one, so the fewer
+// problems a round holds the more of it is spent waiting; two launches that leave their own last round
+// nearly empty are slow enough for it up to two problems a round.  us in two launches, in one (with a prior):
+// two even launches: 16 heads x 64 ranges 71.7, 66.5, x 96 101, 105, x 192 204, 258; 64 x 128 565, 562, x 192 867,
+// 1003; uneven: 24 x 64 130, 94, x 256 559, 471, x 320 713, 793.
+static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
+    const bool uneven = (int64_t)pl.Z * pl.nchunks > 512;
+    return pl.Z * parts >= 1024 && parts <= (uneven ? kHeldAtOnce / 2 : pl.Z >= 64 ? 128 : 64);
+}
 static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.win_nb = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -184,11 +199,11 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
         // the shortest ranges of which two per CU cover the problem, else the longest that can be held
         nb = blocks;
         int per = 1;
-        while (2 * per * nb <= 4 && pl.Z * ((steps + per - 1) / per) > 512) per *= 2;
+        while (2 * per * nb <= 4 && pl.Z * ((steps + per - 1) / per) > kHeldAtOnce) per *= 2;
         parts = (steps + per - 1) / per;
         keys = per * kP2Keys;
-        hold = pl.Z * parts <= 512 ? nb <= 2 || parts <= 48
-                                   : nb == 2 && p->head_dim == 128 && pl.Z * parts >= 1024;
+        hold = pl.Z * parts <= kHeldAtOnce ? nb <= 2 || parts <= 48
+                                           : nb == 2 && p->head_dim == 128 && held_in_rounds(pl, parts);
         if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < 800)) return;
         if (!hold) nb = 4;
     } else if (blocks <= 8) {
