@@ -356,9 +356,9 @@ int32_t aha_profile_events(void *const *events, int32_t count);
 
 /*
  * How patient the workgroups of a launch that exchange parts of a result inside it are, for the
- * calls of this thread: a workgroup that has looked `looks` times (about a microsecond each;
- * 4000 at first) without finding the others' parts does the missing ones itself.  Results do
- * not depend on it.
+ * calls of this thread: a workgroup that has looked `looks` times (1.4 us each; 4000 at first;
+ * fewer where forming a part takes much less) without finding the others' parts does missing
+ * ones itself.  Results do not depend on it.
  */
 int32_t aha_exchange_looks(int32_t looks);
 

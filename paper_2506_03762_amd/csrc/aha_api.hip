@@ -19,8 +19,8 @@ static hipError_t stage(int i, hipStream_t st) {
     return g_stage_on ? hipEventRecord(g_stage_ev[i], st) : hipSuccess;
 }
 
-// Looks at the other workgroups' announcements before a workgroup does missing parts itself: about a
-// microsecond each.
+// Looks at the other workgroups' announcements before a workgroup does missing parts itself, at most: 1.4 us each
+// (fewer: patience).
 constexpr int32_t kLooks = 4000;
 
 static int32_t fail(int32_t code, const char *fmt, ...) {
@@ -553,6 +553,24 @@ static uint64_t next_tag() {
 }
 static thread_local int32_t g_looks = kLooks;
 
+// Looks of a call of `workgroups` in all, of which the chip holds `resident` at once and each multiplies nb blocks of
+// 32 rows with each of `steps` key blocks per wave for its part.  All of them at once: a few times what a part takes (set-up
+// and exchange 15 us; a step its loads, 15 us with the whole chip loading, or its products, 2.5 us a
+// block).  In several rounds some are waited for until a round ends.
+static int patience(int64_t workgroups, int64_t resident, int64_t steps, int64_t nb) {
+    const int64_t looks = (30 + steps * (20 + 10 * nb)) * (workgroups <= resident ? 1 : 8);
+    return (int)(looks < g_looks ? looks : g_looks);
+}
+static int window_patience(const PrefillPlan &pl) {
+    const bool wide = !pl.win_hold && pl.win_tiles == 1;  // 512 keys to a step
+    return patience((int64_t)pl.Z * pl.win_parts, pl.win_hold && pl.win_tiles == 1 ? kHeldAtOnce : 256,
+                    pl.win_keys / (wide ? 512 : 256), pl.win_nb);
+}
+static int given_patience(const PrefillPlan &pl) {
+    const bool wide = pl.given_nb > 4;
+    return patience((int64_t)pl.Z * pl.given_parts, wide ? 256 : 512, pl.given_keys / (wide ? 512 : 256), pl.given_nb);
+}
+
 // Whether the one-launch scores read the value rows past the caches, given the bytes of K and V.  Kept
 // there they serve the gather of the retained rows, as long as the last-level cache (256 MB) has room for
 // them; read past it they are faster.  us, through the caches and past them: 32 heads x 4096 keys (67 MB), the
@@ -591,8 +609,8 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
     if (with_lse ? pl.given_nb > 0 : pl.win_nb && !rows) {
         if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), g_looks, lse, scores, st)
-                                      : launch_score_window(g, pl, workspace, next_tag(), g_looks, scores, st),
+            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), given_patience(pl), lse, scores, st)
+                                      : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),
                              "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;

@@ -16,8 +16,11 @@
 // bits are the tag's, and an arrival that finds other bits there sets them.
 //
 // Nobody depends on workgroups that may not be running: after `looks` looks at the announcements a
-// workgroup does the missing parts itself, one after the other, and announces them too (a part's
-// result is the same bits whoever forms it).
+// workgroup does missing parts itself and announces them too (a part's result is the same bits whoever
+// forms it).  The workgroups that have waited in vain share what is missing, so together they are done in
+// about the time that the missing ones would have taken, and `looks` is a few times that (patience in
+// aha_api.hip): beside other work that keeps half of a problem's workgroups out, waiting costs about
+// as much as the work.
 #pragma once
 
 #include "aha_dev.h"
@@ -49,21 +52,21 @@ __device__ __forceinline__ void announce(const Exchange &x, int z, int nparts, i
     if (tid == 0) put(x.tags + (int64_t)z * nparts + part, x.tag);
 }
 
-// The first part of problem z that has not been announced after x.looks looks, nparts if there is
-// none.  Called by one wave (more of them would get in the way of the data's loads); every lane gets
-// the result.
-__device__ __forceinline__ int first_missing(const Exchange &x, int z, int nparts, int lane) {
+// A part of problem z that has not been announced after x.looks looks, nparts if there is none.  Of several the one
+// nearest to the workgroup's own by exclusive or, so that each begins with another one.  Called by one wave of workgroup `own` (more of them would get in the way of the data's loads);
+// every lane gets the result.
+__device__ __forceinline__ int first_missing(const Exchange &x, int z, int nparts, int own, int lane) {
     const uint64_t *t = x.tags + (int64_t)z * nparts;
-    int missing = nparts;
+    int missing;
     for (int look = 0;; ++look) {
-        missing = nparts;
+        missing = INT32_MAX;
         for (int p = lane; p < nparts; p += kWave)
-            if (get(t + p) != x.tag) missing = min(missing, p);
-        if (__builtin_amdgcn_ballot_w64(missing < nparts) == 0) return nparts;
+            if (get(t + p) != x.tag) missing = min(missing, p ^ own);
+        if (__builtin_amdgcn_ballot_w64(missing != INT32_MAX) == 0) return nparts;
         if (look >= x.looks) break;
         __builtin_amdgcn_s_sleep(4);
     }
-    return reduce_lanes<1, 64>(missing, OpMinI{});
+    return reduce_lanes<1, 64>(missing, OpMinI{}) ^ own;
 }
 
 // Where all that a part leaves is one float, the announcement carries it: two words per part, the tag with
@@ -77,7 +80,7 @@ __device__ __forceinline__ void announce_value(const Exchange &x, int z, int npa
 // first_missing() of such parts; the largest value (none is below 0) if there is none missing.  Two parts per
 // lane at a time, and only by lanes that still miss one: waiting workgroups then stay out of the way
 // of those that announce.
-__device__ __forceinline__ int largest_value(const Exchange &x, int z, int nparts, int lane, float &largest) {
+__device__ __forceinline__ int largest_value(const Exchange &x, int z, int nparts, int own, int lane, float &largest) {
     const uint64_t *t = x.tags + (int64_t)z * nparts * 2;
     largest = 0.f;
     for (int p0 = 0; p0 < nparts; p0 += 2 * kWave) {
@@ -97,7 +100,8 @@ __device__ __forceinline__ int largest_value(const Exchange &x, int z, int npart
                 missing = there0 ? (there1 ? nparts : p1) : p0 + lane;
             }
             if (__builtin_amdgcn_ballot_w64(missing < nparts) == 0) break;
-            if (look >= x.looks) return reduce_lanes<1, 64>(missing, OpMinI{});
+            if (look >= x.looks)
+                return reduce_lanes<1, 64>(missing < nparts ? missing ^ own : INT32_MAX, OpMinI{}) ^ own;
             __builtin_amdgcn_s_sleep(4);
         }
     }

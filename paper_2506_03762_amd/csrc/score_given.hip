@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
 #pragma unroll
                 for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
                 announce_value(x, z, nparts, part, gm, tid);
-                const int missing = largest_value(x, z, nparts, lane, gm);
+                const int missing = largest_value(x, z, nparts, own, lane, gm);
                 if (lane == 0) {
                     *sMissing = missing;
                     sMax[0] = gm;

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         }
         announce(x, z, nparts, part, tid);
         if (wave == 0) {
-            const int missing = first_missing(x, z, nparts, lane);
+            const int missing = first_missing(x, z, nparts, own, lane);
             if (lane == 0) *sMissing = missing;
         }
         __syncthreads();
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
         if (PRIOR) pool_range(part, halo, tid);
         announce(x, z, nparts, part, tid);
         if (wave == 0) {
-            const int missing = first_missing(x, z, nparts, lane);
+            const int missing = first_missing(x, z, nparts, own, lane);
             if (lane == 0) *sMissing = missing;
         }
         __syncthreads();

@@ -103,3 +103,39 @@ def test_two_streams_at_once():
                 B.aha_prefill_scores(p, q, k, v, o, ws)
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[2]) and torch.equal(outs[1], outs[2])
+
+
+def test_beside_other_work():
+    """A problem with as many ranges as the chip holds workgroups, beside launches that fill the chip for
+    milliseconds: the ones of its workgroups that run must not keep the chip while they wait for the others."""
+    import torch
+    def problem(hkv, group, n, window):
+        q, k, v = (torch.randn((1, h, n, 128), device="cuda", dtype=torch.bfloat16) for h in (hkv * group, hkv, hkv))
+        p = B.Params(batch=1, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=128, seq_len=n, window=window, budget=512,
+                     recent=16).with_strides(q, k, v)
+        return p, q, k, v, torch.empty((1, hkv, n), dtype=torch.float32, device="cuda"), B.alloc_workspace(p)
+    other, one = problem(8, 4, 32768, 32768), problem(1, 1, 131072, 64)
+    jobs = [lambda: [B.aha_prefill_scores(*other) for _ in range(2)], lambda: [B.aha_prefill_scores(*one) for _ in range(40)]]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def span(which):
+        """ms until the given jobs, a stream each, are done"""
+        torch.cuda.synchronize()
+        begin, ends = torch.cuda.Event(enable_timing=True), []
+        begin.record(streams[which[0]])
+        for i in which:
+            with torch.cuda.stream(streams[i]):
+                jobs[i]()
+                ends.append(torch.cuda.Event(enable_timing=True))
+                ends[-1].record()
+        torch.cuda.synchronize()
+        return max(begin.elapsed_time(e) for e in ends)
+
+    span((0,)), span((1,))
+    want = one[4].clone()
+    alone = span((0,)) + span((1,))
+    together = min(span((0, 1)) for _ in range(3))
+    # one after the other they take 18 ms, together 19.5; 48 while a workgroup waited up to 5 ms at a time and all of
+    # them then formed the same parts
+    assert together < 1.8 * alone, (together, alone)
+    assert torch.equal(one[4], want)
