@@ -4,6 +4,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 
@@ -155,8 +156,8 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
     parts = (n + keys - 1) / keys;
 }
 
-// Windowed bf16 scores in one launch, in the same bytes as the two-launch layout.  Where, and which
-// kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
+// Windowed bf16 scores in one launch.  Its layout starts where the one of two launches does, but may be longer: a
+// call whose workspace does not hold it takes two launches.  Where, and which kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
 // heads, 400 to 65536 keys, d = 64 and 128): 1.30 times as fast as two launches on average, none
 // more than 3 % slower.  us in two launches, in one:
 //  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
@@ -229,14 +230,14 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.off_wmax = take(8 * sizeof(float) * (size_t)pl.Z * parts);  // per wave
     pl.off_wtags = take(sizeof(uint64_t) * (size_t)pl.Z * parts);
     pl.off_wcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
-    if (!hold) {
+    if (!hold && p->value_prior) {
         pl.off_wnu = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
         pl.off_wgamma = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
     }
-    if (off > pl.bytes) pl.bytes = off;
+    pl.win_bytes = off;
 }
 
-// Windowed bf16 scores from given normalisers in one launch (score_given.hip), in the same bytes: one query
+// Windowed bf16 scores from given normalisers in one launch (score_given.hip), likewise: one query
 // tile, and a prior whose pooling halo a workgroup holds.  Against two launches 1.15 times as fast on average
 // over 110 shapes (1 to 256 rows, 2 to 128 KV heads, 250 to 61000 keys), us in two, in one: 8 heads x 32768 keys x
 // 256 rows 46.3, 39.7; 128 x 16384 x 64 198, 172; 32 x 4096 x 64 19.7, 19.1; 2 x 512 x 32 8.3, 7.2.  Not taken
@@ -263,7 +264,7 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
         pl.off_gtags = take(2 * sizeof(uint64_t) * (size_t)pl.Z * parts);
         pl.off_gcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
     }
-    if (off > pl.bytes) pl.bytes = off;
+    pl.given_bytes = off;
 }
 
 // Workspace layout of aha_prefill_scores.
@@ -533,8 +534,8 @@ int32_t aha_workspace_bytes(const aha_params *p, size_t *out_bytes) {
     }
     int32_t rc = check_prefill(p, false);
     if (rc) return rc;
-    const size_t a = plan_prefill(p).bytes, d = plan_decode(p).bytes, t = topk_ws_bytes(p);
-    *out_bytes = a > d ? (a > t ? a : t) : (d > t ? d : t);
+    const PrefillPlan pl = plan_prefill(p);
+    *out_bytes = std::max({pl.bytes, pl.win_bytes, pl.given_bytes, plan_decode(p).bytes, topk_ws_bytes(p)});
     return AHA_OK;
 }
 
@@ -607,7 +608,8 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     g.v_once = values_once((int64_t)4 * pl.Z * g.n * g.d, with_lse);
     hipStream_t st = (hipStream_t)stream;
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
-    if (with_lse ? pl.given_nb > 0 : pl.win_nb && !rows) {
+    if (with_lse ? pl.given_nb && workspace_bytes >= pl.given_bytes
+                 : pl.win_nb && !rows && workspace_bytes >= pl.win_bytes) {
         if ((rc = hip_result(stage(1, st), "stage event")) ||
             (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), given_patience(pl), lse, scores, st)
                                       : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),

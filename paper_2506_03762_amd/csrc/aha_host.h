@@ -62,12 +62,12 @@ struct PrefillPlan {
     // prior maxima, announcements and their counts, the value norms and the prior live
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold;
-    size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma;
+    size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma, win_bytes;
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
-    size_t off_gtags, off_gcounts;
+    size_t off_gtags, off_gcounts, given_bytes;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
-    size_t bytes;
+    size_t bytes;  // of the layout of two launches
 };
 
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup

@@ -49,3 +49,40 @@ def _one_launch(name, p, size=None):
 def test_ranges_of_a_problem_fit_the_chip(z, n, one):
     for group, window in ((1, 64), (2, 17), (3, 20)):
         assert _one_launch("aha_prefill_scores", _params(z, group, window, n)) == one
+
+
+# KV heads, group, window, keys, d, and a workspace that holds two launches; one launch needs up to twice as much
+SMALLER = [(64, 7, 32, 3170, 64, 1863424), (64, 5, 77, 7257, 64, 3962368), (64, 7, 64, 6233, 128, 3699200),
+           (128, 3, 128, 77252, 64, 41804800), (89, 4, 100, 14177, 128, 7254272)]
+
+
+@pytest.mark.parametrize("z,group,window,n,d,size", SMALLER)
+def test_workspace_of_two_launches_is_served(z, group, window, n, d, size):
+    p = _params(z, group, window, n, d)
+    assert B.workspace_bytes(p) > size
+    assert _one_launch("aha_prefill_scores", p)
+    for name in ("aha_prefill_scores", "aha_prefill_scores_lse"):
+        _one_launch(name, p, size)
+    assert not _one_launch("aha_prefill_scores", p, size)
+    assert _call("aha_prefill_row_stats", p, size) == B.AHA_ERR_HIP
+    assert _call("aha_prefill_scores_rows", p, size) != B.AHA_ERR_WORKSPACE
+    for name in ("aha_prefill_scores", "aha_prefill_scores_lse", "aha_prefill_row_stats"):
+        assert _call(name, p, size // 4) == B.AHA_ERR_WORKSPACE
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("z,group,window,n,d,size", SMALLER[:3])
+def test_results_in_it(z, group, window, n, d, size):
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    q, k, v = (torch.randn((1, h, n, d), generator=gen, device="cuda").to(torch.bfloat16) for h in (z * group, z, z))
+    p = _params(z, group, window, n, d).with_strides(q, k, v)
+    got = []
+    for have in (B.workspace_bytes(p), size):
+        scores = torch.empty((1, z, n), dtype=torch.float32, device="cuda")
+        B.aha_prefill_scores(p, q, k, v, scores, torch.full((have,), 0xA5, dtype=torch.uint8, device="cuda"))
+        got.append(scores.double())
+    # fp32 arithmetic on exact products: logits of a few tens carry 1e-5 absolute, which is the relative error of their
+    # exponentials, on either side
+    assert ((got[0] - got[1]).abs() <= 4e-4 * got[0] + 2e-7 * got[0].mean()).all()
