@@ -399,7 +399,9 @@ static WindowAttnPlan plan_window_attn(const aha_params *p) {
 // Wider groups always split (bf16, d = 128, G = 8: 8 x 100 17.8 and 11.9, 112 x 257 18.9 and 14.1).
 // Exactly 128 heads in groups of four: 128 x 257 13.0 and 13.1, d = 64 x 801 14.4 and 14.4, d = 128 x 801
 // 20.9 and 19.1.
-static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
+// `room`: the workspace holds the split.  Without it the steps of four query heads that were served in one launch and
+// without a workspace while the split was the slower one (112 x 1000 25.0 and 26.0 us) still are.
+static bool decode_one_launch(int dtype, int Z, int G, int d, int live, bool room) {
     if (G > 4) return false;
     const int ways = (256 + Z - 1) / Z;  // workgroups per head if split
     constexpr int kAny = INT32_MAX;
@@ -415,7 +417,8 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live) {
     if (Z >= kDecodeSplitHeads) return G < 4 || (int64_t)live * (2 * d * esize(dtype) + 64) <= 250 * 1000;
     const int row = ways >= 7 ? 0 : ways >= 5 ? 1 : ways == 4 ? 2 : 3;
     const int64_t size = (int64_t)live * (2 * d * esize(dtype) + 64);
-    return size <= (int64_t)limit[dtype == AHA_BF16][row][G - 1] * 1000;
+    const int most = !room && dtype == AHA_BF16 && G == 4 && row == 3 ? 580 : limit[dtype == AHA_BF16][row][G - 1];
+    return size <= (int64_t)most * 1000;
 }
 
 // Decode: split a head's slots over workgroups when there are too few heads to fill the GPU.
@@ -470,6 +473,7 @@ static DecodePlan plan_decode(const aha_params *p, size_t limit = SIZE_MAX) {
     };
     pl.static_bytes = layout(2);
     pl.bytes = layout(kPartStats);
+    bool room = pl.bytes <= limit;
     if (p->dtype == AHA_BF16 && G >= kDecodeSplitMfmaGroup && pl.fits &&
         (Z < kDecodeSplitHeads ? pl.nsplit > 1 : Z == kDecodeSplitHeads && one_fits)) {
         auto cost = [&](int sps, int ns) {
@@ -487,9 +491,10 @@ static DecodePlan plan_decode(const aha_params *p, size_t limit = SIZE_MAX) {
             }
         }
         pl.bytes = layout(kPartStats);
-        if (pl.bytes > limit) pl = former;
+        room = pl.bytes <= limit;
+        if (!room) pl = former;
     }
-    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live)))
+    if (pl.nsplit > 1 && !(one_fits && pl.fits && decode_one_launch(p->dtype, Z, G, p->head_dim, live, room)))
         return pl;
     if (pl.nsplit <= 1 && !one_fits) pl.fits = false;
     pl.nsplit = 1;
@@ -777,7 +782,9 @@ static int32_t decode_step_check(const aha_params *p, const void *q_new, const v
     const int G = p->n_q_heads / p->n_kv_heads;
     if (G > 8)
         return fail(AHA_ERR_UNSUPPORTED, "decode is built for query groups of up to 8 heads, not %d", G);
-    *plan = plan_decode(p, scratch_limit ? kScratchBytes + kScratchMargin : workspace ? workspace_bytes : 0);
+    // (a workspace that cannot be used counts as none: steps that need none do not look at it)
+    const bool usable = workspace && (uintptr_t)workspace % 256 == 0;
+    *plan = plan_decode(p, scratch_limit ? kScratchBytes + kScratchMargin : usable ? workspace_bytes : 0);
     if (!plan->fits)
         return fail(AHA_ERR_UNSUPPORTED,
                     "decode keeps group * (budget + 1) dots in LDS; %d * %d does not fit (%d splits)",
