@@ -421,6 +421,14 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live, bool roo
     return size <= (int64_t)most * 1000;
 }
 
+// The most heads whose slots the matrix-core split stage divides.  Four or six splits of 128 heads fill the three
+// slots of every CU; five of 129 do not, while one workgroup per head keeps more than half of the chip busy.
+// With d = 128 and six and more query heads the split is the faster one all the same up to 144 heads (100 to
+// 3100 slots: 1.11 times as fast on average, 3 % slower at worst).  us in one launch, split, d = 128: G = 8, 144
+// heads x 300 slots 19.0, 16.4, x 801 24.8, 25.1, x 1200 32.9, 30.0, 160 x 801 25.3, 26.0, 192 x 1537 41.1, 43.6; G = 4, 128 x 801 22.1, 20.8, 129 x 801
+// 22.4, 23.9; d = 64, G = 5, 128 x 801 14.7, 14.8, 129 x 801 15.1, 16.5.
+static int most_split_heads(int G, int d) { return d == 128 && G >= 6 ? 144 : kDecodeSplitHeads; }
+
 // Decode: split a head's slots over workgroups when there are too few heads to fill the GPU.
 // A split workgroup keeps group * (slots of its range) dots and 4 * group * head_dim partial
 // outputs in LDS; the number of splits is raised until that fits kDecodeSplitLds (the limit
@@ -428,8 +436,8 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live, bool roo
 // splits were enough.
 //
 // The matrix-core split stage (bf16, G >= 4) is resident three times per CU, so more splits than
-// one workgroup per CU may pay, also for exactly 128 heads; what matters is that the chip is evenly
-// filled.  Its time goes with the slots per CU (64 of them, d = 128, weigh as much as a wave's block of 32
+// one workgroup per CU may pay, also for 128 heads and some more (most_split_heads); what matters is that the chip is
+// evenly filled.  Its time goes with the slots per CU (64 of them, d = 128, weigh as much as a wave's block of 32
 // slots) and the blocks of a wave one after the other; a further split costs the merge a twelfth of a
 // block.  us of the step at the former count and at this rule's, d = 128, G = 8: 96 heads x 1537 slots 32.7
 // (3 splits), 26.3 (5); 48 x 3073 33.7, 27.5; 128 x 1537 38.3 (one launch), 33.0 (4); over 156 shapes
@@ -475,7 +483,7 @@ static DecodePlan plan_decode(const aha_params *p, size_t limit = SIZE_MAX) {
     pl.bytes = layout(kPartStats);
     bool room = pl.bytes <= limit;
     if (p->dtype == AHA_BF16 && G >= kDecodeSplitMfmaGroup && pl.fits &&
-        (Z < kDecodeSplitHeads ? pl.nsplit > 1 : Z == kDecodeSplitHeads && one_fits)) {
+        (Z < kDecodeSplitHeads ? pl.nsplit > 1 : Z <= most_split_heads(G, p->head_dim) && one_fits)) {
         auto cost = [&](int sps, int ns) {
             const int64_t per_cu = ((int64_t)Z * ns + 255) / 256;
             return per_cu * sps * p->head_dim / (128. * 64.) + ((sps + 31) / 32 + 3) / 4 + 0.08 * ns;

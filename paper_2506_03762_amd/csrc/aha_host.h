@@ -151,7 +151,7 @@ struct DecodeGeom {
 // With few (batch, KV head) problems the slots of a head are split over nsplit workgroups
 // (two launches, partials in the workspace); otherwise one workgroup handles a head.
 constexpr int kDecodeSplitHeads = 128;  // a head's slots may be split with fewer (batch, KV head) problems (on the
-                                        // matrix core also with exactly as many)
+                                        // matrix core also with as many or a few more)
 constexpr int kMaxDecodeSplit = 64;  // most workgroups a head's slots are split over
 // a split's partial outputs of a head: d channels, then maximum, output sum, score sum, unused
 constexpr int kPartStats = 4;

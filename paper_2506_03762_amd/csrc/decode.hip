@@ -9,8 +9,8 @@
 // bf16: with four or more query heads per KV head the values, with five or more
 // the dots of whole 32-slot blocks as well, go through the matrix core.
 //
-// Fewer than 128 heads (bf16 groups of four and more: up to 128): their slots are split over workgroups unless one per head is
-// faster (decode_one_launch).  decode_split_kernel (vector ALU) or decode_split_mfma_kernel
+// Fewer than 128 heads (bf16 groups of four and more: up to 128 or 144): their slots are split over workgroups
+// unless one per head is faster (decode_one_launch, most_split_heads).  decode_split_kernel (vector ALU) or decode_split_mfma_kernel
 // (bf16, four or more query heads per KV head) leaves the raw dots and each range's
 // partial output and softmax sums in the workspace; decode_merge_kernel merges the
 // outputs and updates the running scores.

@@ -77,6 +77,7 @@ def test_results_do_not_depend_on_it(z, group, d, live):
 NO_ROOM = [
     # heads, group, d, live slots: a head may keep one workgroup, whatever is passed as workspace
     (96, 4, 128, 801), (87, 4, 128, 899), (114, 4, 64, 1053), (127, 4, 128, 600), (128, 4, 128, 801), (128, 8, 64, 1111),
+    (129, 8, 128, 801), (144, 6, 128, 97), (137, 7, 128, 1537),
 ]
 
 
@@ -123,3 +124,14 @@ def test_results_without_one(z, group, d, live):
     np.testing.assert_allclose(a[1], b[1], rtol=1e-5, atol=1e-7)
     for x, y in zip(a[2:], b[2:]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("z,group,d,live,split", [
+    # us in one launch, split
+    (129, 4, 128, 801, False),    # 22.4, 23.9
+    (129, 5, 64, 801, False),     # 15.1, 16.5
+    (129, 8, 128, 801, True), (144, 8, 128, 300, True), (136, 6, 128, 2500, True),
+    (145, 8, 128, 300, False), (192, 8, 128, 1537, False),   # 41.1, 43.6
+])
+def test_most_heads_that_are_split(z, group, d, live, split):
+    assert (B.workspace_bytes(_params(z, group, d, live)) > 0) == split
