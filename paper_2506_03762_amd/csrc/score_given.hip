@@ -22,7 +22,7 @@ namespace aha {
 template <int D, int NB, bool PRIOR>
 struct GivenSmem {
     static constexpr int KEYS = PRIOR ? given_keys(D, NB) : 0;
-    static constexpr size_t off_misc = (TileSmem<D, NB>::bytes + 15) / 16 * 16;
+    static constexpr size_t off_misc = TileSmem<D, NB>::stride;
     static constexpr size_t off_nu = off_misc + 16 * sizeof(float);
     static constexpr size_t off_gam = off_nu + (KEYS + kPriorMaxHalo) * sizeof(float);
     static constexpr size_t off_sum = off_gam + KEYS * sizeof(float);

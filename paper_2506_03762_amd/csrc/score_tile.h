@@ -21,6 +21,7 @@ struct TileSmem {
     static constexpr size_t q_bytes = (size_t)ROWS * LD * 2;
     // query tile, then per row: scale, position, log-sum-exp; then per block: max / min position
     static constexpr size_t bytes = q_bytes + ROWS * 4 * 3 + NB * 4 * 2;
+    static constexpr size_t stride = (bytes + 15) / 16 * 16;  // between tiles: their rows are 16-byte aligned too
 };
 
 // Query tile -> LDS: rows rho0 .. rho0+ROWS of the KV head's flattened query

@@ -30,12 +30,13 @@ namespace aha {
 template <int D, int NB, int NT, int KEYS, bool PRIOR>
 struct HoldSmem {
     static constexpr int TROWS = NB * 32, ROWS = NT * TROWS;
-    static constexpr size_t off_red = NT * TileSmem<D, NB>::bytes;  // float2 [wave][row of its tile], then column sums
+    static constexpr size_t off_red = NT * TileSmem<D, NB>::stride;  // float2 [wave][row of its tile], then column sums
     static constexpr size_t off_nu = off_red + 4 * ROWS * sizeof(float2);
     static constexpr size_t off_gam = off_nu + (PRIOR ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
     static constexpr size_t off_misc = off_gam + (PRIOR ? KEYS * sizeof(float) : 0);
     static constexpr size_t bytes = off_misc + 12 * sizeof(float);
     static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
+    static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
 };
 
 // The pair held by lane ^ 32.
@@ -119,8 +120,8 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wave = uniform((int)threadIdx.x >> 6), tile = NT == 2 ? wave >> 2 : 0, kw = wave & 3;
-    __bf16 *sQ = (__bf16 *)(smem + tile * S::bytes);
-    float *sLam = (float *)(smem + tile * S::bytes + S::q_bytes);
+    __bf16 *sQ = (__bf16 *)(smem + tile * S::stride);
+    float *sLam = (float *)(smem + tile * S::stride + S::q_bytes);
     int *sPos = (int *)(sLam + S::ROWS);
     float *sL = (float *)(sPos + S::ROWS);
     int *sBlk = (int *)(sL + S::ROWS);
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 #pragma unroll
         for (int wv = 0; wv < 4; ++wv) merge_stats(M, sum, src[wv * H::TROWS].x, src[wv * H::TROWS].y);
         // (rows past the last one add nothing)
-        ((float *)(smem + t * S::bytes + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
+        ((float *)(smem + t * S::stride + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
     }
     __syncthreads();
     float ginv = 1.f, L[NB];
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 template <int D, int NB, int NT>
 struct StreamSmem {
     static constexpr int TROWS = NB * 32, ROWS = NT * TROWS, KW = 8 / NT, STEP = KW * kWaveKeys;
-    static constexpr size_t off_red = NT * TileSmem<D, NB>::bytes;  // float2 [8][TROWS], then norms, then column sums
+    static constexpr size_t off_red = NT * TileSmem<D, NB>::stride;  // float2 [8][TROWS], then norms, then column sums
     static constexpr size_t red_bytes = 8 * TROWS * sizeof(float2) > (kPriorPiece + kPriorMaxHalo) * sizeof(float)
                                             ? 8 * TROWS * sizeof(float2)
                                             : (kPriorPiece + kPriorMaxHalo) * sizeof(float);
@@ -333,6 +334,7 @@ struct StreamSmem {
     static constexpr size_t off_gam = off_nu + (KEYS ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
     static constexpr size_t bytes = off_gam + KEYS * sizeof(float);
     static_assert(2 * 4 * kWaveKeys * sizeof(float) <= red_bytes, "column sums of two steps");
+    static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
     static_assert(bytes <= 160 * 1024, "LDS of a CU");
 };
 
@@ -347,8 +349,8 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wave = uniform((int)threadIdx.x >> 6), half = wave >> 2;
     const int tile = NT == 2 ? half : 0, kw = NT == 2 ? wave & 3 : wave;
-    __bf16 *sQ = (__bf16 *)(smem + tile * S::bytes);
-    float *sLam = (float *)(smem + tile * S::bytes + S::q_bytes);
+    __bf16 *sQ = (__bf16 *)(smem + tile * S::stride);
+    float *sLam = (float *)(smem + tile * S::stride + S::q_bytes);
     int *sPos = (int *)(sLam + S::ROWS);
     float *sL = (float *)(sPos + S::ROWS);
     int *sBlk = (int *)(sL + S::ROWS);
@@ -658,7 +660,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
 #pragma unroll
         for (int wv = 0; wv < W::KW; ++wv) merge_stats(M, sum, src[wv * W::TROWS].x, src[wv * W::TROWS].y);
         // (rows past the last one add nothing)
-        ((float *)(smem + t * S::bytes + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
+        ((float *)(smem + t * S::stride + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
     }
     __syncthreads();
     second_sweep(PRIOR ? prior_inverse(largest()) : 1.f);
