@@ -90,3 +90,36 @@ def test_graph_replays(shape):
         torch.cuda.synchronize()
         assert torch.equal(scores, want[i])
         B.aha_prefill_scores_lse(p, *sets[1], lse, scores, ws)  # other work of the same workspace in between
+
+
+def test_time_per_key():
+    """Ranges that leave a round of the chip with parts of problems make a longer prompt slower per key."""
+    import torch
+    hkv, group, window, longest, d = 8, 4, 64, 1 << 20, 128
+    q = torch.randn((1, hkv * group, window, d), device="cuda", dtype=torch.bfloat16)
+    k, v = (torch.randn((1, hkv, longest, d), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    lse = torch.full((1, hkv * group, window), 10.0, device="cuda")
+    scores = torch.empty((1, hkv, longest), dtype=torch.float32, device="cuda")
+
+    class LastRows:  # (only the last rows are read)
+        def __init__(self, n):
+            self.n = n
+
+        def data_ptr(self):
+            return q.data_ptr() - (self.n - window) * d * 2
+
+    def per_key(n):
+        p = B.Params(batch=1, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, seq_len=n, window=window, budget=64, recent=8,
+                     q_stride=(0, window * d, d), k_stride=(0, longest * d, d), v_stride=(0, longest * d, d))
+        ws, times = B.alloc_workspace(p), []
+        for _ in range(12):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            B.aha_prefill_scores_lse(p, LastRows(n), k, v, lse, scores, ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[6] / n
+
+    # 0.87 ns per key either way; 1.24 for the longer one in 158 ranges to a problem
+    assert per_key(longest) < 1.12 * per_key(700000)
