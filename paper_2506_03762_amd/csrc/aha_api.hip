@@ -247,8 +247,9 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
 // over 110 shapes (1 to 256 rows, 2 to 128 KV heads, 250 to 61000 keys), us in two, in one: 8 heads x 32768 keys x
 // 256 rows 46.3, 39.7; 128 x 16384 x 64 198, 172; 32 x 4096 x 64 19.7, 19.1; 2 x 512 x 32 8.3, 7.2.  Not taken
 // where it was the slower one: few heads in many ranges of a step or two, where the exchange is most of the time (8 x
-// 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), and without a prior, of which a
-// second launch would have to be saved, many steps of the larger tiles (32 x 31856 x 256 79.3, 82.3).
+// 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), eight blocks of rows in steps of 512 keys
+// for at most half of the CUs (8 x 3600 x 256 18.5, 19.9, 4 x 12000, d = 64 13.7, 15.4; not 8 x 12000 23.9, 22.3), and without a prior,
+// of which a second launch would have to be saved, many steps of the larger tiles (32 x 31856 x 256 79.3, 82.3).
 static void plan_given(const aha_params *p, PrefillPlan &pl) {
     pl.given_nb = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -260,6 +261,7 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
                 p->value_prior, parts, keys);
     if (pl.Z * parts > 1 << 30 || parts > resident) return;  // (all of a problem's workgroups have to run at once)
     if (p->value_prior ? nb <= 4 && pl.Z <= 8 && parts > (nb <= 2 ? 24 : 50) : nb > 4 && (int64_t)pl.Z * p->seq_len > 1 << 19) return;
+    if (p->value_prior && blocks == 8 && pl.Z * (((int64_t)p->seq_len + 511) / 512) <= 128) return;
     pl.given_nb = nb;
     pl.given_parts = (int)parts;
     pl.given_keys = (int)keys;

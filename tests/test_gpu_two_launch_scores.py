@@ -61,3 +61,24 @@ def test_ranges_longer_than_the_lds_keeps(shape):
     finally:
         B.load().aha_exchange_looks(4000)
     assert np.array_equal(alone.scores, gpu.scores)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1, 12, 8, 32, 6001, 128), (2, 9, 4, 57, 4100, 64), (1, 33, 8, 32, 1800, 128)])
+def test_given_normalisers_of_a_full_tile(shape):
+    """225 to 256 rows in one launch, several steps and ranges."""
+    import torch
+    w, opts, inputs = _case(shape)
+    p = H.gpu_params(w, opts)
+    q, k, v = (H.to_device(a, w.dtype) for a in inputs)
+    lse = torch.empty((w.batch, w.n_q_heads, w.window), dtype=torch.float32, device="cuda")
+    B.aha_prefill_row_stats(p.with_strides(q, k, v), q, k, lse, None, B.alloc_workspace(p))
+    got = H.run_scores_from_lse_gpu(w, opts, inputs, lse.cpu().numpy())
+    ref = H.run_prefill_oracle(w, opts, inputs).scores
+    np.testing.assert_allclose(got, ref, rtol=2e-4, atol=2e-4 * 1e-3 * ref.mean())
+    assert B.load().aha_exchange_looks(0) == B.AHA_OK
+    try:
+        alone = H.run_scores_from_lse_gpu(w, opts, inputs, lse.cpu().numpy())
+    finally:
+        B.load().aha_exchange_looks(4000)
+    assert np.array_equal(alone, got)

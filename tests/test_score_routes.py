@@ -51,6 +51,21 @@ def test_ranges_of_a_problem_fit_the_chip(z, n, one):
         assert _one_launch("aha_prefill_scores", _params(z, group, window, n)) == one
 
 
+@pytest.mark.parametrize("z,n,d,prior,one", [
+    # 225 to 256 rows from given normalisers (us: two launches, one)
+    (8, 3600, 128, 1, False),     # 18.5, 19.9
+    (4, 12000, 64, 1, False),     # 13.7, 15.4
+    (16, 3600, 128, 1, False),    # 19.2, 20.3
+    (8, 12000, 128, 1, True),     # 23.9, 22.3
+    (32, 2300, 128, 1, True),     # 25.7, 19.6
+    (8, 3600, 128, 0, True),
+])
+def test_few_steps_of_large_tiles(z, n, d, prior, one):
+    for window in (58, 64):
+        assert _one_launch("aha_prefill_scores_lse", _params(z, 4, window, n, d, value_prior=prior)) == one
+    assert _one_launch("aha_prefill_scores_lse", _params(z, 4, 56, n, d, value_prior=prior))
+
+
 # KV heads, group, window, keys, d, and a workspace that holds two launches; one launch needs up to twice as much
 SMALLER = [(64, 7, 32, 3170, 64, 1863424), (64, 5, 77, 7257, 64, 3962368), (64, 7, 64, 6233, 128, 3699200),
            (128, 3, 128, 77252, 64, 41804800), (89, 4, 100, 14177, 128, 7254272)]
