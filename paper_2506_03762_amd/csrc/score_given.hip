@@ -273,8 +273,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
 
 // ---------------------------------------------------------------- launch --
 template <int D, int NB, int WAVES, int PRIOR>
-static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, const float *lse,
-                           float *scores, hipStream_t st) {
+static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, const float *lse, float *scores,
+                           hipStream_t st) {
     using W = GivenSmem<D, NB, PRIOR != 0>;
     const auto kernel = window_given_kernel<D, NB, WAVES, PRIOR>;
     if (W::bytes > 64 * 1024) {
@@ -290,14 +290,14 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 }
 
 template <int D, int PRIOR>
-static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, char *w, const float *lse,
-                           float *scores, hipStream_t st) {
+static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, const float *lse, float *scores,
+                           hipStream_t st) {
     switch (pl.given_nb) {
-        case 1: return launch_t<D, 1, 4, PRIOR>(g, pl, x, w, lse, scores, st);
-        case 2: return launch_t<D, 2, 4, PRIOR>(g, pl, x, w, lse, scores, st);
-        case 4: return launch_t<D, 4, 4, PRIOR>(g, pl, x, w, lse, scores, st);
-        case 6: return launch_t<D, 6, 8, PRIOR>(g, pl, x, w, lse, scores, st);
-        case 8: return launch_t<D, 8, 8, PRIOR>(g, pl, x, w, lse, scores, st);
+        case 1: return launch_t<D, 1, 4, PRIOR>(g, pl, x, lse, scores, st);
+        case 2: return launch_t<D, 2, 4, PRIOR>(g, pl, x, lse, scores, st);
+        case 4: return launch_t<D, 4, 4, PRIOR>(g, pl, x, lse, scores, st);
+        case 6: return launch_t<D, 6, 8, PRIOR>(g, pl, x, lse, scores, st);
+        case 8: return launch_t<D, 8, 8, PRIOR>(g, pl, x, lse, scores, st);
     }
     return hipErrorInvalidValue;
 }
@@ -308,8 +308,8 @@ hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *w
     const Exchange x{(uint64_t *)(w + pl.off_gtags), (uint64_t *)(w + pl.off_gcounts), tag, looks};
     auto launch = [&](auto prior) {
         constexpr int PRIOR = decltype(prior)::value;
-        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, w, lse, scores, st)
-                         : launch_d<128, PRIOR>(g, pl, x, w, lse, scores, st);
+        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, lse, scores, st)
+                         : launch_d<128, PRIOR>(g, pl, x, lse, scores, st);
     };
     if (!g.value_prior) return launch(std::integral_constant<int, kNoValues>{});
     return g.v_once ? launch(std::integral_constant<int, kValuesOnce>{}) : launch(std::integral_constant<int, kValuesCached>{});
