@@ -229,7 +229,8 @@ def main():
                       "GBps": alg[name] / (kt[name] * 1e-3) / 1e9 if kt[name] > 1e-6 else None}
                for name in kt}
     score_flops_pass = 2.0 * d * b * hq * (w.window * n - w.window * (w.window - 1) / 2)
-    # (the kernel of this shape sweeps its keys twice and forms the products in both)
+    # the kernel of this shape sweeps its keys twice and forms the products in both
+    kernels["scores"]["products_formed"] = 2
     kernels["scores"]["TFLOPs"] = 2 * score_flops_pass / (kt["scores"] * 1e-3) / 1e12
     dom = max(("scores", "topk", "compact"), key=lambda nm: kt[nm])
     # HBM bytes per launch from the committed rocprofv3 counter summary of this workload
@@ -251,7 +252,7 @@ def main():
     roofline_stage = {"stage": "prefill_scores (all its launches)", "bound": "hbm",
                       "achieved": stage_bytes / (stage_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                       "unit": "GB/s", "frac": stage_bytes / (stage_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                      "mfma_TFLOPs": 2 * score_flops_pass / (stage_ms * 1e-3) / 1e12}
+                      "products_formed": 2, "mfma_TFLOPs": 2 * score_flops_pass / (stage_ms * 1e-3) / 1e12}
 
     result = {
         "metric": "prefill eviction us/layer @32K ctx (scores + top-k + compaction)",
