@@ -141,8 +141,8 @@ int32_t aha_workspace_bytes(const aha_params *p, size_t *out_bytes);
  *  k, v    [batch, n_kv_heads, seq_len, head_dim] by k_stride / v_stride.
  *  scores  out, fp32, dense [batch, n_kv_heads, seq_len].
  * The probability matrix is never written to memory: one pass over the keys
- * finds each row's maximum and log-sum-exp, a second pass recomputes the
- * logits and accumulates the column sums.
+ * finds each row's maximum and log-sum-exp, a second pass accumulates the column
+ * sums from logits that are formed again or, where they fit, kept in registers.
  */
 int32_t aha_prefill_scores(const aha_params *p, const void *q, const void *k,
                            const void *v, float *scores, void *workspace,
@@ -165,7 +165,7 @@ int32_t aha_prefill_scores(const aha_params *p, const void *q, const void *k,
  * The probabilities are formed as exp(s_i * Q_i . K_j - lse_i): a normaliser
  * that does not belong to the row scales that row's contribution and is not
  * detected.  The stage events of aha_profile_events are recorded as for
- * aha_prefill_scores (events[1] and [2] then bracket nothing).
+ * aha_prefill_scores (in two launches, events[1] and [2] bracket nothing).
  */
 int32_t aha_prefill_scores_lse(const aha_params *p, const void *q, const void *k,
                                const void *v, const float *lse, float *scores,
@@ -298,8 +298,9 @@ int32_t aha_compact_kv(const aha_params *p, const void *k, const void *v,
  * Exactly budget + 1 slots must be live on entry (budget occupied + the free
  * one), which aha_compact_kv and every previous step guarantee.
  * The dots of a head's live slots are kept on chip.  With 128 and more
- * (batch, KV head) problems one workgroup holds a head: about 8 * group *
- * (budget + 1) bytes, at most 150 KiB.  With fewer the shape has to fit a split
+ * (batch, KV head) problems a head has to fit one workgroup, about 8 * group *
+ * (budget + 1) bytes, at most 150 KiB (up to 144 such problems are split all the
+ * same where that is faster and the workspace holds it).  With fewer the shape has to fit a split
  * of the slots over up to 64 workgroups (group * slots-per-split * 4 + 16 *
  * group * head_dim bytes each, at most 64 KiB; no more than 64 slots: one
  * workgroup as above), whether it is then split or, where that is faster, served
@@ -321,7 +322,8 @@ int32_t aha_decode_step(const aha_params *p, const void *q_new, const void *k_ne
  * over workgroups and without the value prior, counts up to 4 MiB: 4 * heads *
  * group * (budget + 1) bytes of dots and 4 * heads * splits * group *
  * (head_dim + 2) of partial outputs, each rounded up to 256 (heads = batch *
- * n_kv_heads < 128, splits as in aha_decode_step; nothing for 128 and more); the
+ * n_kv_heads < 128, splits counted as the fewest that make 256 workgroups, with at
+ * least 64 slots each; nothing for 128 and more); the
  * prior adds 4 * heads * (budget + 2).  Other shapes return AHA_ERR_UNSUPPORTED
  * before anything is launched, whichever way the step would be served and
  * whatever aha_workspace_bytes says - e.g. 8 KV heads x 4 query heads x budget

@@ -163,8 +163,8 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 
 // Windowed bf16 scores in one launch.  Its layout starts where the one of two launches does, but may be longer: a
 // call whose workspace does not hold it takes two launches.  Where, and which kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
-// heads, 400 to 65536 keys, d = 64 and 128): 1.30 times as fast as two launches on average, none
-// more than 3 % slower.  us in two launches, in one:
+// heads, 400 to 65536 keys, d = 64 and 128), 1.30 times as fast as two launches on average.  us in two
+// launches, in one:
 //  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
 //    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0.  In
 //    several rounds the exchange is waited for in each: a gain only with enough bytes behind it (64 rows,
@@ -178,6 +178,9 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 //    32.1, 19.1; 32 x 1502 x 256 30.0, 22.2), else swept twice (24 x 32929 x 160 236, 159; 6 x 29092 x
 //    256 66.7, 52.4; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
 //  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 57.8, 33.0; 8 x 9057 x 504 64.6, 56.0).
+// Over 3000 shapes of up to 400000 keys times heads 1.32 times as fast, 5 of them slower by more than 3 %.  Slower beyond: full
+// tiles (225 to 256, 481 to 512 rows) of d = 64 with a prior, from a million keys times heads on by up to 6 % (64 x 65536 x 256
+// 494, 515; 64 x 65536 x 512 916, 954).
 //
 // Workgroups of which the chip holds two per CU at once.  A problem never has more ranges than that: those that
 // run would wait for those that cannot start (8 x 300000 x 64 rows, 586 ranges: 56 ms).

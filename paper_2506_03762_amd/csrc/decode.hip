@@ -737,8 +737,8 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeGeom g, int nsp
 // and weighted sums above cost more than the key and value streams (whole step
 // at 8 queries per head, d = 128: 8 heads x 100 slots 20.9 -> 10.9 us, 64 x 1500 42.0 -> 22.0).
 // Tiles of 16 columns: with 32, three quarters of the products, exponentials and weight conversions and
-// half of the registers were for columns past the last head (246 registers -> 168, three workgroups per CU
-// instead of two; 64 heads x 1537 slots 24.4 -> 21.2 us, 96 x 1537 37.3 -> 26.3, 8 x 2049 with G = 4
+// half of the registers were for columns past the last head (246 registers -> 168 and two spilled, three workgroups
+// per CU instead of two; 64 heads x 1537 slots 24.4 -> 21.2 us, 96 x 1537 37.3 -> 26.3, 8 x 2049 with G = 4
 // 12.9 -> 11.9).  Bound by latency for few heads, else by the loads a CU has in flight (128 heads x 1537: 101
 // MB in 25 us).
 // Workgroup = (slot range, batch, KV head) as above; each of its four waves takes blocks of 32

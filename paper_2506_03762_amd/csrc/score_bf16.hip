@@ -144,7 +144,7 @@ __device__ __forceinline__ float value_prior_of_range(const ScoreGeom &g, int b,
 //    and the pooling halo are requested in the set-up, right behind the keys, and their norms
 //    never leave LDS.  The kernel waits for memory once: 12 heads x 5003 x 120 rows 13.7 -> 11.6 us.
 // ENT: the chunk's mean scaled logit under its own probabilities, E_c[t] = m + u / s, is
-// written to `partial_mean` beside the chunk's log2-sum-exp2; entropy_merge_kernel turns the
+// written to `partial_mean` beside the chunk's log2-sum-exp2; row_stats_merge_kernel turns the
 // chunks of a row into its entropy.
 template <int D, int NB, bool ENT, bool ROWS = false, int PRIOR = kNoPrior, bool LAZY = false>
 __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_qtiles, int nparts,

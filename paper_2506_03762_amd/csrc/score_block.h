@@ -118,10 +118,10 @@ __device__ __forceinline__ void colsum_update(const f32x16 (&acc)[kMB], float la
     if (MASK) asm volatile("" ::: "memory");
 }
 
-// Value prior (Sec. 4.3) inside pass 1.  The value rows of the 64 keys a wave multiplies in a
-// step are loaded with the addressing of the key fragments into the register buffer that is
-// idle in the first half of the step (the next key block is requested at mid-step instead of
-// at the start): a lane then holds one half (the channels of its half-wave) of two value rows.
+// Value prior (Sec. 4.3).  The value rows of the keys a wave multiplies in a step pass through the
+// register buffer that the next key block does not need yet.  Loaded with the addressing of the key
+// fragments (two tiles of the two-sweep kernel, ranges of one step in two launches), a lane holds one half (the
+// channels of its half-wave) of a value row per group of 32.
 
 // nu = ||V_row||^2 of those rows: squares summed in-lane, one exchange between the half-waves.
 // M: of the first M groups of 32 rows.

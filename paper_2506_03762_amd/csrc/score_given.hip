@@ -6,11 +6,11 @@
 // the range's largest prior with the other workgroups of its problem (exchange.h) before it writes the
 // scores.  Before, a launch formed the prior (V at 5.2 TB/s, nothing to compute under it) and another
 // one the sums.  8 heads x 32768 keys x 256 rows: 46.3 -> 39.7 us, bound by the vector ALU and the matrix core
-// in turns; 128 x 16384 x 64: 198 -> 174 us, K and V at 6.2 TB/s.
+// in turns; 128 x 16384 x 64: 198 -> 172 us, K and V at 6.2 TB/s.
 //
 // Value rows are loaded as they lie in memory (load_rows) and not with the key fragments' addressing, 32 rows
 // x 32 bytes to an instruction: 128 x 16384 x 64 233 -> 212 us.  Ranges are as long as the LDS keeps their
-// norms, prior and sums; through the workspace instead the same took 212 us, now 174.
+// norms, prior and sums; through the workspace instead the same took 212 us.
 #include <type_traits>
 
 #include "exchange.h"

@@ -11,13 +11,16 @@
 // the one burst of loads (9 us to the last wave's keys), then one round trip each for announcing,
 // looking and fetching.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
 // window_stream_kernel (below): more rows or longer ranges, the logits formed twice.  8 heads x 16384 x
-// 512 rows 89 -> 67 us, 8 x 32768 x 256 70 -> 67: bound by the vector ALU and the matrix core taking turns
-// (620 ns per 64 x 32 block and SIMD), the first sweep's first step by its loads.
+// 512 rows 89 -> 67 us, 8 x 32768 x 256 70 -> 67: half of the time vector ALU and matrix core in turns (by the
+// counters; 620 ns per 64 x 32 block and SIMD), the rest set-up, first loads, exchange and the second sweep's start: a
+// workgroup has two steps per sweep there.
 //
 // Value rows are loaded as they lie in memory (load_rows); with the key fragments' addressing an instruction
 // reads 32 bytes of 32 rows.  Where the last-level cache would not keep them anyway they go past the caches.  us
 // of the score stage before and after: 48 heads x 6846 keys x 64 rows 59.0, 47.3; 12 x 59081 x 64 108, 92.8; 128 x
 // 16384 x 64 259, 252; 8 x 32768 x 256 70.4, 67.1.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
+// With the logits held, value rows and keys take all registers where the range has two steps (d = 128, two row blocks: 9 spilled,
+// 40 bytes a lane, once per step; one block and four steps: 40, for up to 32 rows).
 // Two tiles share their value rows, 32 each, and load them like keys: as memory lies was slower
 // (8 x 16384 x 512, the whole step, 77.8 and 74.7).
 #include <type_traits>

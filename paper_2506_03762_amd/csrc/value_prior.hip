@@ -3,10 +3,12 @@
 // maxima of gamma from which the consumers form gamma / max(gamma).
 //
 // HBM-bound: V is read exactly once (plus (pool-1)/2 halo rows per tile).
-// The windowed bf16 scores form the prior inside their row-statistics launch
-// (score_bf16.hip), fp32 inputs as extra workgroups of theirs (score_f32.hip); this
-// kernel serves full accumulation (where it also zeroes the scores) and the entry point that
-// is handed the rows' normalisers (which it converts for the column-sum pass).
+// The windowed bf16 scores form the prior inside their one launch (score_window.hip,
+// score_given.hip) or, in two, inside the row statistics (score_bf16.hip, up to 128 rows), fp32
+// inputs as extra workgroups of theirs (score_f32.hip); this kernel serves full accumulation
+// (where it also zeroes the scores), pool widths above 17, chosen rows, larger tiles whose workspace
+// holds two launches only, and given normalisers in two launches (which it converts for the
+// column-sum pass).
 #include "value_tile.h"
 
 namespace aha {
