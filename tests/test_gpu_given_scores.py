@@ -108,18 +108,17 @@ def test_time_per_key():
         def data_ptr(self):
             return q.data_ptr() - (self.n - window) * d * 2
 
-    def per_key(n):
+    calls, times = [], ([], [])
+    for n in (longest, 700000):
         p = B.Params(batch=1, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, seq_len=n, window=window, budget=64, recent=8,
                      q_stride=(0, window * d, d), k_stride=(0, longest * d, d), v_stride=(0, longest * d, d))
-        ws, times = B.alloc_workspace(p), []
-        for _ in range(12):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            a.record()
-            B.aha_prefill_scores_lse(p, LastRows(n), k, v, lse, scores, ws)
-            b.record()
-            torch.cuda.synchronize()
-            times.append(a.elapsed_time(b))
-        return sorted(times)[6] / n
-
+        calls.append((p, LastRows(n), k, v, lse, scores, B.alloc_workspace(p)))
+    for i in range(24):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        B.aha_prefill_scores_lse(*calls[i % 2])
+        b.record()
+        torch.cuda.synchronize()
+        times[i % 2].append(a.elapsed_time(b) / calls[i % 2][0].seq_len)
     # 0.87 ns per key either way; 1.24 for the longer one in 158 ranges to a problem
-    assert per_key(longest) < 1.12 * per_key(700000)
+    assert sorted(times[0])[6] < 1.12 * sorted(times[1])[6]
