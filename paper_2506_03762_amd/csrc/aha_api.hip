@@ -161,10 +161,24 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
     parts = (n + keys - 1) / keys;
 }
 
+// Workgroups of which the chip holds two per CU at once.  A problem never has more ranges than that: those that
+// run would wait for those that cannot start (8 x 300000 x 64 rows, 586 ranges: 56 ms).
+constexpr int64_t kHeldAtOnce = 512;
+// Logits held in several rounds of the whole chip, 33 to 64 rows, d = 128: up to which number of ranges that is the
+// faster one.  The workgroups of a problem that begins at the end of a round wait for the next one, so the fewer
+// problems a round holds the more of it is spent waiting; two launches that leave their own last round
+// nearly empty are slow enough for it up to two problems a round.  us in two launches, in one (with a prior):
+// two even launches: 16 heads x 64 ranges 71.7, 66.5, x 96 101, 105, x 192 204, 258; 64 x 128 565, 562, x 192 867,
+// 1003; uneven: 24 x 64 130, 94, x 256 559, 471, x 320 713, 793.
+static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
+    const bool uneven = (int64_t)pl.Z * pl.nchunks > 512;
+    return pl.Z * parts >= 1024 && parts <= (uneven ? kHeldAtOnce / 2 : pl.Z >= 64 ? 128 : 64);
+}
+
 // Windowed bf16 scores in one launch.  Its layout starts where the one of two launches does, but may be longer: a
-// call whose workspace does not hold it takes two launches.  Where, and which kernel, follows from the times of the score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV
-// heads, 400 to 65536 keys, d = 64 and 128), 1.30 times as fast as two launches on average.  us in two
-// launches, in one:
+// call whose workspace does not hold it takes two launches.  Where, and which kernel, follows from the times of the
+// score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV heads, 400 to 65536 keys, d = 64 and 128), 1.30
+// times as fast as two launches on average.  us in two launches, in one:
 //  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
 //    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0.  In
 //    several rounds the exchange is waited for in each: a gain only with enough bytes behind it (64 rows,
@@ -181,20 +195,6 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 // Over 3000 shapes of up to 400000 keys times heads 1.32 times as fast, 5 of them slower by more than 3 %.  Slower beyond: full
 // tiles (225 to 256, 481 to 512 rows) of d = 64 with a prior, from a million keys times heads on by up to 6 % (64 x 65536 x 256
 // 494, 515; 64 x 65536 x 512 916, 954).
-//
-// Workgroups of which the chip holds two per CU at once.  A problem never has more ranges than that: those that
-// run would wait for those that cannot start (8 x 300000 x 64 rows, 586 ranges: 56 ms).
-constexpr int64_t kHeldAtOnce = 512;
-// Logits held in several rounds of the whole chip, 33 to 64 rows, d = 128: up to which number of ranges that is the
-// faster one.  The workgroups of a problem that begins at the end of a round wait for the next one, so the fewer
-// problems a round holds the more of it is spent waiting; two launches that leave their own last round
-// nearly empty are slow enough for it up to two problems a round.  us in two launches, in one (with a prior):
-// two even launches: 16 heads x 64 ranges 71.7, 66.5, x 96 101, 105, x 192 204, 258; 64 x 128 565, 562, x 192 867,
-// 1003; uneven: 24 x 64 130, 94, x 256 559, 471, x 320 713, 793.
-static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
-    const bool uneven = (int64_t)pl.Z * pl.nchunks > 512;
-    return pl.Z * parts >= 1024 && parts <= (uneven ? kHeldAtOnce / 2 : pl.Z >= 64 ? 128 : 64);
-}
 static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.win_nb = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -250,8 +250,9 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
 // over 110 shapes (1 to 256 rows, 2 to 128 KV heads, 250 to 61000 keys), us in two, in one: 8 heads x 32768 keys x
 // 256 rows 46.3, 39.7; 128 x 16384 x 64 198, 172; 32 x 4096 x 64 19.7, 19.1; 2 x 512 x 32 8.3, 7.2.  Not taken
 // where it was the slower one: few heads in many ranges of a step or two, where the exchange is most of the time (8 x
-// 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), eight blocks of rows in steps of 512 keys
-// for at most half of the CUs (8 x 3600 x 256 18.5, 19.9, 4 x 12000, d = 64 13.7, 15.4; not 8 x 12000 23.9, 22.3), and without a prior,
+// 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), eight blocks of rows in
+// steps of 512 keys for at most half of the CUs (8 x 3600 x 256 18.5, 19.9, 4 x 12000, d = 64 13.7, 15.4; not 8 x
+// 12000 23.9, 22.3), and without a prior,
 // of which a second launch would have to be saved, many steps of the larger tiles (32 x 31856 x 256 79.3, 82.3).
 static void plan_given(const aha_params *p, PrefillPlan &pl) {
     pl.given_nb = 0;
@@ -435,8 +436,8 @@ static bool decode_one_launch(int dtype, int Z, int G, int d, int live, bool roo
 // slots of every CU; five of 129 do not, while one workgroup per head keeps more than half of the chip busy.
 // With d = 128 and six and more query heads the split is the faster one all the same up to 144 heads (100 to
 // 3100 slots: 1.11 times as fast on average, 3 % slower at worst).  us in one launch, split, d = 128: G = 8, 144
-// heads x 300 slots 19.0, 16.4, x 801 24.8, 25.1, x 1200 32.9, 30.0, 160 x 801 25.3, 26.0, 192 x 1537 41.1, 43.6; G = 4, 128 x 801 22.1, 20.8, 129 x 801
-// 22.4, 23.9; d = 64, G = 5, 128 x 801 14.7, 14.8, 129 x 801 15.1, 16.5.
+// heads x 300 slots 19.0, 16.4, x 801 24.8, 25.1, x 1200 32.9, 30.0, 160 x 801 25.3, 26.0, 192 x 1537 41.1, 43.6;
+// G = 4, 128 x 801 22.1, 20.8, 129 x 801 22.4, 23.9; d = 64, G = 5, 128 x 801 14.7, 14.8, 129 x 801 15.1, 16.5.
 static int most_split_heads(int G, int d) { return d == 128 && G >= 6 ? 144 : kDecodeSplitHeads; }
 
 // Decode: split a head's slots over workgroups when there are too few heads to fill the GPU.
