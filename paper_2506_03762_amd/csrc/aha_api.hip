@@ -651,7 +651,9 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
         return rc;
     if ((rc = hip_result(stage(1, st), "stage event"))) return rc;
     hipEvent_t mid = g_stage_on ? g_stage_ev[2] : nullptr;
-    if (p->dtype == AHA_BF16)
+    if (p->dtype == AHA_BF16 && pl.n_qtiles > 1)
+        rc = hip_result(launch_score_full(g, pl, workspace, scores, st, mid, with_lse), "bf16 score kernels");
+    else if (p->dtype == AHA_BF16)
         rc = hip_result(launch_score_bf16(g, pl, workspace, scores, st, mid, with_lse, fold_prior),
                         "bf16 score kernels");
     else

@@ -91,6 +91,10 @@ hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
 hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
                              float *scores, hipStream_t st, hipEvent_t mid, bool have_lse,
                              bool fold_prior);
+// score_full.hip
+// The same with more rows than one tile (pl.n_qtiles > 1); the prior has been formed, the scores are zero.
+hipError_t launch_score_full(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores, hipStream_t st,
+                             hipEvent_t mid, bool have_lse);
 // score_window.hip
 // Windowed scores in one launch (pl.win_nb > 0).  `tag`: a number no other call uses, its low 20 bits
 // zero; `looks`: at the other workgroups' announcements before missing parts are done in place.

@@ -1,5 +1,5 @@
-// bf16 eviction scores on the gfx950 matrix cores (Sec. 4.1 - 4.3; Alg. 1
-// Prefill).  Two passes, both recomputing tiles of K Q^T with
+// bf16 eviction scores of up to 256 rows in two launches on the gfx950 matrix cores (Sec. 4.1 - 4.3;
+// Alg. 1 Prefill), and the row statistics' output of any number.  Two passes, both recomputing tiles of K Q^T with
 // v_mfma_f32_32x32x16_bf16 (keys on M, queries on N); the n x n probability
 // matrix never exists in memory.
 //
@@ -23,44 +23,6 @@
 #include "score_block.h"
 
 namespace aha {
-
-
-// Work split shared by pass 1 and by pass 2 in full accumulation.  Query tile `pair` is
-// teamed with tile T-1-pair: a tile of late rows sees many keys, its partner few, together
-// about the same as any other pair.  The pair's work is laid out on a line - the first
-// tile's 256-key steps, the set-up of the partner (loading a query tile costs about one
-// step; every workgroup pays one set-up anyway, only a second one counts), the partner's
-// steps - and the line is cut into `nparts` equal ranges.  Segment `seg` (0: first tile,
-// 1: partner) of a workgroup is the part of its range that falls on that tile's steps.
-// A single tile (windowed scores, or the middle tile of an odd count) is cut into equal
-// ranges of steps.
-struct Segment {
-    int qt;          // query tile, -1: no such segment
-    int kbeg, kend;  // keys [kbeg, kend); empty when kbeg >= kend
-};
-__device__ __forceinline__ Segment pair_segment(const RowMap &rm, int rows, int T, int pair,
-                                                int part, int nparts, int seg) {
-    const int tA = pair, tB = T - 1 - pair;
-    const bool two = tB != tA;
-    // (chosen accumulator rows - a single tile - may sit anywhere: the whole sequence)
-    const int endA = rm.rows ? rm.n : rm.max_pos(tA * rows, (tA + 1) * rows) + 1;
-    const int endB = two ? rm.max_pos(tB * rows, (tB + 1) * rows) + 1 : 0;
-    const int sA = (endA + kWgKeys - 1) / kWgKeys, sB = (endB + kWgKeys - 1) / kWgKeys;
-    // positions on the line: first tile's steps start at oA, the partner's at oB
-    const int oA = 0, oB = sA + 1, V = two ? sA + sB + 1 : sA;
-    const int v0 = (int)((int64_t)part * V / nparts), v1 = (int)((int64_t)(part + 1) * V / nparts);
-    Segment r;
-    if (seg == 0) {
-        r.qt = tA;
-        r.kbeg = (max(v0, oA) - oA) * kWgKeys;
-        r.kend = min(endA, (min(v1, oA + sA) - oA) * kWgKeys);
-    } else {
-        r.qt = two ? tB : -1;
-        r.kbeg = (max(v0, oB) - oB) * kWgKeys;
-        r.kend = min(endB, (min(v1, oB + sB) - oB) * kWgKeys);
-    }
-    return r;
-}
 
 // ---------------------------------------------------------------- pass 1 --
 constexpr int kNoPrior = 0, kPriorFold = 1, kPriorOneStep = 2;  // value prior inside pass 1 (below)
@@ -146,7 +108,7 @@ __device__ __forceinline__ float value_prior_of_range(const ScoreGeom &g, int b,
 // ENT: the chunk's mean scaled logit under its own probabilities, E_c[t] = m + u / s, is
 // written to `partial_mean` beside the chunk's log2-sum-exp2; row_stats_merge_kernel turns the
 // chunks of a row into its entropy.
-template <int D, int NB, bool ENT, bool ROWS = false, int PRIOR = kNoPrior, bool LAZY = false>
+template <int D, int NB, bool ENT, bool ROWS = false, int PRIOR = kNoPrior>
 __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_qtiles, int nparts,
                                                             int total_wgs, float *partial,
                                                             float *partial_mean, float *gamma,
@@ -250,7 +212,7 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                 for (int nb = nb0; nb < nb1; ++nb) {
                     f32x16 acc[kMB];
                     mma_block_stream<D, NB>(a, sQ, nb, nb + 1 < nb1 ? nb + 1 : nb0, lane, qf, acc);
-                    stats_update<false, ENT, LAZY>(acc, lam[nb], 0, kb, lane, m[nb], s[nb], u[ENT ? nb : 0]);
+                    stats_update<false, ENT>(acc, lam[nb], 0, kb, lane, m[nb], s[nb], u[ENT ? nb : 0]);
                 }
                 return;
             }
@@ -350,54 +312,10 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
 }
 
 // ---------------------------------------------------------------- pass 2 --
-// Log2-sum-exp2 of one query row from the per-chunk log2-sum-exp2 values that pass 1 left.
-// A batch of values is requested at once (request), so that it travels together with the
-// other loads of the tile set-up, and merged later (merge) into the running (M, sum) with
-// sum = sum over chunks of exp2(value - M).  Both go by groups of eight and skip the
-// groups past the last chunk.
-template <int BATCH>
-__device__ __forceinline__ void chunk_request(const float *src, int stride, int c0, int nchunks,
-                                              float (&e)[BATCH]) {
-    static_assert(BATCH % 8 == 0, "groups of eight");
-#pragma unroll
-    for (int g8 = 0; g8 < BATCH; g8 += 8) {
-        if (c0 + g8 >= nchunks) break;  // uniform
-        // entries past the last chunk re-read it (branch-free, back-to-back loads) and are
-        // neutralised in the merge
-#pragma unroll
-        for (int t = g8; t < g8 + 8; ++t) e[t] = src[(int64_t)min(c0 + t, nchunks - 1) * stride];
-    }
-}
-template <int BATCH>
-__device__ __forceinline__ void chunk_merge(const float (&e)[BATCH], int count, float &M,
-                                            float &sum) {
-    float bm = -INFINITY;
-#pragma unroll
-    for (int g8 = 0; g8 < BATCH; g8 += 8) {
-        if (g8 >= count) break;  // uniform
-#pragma unroll
-        for (int t = g8; t < g8 + 8; ++t) bm = fmaxf(bm, t < count ? e[t] : -INFINITY);
-    }
-    const float mn = fmaxf(M, bm);
-    const float mref = mn == -INFINITY ? 0.f : mn;
-    sum *= fast_exp2(M - mref);
-#pragma unroll
-    for (int g8 = 0; g8 < BATCH; g8 += 8) {
-        if (g8 >= count) break;
-#pragma unroll
-        for (int t = g8; t < g8 + 8; ++t) sum += t < count ? fast_exp2(e[t] - mref) : 0.f;
-    }
-    M = mn;
-}
-
-// SINGLE: all observed rows fit one query tile (the windowed score).  The tile is loaded
-// once, the workgroup walks over several 256-key steps and the A fragments of the next
-// step load while the current one multiplies; every score is written exactly once.
-// Otherwise (full accumulation) the grid is (part, tile pair, problem) as in pass 1 and the
-// tiles' contributions meet in the scores through float atomics.
-template <int D, int NB, bool SINGLE, bool ROWS = false>
-__global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int n_qtiles,
-                                                            int total_wgs, int wg_keys, int nchunks,
+// All observed rows fit one query tile, which is loaded once; the workgroup walks over several 256-key steps and the A
+// fragments of the next step load while the current one multiplies; every score is written exactly once.
+template <int D, int NB, bool ROWS = false>
+__global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int total_wgs, int wg_keys, int nchunks,
                                                             const float *partial,
                                                             const float *gamma,
                                                             const float *gblockmax,
@@ -411,8 +329,8 @@ __global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int n_q
     int *sBlk = (int *)(sL + S::ROWS);
     __shared__ float s_gmax[4];
 
-    // logical workgroup index -> SINGLE: (key range, problem); else (part, tile pair, problem)
-    const int wg = logical_wg_index(total_wgs, !SINGLE);
+    // logical workgroup index -> (key range, problem)
+    const int wg = logical_wg_index(total_wgs, false);
     if (wg >= total_wgs) return;
     const int per_problem = total_wgs / (g.batch * g.Hkv);
     const int z = wg / per_problem, wg_in_z = wg % per_problem;
@@ -421,9 +339,7 @@ __global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int n_q
     const RowMap rm{g.n, g.r, g.R,
                     ROWS ? g.rows + ((int64_t)b * g.Hq + (int64_t)h * g.G) * g.r : nullptr};
     const __bf16 *kbase = (const __bf16 *)g.k + b * g.ks[0] + h * g.ks[1];
-    // SINGLE: the workgroup's key range; otherwise ranges come per tile segment (below)
-    int key_begin = wg_in_z * wg_keys;
-    int key_end = min(g.n, key_begin + wg_keys);
+    const int key_begin = wg_in_z * wg_keys, key_end = min(g.n, key_begin + wg_keys);
 
     bf16x8 a0[kMB][D / 16];
     // (the windowed pass walks its key range from the last step to the first)
@@ -432,69 +348,48 @@ __global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int n_q
     // this thread's share of the value prior's per-tile maxima (requested here, reduced
     // during the first tile set-up)
     float gm = (g.value_prior && tid < n_vtiles) ? gblockmax[z * n_vtiles + tid] : 0.f;
-    bool gmax_pending = g.value_prior;
-    float lamr[NB], Lr[NB];  // scale and log-sum-exp of this lane's query column, per block
 
-    // query tile qt -> LDS, with the log-sum-exp of its rows folded from pass 1's chunks
+    // query tile -> LDS, with the log-sum-exp of its rows folded from pass 1's chunks
     static_assert(S::ROWS <= 256, "one thread folds the statistics of one tile row");
-    // `first_kb`: the wave's first key block of the tile, requested right behind the tile's
-    // own (L2-served) loads so that those are not queued behind the keys coming from HBM
-    int tile_min = 0;  // smallest position among the rows of the tile in LDS
-    auto load_tile = [&](int qt, int first_kb) {
-        const int rho0 = qt * S::ROWS;
-        // Full accumulation sets up a tile per segment: there the thread index and the chunk
-        // count go through an opaque move, so that the set-up's address arithmetic is
-        // redone per tile instead of being kept (and spilled) across the main loop, where
-        // a reload of a spilled address would have to wait for every load in flight.
-        int tid = threadIdx.x, nchunks_t = nchunks;
-        if (!SINGLE) {
-            asm volatile("" : "+v"(tid));
-            asm volatile("" : "+s"(nchunks_t));
+    {
+        // tile rows, chunk statistics and scales are requested together, then used
+        QTileRegs<D, NB> qt_regs;
+        constexpr int kChunkBatch = 64;
+        float ch[kChunkBatch];
+        const bool row_ok = tid < S::ROWS && tid < g.R;
+        // (threads without a row of their own read row 0's statistics and drop them)
+        const float *psrc = partial + (int64_t)z * nchunks * S::ROWS + (tid < S::ROWS ? tid : 0);
+        q_tile_request<D, NB, ROWS>(g, b, h, 0, tid, qt_regs);
+        chunk_request(psrc, S::ROWS, 0, nchunks, ch);
+        const float lam_req = q_tile_scale<D, NB>(g, rm, 0, tid);
+        __builtin_amdgcn_sched_barrier(0);  // the key block is requested last
+        // (right behind the tile's own, L2-served loads, so that those are not queued behind keys from HBM)
+        load_a<D>(kbase, g.ks[2], last_step + wave * kWaveKeys, key_end, lane, a0);
+        q_tile_meta<D, NB>(g, rm, 0, tid, lam_req, sLam, sPos, sBlk);
+        if (g.value_prior) {
+            for (int t = tid + 256; t < n_vtiles; t += 256) gm = fmaxf(gm, gblockmax[z * n_vtiles + t]);
+            gm = wave_max(gm);
+            if (lane == 0) s_gmax[wave] = gm;
         }
-        {
-            // tile rows, chunk statistics and scales are requested together, then used
-            QTileRegs<D, NB> qt_regs;
-            // (windowed mode has up to 64 chunks per row; full accumulation a few, and less
-            // room in the register file at this point)
-            constexpr int kChunkBatch = SINGLE ? 64 : 8;
-            float ch[kChunkBatch];
-            const bool row_ok = tid < S::ROWS && rho0 + tid < g.R;
-            // (threads without a row of their own read row 0's statistics and drop them)
-            const float *psrc = partial + ((int64_t)(z * n_qtiles + qt) * nchunks_t) * S::ROWS +
-                                 (tid < S::ROWS ? tid : 0);
-            q_tile_request<D, NB, ROWS>(g, b, h, rho0, tid, qt_regs);
-            chunk_request(psrc, S::ROWS, 0, nchunks_t, ch);
-            const float lam_req = q_tile_scale<D, NB>(g, rm, rho0, tid);
-            __builtin_amdgcn_sched_barrier(0);  // the key block is requested last
-            load_a<D>(kbase, g.ks[2], first_kb, key_end, lane, a0);
-            q_tile_meta<D, NB>(g, rm, rho0, tid, lam_req, sLam, sPos, sBlk);
-            if (gmax_pending) {
-                for (int t = tid + 256; t < n_vtiles; t += 256)
-                    gm = fmaxf(gm, gblockmax[z * n_vtiles + t]);
-                gm = wave_max(gm);
-                if (lane == 0) s_gmax[wave] = gm;
-                gmax_pending = false;
-            }
-            float M = -INFINITY, sum = 0.f;
-            chunk_merge(ch, nchunks_t, M, sum);
-            for (int c0 = kChunkBatch; c0 < nchunks_t; c0 += kChunkBatch) {
-                chunk_request(psrc, S::ROWS, c0, nchunks_t, ch);
-                chunk_merge(ch, nchunks_t - c0, M, sum);
-            }
-            if (tid < S::ROWS) sL[tid] = row_ok ? M + log2f(sum) : INFINITY;
-            q_tile_commit<D, NB>(qt_regs, tid, sQ);
+        float M = -INFINITY, sum = 0.f;
+        chunk_merge(ch, nchunks, M, sum);
+        for (int c0 = kChunkBatch; c0 < nchunks; c0 += kChunkBatch) {
+            chunk_request(psrc, S::ROWS, c0, nchunks, ch);
+            chunk_merge(ch, nchunks - c0, M, sum);
         }
-        __syncthreads();
-        tile_min = ROWS ? tile_min_pos<NB>(sBlk) : rm.min_pos(rho0, rho0 + S::ROWS);
+        if (tid < S::ROWS) sL[tid] = row_ok ? M + log2f(sum) : INFINITY;
+        q_tile_commit<D, NB>(qt_regs, tid, sQ);
+    }
+    __syncthreads();
+    const int tile_min = ROWS ? tile_min_pos<NB>(sBlk) : rm.min_pos(0, S::ROWS);  // smallest position among the tile's rows
+    float lamr[NB], Lr[NB];  // scale and log-sum-exp of this lane's query column, per block
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            lamr[nb] = sLam[nb * 32 + (tid & 31)];
-            Lr[nb] = sL[nb * 32 + (tid & 31)];
-        }
-    };
+    for (int nb = 0; nb < NB; ++nb) {
+        lamr[nb] = sLam[nb * 32 + (lane & 31)];
+        Lr[nb] = sL[nb * 32 + (lane & 31)];
+    }
     // this wave's 64 keys (A fragments a) against the query tile in LDS
-    auto tile_times_keys = [&](const bf16x8 (&a)[kMB][D / 16], int kb, int rho0,
-                               f32x16 (&col)[kMB]) {
+    auto tile_times_keys = [&](const bf16x8 (&a)[kMB][D / 16], int kb, f32x16 (&col)[kMB]) {
         if (kb + kWaveKeys - 1 <= tile_min) {
             // all rows of the tile see all 64 keys: no masks, no skipped blocks
             bf16x8 qf = query_fragment<D, NB>(sQ, 0, 0, lane);
@@ -548,82 +443,26 @@ __global__ __launch_bounds__(256, 2) void bf16_pass2_kernel(ScoreGeom g, int n_q
             for (int v = 0; v < 16; ++v) col[mb][v] = 0.f;
     };
 
-    if constexpr (SINGLE) {
-        load_tile(0, last_step + wave * kWaveKeys);
-        bf16x8 a1[kMB][D / 16];
-        auto step = [&](const bf16x8 (&a)[kMB][D / 16], int kb0) {
-            const int kb = kb0 + wave * kWaveKeys;
-            if (kb >= g.n) return;
-            float gam[kMB];
-            request_gamma(kb, gam);
-            f32x16 col[kMB];
-            zero(col);
-            tile_times_keys(a, kb, 0, col);
-            write_scores(col, kb, gam);
-        };
-        // (unconditional prefetch, as in pass 1)
-        for (int kb0 = last_step; kb0 >= key_begin; kb0 -= 2 * kWgKeys) {
-            const int k1 = kb0 - kWgKeys, k2 = k1 - kWgKeys;
-            // before the range: kb = key_end makes every row read the range's last one
-            load_a<D>(kbase, g.ks[2], k1 >= key_begin ? k1 + wave * kWaveKeys : key_end, key_end,
-                      lane, a1);
-            step(a0, kb0);
-            if (k1 < key_begin) break;
-            load_a<D>(kbase, g.ks[2], k2 >= key_begin ? k2 + wave * kWaveKeys : key_end, key_end,
-                      lane, a0);
-            step(a1, k1);
-        }
-    } else {
-        // full accumulation: this workgroup keeps ONE query tile in LDS and streams its keys
-        // like pass 1; the 64 column sums of a wave step are this tile's contribution and are
-        // added to the (zero-initialised) scores with hardware float atomics, already
-        // multiplied by the value prior.  The order of the additions over the tiles is not
-        // fixed, so repeated calls may differ in the last bits.
-        // wg_keys carries the number of parts a tile pair's key steps are cut into
-        const int nparts = wg_keys, part = wg_in_z % nparts, pair = wg_in_z / nparts;
-        bf16x8 a1[kMB][D / 16];
-        for (int seg = 0; seg < 2; ++seg) {
-            const Segment sg = pair_segment(rm, S::ROWS, n_qtiles, pair, part, nparts, seg);
-            if (sg.qt < 0) break;
-            key_begin = sg.kbeg;
-            key_end = sg.kend;
-            if (key_begin >= key_end) continue;  // workgroup-uniform
-            const int rho0 = sg.qt * S::ROWS;
-            if (seg) __syncthreads();  // the previous tile is done with
-            // (first tile upwards, partner downwards: see pass 1)
-            const int nsteps = (key_end - key_begin + kWgKeys - 1) / kWgKeys;
-            const int kdir = seg ? -kWgKeys : kWgKeys;
-            const int k_at0 = seg ? key_begin + (nsteps - 1) * kWgKeys : key_begin;
-            auto kb0_of = [&](int i) { return k_at0 + i * kdir; };
-            auto load_kb_of = [&](int i) { return i < nsteps ? kb0_of(i) + wave * kWaveKeys : key_end; };
-            load_tile(sg.qt, load_kb_of(0));
-            float ginv = 1.f;
-            if (g.value_prior)
-                ginv = prior_inverse(fmaxf(fmaxf(s_gmax[0], s_gmax[1]), fmaxf(s_gmax[2], s_gmax[3])));
-            auto step = [&](const bf16x8 (&a)[kMB][D / 16], int kb0) {
-                const int kb = kb0 + wave * kWaveKeys;
-                if (kb >= key_end) return;
-                float gam[kMB];
-                request_gamma(kb, gam);
-                f32x16 col[kMB];
-                zero(col);
-                tile_times_keys(a, kb, rho0, col);
-#pragma unroll
-                for (int mb = 0; mb < kMB; ++mb) {
-                    const float tot = fold16_over32(col[mb], lane);
-                    const int j = acc_key(kb, mb, my_v, lane);
-                    if ((lane & 1) == 0 && j < key_end)
-                        unsafeAtomicAdd(&scores[(int64_t)z * g.n + j], tot * prior_factor(gam[mb], ginv));
-                }
-            };
-            for (int i = 0; i < nsteps; i += 2) {
-                load_a<D>(kbase, g.ks[2], load_kb_of(i + 1), key_end, lane, a1);
-                step(a0, kb0_of(i));
-                if (i + 1 >= nsteps) break;
-                load_a<D>(kbase, g.ks[2], load_kb_of(i + 2), key_end, lane, a0);
-                step(a1, kb0_of(i + 1));
-            }
-        }
+    bf16x8 a1[kMB][D / 16];
+    auto step = [&](const bf16x8 (&a)[kMB][D / 16], int kb0) {
+        const int kb = kb0 + wave * kWaveKeys;
+        if (kb >= g.n) return;
+        float gam[kMB];
+        request_gamma(kb, gam);
+        f32x16 col[kMB];
+        zero(col);
+        tile_times_keys(a, kb, col);
+        write_scores(col, kb, gam);
+    };
+    // (unconditional prefetch, as in pass 1)
+    for (int kb0 = last_step; kb0 >= key_begin; kb0 -= 2 * kWgKeys) {
+        const int k1 = kb0 - kWgKeys, k2 = k1 - kWgKeys;
+        // before the range: kb = key_end makes every row read the range's last one
+        load_a<D>(kbase, g.ks[2], k1 >= key_begin ? k1 + wave * kWaveKeys : key_end, key_end, lane, a1);
+        step(a0, kb0);
+        if (k1 < key_begin) break;
+        load_a<D>(kbase, g.ks[2], k2 >= key_begin ? k2 + wave * kWaveKeys : key_end, key_end, lane, a0);
+        step(a1, k1);
     }
 }
 
@@ -673,15 +512,13 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
     constexpr int kFold = NB <= 4 ? kPriorFold : kNoPrior, kOneStep = NB == 4 ? kPriorOneStep : kFold;
     static DeviceOnce once;
     const hipError_t ea = device_once(once, [] {
-        const void *kernels[9] = {(const void *)bf16_pass1_kernel<D, NB, false>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>,
+        const void *kernels[7] = {(const void *)bf16_pass1_kernel<D, NB, false>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, false, kFold>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, false, kOneStep>,
                                   (const void *)bf16_pass1_kernel<D, NB, true>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, true>,
-                                  (const void *)bf16_pass2_kernel<D, NB, true>,
-                                  (const void *)bf16_pass2_kernel<D, NB, true, true>,
-                                  (const void *)bf16_pass2_kernel<D, NB, false>};
+                                  (const void *)bf16_pass2_kernel<D, NB>,
+                                  (const void *)bf16_pass2_kernel<D, NB, true>};
         for (const void *kf : kernels) {
             const hipError_t e = hipFuncSetAttribute(
                 kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(S::bytes + kPriorSmem));
@@ -708,10 +545,6 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kFold>), xcd_grid(wgs1),
                                dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
                                partial, (float *)nullptr, gamma, gbm);
-        else if (pl.n_qtiles > 1)  // full accumulation: block sums against a lazy reference
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kNoPrior, true>), xcd_grid(wgs1),
-                               dim3(256), S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
-                               partial, (float *)nullptr, (float *)nullptr, (float *)nullptr);
         else
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false>), xcd_grid(wgs1), dim3(256),
                                S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial,
@@ -721,18 +554,12 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
     // the prior's per-range maxima: one per key chunk when pass 1 formed it, else per tile
     const int n_maxima = fold_prior ? pl.nchunks : pl.n_vtiles;
     if (mid) (void)hipEventRecord(mid, st);
-    if (pl.n_qtiles == 1 && g.rows)
-        hipLaunchKernelGGL((bf16_pass2_kernel<D, NB, true, true>), xcd_grid(wgs2), dim3(256),
-                           S::bytes, st, g, pl.n_qtiles, (int)wgs2, pl.p2_keys, stat_chunks,
-                           partial, gamma, gbm, n_maxima, scores);
-    else if (pl.n_qtiles == 1)
-        hipLaunchKernelGGL((bf16_pass2_kernel<D, NB, true>), xcd_grid(wgs2), dim3(256), S::bytes,
-                           st, g, pl.n_qtiles, (int)wgs2, pl.p2_keys, stat_chunks, partial,
-                           gamma, gbm, n_maxima, scores);
+    if (g.rows)
+        hipLaunchKernelGGL((bf16_pass2_kernel<D, NB, true>), xcd_grid(wgs2), dim3(256), S::bytes, st, g, (int)wgs2, pl.p2_keys,
+                           stat_chunks, partial, gamma, gbm, n_maxima, scores);
     else
-        hipLaunchKernelGGL((bf16_pass2_kernel<D, NB, false>), xcd_grid(wgs1), dim3(256), S::bytes,
-                           st, g, pl.n_qtiles, (int)wgs1, pl.nchunks, stat_chunks, partial,
-                           gamma, gbm, n_maxima, scores);
+        hipLaunchKernelGGL((bf16_pass2_kernel<D, NB>), xcd_grid(wgs2), dim3(256), S::bytes, st, g, (int)wgs2, pl.p2_keys,
+                           stat_chunks, partial, gamma, gbm, n_maxima, scores);
     return hipGetLastError();
 }
 

@@ -11,40 +11,10 @@ namespace aha {
 // times the maximum raw dot.
 // With ENT the first moment u = sum of exp2(t - m) * (t - m) is kept beside the sum: the
 // row's entropy is ln 2 * (log2 s - u / s) (Sec. 4.2, entropy of a softmax row).
-template <bool MASK, bool ENT, bool LAZY = false>
+template <bool MASK, bool ENT>
 __device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam, int pos, int kb,
                                              int lane, float &m, float &s, float &u) {
     if (MASK) asm volatile("" ::: "memory");
-    if constexpr (!MASK && LAZY) {
-        // (LAZY: full accumulation, where this loop is the kernel; in the windowed kernel the
-        // second code path costs registers that spill.)
-        // Unmasked blocks: `m` is a REFERENCE that sum and moment are relative to, not
-        // necessarily the running maximum (the final statistics m + log2 s and u / s do not
-        // depend on it).  As long as every lane has one, the block is summed against it as it
-        // stands - no maximum over the block's 32 elements - and the reference is only moved
-        // (by the exact update below, which also redoes this block) when a block's sum says
-        // that it has fallen more than 40 binades behind: fp32 has room for that, and a
-        // reference never lies above the largest logit seen, so nothing underflows that the
-        // exact update would have kept.
-        if (__builtin_amdgcn_ballot_w64(m == -INFINITY) == 0) {
-            float sum[4] = {0.f, 0.f, 0.f, 0.f}, mom[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float x = fmaf(acc[mb][v], lam, -m);
-                    const float e = fast_exp2(x);
-                    sum[v & 3] += e;
-                    if (ENT) mom[v & 3] = fmaf(e, x, mom[v & 3]);
-                }
-            const float bs = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-            if (__builtin_amdgcn_ballot_w64(!(bs < 0x1p40f)) == 0) {  // (also: not a NaN)
-                s += bs;
-                if (ENT) u += (mom[0] + mom[1]) + (mom[2] + mom[3]);
-                return;
-            }
-        }
-    }
     float amax = -INFINITY;
 #pragma unroll
     for (int mb = 0; mb < kMB; ++mb)
@@ -290,6 +260,84 @@ __device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, 
         __syncthreads();
     }
     return gmax;
+}
+
+// Work split of several query tiles (score_full.hip, and pass 1 for the row statistics' output).  Query tile `pair` is
+// teamed with tile T-1-pair: a tile of late rows sees many keys, its partner few, together
+// about the same as any other pair.  The pair's work is laid out on a line - the first
+// tile's key steps, the set-up of the partner (`set_up` steps' worth; every workgroup pays
+// one set-up anyway, only a second one counts), the partner's steps - and the line is cut into `nparts` equal ranges.  Segment `seg` (0: first tile,
+// 1: partner) of a workgroup is the part of its range that falls on that tile's steps.
+// A single tile (windowed scores, or the middle tile of an odd count) is cut into equal
+// ranges of steps.
+struct Segment {
+    int qt;          // query tile, -1: no such segment
+    int kbeg, kend;  // keys [kbeg, kend); empty when kbeg >= kend
+};
+template <class Map>
+__device__ __forceinline__ Segment pair_segment(const Map &rm, int rows, int T, int pair,
+                                                int part, int nparts, int seg,
+                                                int step = kWgKeys, int set_up = 1) {
+    const int tA = pair, tB = T - 1 - pair;
+    const bool two = tB != tA;
+    // (chosen accumulator rows - a single tile - may sit anywhere: the whole sequence)
+    const int endA = rm.rows ? rm.n : rm.max_pos(tA * rows, (tA + 1) * rows) + 1;
+    const int endB = two ? rm.max_pos(tB * rows, (tB + 1) * rows) + 1 : 0;
+    const int sA = (endA + step - 1) / step, sB = (endB + step - 1) / step;
+    // positions on the line: first tile's steps start at oA, the partner's at oB
+    const int oA = 0, oB = sA + set_up, V = two ? sA + sB + set_up : sA;
+    const int v0 = (int)((int64_t)part * V / nparts), v1 = (int)((int64_t)(part + 1) * V / nparts);
+    Segment r;
+    if (seg == 0) {
+        r.qt = tA;
+        r.kbeg = (max(v0, oA) - oA) * step;
+        r.kend = min(endA, (min(v1, oA + sA) - oA) * step);
+    } else {
+        r.qt = two ? tB : -1;
+        r.kbeg = (max(v0, oB) - oB) * step;
+        r.kend = min(endB, (min(v1, oB + sB) - oB) * step);
+    }
+    return r;
+}
+
+// Log2-sum-exp2 of one query row from the per-chunk log2-sum-exp2 values that pass 1 left.
+// A batch of values is requested at once (request), so that it travels together with the
+// other loads of the tile set-up, and merged later (merge) into the running (M, sum) with
+// sum = sum over chunks of exp2(value - M).  Both go by groups of eight and skip the
+// groups past the last chunk.
+template <int BATCH>
+__device__ __forceinline__ void chunk_request(const float *src, int stride, int c0, int nchunks,
+                                              float (&e)[BATCH]) {
+    static_assert(BATCH % 8 == 0, "groups of eight");
+#pragma unroll
+    for (int g8 = 0; g8 < BATCH; g8 += 8) {
+        if (c0 + g8 >= nchunks) break;  // uniform
+        // entries past the last chunk re-read it (branch-free, back-to-back loads) and are
+        // neutralised in the merge
+#pragma unroll
+        for (int t = g8; t < g8 + 8; ++t) e[t] = src[(int64_t)min(c0 + t, nchunks - 1) * stride];
+    }
+}
+template <int BATCH>
+__device__ __forceinline__ void chunk_merge(const float (&e)[BATCH], int count, float &M,
+                                            float &sum) {
+    float bm = -INFINITY;
+#pragma unroll
+    for (int g8 = 0; g8 < BATCH; g8 += 8) {
+        if (g8 >= count) break;  // uniform
+#pragma unroll
+        for (int t = g8; t < g8 + 8; ++t) bm = fmaxf(bm, t < count ? e[t] : -INFINITY);
+    }
+    const float mn = fmaxf(M, bm);
+    const float mref = mn == -INFINITY ? 0.f : mn;
+    sum *= fast_exp2(M - mref);
+#pragma unroll
+    for (int g8 = 0; g8 < BATCH; g8 += 8) {
+        if (g8 >= count) break;
+#pragma unroll
+        for (int t = g8; t < g8 + 8; ++t) sum += t < count ? fast_exp2(e[t] - mref) : 0.f;
+    }
+    M = mn;
 }
 
 }  // namespace aha

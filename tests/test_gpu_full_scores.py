@@ -1,0 +1,67 @@
+"""bf16 scores of more rows than one tile holds (plain accumulation and wide windows): ends of tiles, of steps and of query
+heads, both scale modes, the value prior, given normalisers, and logits that outgrow the first keys' by far."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2506_03762_amd import binding as B
+from paper_2506_03762_amd import synth
+from tests import harness as H
+from tests.harness import Opts
+
+SHAPES = [
+    # batch, KV heads, group, window, n, d
+    (1, 2, 1, 513, 513, 128), (1, 1, 1, 1025, 1025, 64),      # one row more than the tiles; a single key in the last step
+    (1, 2, 3, 333, 333, 128), (2, 1, 5, 257, 320, 64),        # ends of heads inside a tile
+    (1, 3, 7, 100, 1111, 128), (1, 1, 6, 87, 700, 64),        # rows of two heads in one wave
+    (1, 1, 2, 2500, 2500, 128), (1, 4, 2, 640, 4000, 64),     # several tiles and parts, odd and even counts
+    (1, 2, 3, 50, 900, 128), (1, 1, 5, 40, 600, 64),          # 129 to 224 rows with a wide pool: tiles of 128 rows
+]
+
+
+def _case(shape, prior, fixed, grow=False):
+    batch, hkv, group, window, n, d = shape
+    w = synth.scaled(synth.C2, name="full", batch=batch, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, seq_len=n,
+                     window=window, budget=max(1, n // 9), recent=min(20, n // 9))
+    wide = group * window <= 224
+    opts = Opts(value_prior=prior or wide, pool=19 if wide else 7, scale_mode=oracle.SCALE_FIXED if fixed else oracle.SCALE_ADAPTIVE,
+                fixed_scale=d ** -0.5 if fixed else 0.0)
+    q, k, v = synth.make_prefill(w)
+    if grow:  # some late keys far along the queries: 2^100 and more times the first ones' weight
+        k = k.copy()
+        k[:, :, n // 2::97] = q[:, ::group, n - 1:n] * 8.0
+    return w, opts, (q, k, v)
+
+
+def _close(got, ref, rtol):
+    # fp32 sums of exact products: logits of x carry x * 1e-6 or so, the relative error of their exponentials
+    np.testing.assert_allclose(got, ref, rtol=rtol, atol=rtol * 1e-3 * ref.mean())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prior,fixed", [(False, True), (True, True), (False, False), (True, False)])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_scores(shape, prior, fixed):
+    w, opts, inputs = _case(shape, prior, fixed)
+    _close(H.run_prefill_gpu(w, opts, inputs).scores, H.run_prefill_oracle(w, opts, inputs).scores, 2e-4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[6]])
+def test_late_keys_that_outweigh_the_first(shape):
+    w, opts, inputs = _case(shape, False, True, grow=True)
+    # (logits of several hundred: 2e-3)
+    _close(H.run_prefill_gpu(w, opts, inputs).scores, H.run_prefill_oracle(w, opts, inputs).scores, 2e-3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[4], SHAPES[7]])
+def test_given_normalisers(shape):
+    import torch
+    w, opts, inputs = _case(shape, True, False)
+    p = H.gpu_params(w, opts)
+    q, k, v = (H.to_device(a, w.dtype) for a in inputs)
+    lse = torch.empty((w.batch, w.n_q_heads, w.window), dtype=torch.float32, device="cuda")
+    B.aha_prefill_row_stats(p.with_strides(q, k, v), q, k, lse, None, B.alloc_workspace(p))
+    got = H.run_scores_from_lse_gpu(w, opts, inputs, lse.cpu().numpy())
+    _close(got, H.run_prefill_oracle(w, opts, inputs).scores, 2e-4)
