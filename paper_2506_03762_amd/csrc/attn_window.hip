@@ -426,8 +426,8 @@ struct WideAttn {
     static constexpr int WAVES = 8, KEYS = 64, CPR = D / 8, RPI = 64 / CPR;
     static constexpr int NI = KEYS / RPI / WAVES;         // load instructions per wave for a step's keys (and values)
     static constexpr int kStages = 4;
-    static constexpr int half = KEYS * D * 2;             // bytes of a step's key rows
-    static constexpr size_t bytes = (size_t)kStages * 2 * half;
+    static constexpr int kbytes = KeyRows<D>::bytes(KEYS), stage = kbytes + KEYS * D * 2;  // a step's key, key and value rows
+    static constexpr size_t bytes = (size_t)kStages * stage;
     static_assert(KEYS % (RPI * WAVES) == 0 && bytes <= 160 * 1024, "whole instructions per wave, one CU's LDS");
 };
 
@@ -483,28 +483,27 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
 
     // The wave's share of a step's rows -> stage st: instruction i = wave + 8 j covers RPI rows, lane
     // -> row lane / CPR, position lane % CPR; the 16-byte chunks of a row are permuted by XOR on the
-    // way (keys: with row mod 8, so that eight lanes reading one chunk of eight rows meet eight
-    // bank groups; values: as above).  Rows past the range re-read its last one.  The loads
+    // way (keys: KeyRows; values: as above).  Rows past the range re-read its last one.  The loads
     // are assembly and the waits for them by hand, for the reason given at ValueRequest; nothing
     // else loads from global memory inside the loop.
     const uint32_t lds0 = uniform((int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem);
-    const int lr = lane / A::CPR, lc = lane % A::CPR;
+    const int lr = lane / A::CPR, lc = lane % A::CPR, place = key_place<D>(lane);
     auto request = [&](int step, int st) {
         const int kb = key_begin + step * A::KEYS;
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int i = wave + A::WAVES * j, r = i * A::RPI + lr;
             const int64_t row = min(kb + r, key_end - 1);
-            const __bf16 *ksrc = kbase + row * g.ks[2] + (lc ^ (r & 7)) * 8;
+            const __bf16 *ksrc = kbase + row * g.ks[2] + (lc ^ KeyRows<D>::swizzle(lr)) * 8;
             const __bf16 *vsrc = vbase + row * g.vs[2] + (lc ^ value_chunk_swizzle<D>(r)) * 8;
-            const uint32_t dst = lds0 + st * (2 * A::half) + i * 1024;
+            const uint32_t dst = lds0 + st * A::stage;
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                          :
-                         : "v"(ksrc), "s"(dst)
+                         : "v"(ksrc), "s"(dst + i * KeyRows<D>::group)
                          : "memory");
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                          :
-                         : "v"(vsrc), "s"(dst + A::half)
+                         : "v"(vsrc), "s"(dst + A::kbytes + i * 1024)
                          : "memory");
         }
     };
@@ -548,7 +547,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         __builtin_amdgcn_sched_barrier(0);
         const int kb = key_begin + i * A::KEYS;
         if (kb > bmax) continue;  // (wave-uniform)
-        const __bf16 *sK = (const __bf16 *)(smem + st * (2 * A::half));
+        const char *sK = smem + st * A::stage;
         f32x16 acc[MB];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -558,7 +557,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
-                const bf16x8 a = *(const bf16x8 *)(sK + (mb * 32 + col) * D + ((2 * ks + hf) ^ (col & 7)) * 8);
+                const bf16x8 a = key_fragment(sK + mb * KeyRows<D>::bytes(32), place, ks);
                 acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], acc[mb], 0, 0, 0);
             }
         // causal limit and the ragged end of the key range
@@ -604,7 +603,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
 #pragma unroll
                 for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
         }
-        const __bf16 *sV = sK + A::half / 2;
+        const __bf16 *sV = (const __bf16 *)(sK + A::kbytes);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll

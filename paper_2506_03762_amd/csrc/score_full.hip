@@ -48,18 +48,6 @@ struct PlaceMap {
     }
 };
 
-// Key rows in LDS: what one load instruction brings, 1 KB or 512 / D rows, lies together, with 64 bytes between; the
-// 16-byte chunks of a row are permuted by XOR, the low two bits of their number, with the row's (d = 128) or the row
-// pair's number mod 4.  So 16 lanes that read one chunk of 16 rows meet 16 different groups of four banks (with XOR by row mod
-// 8 and nothing between half of the cycles of a read were conflicts), and the chunks of a row are two lane
-// offsets and constants.
-template <int D>
-struct KeyRows {
-    static constexpr int CPR = D / 8, RPI = 64 / CPR, group = 1024 + 64;
-    static constexpr int bytes(int rows) { return rows / RPI * group; }
-    static __device__ __forceinline__ int swizzle(int row) { return D == 128 ? row & 3 : (row >> 1) & 3; }
-};
-
 template <int D, int NQ>
 struct FullSmem {
     static constexpr int ROWS = 128 * NQ;
@@ -153,17 +141,6 @@ __device__ __forceinline__ void load_rows_of_wave(const ScoreGeom &g, const Plac
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) qf[q][ks] = *(const bf16x8 *)(p + ks * 16);
     }
-}
-
-// Fragment ks of 32 keys: chunk 2 ks + lane / 32 of row lane % 32; `place`: that of ks = 0.
-template <int D>
-__device__ __forceinline__ int key_place(int lane) {
-    using R = KeyRows<D>;
-    const int row = lane & 31;
-    return row / R::RPI * R::group + row % R::RPI * (D * 2) + ((lane >> 5) ^ R::swizzle(row)) * 16;
-}
-__device__ __forceinline__ bf16x8 key_fragment(const char *keys, int place, int ks) {
-    return *(const bf16x8 *)(keys + (place ^ ((ks & 1) * 32)) + (ks >> 1) * 64);
 }
 
 // The products `acc` of 32 keys (fragments kf) and 32 query rows (qf); with LAST, the last rows for these keys, the key

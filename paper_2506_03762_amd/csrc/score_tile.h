@@ -267,6 +267,28 @@ __device__ __forceinline__ float fold16_over32(const f32x16 &xv, int lane) {
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// Key rows in LDS: what one load instruction brings, 1 KB or 512 / D rows, lies together, with 64 bytes between; the
+// 16-byte chunks of a row are permuted by XOR, the low two bits of their number, with the row's (d = 128) or the row
+// pair's number mod 4.  So 16 lanes that read one chunk of 16 rows meet 16 different groups of four banks (with XOR by row mod
+// 8 and nothing between half of the cycles of a read were conflicts), and the chunks of a row are two lane
+// offsets and constants.
+template <int D>
+struct KeyRows {
+    static constexpr int CPR = D / 8, RPI = 64 / CPR, group = 1024 + 64;
+    static constexpr int bytes(int rows) { return rows / RPI * group; }
+    static __device__ __forceinline__ int swizzle(int row) { return D == 128 ? row & 3 : (row >> 1) & 3; }
+};
+// Fragment ks of 32 keys: chunk 2 ks + lane / 32 of row lane % 32; `place`: that of ks = 0.
+template <int D>
+__device__ __forceinline__ int key_place(int lane) {
+    using R = KeyRows<D>;
+    const int row = lane & 31;
+    return row / R::RPI * R::group + row % R::RPI * (D * 2) + ((lane >> 5) ^ R::swizzle(row)) * 16;
+}
+__device__ __forceinline__ bf16x8 key_fragment(const char *keys, int place, int ks) {
+    return *(const bf16x8 *)(keys + (place ^ ((ks & 1) * 32)) + (ks >> 1) * 64);
+}
+
 // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by
 // their linear index.  The score kernels are launched on a one-dimensional grid of
 // 8 * ceil(total / 8) workgroups and work on the logical index returned here; indices
