@@ -195,6 +195,11 @@ static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
 // Over 3000 shapes of up to 400000 keys times heads 1.32 times as fast, 5 of them slower by more than 3 %.  Slower beyond: full
 // tiles (225 to 256, 481 to 512 rows) of d = 64 with a prior, from a million keys times heads on by up to 6 % (64 x 65536 x 256
 // 494, 515; 64 x 65536 x 512 916, 954).
+// Full tiles that are swept twice, waves that share the keys (win_share): us with the keys in each wave's registers,
+// shared, d = 128: 8 heads x 24576 x 256 55.7, 48.0; 32 x 3000 x 256 38.4, 31.3; 8 x 12000 x 400 51.3, 42.5; 2 x
+// 50000 x 512 52.3, 41.7; 64 x 700 x 512 38.8, 28.0; 2 x 30000 x 256 25.2, 25.2; 64 x 40000 x 256 457, 457; d = 64: 8 x
+// 12000 x 512 39.5, 38.2; 64 x 6000 x 512 91.7, 79.8.  Not taken: d = 64, 8 x 24576 x 256 41.2, 41.7, x 224 39.9, 41.5
+// (half the products per byte of LDS); tiles of 192 rows in places for 256, d = 128, 8 x 24576 x 160 45.8, 46.7.
 static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.win_nb = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -230,6 +235,7 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.win_nb = nb;
     pl.win_tiles = tiles;
     pl.win_hold = hold;
+    pl.win_share = !hold && nb == 8 && (p->head_dim == 128 || tiles == 2);
     pl.win_parts = (int)parts;
     pl.win_keys = (int)keys;
     size_t off = 0;
@@ -636,7 +642,9 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
                  : pl.win_nb && !rows && workspace_bytes >= pl.win_bytes) {
         if ((rc = hip_result(stage(1, st), "stage event")) ||
             (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), given_patience(pl), lse, scores, st)
-                                      : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),
+                                      : pl.win_share
+                                          ? launch_score_share(g, pl, workspace, next_tag(), window_patience(pl), scores, st)
+                                          : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),
                              "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;

@@ -61,7 +61,7 @@ struct PrefillPlan {
     // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
     // prior maxima, announcements and their counts, the value norms and the prior live
     int win_nb, win_tiles, win_parts, win_keys;
-    bool win_hold;
+    bool win_hold, win_share;  // (share: by the kernel whose waves share the keys)
     size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma, win_bytes;
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
@@ -100,6 +100,10 @@ hipError_t launch_score_full(const ScoreGeom &g, const PrefillPlan &pl, void *ws
 // zero; `looks`: at the other workgroups' announcements before missing parts are done in place.
 hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                                float *scores, hipStream_t st);
+// score_share.hip
+// The same with pl.win_share.
+hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+                              float *scores, hipStream_t st);
 // score_given.hip
 // Keys of a range whose norms, prior and column sums (12 bytes) fit beside a tile of nb blocks of query
 // rows (and 1 KB of other values) with two workgroups per CU (up to four blocks) or one.

@@ -135,4 +135,75 @@ __device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, cons
     if (lane == 0) put(x.counts + z, (uint64_t)0);
 }
 
+// Row statistics.
+// The pair held by lane ^ 32.
+__device__ __forceinline__ void from_other_half(float M, float s, float &M2, float &s2) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(M), __float_as_uint(M), false, false);
+    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    const bool hi = threadIdx.x & 32;  // the swap leaves (low half's, high half's) in both
+    M2 = __uint_as_float(hi ? a[0] : a[1]);
+    s2 = __uint_as_float(hi ? c[0] : c[1]);
+}
+
+// (max, sum of exp2(value - max)) of (M, s) and (M2, s2)
+__device__ __forceinline__ void merge_stats(float &M, float &s, float M2, float s2) {
+    const float mn = fmaxf(M, M2), ref = mn == -INFINITY ? 0.f : mn;
+    s = s * fast_exp2(M - ref) + s2 * fast_exp2(M2 - ref);
+    M = mn;
+}
+
+// A wave's share of merging the ranges' values of a problem's ROWS rows: parts wave + WAVES * i, lanes
+// over rows (and parts, for fewer than 64 rows), several loads in flight; its (max, sum) pairs into
+// red[wave][row] (`first`: its entry of row 0).  `ld`: floats between parts.
+template <int ROWS, int WAVES>
+__device__ __forceinline__ void merge_parts(const float *src, int ld, int nparts, float2 *first, int wave, int lane) {
+    constexpr int RW = ROWS < 64 ? ROWS : 64, SUBS = 64 / RW, RPL = (ROWS + 63) / 64;
+    constexpr int BATCH = RPL == 1 ? 8 : 4;  // loads of a row in flight
+    const int sub = lane / RW;
+    const float *p0 = src + lane % RW;
+    float M[RPL], s[RPL];
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) M[r] = -INFINITY, s[r] = 0.f;
+    for (int i0 = 0; wave + WAVES * i0 * SUBS < nparts; i0 += BATCH) {
+        float e[RPL][BATCH];
+#pragma unroll
+        for (int h = 0; h < BATCH; h += 4) {
+            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;  // uniform
+#pragma unroll
+            for (int t = h; t < h + 4; ++t)
+#pragma unroll
+                for (int r = 0; r < RPL; ++r)
+                    e[r][t] = get(p0 + (int64_t)min(wave + WAVES * ((i0 + t) * SUBS + sub), nparts - 1) * ld +
+                                  (ROWS % 64 && r ? min(64, ROWS - 1 - lane % RW) : 64 * r));
+        }
+#pragma unroll
+        for (int h = 0; h < BATCH; h += 4) {
+            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                float bm = -INFINITY, bs = 0.f;
+#pragma unroll
+                for (int t = h; t < h + 4; ++t) {
+                    if (wave + WAVES * ((i0 + t) * SUBS + sub) >= nparts) e[r][t] = -INFINITY;
+                    bm = fmaxf(bm, e[r][t]);
+                }
+                const float ref = bm == -INFINITY ? 0.f : bm;
+#pragma unroll
+                for (int t = h; t < h + 4; ++t) bs += fast_exp2(e[r][t] - ref);
+                merge_stats(M[r], s[r], bm, bs);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        if constexpr (SUBS == 2) {
+            float M2, s2;
+            from_other_half(M[r], s[r], M2, s2);
+            merge_stats(M[r], s[r], M2, s2);
+        }
+        const int row = lane % RW + 64 * r;
+        if (sub == 0 && row < ROWS) first[row] = make_float2(M[r], s[r]);
+    }
+}
+
 }  // namespace aha

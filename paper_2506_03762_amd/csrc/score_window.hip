@@ -10,19 +10,16 @@
 // in the accumulators while the statistics travel.  32 heads x 4096 keys x 64 rows: 29 -> 22 us; bound by
 // the one burst of loads (9 us to the last wave's keys), then one round trip each for announcing,
 // looking and fetching.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
-// window_stream_kernel (below): more rows or longer ranges, the logits formed twice.  8 heads x 16384 x
-// 512 rows 89 -> 67 us, 8 x 32768 x 256 70 -> 67: half of the time vector ALU and matrix core in turns (by the
-// counters; 620 ns per 64 x 32 block and SIMD), the rest set-up, first loads, exchange and the second sweep's start: a
-// workgroup has two steps per sweep there.
+// window_stream_kernel (below): more rows or longer ranges, the logits formed twice, 620 ns per 64 x 32 block and SIMD; full
+// tiles are score_share.hip's, but for those of 256 rows with d = 64.
 //
 // Value rows are loaded as they lie in memory (load_rows); with the key fragments' addressing an instruction
 // reads 32 bytes of 32 rows.  Where the last-level cache would not keep them anyway they go past the caches.  us
 // of the score stage before and after: 48 heads x 6846 keys x 64 rows 59.0, 47.3; 12 x 59081 x 64 108, 92.8; 128 x
-// 16384 x 64 259, 252; 8 x 32768 x 256 70.4, 67.1.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
+// 16384 x 64 259, 252.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
 // With the logits held, value rows and keys take all registers where the range has two steps (d = 128, two row blocks: 9 spilled,
 // 40 bytes a lane, once per step; one block and four steps: 40, for up to 32 rows).
-// Two tiles share their value rows, 32 each, and load them like keys: as memory lies was slower
-// (8 x 16384 x 512, the whole step, 77.8 and 74.7).
+// Two tiles share their value rows, 32 each, and load them like keys (as memory lies was slower).
 #include <type_traits>
 
 #include "exchange.h"
@@ -41,76 +38,6 @@ struct HoldSmem {
     static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
     static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
 };
-
-// The pair held by lane ^ 32.
-__device__ __forceinline__ void from_other_half(float M, float s, float &M2, float &s2) {
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(M), __float_as_uint(M), false, false);
-    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    const bool hi = threadIdx.x & 32;  // the swap leaves (low half's, high half's) in both
-    M2 = __uint_as_float(hi ? a[0] : a[1]);
-    s2 = __uint_as_float(hi ? c[0] : c[1]);
-}
-
-// (max, sum of exp2(value - max)) of (M, s) and (M2, s2)
-__device__ __forceinline__ void merge_stats(float &M, float &s, float M2, float s2) {
-    const float mn = fmaxf(M, M2), ref = mn == -INFINITY ? 0.f : mn;
-    s = s * fast_exp2(M - ref) + s2 * fast_exp2(M2 - ref);
-    M = mn;
-}
-
-// A wave's share of merging the ranges' values of a problem's ROWS rows: parts wave + WAVES * i, lanes
-// over rows (and parts, for fewer than 64 rows), several loads in flight; its (max, sum) pairs into
-// red[wave][row] (`first`: its entry of row 0).  `ld`: floats between parts.
-template <int ROWS, int WAVES>
-__device__ __forceinline__ void merge_parts(const float *src, int ld, int nparts, float2 *first, int wave, int lane) {
-    constexpr int RW = ROWS < 64 ? ROWS : 64, SUBS = 64 / RW, RPL = (ROWS + 63) / 64;
-    constexpr int BATCH = RPL == 1 ? 8 : 4;  // loads of a row in flight
-    const int sub = lane / RW;
-    const float *p0 = src + lane % RW;
-    float M[RPL], s[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) M[r] = -INFINITY, s[r] = 0.f;
-    for (int i0 = 0; wave + WAVES * i0 * SUBS < nparts; i0 += BATCH) {
-        float e[RPL][BATCH];
-#pragma unroll
-        for (int h = 0; h < BATCH; h += 4) {
-            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;  // uniform
-#pragma unroll
-            for (int t = h; t < h + 4; ++t)
-#pragma unroll
-                for (int r = 0; r < RPL; ++r)
-                    e[r][t] = get(p0 + (int64_t)min(wave + WAVES * ((i0 + t) * SUBS + sub), nparts - 1) * ld +
-                                  (ROWS % 64 && r ? min(64, ROWS - 1 - lane % RW) : 64 * r));
-        }
-#pragma unroll
-        for (int h = 0; h < BATCH; h += 4) {
-            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                float bm = -INFINITY, bs = 0.f;
-#pragma unroll
-                for (int t = h; t < h + 4; ++t) {
-                    if (wave + WAVES * ((i0 + t) * SUBS + sub) >= nparts) e[r][t] = -INFINITY;
-                    bm = fmaxf(bm, e[r][t]);
-                }
-                const float ref = bm == -INFINITY ? 0.f : bm;
-#pragma unroll
-                for (int t = h; t < h + 4; ++t) bs += fast_exp2(e[r][t] - ref);
-                merge_stats(M[r], s[r], bm, bs);
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        if constexpr (SUBS == 2) {
-            float M2, s2;
-            from_other_half(M[r], s[r], M2, s2);
-            merge_stats(M[r], s[r], M2, s2);
-        }
-        const int row = lane % RW + 64 * r;
-        if (sub == 0 && row < ROWS) first[row] = make_float2(M[r], s[r]);
-    }
-}
 
 // STEPS: 256-key steps of a workgroup's range, all of whose logits are held: NB * STEPS <= 4.
 // NT = 2: two tiles of rows, eight waves; waves w and w + 4 take the same keys, one tile each.
@@ -716,8 +643,8 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
         return launch_stream<D, NB, NT, NT == 2 && PRIOR ? kValuesCached : PRIOR>(g, pl, x, w, scores, st);
     AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(1, 1, 4) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
     AHA_HOLD(4, 1, 1) AHA_HOLD(3, 2, 1) AHA_HOLD(4, 2, 1)
-    if constexpr (D == 64) { AHA_STREAM(4, 1) }  // (d = 128: held, or two launches)
-    AHA_STREAM(6, 1) AHA_STREAM(8, 1) AHA_STREAM(6, 2) AHA_STREAM(8, 2)
+    if constexpr (D == 64) { AHA_STREAM(4, 1) AHA_STREAM(8, 1) }  // (d = 128: held, or two launches; score_share.hip)
+    AHA_STREAM(6, 1) AHA_STREAM(6, 2)
 #undef AHA_HOLD
 #undef AHA_STREAM
     return hipErrorInvalidValue;
