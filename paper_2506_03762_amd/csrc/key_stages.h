@@ -114,6 +114,13 @@ __device__ __forceinline__ void wait_vm() {
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// M + log2 s.  The logarithm is taken of s's mantissa: that of a sum of hundreds, relative to a reference of the first keys, is
+// rounded down at its own size (with it the normalisers were 1.0e-7 too small on average, 4e-8 with waves that share a
+// range's keys, whose sums are smaller).
+__device__ __forceinline__ float log2_sum(float M, float s) {
+    return (M + (float)__builtin_amdgcn_frexp_expf(s)) + log2f(__builtin_amdgcn_frexp_mantf(s));
+}
+
 // Exact update of a row's (m, s) with 32 keys.
 template <bool MASK>
 __device__ __forceinline__ void exact_stats(const f32x16 &acc, float lam, int pos, int kb, int lane, float &m, float &s) {

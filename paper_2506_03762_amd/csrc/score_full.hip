@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, 2) void full_stats_kernel(ScoreGeom g, int pr,
             const float m2 = __shfl_xor(m[q], 32), s2 = __shfl_xor(s[q], 32);
             const float mn = fmaxf(m[q], m2), mref = mn == -INFINITY ? 0.f : mn;
             const float sum = s[q] * fast_exp2(m[q] - mref) + s2 * fast_exp2(m2 - mref);
-            if (lane < 32) out[32 * q + lane] = mn + log2f(sum);  // -inf for a row that saw no key
+            if (lane < 32) out[32 * q + lane] = log2_sum(mn, sum);  // -inf for a row that saw no key
         }
     };
 
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void full_colsum_kernel(ScoreGeom g, int pr
                 chunk_request(src, S::ROWS, c0, nchunks, ch);
                 chunk_merge(ch, nchunks - c0, M, sum);
             }
-            sL[tid] = p >= 0 ? M + log2f(sum) : INFINITY;
+            sL[tid] = p >= 0 ? log2_sum(M, sum) : INFINITY;
             sLam[tid] = row_scale_log2_f32(g.scale_mode, g.fixed_scale, g.lambda_floor, max(p, 0) + 1, g.budget, g.d);
             sPos[tid] = p;
         }

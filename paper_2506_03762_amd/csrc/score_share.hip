@@ -370,7 +370,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
         if (tid < W::ROWS) {
             float M = sRed[tid].x, total = sRed[tid].y;
             if constexpr (W::KG == 2) merge_stats(M, total, sRed[W::ROWS + tid].x, sRed[W::ROWS + tid].y);
-            put(stats + ((int64_t)z * nparts + part) * W::ROWS + tid, M + log2f(total));
+            put(stats + ((int64_t)z * nparts + part) * W::ROWS + tid, log2_sum(M, total));
         }
         announce(x, z, nparts, part, tid);
         // (what the second sweep begins with travels while the others are waited for, but not in front of wave 0's looks)
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
             const float2 *src = sRed + tid / 256 * MW * 256 + tid % 256;
 #pragma unroll
             for (int wv = 0; wv < MW; ++wv) merge_stats(M, total, src[wv * 256].x, src[wv * 256].y);
-            sL[tid] = tid < g.R ? M + log2f(total) : INFINITY;  // (rows past the last one add nothing)
+            sL[tid] = tid < g.R ? log2_sum(M, total) : INFINITY;  // (rows past the last one add nothing)
         }
         __syncthreads();
 #pragma unroll
