@@ -25,7 +25,7 @@
 // fp32 (the small high-accuracy path): plain vector-ALU kernel, one workgroup per row.
 #include <type_traits>
 
-#include "score_tile.h"
+#include "key_stages.h"
 
 namespace aha {
 
@@ -426,8 +426,9 @@ struct WideAttn {
     static constexpr int WAVES = 8, KEYS = 64, CPR = D / 8, RPI = 64 / CPR;
     static constexpr int NI = KEYS / RPI / WAVES;         // load instructions per wave for a step's keys (and values)
     static constexpr int kStages = 4;
-    static constexpr int kbytes = KeyRows<D>::bytes(KEYS), stage = kbytes + KEYS * D * 2;  // a step's key, key and value rows
-    static constexpr size_t bytes = (size_t)kStages * stage;
+    static constexpr int kbytes = KeyRows<D>::bytes(KEYS), vbytes = KEYS * D * 2;  // a step's key rows, value rows
+    static constexpr int off_values = kStages * kbytes;
+    static constexpr size_t bytes = off_values + kStages * vbytes;
     static_assert(KEYS % (RPI * WAVES) == 0 && bytes <= 160 * 1024, "whole instructions per wave, one CU's LDS");
 };
 
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
                                                                   int units, float *part_o,
                                                                   float2 *part_ms) {
     using A = WideAttn<D>;
-    constexpr int KS = D / 16, CB = D / 32, MB = 2, NI = A::NI, S = A::kStages;
+    constexpr int KS = D / 16, CB = D / 32, MB = 2, NI = A::NI, S = A::kStages, kAhead = 4;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     // (groups of one (problem, key range) on one XCD, as above)
@@ -488,22 +489,32 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
     // else loads from global memory inside the loop.
     const uint32_t lds0 = uniform((int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem);
     const int lr = lane / A::CPR, lc = lane % A::CPR, place = key_place<D>(lane);
+    const KeyRequest<D, A::KEYS, A::WAVES> request_keys(kbase, g.ks[2], key_end, lane, wave, smem);
+    // (the swizzle of row i RPI + lr does not depend on i: RPI is a multiple of 4)
+    const int vchunk = lc ^ value_chunk_swizzle<D>(lr);
+    const uint32_t v_off = (uint32_t)(lr * g.vs[2] * 2) + (uint32_t)(vchunk * 16);
+    const bool v_far = g.vs[2] * 2 * A::RPI >= ((int64_t)1 << 31);  // the token stride does not fit the 32-bit offset
     auto request = [&](int step, int st) {
         const int kb = key_begin + step * A::KEYS;
+        request_keys(kb, st);
+        const uint32_t dst = lds0 + A::off_values + st * A::vbytes + wave * 1024;
+        if (kb + A::KEYS <= key_end && !v_far) {
+            const __bf16 *row0 = vbase + (int64_t)(kb + wave * A::RPI) * g.vs[2];
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                             :
+                             : "v"(v_off), "s"(row0 + (int64_t)(A::WAVES * A::RPI * j) * g.vs[2]),
+                               "s"(dst + j * A::WAVES * 1024)
+                             : "memory");
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
-            const int i = wave + A::WAVES * j, r = i * A::RPI + lr;
-            const int64_t row = min(kb + r, key_end - 1);
-            const __bf16 *ksrc = kbase + row * g.ks[2] + (lc ^ KeyRows<D>::swizzle(lr)) * 8;
-            const __bf16 *vsrc = vbase + row * g.vs[2] + (lc ^ value_chunk_swizzle<D>(r)) * 8;
-            const uint32_t dst = lds0 + st * A::stage;
+            const int64_t row = min(kb + (wave + A::WAVES * j) * A::RPI + lr, key_end - 1);
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                          :
-                         : "v"(ksrc), "s"(dst + i * KeyRows<D>::group)
-                         : "memory");
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                         :
-                         : "v"(vsrc), "s"(dst + A::kbytes + i * 1024)
+                         : "v"(vbase + row * g.vs[2] + vchunk * 8), "s"(dst + j * A::WAVES * 1024)
                          : "memory");
         }
     };
@@ -521,7 +532,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
     }
     const int pos = rm.pos(rho0 + col);  // -1 for rows past the last one: every key masked
-    const int bmin = rm.min_pos(rho0, rho0 + 32), bmax = mine ? rm.max_pos(rho0, rho0 + 32) : -1;
+    const int bmin = mine ? rm.min_pos(rho0, rho0 + 32) : -1;
     const float c_out = kLog2e * rsqrtf((float)D);
     constexpr float kRefSlack = 1.f;  // log2 units
 
@@ -546,20 +557,38 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         request(i + S - 1, st == 0 ? S - 1 : st - 1);
         __builtin_amdgcn_sched_barrier(0);
         const int kb = key_begin + i * A::KEYS;
-        if (kb > bmax) continue;  // (wave-uniform)
-        const char *sK = smem + st * A::stage;
+        // (waves whose rows see none of these keys go on all the same: with a way round, and without, the outputs were
+        // copied between two sets of registers twice a step)
+        const char *sK = smem + st * A::kbytes;
+        // the key fragments are read kAhead contraction steps before their products, the first value fragments in front of
+        // the exponentials (the scheduling barriers keep the reads there)
         f32x16 acc[MB];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
+        bf16x8 kf[kAhead][MB], vf[kAhead];
+        const __bf16 *sV = (const __bf16 *)(smem + A::off_values + st * A::vbytes);
+        auto read_values = [&](int i) { return value_fragment<D>(sV, i / (2 * CB), i / CB % 2, i % CB, lane); };
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < kAhead; ++ks)
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const bf16x8 a = key_fragment(sK + mb * KeyRows<D>::bytes(32), place, ks);
-                acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], acc[mb], 0, 0, 0);
+            for (int mb = 0; mb < MB; ++mb) kf[ks][mb] = key_fragment(sK + mb * KeyRows<D>::bytes(32), place, ks);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks % kAhead][mb], qf[ks], acc[mb], 0, 0, 0);
+            if (ks + kAhead < KS) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    kf[ks % kAhead][mb] = key_fragment(sK + mb * KeyRows<D>::bytes(32), place, ks + kAhead);
+            } else {
+                vf[ks + kAhead - KS] = read_values(ks + kAhead - KS);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // causal limit and the ragged end of the key range
         if (kb + A::KEYS - 1 > bmin || kb + A::KEYS > key_end) {
 #pragma unroll
@@ -570,12 +599,12 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
                     if (key > pos || key >= key_end) acc[mb][v] = -INFINITY;
                 }
         }
-        float amax = -INFINITY;
+        float am[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) amax = fmaxf(amax, acc[mb][v]);
-        amax = combine_lane_xor<32>(amax, OpMax{});
+            for (int v = 0; v < 16; ++v) am[v & 3] = fmaxf(am[v & 3], acc[mb][v]);
+        const float amax = combine_lane_xor<32>(fmaxf(fmaxf(am[0], am[1]), fmaxf(am[2], am[3])), OpMax{});
         // (the reference follows the running maximum lazily, as above; without the maximum, a step
         // summed first and redone if its sum passes 2^8, 52.0 us instead of 50.5)
         const float bm = amax == -INFINITY ? -INFINITY : amax * c_out;
@@ -603,17 +632,14 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
 #pragma unroll
                 for (int v = 0; v < 16; ++v) O[cb][v] *= corr;
         }
-        const __bf16 *sV = (const __bf16 *)(sK + A::kbytes);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    const bf16x8 vf = value_fragment<D>(sV, mb, ks, cb, lane);
-                    O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[mb][ks], O[cb], 0, 0, 0);
-                    if (FINE) O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[mb][ks], O[cb], 0, 0, 0);
-                }
+        for (int i = 0; i < MB * 2 * CB; ++i) {
+            const int mb = i / (2 * CB), ks = i / CB % 2, cb = i % CB;
+            O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % kAhead], pf[mb][ks], O[cb], 0, 0, 0);
+            if (FINE) O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % kAhead], pl[mb][ks], O[cb], 0, 0, 0);
+            if (i + kAhead < MB * 2 * CB) vf[i % kAhead] = read_values(i + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     wait_loads<0>();  // (the last requests, past the range, write to LDS)
     if (!mine) return;
