@@ -24,7 +24,9 @@
 // Bound by the latency of its chain (launch, first loads, six barriers) and, from 8K tokens on,
 // by the one CU that works on a problem.  In-kernel stamps at 8 x 32768 scores (cycles at
 // 2.4 GHz): loads and range 5.4 K, histogram 5.2 K (the LDS atomics' rate), scan 2.0 K, candidates
-// 5.0 K, rank 1.0 K, output 4.5 K.  Against lanes that own consecutive positions (scattered
+// 5.0 K, rank 1.0 K, output 4.5 K with all comparisons made again there; the masks of the candidates' pass, kept on the scalar
+// unit, leave it those of the steps with keys in the threshold bin (back to back 8 x 32768 13.4 -> 12.5 us, 8 x 16384 8.6 ->
+// 8.2, 128 x 16384 8.95 -> 8.65).  Against lanes that own consecutive positions (scattered
 // loads, per-lane bit masks, a second scan), back to back: 2 x 512 scores 5.9 -> 3.4 us,
 // 32 x 4096 6.6 -> 4.8, 12 x 5003 9.0 -> 5.4, 8 x 16384 10.0 -> 8.4, 128 x 16384 11.2 -> 9.5,
 // 8 x 32768 16.1 -> 13.2, 8 x 65536 34.8 -> 31.8, 8 x 120000 290 -> 67.
@@ -209,14 +211,23 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
         for_steps([&](uint32_t u, int t) { c += __popcll(ballot(selected(u, t))); });
         if (lane == 0) sm.wcnt[wave] = c;
     };
-    if (nbin <= kCandMax) {
+    const bool ranked = nbin <= kCandMax;  // (uniform)
+    // of a ranked bin, per step: the lanes whose keys are above it, and whether any are inside
+    constexpr bool KEPT = !LONG;
+    unsigned long long over[KEPT ? ITEMS : 1];
+    uint32_t inside = 0;
+    static_assert(!KEPT || ITEMS <= 32, "a bit per step");
+    if (ranked) {
         // 3a. exact rank among the keys of the threshold bin
         int above = 0;  // keys of this wave above the bin
         for_steps([&](uint32_t u, int t) {
             const bool gt = u > hi, cand = (u >= lo) & !gt;
-            above += __popcll(ballot(gt));
+            const unsigned long long gts = ballot(gt);
+            if constexpr (KEPT) over[t] = gts;
+            above += __popcll(gts);
             const unsigned long long in = ballot(cand);
             if (in) {
+                if (KEPT) inside |= 1u << t;
                 int slot = 0;
                 if (lane == 0) slot = atomicAdd(&sm.ncand, __popcll(in));
                 slot = __builtin_amdgcn_readfirstlane(slot);
@@ -296,11 +307,23 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
     int o = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) o += w < wave ? sm.wcnt[w] : 0;
-    for_steps([&](uint32_t u, int t) {
-        const bool sel = selected(u, t);
-        const unsigned long long m = ballot(sel);
+    auto put = [&](unsigned long long m, bool sel, int t) {
         if (sel) out[mask_rank(m, o)] = base + t * 64 + lane;
         o += __popcll(m);
+    };
+    if constexpr (KEPT) {
+        if (ranked) {  // (the comparisons have been made, but for keys in the bin)
+            for_steps([&](uint32_t u, int t) {
+                unsigned long long m = over[t];
+                if (inside & (1u << t)) m = ballot(selected(u, t));
+                put(m, __builtin_amdgcn_inverse_ballot_w64(m), t);
+            });
+            return;
+        }
+    }
+    for_steps([&](uint32_t u, int t) {
+        const bool sel = selected(u, t);
+        put(ballot(sel), sel, t);
     });
 }
 
