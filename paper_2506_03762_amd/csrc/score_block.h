@@ -50,18 +50,6 @@ __device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam
     m = mn;
 }
 
-// A block's products with keys that a row does not see become -inf, which any update that follows then counts as
-// nothing, given a scale above 0 (hidden_scale); `room`: the row's position less the key of accumulator element 0.
-__device__ __forceinline__ void hide_unseen(f32x16 (&acc)[kMB], int room) {
-    asm volatile("" ::: "memory");  // (else the branch that leads here becomes a choice per element in every block)
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            if (mb * 32 + 8 * (v >> 2) + (v & 3) > room) acc[mb][v] = -INFINITY;  // (acc_key)
-}
-__device__ __forceinline__ float hidden_scale(float lam) { return fmaxf(lam, 1e-30f); }
-
 template <bool MASK>
 __device__ __forceinline__ void colsum_update(const f32x16 (&acc)[kMB], float lam, float L,
                                               int pos, int kb, int lane, f32x16 (&col)[kMB]) {
