@@ -532,7 +532,11 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
     }
     const int pos = rm.pos(rho0 + col);  // -1 for rows past the last one: every key masked
-    const int bmin = mine ? rm.min_pos(rho0, rho0 + 32) : -1;
+    const int bmin = rm.min_pos(rho0, rho0 + 32), bmax = mine ? rm.max_pos(rho0, rho0 + 32) : -1;
+    // Steps up to the last one with a key that a row of the wave sees, none without rows.  Beyond them the wave only requests
+    // its share: what it would multiply by 0 might not be finite, and LDS is shared (us of both launches with all steps multiplied
+    // by all waves, and so: 8 heads x 32768 keys, five blocks 50.3, 43.2, nine 82.9, 69.1, eight 52.1, 52.2).
+    const int seen = uniform(bmax < key_begin ? 0 : min(nsteps, (bmax - key_begin) / A::KEYS + 1));
     const float c_out = kLog2e * rsqrtf((float)D);
     constexpr float kRefSlack = 1.f;  // log2 units
 
@@ -544,11 +548,10 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         for (int v = 0; v < 16; ++v) O[cb][v] = 0.f;
 #pragma unroll
     for (int i = 1; i < S - 1; ++i) request(i, i);
-    int st = 0;
-    for (int i = 0; i < nsteps; ++i, st = st + 1 == S ? 0 : st + 1) {
-        // this wave's loads of step i have landed (those of the S - 2 steps after it may be in
-        // flight); behind the barrier so have all waves', and all waves are done with step i - 1,
-        // whose stage the next request overwrites
+    // this wave's loads of step i have landed (those of the S - 2 steps after it may be in
+    // flight); behind the barrier so have all waves', and all waves are done with step i - 1,
+    // whose stage the next request overwrites
+    auto advance = [&](int i, int st) {
         __builtin_amdgcn_sched_barrier(0);
         wait_loads<2 * NI * (S - 2)>();
         asm volatile("" ::: "memory");
@@ -556,9 +559,12 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
         asm volatile("" ::: "memory");
         request(i + S - 1, st == 0 ? S - 1 : st - 1);
         __builtin_amdgcn_sched_barrier(0);
+    };
+    int i = 0, st = 0;
+    // (a way round inside one loop instead of two: the outputs were copied between two sets of registers twice a step)
+    for (; i < seen; ++i, st = st + 1 == S ? 0 : st + 1) {
+        advance(i, st);
         const int kb = key_begin + i * A::KEYS;
-        // (waves whose rows see none of these keys go on all the same: with a way round, and without, the outputs were
-        // copied between two sets of registers twice a step)
         const char *sK = smem + st * A::kbytes;
         // the key fragments are read kAhead contraction steps before their products, the first value fragments in front of
         // the exponentials (the scheduling barriers keep the reads there)
@@ -641,6 +647,7 @@ __global__ __launch_bounds__(512, 2) void window_attn_wide_kernel(ScoreGeom g, i
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    for (; i < nsteps; ++i, st = st + 1 == S ? 0 : st + 1) advance(i, st);
     wait_loads<0>();  // (the last requests, past the range, write to LDS)
     if (!mine) return;
     const float sc = combine_lane_xor<32>(s, OpSum{});  // the column's sum over both half-waves
