@@ -463,11 +463,17 @@ static hipError_t launch_full(const ScoreGeom &g, const PrefillPlan &pl, void *w
     });
     if (ea != hipSuccess) return ea;
     // Places of a query head: whole waves', unless the tiles become many more (their statistics use the room behind, which
-    // only the row statistics' output needs, too).  Given normalisers stay in the order of the rows; us with the rows'
-    // places in that order, too, and so: 4 x 7 heads x 5000 rows 175, 129, d = 64 141, 97.
+    // only the row statistics' output needs, too).  A further tile costs its products with all keys, whole waves save masks for
+    // the share r / n of them; where the chip holds all workgroups at once it costs nothing.  us with the rows' places in their
+    // order, and so: 16 x 8 heads x 263 of 4208 rows, d = 64, 9 tiles or 10, 77, 95 (not taken); 16 x 3 x 400 of 12822, 5 or 6,
+    // 158, 213 (not taken), of 1941, d = 64, 40.4, 36.9; 1 x 3 x 1450 of 5800, d = 64, 17 or 18, 35.1, 30.8; 32 x 3 x 899 of
+    // 1168, 11 or 12, 87.8, 76.1; 4 x 4 x 4891 of 9782, d = 64, 77 either way, 345, 264.  Given normalisers stay in the order of
+    // the rows; us with their places so, too, and whole waves: 4 x 7 heads x 5000 rows 175, 129, d = 64 141, 97.
     int pr = g.r, tiles = pl.n_qtiles;
     const int64_t padded = (int64_t)(g.r + 32 * NQ - 1) / (32 * NQ) * (32 * NQ), padded_tiles = (g.G * padded + S::ROWS - 1) / S::ROWS;
-    if (4 * padded_tiles <= 5 * (int64_t)pl.n_qtiles) pr = (int)padded, tiles = (int)padded_tiles;
+    const int64_t more = padded_tiles - pl.n_qtiles, padded_wgs = (padded_tiles + 1) / 2 * pl.Z * pl.nchunks;
+    if (4 * more <= pl.n_qtiles && (padded_wgs <= 512 || 5 * more * g.n <= 2 * (int64_t)pl.n_qtiles * g.r))
+        pr = (int)padded, tiles = (int)padded_tiles;
     const int64_t wgs = (int64_t)pl.nchunks * ((tiles + 1) / 2) * pl.Z;
     if (!have_lse)
         hipLaunchKernelGGL((full_stats_kernel<D, NQ>), xcd_grid(wgs), dim3(256), S::keys, st, g, pr, tiles, pl.nchunks, (int)wgs,

@@ -103,3 +103,14 @@ def test_time_of_given_normalisers():
         calls.append(lambda p=p, q=q, k=k, v=v, lse=lse, s=scores, ws=ws: B.aha_prefill_scores_lse(p, q, k, v, lse, s, ws))
     t = _time(calls)
     assert t[0] < 1.15 * t[1], t
+
+
+@pytest.mark.gpu
+def test_time_of_rows_that_fill_no_tile():
+    """Windows of 3 x 400 rows fill 5 tiles, 6 with whole waves to a head: us in six 205 against 160 of 3 x 384 rows, in five 165."""
+    calls = []
+    for window in (400, 384):
+        args = _random(16, 3, window, 12822, 128)
+        calls.append(lambda args=args: B.aha_prefill_scores(*args))
+    t = _time(calls)
+    assert t[0] < 1.15 * t[1], t
