@@ -284,6 +284,27 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
     pl.given_bytes = off;
 }
 
+// Several query tiles (score_full.hip).
+// Places of a query head: whole waves', unless the tiles become many more (their statistics use the room behind, which only
+// the row statistics' output needs, too).  A further tile costs its products with all keys, whole waves save masks for the
+// share r / n of them; where the chip holds all workgroups at once it costs nothing.  us with the rows' places in their order,
+// and so: 16 x 8 heads x 263 of 4208 rows, d = 64, 9 tiles or 10, 77, 95 (not taken); 16 x 3 x 400 of 12822, 5 or 6, 158, 213
+// (not taken), of 1941, d = 64, 40.4, 36.9; 1 x 3 x 1450 of 5800, d = 64, 17 or 18, 35.1, 30.8; 32 x 3 x 899 of 1168, 11 or 12,
+// 87.8, 76.1; 4 x 4 x 4891 of 9782, d = 64, 77 either way, 345, 264.  (No more workgroups than a launch takes, 2^32 threads.)
+static void plan_full(const aha_params *p, PrefillPlan &pl) {
+    const int64_t G = p->n_q_heads / p->n_kv_heads, wave_rows = pl.NB * 8;
+    pl.full_pr = p->window;
+    pl.full_tiles = pl.n_qtiles;
+    pl.full_parts = pl.full_sum_parts = pl.nchunks;
+    if (pl.n_qtiles == 1) return;
+    const int64_t padded = (p->window + wave_rows - 1) / wave_rows * wave_rows, tiles = (G * padded + pl.qtile - 1) / pl.qtile;
+    const int64_t more = tiles - pl.n_qtiles, wgs = (tiles + 1) / 2 * pl.Z * pl.nchunks;
+    if (4 * more <= pl.n_qtiles && (wgs <= 512 || (wgs < 1 << 24 && 5 * more * p->seq_len <= 2 * (int64_t)pl.n_qtiles * p->window))) {
+        pl.full_pr = (int)padded;
+        pl.full_tiles = (int)tiles;
+    }
+}
+
 // Workspace layout of aha_prefill_scores.
 static PrefillPlan plan_prefill(const aha_params *p) {
     PrefillPlan pl{};
@@ -313,6 +334,7 @@ static PrefillPlan plan_prefill(const aha_params *p) {
         pl.chunk_keys = (int)(((steps + want - 1) / want) * kP2Keys);
         // windowed pass 2 (one tile) walks over the same key ranges, several steps per workgroup
         pl.p2_keys = pl.chunk_keys;
+        plan_full(p, pl);
     } else {
         pl.NB = 0;
         pl.qtile = 1;

@@ -55,6 +55,9 @@ struct PrefillPlan {
     int nchunks;     // pass-1 key chunks per (problem, query tile)
     int p2_keys;     // keys per pass-2 workgroup (a multiple of kP2Keys)
     int n_vtiles;    // value-prior tiles per problem (separate launch)
+    // bf16 scores of several query tiles (score_full.hip): places of a query head and the tiles they fill, parts of a tile
+    // pair's keys in the row statistics and in the column sums
+    int full_pr, full_tiles, full_parts, full_sum_parts;
     bool f32_mfma;   // fp32 scores on the matrix core (pass 1 in nchunks key ranges)
     bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
     // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
@@ -72,10 +75,11 @@ struct PrefillPlan {
 
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup
 constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)
+constexpr int kFullKeys = 64;     // keys of a step with several query tiles
 
 // value_prior.hip
 // `lse`, when not null, holds the caller's natural-log row normalisers
-// [batch, Hq, window]; the launch then also writes them, in the log2 domain, where pass 2
+// [batch, Hq, window]; the launch then also writes them, in the log2 domain, where and in the order in which pass 2
 // expects the row statistics (and the score launchers skip pass 1).
 // `prior_here`: this launch forms the value prior (the windowed bf16 scores and the fp32 scores
 // form it inside their row-statistics launch instead).  Launches nothing when there is nothing to do.

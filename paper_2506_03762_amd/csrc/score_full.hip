@@ -21,7 +21,6 @@
 
 namespace aha {
 
-constexpr int kFullKeys = 64;    // keys of a step
 constexpr int kFullStages = 4;   // steps whose keys LDS holds
 constexpr int kFullSetup = 2;    // a tile's set-up, in steps
 
@@ -231,10 +230,9 @@ __global__ __launch_bounds__(256, 2) void full_stats_kernel(ScoreGeom g, int pr,
 // exchange between the half-waves and one addition in LDS per key; with the keys on M the sums of every
 // 32 keys would have to be folded over 32 lanes.  A row's scale (unless it is one for all rows, FIXED) and
 // normaliser are then 16 values of a lane per 32 rows, in registers.
-// `given_rows`: 0, or the normalisers were given, so many to a problem, in the order of the rows (one "chunk").
 template <int D, int NQ, bool FIXED, bool PRIOR>
 __global__ __launch_bounds__(256, 2) void full_colsum_kernel(ScoreGeom g, int pr, int n_qtiles, int nparts, int total_wgs,
-                                                             int nchunks, int given_rows, const float *partial, const float *gamma,
+                                                             int nchunks, const float *partial, const float *gamma,
                                                              const float *gblockmax, int n_vtiles, float *scores) {
     using S = FullSmem<D, NQ>;
     constexpr int KS = D / 16, NI = KeyRequest<D, kFullKeys, 4>::NI + (PRIOR ? 1 : 0), EP = 16 / KS;
@@ -351,8 +349,7 @@ __global__ __launch_bounds__(256, 2) void full_colsum_kernel(ScoreGeom g, int pr
             constexpr int kBatch = 8;
             float ch[kBatch];
             const int rho = rho0 + tid, p = rm.pos(rho);
-            const float *src = given_rows ? partial + (int64_t)z * given_rows + (p >= 0 ? rho / pr * g.r + rho % pr : 0)
-                                          : partial + ((int64_t)(z * n_qtiles + qt) * nchunks) * S::ROWS + tid;
+            const float *src = partial + ((int64_t)(z * n_qtiles + qt) * nchunks) * S::ROWS + tid;
             float M = -INFINITY, sum = 0.f;
             for (int c0 = 0; c0 < nchunks; c0 += kBatch) {
                 chunk_request(src, S::ROWS, c0, nchunks, ch);
@@ -462,27 +459,16 @@ static hipError_t launch_full(const ScoreGeom &g, const PrefillPlan &pl, void *w
         return hipSuccess;
     });
     if (ea != hipSuccess) return ea;
-    // Places of a query head: whole waves', unless the tiles become many more (their statistics use the room behind, which
-    // only the row statistics' output needs, too).  A further tile costs its products with all keys, whole waves save masks for
-    // the share r / n of them; where the chip holds all workgroups at once it costs nothing.  us with the rows' places in their
-    // order, and so: 16 x 8 heads x 263 of 4208 rows, d = 64, 9 tiles or 10, 77, 95 (not taken); 16 x 3 x 400 of 12822, 5 or 6,
-    // 158, 213 (not taken), of 1941, d = 64, 40.4, 36.9; 1 x 3 x 1450 of 5800, d = 64, 17 or 18, 35.1, 30.8; 32 x 3 x 899 of
-    // 1168, 11 or 12, 87.8, 76.1; 4 x 4 x 4891 of 9782, d = 64, 77 either way, 345, 264.  Given normalisers stay in the order of
-    // the rows; us with their places so, too, and whole waves: 4 x 7 heads x 5000 rows 175, 129, d = 64 141, 97.
-    int pr = g.r, tiles = pl.n_qtiles;
-    const int64_t padded = (int64_t)(g.r + 32 * NQ - 1) / (32 * NQ) * (32 * NQ), padded_tiles = (g.G * padded + S::ROWS - 1) / S::ROWS;
-    const int64_t more = padded_tiles - pl.n_qtiles, padded_wgs = (padded_tiles + 1) / 2 * pl.Z * pl.nchunks;
-    if (4 * more <= pl.n_qtiles && (padded_wgs <= 512 || 5 * more * g.n <= 2 * (int64_t)pl.n_qtiles * g.r))
-        pr = (int)padded, tiles = (int)padded_tiles;
-    const int64_t wgs = (int64_t)pl.nchunks * ((tiles + 1) / 2) * pl.Z;
+    const int pr = pl.full_pr, tiles = pl.full_tiles;
+    const int64_t pairs = (int64_t)((tiles + 1) / 2) * pl.Z, wgs = pl.full_parts * pairs, wgs2 = pl.full_sum_parts * pairs;
     if (!have_lse)
-        hipLaunchKernelGGL((full_stats_kernel<D, NQ>), xcd_grid(wgs), dim3(256), S::keys, st, g, pr, tiles, pl.nchunks, (int)wgs,
+        hipLaunchKernelGGL((full_stats_kernel<D, NQ>), xcd_grid(wgs), dim3(256), S::keys, st, g, pr, tiles, pl.full_parts, (int)wgs,
                            partial);
     if (mid) (void)hipEventRecord(mid, st);
-    const int stat_chunks = have_lse ? 1 : pl.nchunks, given_rows = have_lse ? pl.n_qtiles * S::ROWS : 0;
-#define AHA_COLSUM(FIXED, PRIOR)                                                                                        \
-    hipLaunchKernelGGL((full_colsum_kernel<D, NQ, FIXED, PRIOR>), xcd_grid(wgs), dim3(256), S::bytes2, st, g, pr, tiles, \
-                       pl.nchunks, (int)wgs, stat_chunks, given_rows, partial, gamma, gbm, pl.n_vtiles, scores)
+    const int stat_chunks = have_lse ? 1 : pl.full_parts;
+#define AHA_COLSUM(FIXED, PRIOR)                                                                                         \
+    hipLaunchKernelGGL((full_colsum_kernel<D, NQ, FIXED, PRIOR>), xcd_grid(wgs2), dim3(256), S::bytes2, st, g, pr, tiles, \
+                       pl.full_sum_parts, (int)wgs2, stat_chunks, partial, gamma, gbm, pl.n_vtiles, scores)
     if (g.scale_mode == AHA_SCALE_FIXED) {
         if (g.value_prior) AHA_COLSUM(true, true);
         else AHA_COLSUM(true, false);

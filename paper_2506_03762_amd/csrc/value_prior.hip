@@ -19,19 +19,16 @@ template <int ESIZE>
 __global__ __launch_bounds__(256) void vprior_kernel(ScoreGeom g, int n_vtiles, float *gamma,
                                                      float *gblockmax,
                                                      float *zero_scores, const float *lse,
-                                                     float *row_stats, int rows_pad) {
+                                                     float *row_stats, int rows_pad, int pr) {
     const int z = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x;
     if (lse) {
         // the caller's row normalisers (natural log, [batch, Hq, window]) -> log2 domain, in
-        // the order of the flattened query rows of each KV head (padding rows: unused)
+        // the order of each KV head's places, pr per query head (those without a row: unused)
         const int b = z / g.Hkv, h = z % g.Hkv;
-        for (int rho = tile * 256 + tid; rho < rows_pad; rho += gridDim.x * 256) {
-            float L = 0.f;
-            if (rho < g.R) {
-                const int gi = rho / g.r, ii = rho - gi * g.r;
-                L = lse[((int64_t)b * g.Hq + h * g.G + gi) * g.r + ii] * kLog2e;
-            }
-            row_stats[(int64_t)z * rows_pad + rho] = L;
+        for (uint32_t at = tile * 256 + tid; at < (uint32_t)rows_pad; at += gridDim.x * 256) {
+            const int gi = at / (uint32_t)pr, ii = at - gi * pr;
+            const bool row = gi < g.G && ii < g.r;
+            row_stats[(int64_t)z * rows_pad + at] = row ? lse[((int64_t)b * g.Hq + h * g.G + gi) * g.r + ii] * kLog2e : 0.f;
         }
     }
     if (zero_scores && tile < n_vtiles) {
@@ -58,13 +55,13 @@ hipError_t launch_value_prior(const ScoreGeom &g, const PrefillPlan &pl, void *w
     // where pass 2 reads the row statistics: one chunk per (problem, tile, row) on the bf16
     // path (rows padded to whole tiles), one value per row on the fp32 path
     float *row_stats = (float *)(w + (g.dtype == AHA_BF16 ? pl.off_partial : pl.off_rowL));
-    const int rows_pad = g.dtype == AHA_BF16 ? pl.n_qtiles * pl.qtile : g.R;
+    const int rows_pad = g.dtype == AHA_BF16 ? pl.full_tiles * pl.qtile : g.R, pr = g.dtype == AHA_BF16 ? pl.full_pr : g.r;
     if (g.dtype == AHA_BF16)
         hipLaunchKernelGGL(vprior_kernel<2>, grid, dim3(256), 0, st, gl, pl.n_vtiles, gamma, gbm,
-                           zero_scores, lse, row_stats, rows_pad);
+                           zero_scores, lse, row_stats, rows_pad, pr);
     else
         hipLaunchKernelGGL(vprior_kernel<4>, grid, dim3(256), 0, st, gl, pl.n_vtiles, gamma, gbm,
-                           zero_scores, lse, row_stats, rows_pad);
+                           zero_scores, lse, row_stats, rows_pad, pr);
     return hipGetLastError();
 }
 
