@@ -291,6 +291,12 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
 // and so: 16 x 8 heads x 263 of 4208 rows, d = 64, 9 tiles or 10, 77, 95 (not taken); 16 x 3 x 400 of 12822, 5 or 6, 158, 213
 // (not taken), of 1941, d = 64, 40.4, 36.9; 1 x 3 x 1450 of 5800, d = 64, 17 or 18, 35.1, 30.8; 32 x 3 x 899 of 1168, 11 or 12,
 // 87.8, 76.1; 4 x 4 x 4891 of 9782, d = 64, 77 either way, 345, 264.  (No more workgroups than a launch takes, 2^32 threads.)
+// Parts of a pair's keys: as many as the chip holds at once, down to one or two steps each in the column sums, rather two
+// where a CU gets two of them (32 x 7 heads x 160 rows 28.3 us, 31.0 with one); the row statistics leave a value per row and
+// part, so no more of them than the workspace has chunks.  us in nchunks parts, and so: given normalisers, few pairs, parts of
+// a step of 256 keys: 1 x 2 heads x 300 of 2676 rows, d = 64 15.7, 10.4, 2 x 1020 of 4080 21.4, 14.4; both kernels, 520 and
+// more workgroups for 512 places: 8 x 2 x 1237 of 3711 67.8, 52.1, 8 x 2867 of 5734 90.6, 72.9.  Not taken: two parts for
+// three, 4 x 7 x 4395, d = 64 138, 150, 8 x 3 x 4654 of 6050 264, 279.
 static void plan_full(const aha_params *p, PrefillPlan &pl) {
     const int64_t G = p->n_q_heads / p->n_kv_heads, wave_rows = pl.NB * 8;
     pl.full_pr = p->window;
@@ -303,6 +309,10 @@ static void plan_full(const aha_params *p, PrefillPlan &pl) {
         pl.full_pr = (int)padded;
         pl.full_tiles = (int)tiles;
     }
+    const int64_t pairs = (int64_t)((pl.full_tiles + 1) / 2) * pl.Z, steps = (p->seq_len + kFullKeys - 1) / kFullKeys;
+    const int64_t held = std::min(512 / pairs, std::max(2 * steps / 3, std::min(steps, 256 / pairs)));  // parts
+    if (held >= pl.nchunks || (held >= 3 && steps >= 2 * held)) pl.full_sum_parts = (int)held;
+    pl.full_parts = std::min(pl.nchunks, pl.full_sum_parts);
 }
 
 // Workspace layout of aha_prefill_scores.
