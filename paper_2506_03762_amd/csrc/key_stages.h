@@ -116,9 +116,12 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 
 // M + log2 s.  The logarithm is taken of s's mantissa: that of a sum of hundreds, relative to a reference of the first keys, is
 // rounded down at its own size (with it the normalisers were 1.0e-7 too small on average, 4e-8 with waves that share a
-// range's keys, whose sums are smaller).
+// range's keys, whose sums are smaller).  The mantissa lies around 1, so that a single value, s = 1, stays as it is: from 0.5
+// on, M + 1 - 1, given normalisers around 0.69 made the scores 5.0e-8 to 5.8e-8 wrong (rms) instead of 3.5e-8.
 __device__ __forceinline__ float log2_sum(float M, float s) {
-    return (M + (float)__builtin_amdgcn_frexp_expf(s)) + log2f(__builtin_amdgcn_frexp_mantf(s));
+    const float m = __builtin_amdgcn_frexp_mantf(s);
+    const bool low = m < 0.70710678f;
+    return (M + (float)(__builtin_amdgcn_frexp_expf(s) - (low ? 1 : 0))) + log2f(low ? 2.f * m : m);
 }
 
 // Exact update of a row's (m, s) with 32 keys.
