@@ -132,3 +132,29 @@ def test_time_of_rows_that_fill_no_tile():
         calls.append(lambda args=args: B.aha_prefill_scores(*args))
     t = _time(calls)
     assert t[0] < 1.15 * t[1], t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[3], SHAPES[4], SHAPES[5], SHAPES[7], SHAPES[8], SHAPES[9]])
+def test_token_major(shape, given):
+    """Neighbouring tokens of a head lie a row of all heads apart: as from heads that lie together (sums by atomics)."""
+    import torch
+    batch, hkv, group, window, n, d = shape
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    heads = [torch.randn((batch, h, n, d), generator=gen, device="cuda", dtype=torch.bfloat16) for h in (hkv * group, hkv, hkv)]
+    tokens = [t.transpose(1, 2).contiguous().transpose(1, 2) for t in heads]
+    got = []
+    for q, k, v in (heads, tokens):
+        p = B.Params(batch=batch, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, seq_len=n, window=window, budget=n // 9,
+                     recent=0, pool_kernel=19 if group * window <= 224 else 7).with_strides(q, k, v)
+        ws = B.alloc_workspace(p)
+        ws.fill_(0xA5)
+        scores = torch.full((batch, hkv, n), float("nan"), device="cuda")
+        if given:
+            lse = torch.full((batch, hkv * group, window), 7.0, device="cuda")
+            B.aha_prefill_scores_lse(p, q, k, v, lse, scores, ws)
+        else:
+            B.aha_prefill_scores(p, q, k, v, scores, ws)
+        got.append(scores)
+    torch.testing.assert_close(got[1], got[0], rtol=1e-5, atol=0)
