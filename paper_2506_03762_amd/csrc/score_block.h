@@ -50,6 +50,37 @@ __device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam
     m = mn;
 }
 
+// A block's products with keys that a row does not see become -inf, which counts as nothing in any update that follows, given
+// a scale above 0 and, in the column sums, a normaliser above -inf (below); `room`: the row's position less the key of
+// accumulator element 0.  A scale of (almost) 0 goes into the products instead.
+constexpr float kLeastScale = 1e-30f;
+__device__ __forceinline__ void hide_unseen(f32x16 (&acc)[kMB], int room, float &lam) {
+    asm volatile("" ::: "memory");  // (else the branch that leads here becomes a choice per element in every block)
+    if (__builtin_amdgcn_ballot_w64(lam < kLeastScale) != 0) {
+        const float f = lam < kLeastScale ? lam / kLeastScale : 1.f;
+        lam = fmaxf(lam, kLeastScale);
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][v] *= f;
+    }
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (mb * 32 + 8 * (v >> 2) + (v & 3) > room) acc[mb][v] = -INFINITY;  // (acc_key)
+}
+// Hidden products whose row has no normaliser L (`none`: NaN, or -inf): the keys that the row sees get NaN, the others nothing.
+__device__ __forceinline__ void hide_from_no_normaliser(f32x16 (&acc)[kMB], int room, bool none, float &L) {
+    asm volatile("" ::: "memory");
+    L = none ? 0.f : L;
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (none && mb * 32 + 8 * (v >> 2) + (v & 3) <= room) acc[mb][v] = __builtin_nanf("");
+}
+
 template <bool MASK>
 __device__ __forceinline__ void colsum_update(const f32x16 (&acc)[kMB], float lam, float L,
                                               int pos, int kb, int lane, f32x16 (&col)[kMB]) {

@@ -48,6 +48,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
     static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
     constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
+    constexpr bool HIDE = STEPS == 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wave = uniform((int)threadIdx.x >> 6), tile = NT == 2 ? wave >> 2 : 0, kw = wave & 3;
     __bf16 *sQ = (__bf16 *)(smem + tile * S::stride);
@@ -106,6 +107,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         for (int nb = 0; nb < NB; ++nb) {
             lam[nb] = sLam[nb * 32 + (lane & 31)];
             pos[nb] = sPos[nb * 32 + (lane & 31)];
+            if (HIDE && pos[nb] < 0) lam[nb] = kLeastScale;  // (no row)
             bmin[nb] = uniform(sBlk[NB + nb]);
             m[nb] = -INFINITY;
             s[nb] = 0.f;
@@ -127,7 +129,12 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             for (int nb = 0; nb < NB; ++nb) {
                 mma_block_stream<D, NB>(a, sQ, nb, nb + 1 < NB ? nb + 1 : 0, lane, qf, acc[st][nb]);
                 if (nb == NB - 1 && st + 1 < STEPS) load_a<D>(kbase, g.ks[2], kb_of(st + 1), key_end, lane, a);
-                if (kb + kWaveKeys - 1 > bmin[nb])
+                // (Masked products are hidden once for both updates where the range has one step: the wave whose keys end the
+                // sequence holds its problem up, 32 heads x 4096 keys x 64 rows 30.0 -> 29.7 us; with two steps and all
+                // registers taken 128 x 16384 x 64 340 -> 352.  A masked update left beside it for the rare rows below costs all that it gains.)
+                const bool masked = kb + kWaveKeys - 1 > bmin[nb];
+                if (HIDE && masked) hide_unseen(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), lam[nb]);
+                if (!HIDE && masked)
                     stats_update<true, false>(acc[st][nb], lam[nb], pos[nb], kb, lane, m[nb], s[nb], u);
                 else
                     stats_update<false, false>(acc[st][nb], lam[nb], 0, kb, lane, m[nb], s[nb], u);
@@ -215,7 +222,10 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             for (int v = 0; v < 16; ++v) col[mb][v] = 0.f;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            if (kb + kWaveKeys - 1 > bmin[nb])
+            const bool masked = kb + kWaveKeys - 1 > bmin[nb], none = !(L[nb] > -INFINITY);
+            if (HIDE && masked && __builtin_amdgcn_ballot_w64(none) != 0)
+                hide_from_no_normaliser(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), none, L[nb]);
+            if (!HIDE && masked)
                 colsum_update<true>(acc[st][nb], lam[nb], L[nb], pos[nb], kb, lane, col);
             else
                 colsum_update<false>(acc[st][nb], lam[nb], L[nb], 0, kb, lane, col);

@@ -34,14 +34,18 @@ def _scores(p, q, k, v):
     return scores
 
 
-@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_a_row_that_is_not_finite(shape, bad):
     import torch
     p, q, k, v = _inputs(shape, shape[4] ** -0.5)
+    k[..., 0] = k[..., 0].abs() + 0.5
     want = _scores(p, q, k, v)
     at = p.seq_len - 40
-    q[:, ::shape[1], at] = bad
+    if bad < 0:  # (every product -inf)
+        q[:, ::shape[1], at, 0] = bad
+    else:
+        q[:, ::shape[1], at] = bad
     got = _scores(p, q, k, v)
     assert not torch.isfinite(got[..., :at + 1]).any()
     # (the last bits may differ: a row without a finite sum takes the other rows of its wave the exact way; sums by atomics)
