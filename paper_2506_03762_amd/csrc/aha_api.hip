@@ -189,12 +189,13 @@ static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
 //  - 65 to 128 rows, d = 64, longer problems, swept twice: 6 x 46683 x 126 52.7, 36.3 (d = 128, bound by its
 //    bytes: 8 x 29221 x 128 48.3, 48.9, not taken).
 //  - 129 to 256 rows, held by eight waves where one workgroup per CU covers the problem (16 x 1117 x 152
-//    32.1, 19.1; 32 x 1502 x 256 30.0, 22.2), else swept twice (24 x 32929 x 160 236, 159; 6 x 29092 x
-//    256 66.7, 52.4; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
-//  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 57.8, 33.0; 8 x 9057 x 504 64.6, 56.0).
-// Over 3000 shapes of up to 400000 keys times heads 1.32 times as fast, 5 of them slower by more than 3 %.  Slower beyond: full
-// tiles (225 to 256, 481 to 512 rows) of d = 64 with a prior, from a million keys times heads on by up to 6 % (64 x 65536 x 256
-// 494, 515; 64 x 65536 x 512 916, 954).
+//    22.9, 17.1; 32 x 1502 x 256 32.8, 20.4), else swept twice (24 x 32929 x 160 163, 126; 6 x 29092 x
+//    256 68.5, 47.7; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
+//  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 46.7, 30.4, d = 64 35.3, 22.2; 8 x 9057 x 504 56.3, 42.6, d = 64
+//    42.5, 37.6; 64 x 65536 x 512, d = 64 881, 877).
+// Over 160 shapes of 129 to 512 rows, 700 to 65536 keys, 1 to 64 heads (two launches of several tiles: score_full.hip's) one
+// launch is the slower one in three: 8 x 17721 x 224 without a prior 36.7, 38.1; 8 x 2567 x 384 31.3, 33.4; 1 x 1219 x 384, d =
+// 64, 24.0, 25.0.
 // Full tiles that are swept twice, waves that share the keys (win_share): us with the keys in each wave's registers,
 // shared, d = 128: 8 heads x 24576 x 256 55.7, 48.0; 32 x 3000 x 256 38.4, 31.3; 8 x 12000 x 400 51.3, 42.5; 2 x
 // 50000 x 512 52.3, 41.7; 64 x 700 x 512 38.8, 28.0; 2 x 30000 x 256 25.2, 25.2; 64 x 40000 x 256 457, 457; d = 64: 8 x

@@ -2,15 +2,16 @@
 // keys (key_stages.h; the exchanges: exchange.h).
 //
 // A workgroup of eight waves owns a CU and a range of keys.  First sweep: the range's row statistics, which are
-// exchanged; second sweep, from the last keys to the first, which the caches still hold: the column sums, kept in LDS, and
-// beside them the norms of the range's value rows; then the ranges' largest priors are exchanged and the scores written.
+// exchanged; second sweep, from the last keys to the first: the column sums, kept in LDS, and beside them the norms of the
+// range's value rows (both come from memory or the last-level cache, hardly any from an L2: 203 MB past the L2s at 8 heads x
+// 32768 keys x 256 rows, whose keys are 67 MB, and the value rows as much); then the ranges' largest priors are exchanged and the scores written.
 // The value rows are left to the second sweep because the first one waits for the keys from memory, and nothing but
 // the last factor needs them.
 //
 // us of the step (scores, top-k, compaction) against waves that keep 64 keys in registers and read the rows from LDS: 8 heads x
-// 16384 keys x 512 rows 73.1 -> 59.8, 8 x 32768 x 256 81.7 -> 77.6.  In the latter (stamps, us): first keys 8, first sweep
+// 16384 keys x 512 rows 73.1 -> 59.8 (77.3 -> 66.1 on another box), 8 x 32768 x 256 81.7 -> 77.6.  In the latter (stamps, us): first keys 8, first sweep
 // 18, announced to seen 3.5, merged 1.6, second sweep 22, prior and its exchange 4; 537 and 690 ns per 64 x 32 block and
-// SIMD, where the matrix core and the vector ALU would take 400 together: the sweeps read 134 MB in 40 us besides, a
+// SIMD, where the matrix core and the vector ALU would take 400 together: the sweeps read 200 MB in 40 us besides, a
 // barrier per 64 keys.  Steps on the way: value rows three steps of 64 keys ahead instead of one of 128, 81.6 -> 77.6; value
 // rows beside the first sweep and the wave-private keys, 84.4 instead of 83.5.
 #include <type_traits>
