@@ -56,7 +56,7 @@ __device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam
 constexpr float kLeastScale = 1e-30f;
 __device__ __forceinline__ void hide_unseen(f32x16 (&acc)[kMB], int room, float &lam) {
     asm volatile("" ::: "memory");  // (else the branch that leads here becomes a choice per element in every block)
-    if (__builtin_amdgcn_ballot_w64(lam < kLeastScale) != 0) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(lam < kLeastScale) != 0, 0)) {
         const float f = lam < kLeastScale ? lam / kLeastScale : 1.f;
         lam = fmaxf(lam, kLeastScale);
 #pragma unroll

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const bool masked = kb + kWaveKeys - 1 > bmin[nb], none = !(L[nb] > -INFINITY);
-            if (HIDE && masked && __builtin_amdgcn_ballot_w64(none) != 0)
+            if (HIDE && __builtin_expect(masked && __builtin_amdgcn_ballot_w64(none) != 0, 0))
                 hide_from_no_normaliser(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), none, L[nb]);
             if (!HIDE && masked)
                 colsum_update<true>(acc[st][nb], lam[nb], L[nb], pos[nb], kb, lane, col);
