@@ -20,7 +20,7 @@ static hipError_t stage(int i, hipStream_t st) {
     return g_stage_on ? hipEventRecord(g_stage_ev[i], st) : hipSuccess;
 }
 
-// Looks at the other workgroups' announcements before a workgroup does missing parts itself, at most: 1.4 us each
+// Looks at the other workgroups' parts before a workgroup does missing ones itself, at most: 1.4 us each
 // (fewer: patience).
 constexpr int32_t kLooks = 4000;
 
@@ -241,10 +241,9 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
     pl.win_keys = (int)keys;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
-    pl.off_wstats = take(sizeof(float) * (size_t)pl.Z * parts * tiles * nb * 32);
-    pl.off_wmax = take(8 * sizeof(float) * (size_t)pl.Z * parts);  // per wave
-    pl.off_wtags = take(sizeof(uint64_t) * (size_t)pl.Z * parts);
-    pl.off_wcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
+    pl.off_wstats = take(8 * (size_t)pl.Z * parts * tiles * nb * 32);  // (words of 16 bytes: two values and the tag)
+    pl.off_wmax = take((pl.win_share ? 16 : 8 * 16) * (size_t)pl.Z * parts);  // per wave
+    pl.off_wwords = take(kExchangeBytes * (size_t)pl.Z);
     if (!hold && p->value_prior) {
         pl.off_wnu = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
         pl.off_wgamma = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
@@ -279,8 +278,8 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
     if (p->value_prior) {
-        pl.off_gtags = take(2 * sizeof(uint64_t) * (size_t)pl.Z * parts);
-        pl.off_gcounts = take(sizeof(uint64_t) * (size_t)pl.Z);
+        pl.off_gmax = take(16 * (size_t)pl.Z * parts);
+        pl.off_gwords = take(kExchangeBytes * (size_t)pl.Z);
     }
     pl.given_bytes = off;
 }

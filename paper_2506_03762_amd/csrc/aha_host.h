@@ -62,17 +62,18 @@ struct PrefillPlan {
     bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
     // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
     // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
-    // prior maxima, announcements and their counts, the value norms and the prior live
+    // prior maxima, epochs and counts (exchange.h), the value norms and the prior live
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold, win_share;  // (share: by the kernel whose waves share the keys)
-    size_t off_wstats, off_wmax, off_wtags, off_wcounts, off_wnu, off_wgamma, win_bytes;
+    size_t off_wstats, off_wmax, off_wwords, off_wnu, off_wgamma, win_bytes;
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
-    size_t off_gtags, off_gcounts, given_bytes;
+    size_t off_gmax, off_gwords, given_bytes;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;  // of the layout of two launches
 };
 
+constexpr int kExchangeBytes = 256;  // per problem: count and epoch of an exchange inside a launch
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup
 constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)
 constexpr int kFullKeys = 64;     // keys of a step with several query tiles
@@ -101,7 +102,7 @@ hipError_t launch_score_full(const ScoreGeom &g, const PrefillPlan &pl, void *ws
                              hipEvent_t mid, bool have_lse);
 // score_window.hip
 // Windowed scores in one launch (pl.win_nb > 0).  `tag`: a number no other call uses, its low 20 bits
-// zero; `looks`: at the other workgroups' announcements before missing parts are done in place.
+// zero; `looks`: at the other workgroups' parts before missing ones are done in place.
 hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                                float *scores, hipStream_t st);
 // score_share.hip

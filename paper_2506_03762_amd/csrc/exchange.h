@@ -1,22 +1,27 @@
 // Exchange between the workgroups of one problem inside one launch: every workgroup leaves its
-// part of a result in the workspace, announces it, and uses the others' parts once all of them
-// are announced.
+// part of a result in the workspace, and uses the others' parts once all of them are there.
 //
 // No cache is written back or invalidated for it (a device-scope release does that for the whole
-// L2 of an XCD, microseconds per workgroup): what is exchanged is stored and loaded with relaxed
-// agent-scope accesses, which go past the caches that are not shared, and an announcement is
-// stored once the wave's counter of outstanding accesses says that its data has arrived
-// (announce).  512 workgroups, 16 to 64 to a problem: 1.5 to 3 us from the first store to the last
-// load.
+// L2 of an XCD, microseconds per workgroup): what is exchanged is stored and loaded with agent-scope
+// accesses, which go past the caches that are not shared, and it carries a TAG beside the values (Words),
+// so a reader looks at the data itself, nothing waits for stores to arrive, and there is one trip to memory each way.  With
+// announcements behind the data, which a wave looked at before all fetched the data, it was three.  us of the step before and after:
+// 12 heads x 5003 keys x 120 rows 23.5 -> 21.2, 32 x 4096 x 64 31.6 -> 31.1, 128 x 16384 x 64 338 -> 336, 8 x 16384 x 512 65.6 ->
+// 63.2, 8 x 32768 x 256 79.5 -> 77.0.
+// A line that every wave of a launch reads is slow: with the problems' counts and epochs (below) side by side and the epoch read by
+// each wave 8 x 32768 x 256 took 80.4 and 32 x 4096 x 64 31.8, with a line per problem and one reader per workgroup 78.2 and 30.7.  Taken
+// back: the priors' maxima looked for together with the row statistics (32 x 4096 0.9 slower: they come later), or
+// requested before these are merged (0.3 slower).
 //
-// An announcement is the call's TAG, a 64-bit number that no other call of the process uses, so
-// the workspace needs no clearing launch (3 us) in front: whatever it holds on entry is not this
-// tag.  A captured graph replays a call with its tag, so the workgroup that is the last of its problem to have
-// seen all announcements clears them.  It is found by a counter that starts itself: its upper
-// bits are the tag's, and an arrival that finds other bits there sets them.
+// The tag is a 64-bit number that no other call of the process uses, so the workspace needs no clearing launch
+// (3 us) in front: whatever it holds on entry is not this tag.  A captured graph replays a call with
+// its tag, so a number in the workspace, one per problem and whatever it is on entry, is added to it, and
+// the workgroup that is the last of its problem to have seen all parts moves that number on (everybody has read it by then).  It is
+// found by a counter that starts itself: its upper bits are the call's number, and an arrival that finds other
+// bits there sets them.
 //
-// Nobody depends on workgroups that may not be running: after `looks` looks at the announcements a
-// workgroup does missing parts itself and announces them too (a part's result is the same bits whoever
+// Nobody depends on workgroups that may not be running: after `looks` looks at the others' parts a
+// workgroup does missing parts itself and leaves them too (a part's result is the same bits whoever
 // forms it).  The workgroups that have waited in vain share what is missing, so together they are done in
 // about the time that the missing ones would have taken, and `looks` is a few times that (patience in
 // aha_api.hip): beside other work that keeps half of a problem's workgroups out, waiting costs about
@@ -24,14 +29,16 @@
 #pragma once
 
 #include "aha_dev.h"
+#include "aha_host.h"
 
 namespace aha {
 
 struct Exchange {
-    uint64_t *tags;    // [problem][part], or [problem][part][2] (announce_value)
-    uint64_t *counts;  // [problem]
-    uint64_t tag;      // of this call; the low kCountBits are zero, the rest is not
-    int looks;         // at the announcements before missing parts are done here
+    uint64_t *words;  // [problem][kExchangeBytes / 8], in memory lines of its own: a count, a number that is added to the tag
+    uint64_t tag;     // of this call; the low kCountBits are zero, the rest is not
+    int looks;        // at the others' parts before missing ones are done here
+    __device__ __forceinline__ uint64_t *count(int z) const { return words + (int64_t)z * (kExchangeBytes / 8); }
+    __device__ __forceinline__ uint64_t *epoch(int z) const { return count(z) + 1; }
 };
 constexpr int kCountBits = 20;  // parts of a problem: fewer than 2^20
 
@@ -44,95 +51,98 @@ __device__ __forceinline__ T get(const T *p) {
     return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Every thread's put()s so far belong to part `part` of problem z: wait until they have arrived,
-// then announce the part.  Called by the whole workgroup; one barrier.
-__device__ __forceinline__ void announce(const Exchange &x, int z, int nparts, int part, int tid) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) put(x.tags + (int64_t)z * nparts + part, x.tag);
-}
-
-// A part of problem z that has not been announced after x.looks looks, nparts if there is none.  Of several the one
-// nearest to the workgroup's own by exclusive or, so that each begins with another one.  Called by one wave of workgroup `own` (more of them would get in the way of the data's loads);
-// every lane gets the result.
-__device__ __forceinline__ int first_missing(const Exchange &x, int z, int nparts, int own, int lane) {
-    const uint64_t *t = x.tags + (int64_t)z * nparts;
-    int missing;
-    for (int look = 0;; ++look) {
-        missing = INT32_MAX;
-        for (int p = lane; p < nparts; p += kWave)
-            if (get(t + p) != x.tag) missing = min(missing, p ^ own);
-        if (__builtin_amdgcn_ballot_w64(missing != INT32_MAX) == 0) return nparts;
-        if (look >= x.looks) break;
-        __builtin_amdgcn_s_sleep(4);
+// What a part leaves goes as words of 16 bytes that carry the tag beside two floats: {value, tag, value, tag}, the
+// tag's lower and upper half, stored and loaded in one piece (each half proves its own float
+// if they ever were not).
+struct Words {
+    __amdgpu_buffer_rsrc_t at;
+    uint32_t lo, hi;  // tag halves
+    // (a problem's words lie within 2^31 bytes)
+    __device__ __forceinline__ Words(void *base, uint64_t tag)
+        : at(__builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000)),
+          lo(__builtin_amdgcn_readfirstlane((int)(uint32_t)tag)), hi(__builtin_amdgcn_readfirstlane((int)(uint32_t)(tag >> 32))) {}
+    static constexpr int kAgent = 16;  // (sc1: past the caches that are not shared)
+    __device__ __forceinline__ void put(int word, float a, float b) const {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(a), lo, __float_as_uint(b), hi}, at, word * 16, 0, kAgent);
     }
-    return reduce_lanes<1, 64>(missing, OpMinI{}) ^ own;
+    __device__ __forceinline__ u32x4 get(int word) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(at, word * 16, 0, kAgent);
+    }
+    __device__ __forceinline__ bool there(u32x4 w) const { return w.y == lo && w.w == hi; }
+};
+
+// The words `load(t)` of N parts `part(t)` (nparts and more: none, and what it loads is not used), all requested before the
+// first is looked at; what is not there is asked for again, up to `looks` times.  The least (part ^ own) of a lane's missing
+// parts, INT32_MAX if there is none: of several parts the one nearest to the workgroup's own by exclusive or, so
+// that each begins with another one.
+template <int N, class Part, class Load>
+__device__ __forceinline__ int look_for(const Words &x, int nparts, int own, int looks, u32x4 (&w)[N], Part &&part, Load &&load) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) w[t] = load(t);
+    for (int look = 0;; ++look) {
+        int missing = INT32_MAX;
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+            if (part(t) < nparts && !x.there(w[t])) missing = min(missing, part(t) ^ own);
+        if (__builtin_amdgcn_ballot_w64(missing != INT32_MAX) == 0 || look >= looks) return missing;
+        __builtin_amdgcn_s_sleep(4);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+            if (__builtin_amdgcn_ballot_w64(part(t) < nparts && !x.there(w[t])) != 0) w[t] = load(t);
+    }
+}
+// The least over the wave, for the workgroup's decision.
+__device__ __forceinline__ int least_missing(int missing) {
+    return __builtin_amdgcn_ballot_w64(missing != INT32_MAX) == 0 ? INT32_MAX : reduce_lanes<1, 64>(missing, OpMinI{});
 }
 
-// Where all that a part leaves is one float, the announcement carries it: two words per part, the tag with
-// one half of the value in its low bits each, both of which a reader has to find.  One trip to memory
-// each way instead of two, and nothing to wait for in between.
-__device__ __forceinline__ void announce_value(const Exchange &x, int z, int nparts, int part, float value, int tid) {
-    if (tid >= 2) return;
-    const uint32_t bits = __float_as_uint(value);
-    put(x.tags + ((int64_t)z * nparts + part) * 2 + tid, x.tag | (tid ? bits >> 16 : bits & 0xffffu));
-}
-// first_missing() of such parts; the largest value (none is below 0) if there is none missing.  Two parts per
-// lane at a time, and only by lanes that still miss one: waiting workgroups then stay out of the way
-// of those that announce.
-__device__ __forceinline__ int largest_value(const Exchange &x, int z, int nparts, int own, int lane, float &largest) {
-    const uint64_t *t = x.tags + (int64_t)z * nparts * 2;
+// The largest of EACH values (none below 0) per part, one to a word, over all parts, by `threads` threads; the wave's
+// largest, and what is missing, as look_for().
+template <int EACH>
+__device__ __forceinline__ int largest_of(const Words &x, int nparts, int own, int looks, int tid, int threads, float &largest) {
+    const int words = EACH * nparts;
+    int missing = INT32_MAX;
     largest = 0.f;
-    for (int p0 = 0; p0 < nparts; p0 += 2 * kWave) {
-        int missing = p0 + lane;  // of this lane's parts
-        for (int look = 0;; ++look) {
-            if (missing < nparts) {
-                const int p1 = min(p0 + kWave + lane, nparts - 1);
-                const uint64_t lo0 = get(t + 2 * (p0 + lane)), hi0 = get(t + 2 * (p0 + lane) + 1);
-                const uint64_t lo1 = get(t + 2 * p1), hi1 = get(t + 2 * p1 + 1);
-                const bool there0 = ((lo0 ^ x.tag) | (hi0 ^ x.tag)) >> kCountBits == 0;
-                const bool there1 = ((lo1 ^ x.tag) | (hi1 ^ x.tag)) >> kCountBits == 0;
-                if (there0 && there1) {
-                    const float a = __uint_as_float((uint32_t)(lo0 & 0xffffu) | (uint32_t)(hi0 & 0xffffu) << 16);
-                    const float b = __uint_as_float((uint32_t)(lo1 & 0xffffu) | (uint32_t)(hi1 & 0xffffu) << 16);
-                    largest = fmaxf(largest, fmaxf(a, b));
-                }
-                missing = there0 ? (there1 ? nparts : p1) : p0 + lane;
-            }
-            if (__builtin_amdgcn_ballot_w64(missing < nparts) == 0) break;
-            if (look >= x.looks)
-                return reduce_lanes<1, 64>(missing < nparts ? missing ^ own : INT32_MAX, OpMinI{}) ^ own;
-            __builtin_amdgcn_s_sleep(4);
-        }
+    for (int p0 = tid; p0 - (tid & 63) < words; p0 += 2 * threads) {
+        u32x4 w[2];
+        auto at = [&](int t) { return p0 + t * threads; };
+        missing = look_for(x, nparts, own, looks, w, [&](int t) { return at(t) < words ? at(t) / EACH : INT32_MAX; },
+                           [&](int t) { return x.get(min(at(t), words - 1)); });
+        if (__builtin_amdgcn_ballot_w64(missing != INT32_MAX) != 0) break;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (at(t) < words) largest = fmaxf(largest, __uint_as_float(w[t].x));
     }
     largest = wave_max(largest);
-    return nparts;
+    return missing;
 }
 
-// The count of a problem's workgroups that have seen all announcements, so that the last one can clear
-// them.  Whoever does part 0 sets it to the tag (unless somebody else has) before announcing that part:
+// The count of a problem's workgroups that have seen all parts, so that the last one can move the epoch on.
+// Whoever does part 0 sets it to the tag (unless somebody else has) before leaving that part's words:
 // nobody counts himself before.  One thread of the workgroup: `look` early, `start` some time
-// before announce(), which waits for it.
+// before, `started` (its wave) in front of the barrier before the first word.  It also reads the number that is added to the
+// tag, for the workgroup.
 struct Count {
-    uint64_t found;
-    __device__ __forceinline__ void look(const Exchange &x, int z) { found = get(x.counts + z); }
+    uint64_t found, epoch;
+    __device__ __forceinline__ void look_epoch(const Exchange &x, int z) { epoch = get(x.epoch(z)); }
+    __device__ __forceinline__ void look(const Exchange &x, int z) { found = get(x.count(z)); }
     __device__ __forceinline__ void start(const Exchange &x, int z) {
         if ((found ^ x.tag) >> kCountBits)
-            (void)__hip_atomic_compare_exchange_strong(x.counts + z, &found, x.tag, __ATOMIC_RELAXED,
+            (void)__hip_atomic_compare_exchange_strong(x.count(z), &found, x.tag, __ATOMIC_RELAXED,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // once per workgroup, when it has seen all announcements
+    __device__ __forceinline__ void started() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+    // once per workgroup, when it has seen all parts
     __device__ __forceinline__ void arrive(const Exchange &x, int z) {
-        found = __hip_atomic_fetch_add(x.counts + z, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        found = __hip_atomic_fetch_add(x.count(z), (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
-// By the whole wave of the thread that arrived (its last lane), at the end of the workgroup's work.  WORDS: of
-// an announcement.
-template <int WORDS = 1>
-__device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, const Count &c, int lane) {
-    if (__builtin_amdgcn_ballot_w64(lane == kWave - 1 && c.found == x.tag + (uint64_t)(nparts - 1)) == 0) return;
-    for (int p = lane; p < WORDS * nparts; p += kWave) put(x.tags + (int64_t)z * nparts * WORDS + p, (uint64_t)0);
-    if (lane == 0) put(x.counts + z, (uint64_t)0);
+// By the thread that arrived, at the end of the workgroup's work.
+__device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, const Count &c) {
+    if (c.found != x.tag + (uint64_t)(nparts - 1)) return;
+    put(x.epoch(z), c.epoch + 1);
+    put(x.count(z), (uint64_t)0);
 }
 
 // Row statistics.
@@ -152,58 +162,76 @@ __device__ __forceinline__ void merge_stats(float &M, float &s, float M2, float 
     M = mn;
 }
 
+// The pair held by lane ^ 16.
+__device__ __forceinline__ void from_other_row(float M, float s, float &M2, float &s2) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(M), __float_as_uint(M), false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    const bool odd = threadIdx.x & 16;
+    M2 = __uint_as_float(odd ? a[0] : a[1]);
+    s2 = __uint_as_float(odd ? c[0] : c[1]);
+}
+
+// A row's value (log2-sum-exp2 of a range) of threads 0 .. ROWS - 1, two rows to a word; `first`: the part's first word.
+__device__ __forceinline__ void put_rows(const Words &x, int first, int tid, float value) {
+    const float other = from_lane_xor<1>(value);
+    if ((tid & 1) == 0) x.put(first + (tid >> 1), value, other);
+}
+
 // A wave's share of merging the ranges' values of a problem's ROWS rows: parts wave + WAVES * i, lanes
-// over rows (and parts, for fewer than 64 rows), several loads in flight; its (max, sum) pairs into
-// red[wave][row] (`first`: its entry of row 0).  `ld`: floats between parts.
+// over pairs of rows (and parts, for fewer than 128 rows), several loads in flight; its (max, sum) pairs into
+// `first` (its entry of row 0).  `word0`: of part 0; `ld`: words between parts.  What is missing, as look_for().
 template <int ROWS, int WAVES>
-__device__ __forceinline__ void merge_parts(const float *src, int ld, int nparts, float2 *first, int wave, int lane) {
-    constexpr int RW = ROWS < 64 ? ROWS : 64, SUBS = 64 / RW, RPL = (ROWS + 63) / 64;
-    constexpr int BATCH = RPL == 1 ? 8 : 4;  // loads of a row in flight
-    const int sub = lane / RW;
-    const float *p0 = src + lane % RW;
-    float M[RPL], s[RPL];
+__device__ __forceinline__ int merge_parts(const Words &x, int word0, int ld, int nparts, int own, int looks, float2 *first,
+                                           int wave, int lane) {
+    constexpr int WORDS = ROWS / 2, LW = WORDS <= 16 ? 16 : WORDS <= 32 ? 32 : 64, SUBS = 64 / LW;
+    constexpr int WPL = (WORDS + 63) / 64, BATCH = WPL == 1 ? 8 : 4;  // words of a lane and part; parts in flight
+    const int sub = lane / LW, at = min(lane % LW, WORDS - 1);
+    float M[WPL][2], s[WPL][2];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) M[r] = -INFINITY, s[r] = 0.f;
+    for (int r = 0; r < WPL; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) M[r][c] = -INFINITY, s[r][c] = 0.f;
     for (int i0 = 0; wave + WAVES * i0 * SUBS < nparts; i0 += BATCH) {
-        float e[RPL][BATCH];
+        u32x4 e[WPL * BATCH];
+        auto part = [&](int t) { return wave + WAVES * ((i0 + t / WPL) * SUBS + sub); };
+        const int missing = look_for(x, nparts, own, looks, e, part, [&](int t) {
+            return x.get(word0 + min(part(t), nparts - 1) * ld + (t % WPL ? min(64 + at, WORDS - 1) : at));
+        });
+        if (__builtin_amdgcn_ballot_w64(missing != INT32_MAX) != 0) return missing;
 #pragma unroll
-        for (int h = 0; h < BATCH; h += 4) {
-            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;  // uniform
+        for (int r = 0; r < WPL; ++r)
 #pragma unroll
-            for (int t = h; t < h + 4; ++t)
+            for (int c = 0; c < 2; ++c) {
+                float v[BATCH], bm = -INFINITY, bs = 0.f;
 #pragma unroll
-                for (int r = 0; r < RPL; ++r)
-                    e[r][t] = get(p0 + (int64_t)min(wave + WAVES * ((i0 + t) * SUBS + sub), nparts - 1) * ld +
-                                  (ROWS % 64 && r ? min(64, ROWS - 1 - lane % RW) : 64 * r));
-        }
-#pragma unroll
-        for (int h = 0; h < BATCH; h += 4) {
-            if (wave + WAVES * (i0 + h) * SUBS >= nparts) break;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                float bm = -INFINITY, bs = 0.f;
-#pragma unroll
-                for (int t = h; t < h + 4; ++t) {
-                    if (wave + WAVES * ((i0 + t) * SUBS + sub) >= nparts) e[r][t] = -INFINITY;
-                    bm = fmaxf(bm, e[r][t]);
+                for (int t = 0; t < BATCH; ++t) {
+                    v[t] = part(t * WPL) < nparts ? __uint_as_float(c ? e[t * WPL + r].z : e[t * WPL + r].x) : -INFINITY;
+                    bm = fmaxf(bm, v[t]);
                 }
                 const float ref = bm == -INFINITY ? 0.f : bm;
 #pragma unroll
-                for (int t = h; t < h + 4; ++t) bs += fast_exp2(e[r][t] - ref);
-                merge_stats(M[r], s[r], bm, bs);
+                for (int t = 0; t < BATCH; ++t) bs += fast_exp2(v[t] - ref);
+                merge_stats(M[r][c], s[r][c], bm, bs);
             }
-        }
     }
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        if constexpr (SUBS == 2) {
+    for (int r = 0; r < WPL; ++r) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
             float M2, s2;
-            from_other_half(M[r], s[r], M2, s2);
-            merge_stats(M[r], s[r], M2, s2);
+            if constexpr (SUBS >= 2) {
+                from_other_half(M[r][c], s[r][c], M2, s2);
+                merge_stats(M[r][c], s[r][c], M2, s2);
+            }
+            if constexpr (SUBS == 4) {
+                from_other_row(M[r][c], s[r][c], M2, s2);
+                merge_stats(M[r][c], s[r][c], M2, s2);
+            }
         }
-        const int row = lane % RW + 64 * r;
-        if (sub == 0 && row < ROWS) first[row] = make_float2(M[r], s[r]);
+        const int word = lane % LW + 64 * r;
+        if (sub == 0 && word < WORDS) *(f32x4 *)(first + 2 * word) = f32x4{M[r][0], s[r][0], M[r][1], s[r][1]};
     }
+    return INT32_MAX;
 }
 
 }  // namespace aha

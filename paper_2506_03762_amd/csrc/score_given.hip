@@ -53,7 +53,7 @@ __device__ __forceinline__ void masked_colsum(const f32x16 (&acc)[kMB], float la
 
 // WAVES: 4 with up to four row blocks (two workgroups per CU), 8 with more (one).
 template <int D, int NB, int WAVES, int PRIOR>
-__global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
+__global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x, u32x4 *maxima,
                                                                      const float *lse, float *scores) {
     using S = TileSmem<D, NB>;
     using W = GivenSmem<D, NB, PRIOR != 0>;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
     set_range(own);
     Count count;
     PriorHalo<D> halo;
-    if (PRIOR && own == 0 && threadIdx.x == THREADS - 1) count.look(x, z);
+    if (PRIOR && own == 0 && threadIdx.x == 63) count.look(x, z);
     bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block (or value rows) load while one multiplies
     {
         constexpr int NBL = NB / HALVES;  // row blocks that 256 threads load
@@ -130,6 +130,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         if (PRIOR) store_halo(halo, tid);
     }
     __syncthreads();
+    if (PRIOR && threadIdx.x == 63) count.look_epoch(x, z);
 
     // (one base for what a lane reads per block: scale, position, normaliser)
     int at = threadIdx.x & 31;
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63;
         for (int part = own;;) {
-            if (part == 0 && tid == THREADS - 1) {
+            if (part == 0 && tid == 63) {
                 if (own != 0) count.look(x, z);
                 count.start(x, z);
             }
@@ -232,15 +233,18 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             __syncthreads();
             float gm = wave_max(pool_norms(g, key_begin, key_end, sN, sGam, tid, THREADS));
             if (lane == 0) sMax[wave] = gm;
-            // (the count, where this workgroup started it, has to be there first)
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (part == 0 && wave == 0) count.started();
             __syncthreads();
             if (wave == 0) {
                 gm = sMax[0];
 #pragma unroll
                 for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
-                announce_value(x, z, nparts, part, gm, tid);
-                const int missing = largest_value(x, z, nparts, own, lane, gm);
+                const uint64_t tag = x.tag + count.epoch;  // (of the last lane)
+                const Words priors(maxima + (int64_t)z * nparts,
+                                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(tag >> 32), 63) << 32 |
+                                       (uint32_t)__builtin_amdgcn_readlane((int)tag, 63));
+                if (lane == 0) priors.put(part, gm, 0.f);
+                const int missing = least_missing(largest_of<1>(priors, nparts, own, x.looks, lane, 64, gm));
                 if (lane == 0) {
                     *sMissing = missing;
                     sMax[0] = gm;
@@ -248,10 +252,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             }
             __syncthreads();
             const int missing = *sMissing;
-            if (missing == nparts && part == own) break;
+            if (missing == INT32_MAX && part == own) break;
             // somebody is not there: its norms are formed here (and no more waiting); in the end the own
             // ones again, whose prior the LDS has to hold
-            part = missing < nparts ? missing : own;
+            part = missing != INT32_MAX ? missing ^ own : own;
             x.looks = 0;
             __syncthreads();
             set_range(part);
@@ -262,18 +266,18 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             }
             store_halo(halo, tid);
         }
-        if (tid == THREADS - 1) count.arrive(x, z);
+        if (tid == 63) count.arrive(x, z);
         const float ginv = prior_inverse(sMax[0]);
         float *out = scores + (int64_t)z * g.n;
         for (int j = key_begin + tid; j < key_end; j += THREADS)
             out[j] = sSum[j - key_begin] * prior_factor(sGam[j - key_begin], ginv);
-        if (wave == WAVES - 1) leave<2>(x, z, nparts, count, lane);
+        if (tid == 63) leave(x, z, nparts, count);
     }
 }
 
 // ---------------------------------------------------------------- launch --
 template <int D, int NB, int WAVES, int PRIOR>
-static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, const float *lse, float *scores,
+static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, u32x4 *maxima, const float *lse, float *scores,
                            hipStream_t st) {
     using W = GivenSmem<D, NB, PRIOR != 0>;
     const auto kernel = window_given_kernel<D, NB, WAVES, PRIOR>;
@@ -285,19 +289,19 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.given_parts)), dim3(64 * WAVES), W::bytes, st, g,
-                       pl.given_parts, pl.given_keys, x, lse, scores);
+                       pl.given_parts, pl.given_keys, x, maxima, lse, scores);
     return hipGetLastError();
 }
 
 template <int D, int PRIOR>
-static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, const float *lse, float *scores,
+static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exchange &x, u32x4 *maxima, const float *lse, float *scores,
                            hipStream_t st) {
     switch (pl.given_nb) {
-        case 1: return launch_t<D, 1, 4, PRIOR>(g, pl, x, lse, scores, st);
-        case 2: return launch_t<D, 2, 4, PRIOR>(g, pl, x, lse, scores, st);
-        case 4: return launch_t<D, 4, 4, PRIOR>(g, pl, x, lse, scores, st);
-        case 6: return launch_t<D, 6, 8, PRIOR>(g, pl, x, lse, scores, st);
-        case 8: return launch_t<D, 8, 8, PRIOR>(g, pl, x, lse, scores, st);
+        case 1: return launch_t<D, 1, 4, PRIOR>(g, pl, x, maxima, lse, scores, st);
+        case 2: return launch_t<D, 2, 4, PRIOR>(g, pl, x, maxima, lse, scores, st);
+        case 4: return launch_t<D, 4, 4, PRIOR>(g, pl, x, maxima, lse, scores, st);
+        case 6: return launch_t<D, 6, 8, PRIOR>(g, pl, x, maxima, lse, scores, st);
+        case 8: return launch_t<D, 8, 8, PRIOR>(g, pl, x, maxima, lse, scores, st);
     }
     return hipErrorInvalidValue;
 }
@@ -305,11 +309,12 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                               const float *lse, float *scores, hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_gtags), (uint64_t *)(w + pl.off_gcounts), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_gwords), tag, looks};
+    u32x4 *maxima = (u32x4 *)(w + pl.off_gmax);
     auto launch = [&](auto prior) {
         constexpr int PRIOR = decltype(prior)::value;
-        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, lse, scores, st)
-                         : launch_d<128, PRIOR>(g, pl, x, lse, scores, st);
+        return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, maxima, lse, scores, st)
+                         : launch_d<128, PRIOR>(g, pl, x, maxima, lse, scores, st);
     };
     if (!g.value_prior) return launch(std::integral_constant<int, kNoValues>{});
     return g.v_once ? launch(std::integral_constant<int, kValuesOnce>{}) : launch(std::integral_constant<int, kValuesCached>{});

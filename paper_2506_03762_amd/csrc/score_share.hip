@@ -36,8 +36,8 @@ struct ShareSmem {
     static constexpr int off_row = off_col + 4 * 8 * 64 * 4;  // normaliser, scale, position
     static constexpr int off_misc = off_row + 3 * ROWS * 4;
     // between the sweeps: float2 [8][256], in the fourth stage if it is large enough
-    static constexpr int red_bytes = 8 * 256 * 8, off_red = red_bytes <= stage2 ? 3 * stage2 : off_misc + 16 * 4;
-    static constexpr int off_nu = off_misc + 16 * 4 + (red_bytes <= stage2 ? 0 : red_bytes);
+    static constexpr int red_bytes = 8 * 256 * 8, off_red = red_bytes <= stage2 ? 3 * stage2 : off_misc + 20 * 4;
+    static constexpr int off_nu = off_misc + 20 * 4 + (red_bytes <= stage2 ? 0 : red_bytes);
     // ranges of up to KEYS keys keep their norms, prior and sums in LDS, longer ones in the workspace and the scores
     static constexpr int room = 160 * 1024 - off_nu - kPriorMaxHalo * 4;
     static constexpr int KEYS = !PRIOR ? 0 : room >= 2048 * 12 ? 2048 : room / 12 / 256 * 256;
@@ -48,8 +48,8 @@ struct ShareSmem {
 };
 
 template <int D, int RG, bool FIXED, int PRIOR>
-__global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x, float *stats,
-                                                              uint64_t *largest_tags, float *nu_g, float *gamma, float *scores) {
+__global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x, u32x4 *stats,
+                                                              u32x4 *maxima, float *nu_g, float *gamma, float *scores) {
     using W = ShareSmem<D, RG, PRIOR != 0>;
     using R = KeyRows<D>;
     using Request = KeyRequest<D, W::STEP, 8>;
@@ -62,6 +62,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     int *sPos = (int *)(sLam + W::ROWS);
     float *sMax = (float *)(smem + W::off_misc);
     int *sMissing = (int *)sMax + 8;
+    uint64_t *sTag = (uint64_t *)(sMax + 16);
     float *sN = (float *)(smem + W::off_nu), *sGam = (float *)(smem + W::off_gam), *sSum = (float *)(smem + W::off_sum);
     const bool in_lds = W::KEYS && part_keys <= W::KEYS;
 
@@ -335,6 +336,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     };
 
     Count count;
+    if (threadIdx.x == 511) count.look_epoch(x, z);
     load_rows_of_wave<D, NQ>(g, rm, b, h, w0, (int)threadIdx.x & 63, qf);
     {
         const int tid = threadIdx.x, lane = tid & 63;
@@ -367,25 +369,31 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
             merge_stats(m[q], s[q], m2, s2);
             if (lane < 32) sRed[kg * W::ROWS + w0 + 32 * q + lane] = make_float2(m[q], s[q]);
         }
+        // the last requests, past the range, write to LDS, where the second sweep begins (and the count is to be there first)
+        wait_vm<0>();
+        if (tid == 511) *sTag = x.tag + count.epoch;
         __syncthreads();
+        const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), *sTag);
         if (tid < W::ROWS) {
             float M = sRed[tid].x, total = sRed[tid].y;
             if constexpr (W::KG == 2) merge_stats(M, total, sRed[W::ROWS + tid].x, sRed[W::ROWS + tid].y);
-            put(stats + ((int64_t)z * nparts + part) * W::ROWS + tid, log2_sum(M, total));
+            put_rows(rows, part * (W::ROWS / 2), tid, log2_sum(M, total));
         }
-        announce(x, z, nparts, part, tid);
-        // (what the second sweep begins with travels while the others are waited for, but not in front of wave 0's looks)
-        if (wave != 0) begin_second();
-        if (wave == 0) {
-            const int missing = first_missing(x, z, nparts, own, lane);
-            if (lane == 0) *sMissing = missing;
-            begin_second();
-        }
+        // (what the second sweep begins with travels while the others are waited for)
+        begin_second();
+        sRed = (float2 *)(smem + W::off_red);
+        constexpr int MW = RG == 8 ? 4 : 8;  // waves that share 256 rows
+        const int tile = RG == 8 ? wave >> 2 : 0;
+        int missing = least_missing(merge_parts<256, MW>(rows, tile * 128, W::ROWS / 2, nparts, own, x.looks, sRed + wave * 256,
+                                                         wave % MW, lane));
+        if (lane == 0) sMissing[wave] = missing;
         __syncthreads();
-        const int missing = *sMissing;
-        if (missing == nparts && part == own) break;
+#pragma unroll
+        for (int wv = 0; wv < 8; ++wv) missing = min(missing, sMissing[wv]);
+        missing = uniform(missing);
+        if (missing == INT32_MAX && part == own) break;
         // somebody is not there: done here (and no more waiting); in the end the own part again
-        part = missing < nparts ? missing : own;
+        part = missing != INT32_MAX ? missing ^ own : own;
         x.looks = 0;
         wait_vm<0>();
         __syncthreads();
@@ -393,11 +401,8 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     int tid = threadIdx.x;
     const int lane = tid & 63;
     {
-        float2 *sRed = (float2 *)(smem + W::off_red);
-        constexpr int MW = RG == 8 ? 4 : 8;  // waves that share 256 rows
-        const int tile = RG == 8 ? wave >> 2 : 0;
-        merge_parts<256, MW>(stats + (int64_t)z * nparts * W::ROWS + tile * 256, W::ROWS, nparts, sRed + wave * 256, wave % MW, lane);
-        __syncthreads();
+        const float2 *sRed = (const float2 *)(smem + W::off_red);
+        constexpr int MW = RG == 8 ? 4 : 8;
         if (tid < W::ROWS) {
             float M = -INFINITY, total = 0.f;
             const float2 *src = sRed + tid / 256 * MW * 256 + tid % 256;
@@ -418,10 +423,10 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     second_sweep();
     if constexpr (PRIOR != 0) {
         asm volatile("" : "+v"(tid));
-        const Exchange xm{largest_tags, x.counts, x.tag, x.looks};
+        const Words priors(maxima + (int64_t)z * nparts, *sTag);
         PriorHalo<D> halo;
         halo.request(g, vbase, key_begin, key_end, tid);
-        for (int part = own, looks = xm.looks;;) {
+        for (int part = own, looks = x.looks;;) {
             float gm;
             if (in_lds) {
                 const float hn = halo.norm();
@@ -438,8 +443,8 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
             if (wave == 0) {
                 float all = fmaxf(fmaxf(fmaxf(sMax[0], sMax[1]), fmaxf(sMax[2], sMax[3])),
                                   fmaxf(fmaxf(sMax[4], sMax[5]), fmaxf(sMax[6], sMax[7])));
-                announce_value(xm, z, nparts, part, all, tid);
-                const int missing = largest_value({xm.tags, xm.counts, xm.tag, looks}, z, nparts, own, lane, all);
+                if (lane == 0) priors.put(part, all, 0.f);
+                const int missing = least_missing(largest_of<1>(priors, nparts, own, looks, lane, 64, all));
                 if (lane == 0) {
                     *sMissing = missing;
                     sMax[0] = all;
@@ -447,10 +452,10 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
             }
             __syncthreads();
             const int missing = *sMissing;
-            if (missing == nparts && part == own) break;
-            // somebody is not there: its norms are formed here (and no more waiting); in the end the own
+            if (missing == INT32_MAX && part == own) break;
+        // somebody is not there: its norms are formed here (and no more waiting); in the end the own
             // ones again
-            part = missing < nparts ? missing : own;
+            part = missing != INT32_MAX ? missing ^ own : own;
             looks = 0;
             __syncthreads();
             set_range(part);
@@ -470,10 +475,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
                             : out[j] * prior_factor(gamma[(int64_t)z * g.n + j], ginv);
     }
     if (tid == 511) count.arrive(x, z);
-    if (wave == 7) {
-        leave(x, z, nparts, count, lane);
-        if (PRIOR) leave<2>({largest_tags, x.counts, x.tag, 0}, z, nparts, count, lane);
-    }
+    if (tid == 511) leave(x, z, nparts, count);
 }
 
 // ---------------------------------------------------------------- launch --
@@ -487,7 +489,7 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(512), W::bytes, st, g, pl.win_parts, pl.win_keys, x,
-                       (float *)(w + pl.off_wstats), (uint64_t *)(w + pl.off_wmax), (float *)(w + pl.off_wnu),
+                       (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax), (float *)(w + pl.off_wnu),
                        (float *)(w + pl.off_wgamma), scores);
     return hipGetLastError();
 }
@@ -495,7 +497,7 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,
                               hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_wtags), (uint64_t *)(w + pl.off_wcounts), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_wwords), tag, looks};
     auto scaled = [&](auto d, auto rg, auto prior) {
         constexpr int D = decltype(d)::value, RG = decltype(rg)::value, PRIOR = decltype(prior)::value;
         return g.scale_mode == AHA_SCALE_FIXED ? launch_t<D, RG, true, PRIOR>(g, pl, x, w, scores, st)

@@ -8,8 +8,8 @@
 //
 // window_hold_kernel (up to four blocks of 32 rows, eight with two tiles): the logits of the range stay
 // in the accumulators while the statistics travel.  32 heads x 4096 keys x 64 rows: 29 -> 22 us; bound by
-// the one burst of loads (9 us to the last wave's keys), then one round trip each for announcing,
-// looking and fetching.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
+// the one burst of loads (12 us to the last workgroup's keys), then (stamps, us) statistics and prior 3.5, the exchange 2,
+// the column sums 1.6.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
 // window_stream_kernel (below): more rows or longer ranges, the logits formed twice, 620 ns per 64 x 32 block and SIMD; full
 // tiles are score_share.hip's, but for those of 256 rows with d = 64.
 //
@@ -34,7 +34,7 @@ struct HoldSmem {
     static constexpr size_t off_nu = off_red + 4 * ROWS * sizeof(float2);
     static constexpr size_t off_gam = off_nu + (PRIOR ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
     static constexpr size_t off_misc = off_gam + (PRIOR ? KEYS * sizeof(float) : 0);
-    static constexpr size_t bytes = off_misc + 12 * sizeof(float);
+    static constexpr size_t bytes = off_misc + 20 * sizeof(float);
     static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
     static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
 };
@@ -42,8 +42,8 @@ struct HoldSmem {
 // STEPS: 256-key steps of a workgroup's range, all of whose logits are held: NB * STEPS <= 4.
 // NT = 2: two tiles of rows, eight waves; waves w and w + 4 take the same keys, one tile each.
 template <int D, int NB, int NT, int STEPS, int PRIOR>
-__global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, int nparts, Exchange x, float *stats,
-                                                                  float *maxima, float *scores) {
+__global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, int nparts, Exchange x, u32x4 *stats,
+                                                                  u32x4 *maxima, float *scores) {
     using S = TileSmem<D, NB>;
     using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
     static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
@@ -61,6 +61,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     float *sNu = (float *)(smem + H::off_nu), *sGam = (float *)(smem + H::off_gam);
     float *sMax = (float *)(smem + H::off_misc);
     int *sMissing = (int *)sMax + 8;
+    uint64_t *sTag = (uint64_t *)(sMax + 16);
 
     const int own = (int)blockIdx.x % nparts, z = (int)blockIdx.x / nparts;
     const int b = z / g.Hkv, h = z % g.Hkv;
@@ -124,6 +125,10 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                 if (st + 1 < STEPS) load_values(st + 1);
             }
             // (keys at or past n, in the last range, lie behind every row's position)
+            if (st == STEPS - 1) {  // (used behind the products)
+                if (tid == THREADS - 1) count.look_epoch(x, z);
+                if (part == 0 && tid == THREADS - 1) count.start(x, z);
+            }
             bf16x8 qf = query_fragment<D, NB>(sQ, 0, 0, lane);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
@@ -140,7 +145,6 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                     stats_update<false, false>(acc[st][nb], lam[nb], 0, kb, lane, m[nb], s[nb], u);
             }
         }
-        if (part == 0 && tid == THREADS - 1) count.start(x, z);
         // fold the half-waves (same query row, other keys), then the waves
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -154,43 +158,45 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             if (halo.valid && tid % PriorHalo<D>::CPR == 0)
                 sNu[halo.pos - max(0, key_begin - (g.pool - 1) / 2)] = hn;
         }
+        if (part == 0 && wave == WAVES - 1) count.started();
+        if (tid == THREADS - 1) *sTag = x.tag + count.epoch;
         __syncthreads();
+        const uint64_t tag = *sTag;
+        const Words rows(stats + (int64_t)z * nparts * (H::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * WAVES, tag);
         if (tid < H::ROWS) {
             float M = -INFINITY, sum = 0.f;
             const float2 *src = sRed + (NT == 2 ? tid / H::TROWS * 4 * H::TROWS : 0) + tid % H::TROWS;
 #pragma unroll
             for (int wv = 0; wv < 4; ++wv) merge_stats(M, sum, src[wv * H::TROWS].x, src[wv * H::TROWS].y);
-            put(stats + ((int64_t)z * nparts + part) * H::ROWS + tid, M + log2f(sum));
+            put_rows(rows, part * (H::ROWS / 2), tid, M + log2f(sum));
         }
         if (PRIOR) {
             const float gm = wave_max(pool_norms(g, key_begin, key_end, sNu, sGam, tid, THREADS));
-            if (lane == 0) put(maxima + ((int64_t)z * nparts + part) * WAVES + wave, gm);
-        }
-        announce(x, z, nparts, part, tid);
-        if (wave == 0) {
-            const int missing = first_missing(x, z, nparts, own, lane);
-            if (lane == 0) *sMissing = missing;
+            if (lane == 0) priors.put(part * WAVES + wave, gm, 0.f);
         }
         __syncthreads();
-        const int missing = *sMissing;
-        if (missing == nparts && part == own) break;
+        int missing = merge_parts<H::TROWS, 4>(rows, tile * (H::TROWS / 2), H::ROWS / 2, nparts, own, x.looks,
+                                               sRed + wave * H::TROWS, kw, lane);
+        if (PRIOR) {
+            float gm;
+            missing = min(missing, largest_of<WAVES>(priors, nparts, own, x.looks, tid, THREADS, gm));
+            if (lane == 0) sMax[wave] = gm;
+        }
+        missing = least_missing(missing);
+        if (lane == 0) sMissing[wave] = missing;
+        __syncthreads();
+#pragma unroll
+        for (int wv = 0; wv < WAVES; ++wv) missing = min(missing, sMissing[wv]);
+        missing = uniform(missing);
+        if (missing == INT32_MAX && part == own) break;
         // somebody is not there: done here (and no more waiting); in the end the own part again, whose
         // logits the accumulators have to hold
-        part = missing < nparts ? missing : own;
+        part = missing != INT32_MAX ? missing ^ own : own;
         x.looks = 0;
         __syncthreads();
     }
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid == THREADS - 1) count.arrive(x, z);
-    merge_parts<H::TROWS, 4>(stats + (int64_t)z * nparts * H::ROWS + tile * H::TROWS, H::ROWS, nparts,
-                             sRed + wave * H::TROWS, kw, lane);
-    if (PRIOR) {
-        float gm = 0.f;
-        for (int p = tid; p < WAVES * nparts; p += THREADS) gm = fmaxf(gm, get(maxima + (int64_t)z * nparts * WAVES + p));
-        gm = wave_max(gm);
-        if (lane == 0) sMax[wave] = gm;
-    }
-    __syncthreads();
     if (tid < H::ROWS) {
         float M = -INFINITY, sum = 0.f;
         const int t = tid / H::TROWS, row = tid % H::TROWS;
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                 scores[(int64_t)z * g.n + j] = PRIOR ? tot[mb] * prior_factor(sGam[j - key_begin], ginv) : tot[mb];
         }
     }
-    if (wave == WAVES - 1) leave(x, z, nparts, count, lane);
+    if (tid == THREADS - 1) leave(x, z, nparts, count);
 }
 
 // ---- the logits formed twice --------------------------------------------------------------------
@@ -267,7 +273,7 @@ struct StreamSmem {
                                             ? 8 * TROWS * sizeof(float2)
                                             : (kPriorPiece + kPriorMaxHalo) * sizeof(float);
     static constexpr size_t off_misc = (off_red + red_bytes + 15) / 16 * 16;
-    static constexpr size_t off_nu = off_misc + 16 * sizeof(float);
+    static constexpr size_t off_nu = off_misc + 20 * sizeof(float);
     // ranges of up to KEYS keys keep their norms and prior in LDS, longer ones go through the workspace
     static constexpr size_t room = 160 * 1024 - off_nu - kPriorMaxHalo * sizeof(float);
     static constexpr int KEYS = room >= 2048 * 8 ? 2048 : (int)(room / 8) / 256 * 256;
@@ -280,7 +286,7 @@ struct StreamSmem {
 
 template <int D, int NB, int NT, int PRIOR>
 __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
-                                                               float *stats, float *maxima, float *nu_g,
+                                                               u32x4 *stats, u32x4 *maxima, float *nu_g,
                                                                float *gamma, float *scores) {
     using S = TileSmem<D, NB>;
     using W = StreamSmem<D, NB, NT>;
@@ -298,6 +304,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     float *sCol = (float *)sRed, *sNu = (float *)sRed;
     float *sMax = (float *)(smem + W::off_misc);
     int *sMissing = (int *)sMax + 8;
+    uint64_t *sTag = (uint64_t *)(sMax + 16);
     float *sN = (float *)(smem + W::off_nu), *sGam = (float *)(smem + W::off_gam);
     const bool in_lds = W::KEYS && part_keys <= W::KEYS;
 
@@ -477,8 +484,8 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             step(a1, a0, i - 1);
         }
     };
-    // the prior of the range from its norms; leaves the part's largest gamma
-    auto pool_range = [&](int part, const PriorHalo<D> &halo, int tid) {
+    // the prior of the range from its norms; the wave's largest gamma
+    auto pool_range = [&](const PriorHalo<D> &halo, int tid) {
         float gm;
         if (in_lds) {
             const float hn = halo.norm();
@@ -489,15 +496,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             __syncthreads();  // (the statistics' LDS becomes the norms')
             gm = pool_norms_of_range<D, 512>(g, z, key_begin, key_end, nu_g, halo, sNu, gamma, tid);
         }
-        gm = wave_max(gm);
-        if ((tid & 63) == 0) put(maxima + ((int64_t)z * nparts + part) * 8 + wave, gm);
-    };
-    // the largest gamma of all parts, to sMax (before a barrier); its first values are requested earlier
-    auto request_maxima = [&](int tid) { return get(maxima + (int64_t)z * nparts * 8 + min(tid, 8 * nparts - 1)); };
-    auto fetch_maxima = [&](int tid, float gm) {
-        for (int p = tid + 512; p < 8 * nparts; p += 512) gm = fmaxf(gm, get(maxima + (int64_t)z * nparts * 8 + p));
-        gm = wave_max(gm);
-        if ((tid & 63) == 0) sMax[wave] = gm;
+        return wave_max(gm);
     };
     auto largest = [&]() {
         return fmaxf(fmaxf(fmaxf(sMax[0], sMax[1]), fmaxf(sMax[2], sMax[3])),
@@ -552,6 +551,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             if (i + 1 >= nsteps) break;
             sweep_step(std::bool_constant<PRIOR != 0>{}, blocks, a1, a0, kb_of(i + 1), kb_of(i + 2), false, i + 2 == nsteps);
         }
+        if (tid == 511) count.look_epoch(x, z);
         if (part == 0 && tid == 511) count.start(x, z);
         PriorHalo<D> halo;
         if (PRIOR) halo.request(g, vbase, key_begin, key_end, tid);  // travels while the statistics are reduced
@@ -562,37 +562,46 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             merge_stats(m[nb], s[nb], m2, s2);
             if (lane < 32) sRed[wave * W::TROWS + nb * 32 + lane] = make_float2(m[nb], s[nb]);
         }
+        if (part == 0 && wave == 7) count.started();
+        if (tid == 511) *sTag = x.tag + count.epoch;
         __syncthreads();
+        const uint64_t tag = *sTag;
+        const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * 8, tag);
         if (tid < W::ROWS) {
             float M = -INFINITY, sum = 0.f;
             const float2 *src = sRed + (NT == 2 ? tid / W::TROWS * 4 * W::TROWS : 0) + tid % W::TROWS;
 #pragma unroll
             for (int wv = 0; wv < W::KW; ++wv) merge_stats(M, sum, src[wv * W::TROWS].x, src[wv * W::TROWS].y);
-            put(stats + ((int64_t)z * nparts + part) * W::ROWS + tid, M + log2f(sum));
+            put_rows(rows, part * (W::ROWS / 2), tid, M + log2f(sum));
         }
-        if (PRIOR) pool_range(part, halo, tid);
-        announce(x, z, nparts, part, tid);
-        if (wave == 0) {
-            const int missing = first_missing(x, z, nparts, own, lane);
-            if (lane == 0) *sMissing = missing;
+        if (PRIOR) {
+            const float gm = pool_range(halo, tid);
+            if (lane == 0) priors.put(part * 8 + wave, gm, 0.f);
         }
         __syncthreads();
-        const int missing = *sMissing;
-        if (missing == nparts && part == own) break;
+        int missing = merge_parts<W::TROWS, W::KW>(rows, tile * (W::TROWS / 2), W::ROWS / 2, nparts, own, x.looks,
+                                               sRed + wave * W::TROWS, kw, lane);
+        if (PRIOR) {
+            float gm;
+            missing = min(missing, largest_of<8>(priors, nparts, own, x.looks, tid, 512, gm));
+            if (lane == 0) sMax[wave] = gm;
+        }
+        missing = least_missing(missing);
+        if (lane == 0) sMissing[wave] = missing;
+        __syncthreads();
+#pragma unroll
+        for (int wv = 0; wv < 8; ++wv) missing = min(missing, sMissing[wv]);
+        missing = uniform(missing);
+        if (missing == INT32_MAX && part == own) break;
         // somebody is not there: done here (and no more waiting); in the end the own part again, whose
         // prior the LDS has to hold
-        part = missing < nparts ? missing : own;
+        part = missing != INT32_MAX ? missing ^ own : own;
         x.looks = 0;
         __syncthreads();
     }
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid == 511) count.arrive(x, z);
-    const float my_max = PRIOR ? request_maxima(tid) : 0.f;
-    merge_parts<W::TROWS, W::KW>(stats + (int64_t)z * nparts * W::ROWS + tile * W::TROWS, W::ROWS, nparts,
-                                 sRed + wave * W::TROWS, kw, lane);
-    if (PRIOR) fetch_maxima(tid, my_max);
     load_a<D>(kbase, g.ks[2], kb_of(nsteps - 1), key_end, lane, a0);
-    __syncthreads();
     if (tid < W::ROWS) {
         float M = -INFINITY, sum = 0.f;
         const int t = tid / W::TROWS, row = tid % W::TROWS;
@@ -604,7 +613,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     }
     __syncthreads();
     second_sweep(PRIOR ? prior_inverse(largest()) : 1.f);
-    if (wave == 7) leave(x, z, nparts, count, tid & 63);
+    if (tid == 511) leave(x, z, nparts, count);
 }
 
 // ---------------------------------------------------------------- launch --
@@ -621,7 +630,7 @@ static hipError_t launch_hold(const ScoreGeom &g, const PrefillPlan &pl, const E
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(256 * NT), H::bytes, st, g, pl.win_parts, x,
-                       (float *)(w + pl.off_wstats), (float *)(w + pl.off_wmax), scores);
+                       (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax), scores);
     return hipGetLastError();
 }
 
@@ -636,7 +645,7 @@ static hipError_t launch_stream(const ScoreGeom &g, const PrefillPlan &pl, const
     });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(512), W::bytes, st, g, pl.win_parts,
-                       pl.win_keys, x, (float *)(w + pl.off_wstats), (float *)(w + pl.off_wmax),
+                       pl.win_keys, x, (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax),
                        (float *)(w + pl.off_wnu), (float *)(w + pl.off_wgamma), scores);
     return hipGetLastError();
 }
@@ -663,7 +672,7 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                                float *scores, hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_wtags), (uint64_t *)(w + pl.off_wcounts), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_wwords), tag, looks};
     auto launch = [&](auto prior) {
         constexpr int PRIOR = decltype(prior)::value;
         return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, w, scores, st) : launch_d<128, PRIOR>(g, pl, x, w, scores, st);
