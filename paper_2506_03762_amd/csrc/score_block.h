@@ -50,9 +50,9 @@ __device__ __forceinline__ void stats_update(const f32x16 (&acc)[kMB], float lam
     m = mn;
 }
 
-// A block's products with keys that a row does not see become -inf, which counts as nothing in any update that follows, given
-// a scale above 0 and, in the column sums, a normaliser above -inf (below); `room`: the row's position less the key of
-// accumulator element 0.  A scale of (almost) 0 goes into the products instead.
+// A block's products with keys that a row does not see become -inf, which counts as nothing in the update that follows, given
+// a scale above 0; `room`: the row's position less the key of accumulator element 0.  A scale of (almost) 0 goes into
+// the products instead.
 constexpr float kLeastScale = 1e-30f;
 __device__ __forceinline__ void hide_unseen(f32x16 (&acc)[kMB], int room, float &lam) {
     asm volatile("" ::: "memory");  // (else the branch that leads here becomes a choice per element in every block)
@@ -70,15 +70,38 @@ __device__ __forceinline__ void hide_unseen(f32x16 (&acc)[kMB], int room, float 
         for (int v = 0; v < 16; ++v)
             if (mb * 32 + 8 * (v >> 2) + (v & 3) > room) acc[mb][v] = -INFINITY;  // (acc_key)
 }
-// Hidden products whose row has no normaliser L (`none`: NaN, or -inf): the keys that the row sees get NaN, the others nothing.
-__device__ __forceinline__ void hide_from_no_normaliser(f32x16 (&acc)[kMB], int room, bool none, float &L) {
+// stats_update() that leaves the block's exponentials in the place of its products, relative to `ref`, the running maximum (-inf: no
+// key seen yet), so that a column sum takes one multiplication per element.
+__device__ __forceinline__ void stats_weights(f32x16 (&acc)[kMB], float lam, float &m, float &s, float &ref) {
+    float amax = -INFINITY;
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) amax = fmaxf(amax, acc[mb][v]);
+    const float tmax = amax == -INFINITY ? -INFINITY : amax * lam;
+    ref = fmaxf(m, tmax);
+    const float mref = ref == -INFINITY ? 0.f : ref;
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[mb][v] = fast_exp2(fmaf(acc[mb][v], lam, -mref));
+            sum[v & 3] += acc[mb][v];
+        }
+    s = s * fast_exp2(m - mref) + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
+    m = ref;
+}
+// Weights whose row has no factor (`none`: NaN or infinite): the keys that the row sees get NaN, the others nothing; `room`: the
+// row's position less the key of element 0.
+__device__ __forceinline__ void weights_without_factor(f32x16 (&acc)[kMB], int room, bool none, float &f) {
     asm volatile("" ::: "memory");
-    L = none ? 0.f : L;
+    f = none ? 1.f : f;
 #pragma unroll
     for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            if (none && mb * 32 + 8 * (v >> 2) + (v & 3) <= room) acc[mb][v] = __builtin_nanf("");
+            if (none) acc[mb][v] = mb * 32 + 8 * (v >> 2) + (v & 3) <= room ? __builtin_nanf("") : 0.f;  // (acc_key)
 }
 
 template <bool MASK>

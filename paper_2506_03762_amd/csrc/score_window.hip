@@ -6,8 +6,12 @@
 // own range.  Against two launches this saves the second set-up (query tile, first keys) and, in the
 // held form, the second read of the keys and their products.
 //
-// window_hold_kernel (up to four blocks of 32 rows, eight with two tiles): the logits of the range stay
-// in the accumulators while the statistics travel.  32 heads x 4096 keys x 64 rows: 29 -> 22 us; bound by
+// window_hold_kernel (up to four blocks of 32 rows, eight with two tiles): the exponentials of the range, each block's relative to the
+// running maximum of its rows then, stay in the accumulators while the statistics travel, so that a column sum takes a
+// multiplication per element; with the logits in them it took the exponential again, and where the range has two steps 9
+// registers spilled (now none): us of the step before and after, 128 heads x 16384 keys x 64 rows 336 -> 295, 32 x 4096 x 64 31.1 ->
+// 30.6, 12 x 5003 x 120 21.2 -> 20.5; against float64 the scores' rms error over 20 shapes is 0.73 times that from logits.
+// 32 heads x 4096 keys x 64 rows in two launches 29 us, so 22; bound by
 // the one burst of loads (12 us to the last workgroup's keys), then (stamps, us) statistics and prior 3.5, the exchange 2,
 // the column sums 1.6.  128 heads x 16384 x 64: 287 -> 267 us, K read once instead of twice.
 // window_stream_kernel (below): more rows or longer ranges, the logits formed twice, 620 ns per 64 x 32 block and SIMD; full
@@ -17,8 +21,7 @@
 // reads 32 bytes of 32 rows.  Where the last-level cache would not keep them anyway they go past the caches.  us
 // of the score stage before and after: 48 heads x 6846 keys x 64 rows 59.0, 47.3; 12 x 59081 x 64 108, 92.8; 128 x
 // 16384 x 64 259, 252.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
-// With the logits held, value rows and keys take all registers where the range has two steps (d = 128, two row blocks: 9 spilled,
-// 40 bytes a lane, once per step; one block and four steps: 40, for up to 32 rows).
+// With one block of rows and four steps (up to 32 rows) value rows, keys and exponentials take all registers: 40 spilled, once per step.
 // Two tiles share their value rows, 32 each, and load them like keys (as memory lies was slower).
 #include <type_traits>
 
@@ -48,7 +51,6 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
     static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
     constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
-    constexpr bool HIDE = STEPS == 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wave = uniform((int)threadIdx.x >> 6), tile = NT == 2 ? wave >> 2 : 0, kw = wave & 3;
     __bf16 *sQ = (__bf16 *)(smem + tile * S::stride);
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 
     Count count;
     f32x16 acc[STEPS][NB][kMB];
-    float lam[NB];
+    float ref[STEPS][NB];
     int pos[NB], bmin[NB];
     int key_begin, key_end;
     for (int part = own;;) {
@@ -103,12 +105,12 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             q_tile_commit<D, NB>(qt, ht, sQ);
         }
         __syncthreads();
-        float m[NB], s[NB], u = 0.f;
+        float m[NB], s[NB], lam[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             lam[nb] = sLam[nb * 32 + (lane & 31)];
             pos[nb] = sPos[nb * 32 + (lane & 31)];
-            if (HIDE && pos[nb] < 0) lam[nb] = kLeastScale;  // (no row)
+            if (pos[nb] < 0) lam[nb] = kLeastScale;  // (no row)
             bmin[nb] = uniform(sBlk[NB + nb]);
             m[nb] = -INFINITY;
             s[nb] = 0.f;
@@ -134,15 +136,10 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             for (int nb = 0; nb < NB; ++nb) {
                 mma_block_stream<D, NB>(a, sQ, nb, nb + 1 < NB ? nb + 1 : 0, lane, qf, acc[st][nb]);
                 if (nb == NB - 1 && st + 1 < STEPS) load_a<D>(kbase, g.ks[2], kb_of(st + 1), key_end, lane, a);
-                // (Masked products are hidden once for both updates where the range has one step: the wave whose keys end the
-                // sequence holds its problem up, 32 heads x 4096 keys x 64 rows 30.0 -> 29.7 us; with two steps and all
-                // registers taken 128 x 16384 x 64 340 -> 352.  A masked update left beside it for the rare rows below costs all that it gains.)
                 const bool masked = kb + kWaveKeys - 1 > bmin[nb];
-                if (HIDE && masked) hide_unseen(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), lam[nb]);
-                if (!HIDE && masked)
-                    stats_update<true, false>(acc[st][nb], lam[nb], pos[nb], kb, lane, m[nb], s[nb], u);
-                else
-                    stats_update<false, false>(acc[st][nb], lam[nb], 0, kb, lane, m[nb], s[nb], u);
+                float scale = lam[nb];  // (of this block: hiding may put it into the products)
+                if (masked) hide_unseen(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), scale);
+                stats_weights(acc[st][nb], scale, m[nb], s[nb], ref[st][nb]);
             }
         }
         // fold the half-waves (same query row, other keys), then the waves
@@ -203,19 +200,27 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         const float2 *src = sRed + t * 4 * H::TROWS + row;
 #pragma unroll
         for (int wv = 0; wv < 4; ++wv) merge_stats(M, sum, src[wv * H::TROWS].x, src[wv * H::TROWS].y);
-        // (rows past the last one add nothing)
-        ((float *)(smem + t * S::stride + S::q_bytes) + 2 * S::ROWS)[row] = tid < g.R ? M + log2f(sum) : INFINITY;
+        // (in the scales' place: reciprocal sums; rows past the last one add nothing)
+        float *meta = (float *)(smem + t * S::stride + S::q_bytes) + row;
+        meta[0] = tid < g.R ? 1.f / sum : 0.f;
+        meta[2 * S::ROWS] = tid < g.R ? M : INFINITY;
     }
     __syncthreads();
-    float ginv = 1.f, L[NB];
+    float ginv = 1.f;
     if (PRIOR) {
         float gm = sMax[0];
 #pragma unroll
         for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
         ginv = prior_inverse(gm);
     }
+    // a block's weights -> probabilities
+    float f[STEPS][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) L[nb] = sL[nb * 32 + (lane & 31)];
+    for (int nb = 0; nb < NB; ++nb) {
+        const float M = sL[nb * 32 + (lane & 31)], rs = sLam[nb * 32 + (lane & 31)];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) f[st][nb] = fast_exp2(ref[st][nb] - M) * rs;
+    }
     const int my_v = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 +
                      ((lane >> 1) & 1);
 #pragma unroll
@@ -223,18 +228,15 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         const int kb = key_begin + st * kWgKeys + kw * kWaveKeys;
         f32x16 col[kMB];
 #pragma unroll
-        for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) col[mb][v] = 0.f;
-#pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const bool masked = kb + kWaveKeys - 1 > bmin[nb], none = !(L[nb] > -INFINITY);
-            if (HIDE && __builtin_expect(masked && __builtin_amdgcn_ballot_w64(none) != 0, 0))
-                hide_from_no_normaliser(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), none, L[nb]);
-            if (!HIDE && masked)
-                colsum_update<true>(acc[st][nb], lam[nb], L[nb], pos[nb], kb, lane, col);
-            else
-                colsum_update<false>(acc[st][nb], lam[nb], L[nb], 0, kb, lane, col);
+            const bool masked = kb + kWaveKeys - 1 > bmin[nb], none = !(f[st][nb] < INFINITY);
+            if (__builtin_expect(masked && __builtin_amdgcn_ballot_w64(none) != 0, 0))
+                weights_without_factor(acc[st][nb], pos[nb] - acc_key(kb, 0, 0, lane), none, f[st][nb]);
+#pragma unroll
+            for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    col[mb][v] = nb ? fmaf(acc[st][nb][mb][v], f[st][nb], col[mb][v]) : acc[st][nb][mb][v] * f[st][nb];
         }
         float tot[kMB];
 #pragma unroll

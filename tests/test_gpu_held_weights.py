@@ -1,0 +1,70 @@
+"""Windowed scores whose blocks are held as exponentials relative to the running maximum of their row: ranges of several
+steps of which later ones lie past the last key, rows whose maximum moves from step to step, rows that are not finite, a
+scale of zero."""
+import pytest
+
+from paper_2506_03762_amd import binding as B
+from tests.test_gpu_unseen_keys import _inputs, _scores
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # KV heads, group, window, n, d: ranges of two and four steps (200 and 188 keys in the last), of one, two tiles
+    (8, 1, 60, 24776, 128), (24, 1, 30, 12476, 64), (5, 1, 33, 2113, 128), (2, 1, 100, 300, 64), (3, 1, 200, 700, 128),
+]
+
+
+def _exact(p, q, k):
+    import torch
+    hkv, group, window, n = p.n_kv_heads, p.n_q_heads // p.n_kv_heads, p.window, p.seq_len
+    seen = torch.arange(n, device="cuda")[None] <= torch.arange(n - window, n, device="cuda")[:, None]
+    out = torch.zeros((1, hkv, n), dtype=torch.float64, device="cuda")
+    for h in range(hkv * group):
+        x = (q[0, h, n - window:].double() @ k[0, h // group].double().T) * p.fixed_scale
+        out[0, h // group] += torch.softmax(x.masked_fill(~seen, float("-inf")), -1).sum(0)
+    return out
+
+
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_against_float64(shape, rising):
+    import torch
+    p, q, k, v = _inputs(shape, shape[4] ** -0.5)
+    if rising:  # (longer keys, larger maxima, from block to block)
+        k *= torch.linspace(0.5, 3.0, shape[3], device="cuda")[:, None].to(k.dtype)
+    want, got = _exact(p, q, k), _scores(p, q, k, v).double()
+    # Per term: the exponent's two roundings and the normaliser's three, each of a number below 128 (2^-17 at most, times ln 2),
+    # two exponentials and a product (2^-23 each), the products' sums of 128 terms (2^-24 of 128 at most)
+    assert ((got - want).abs() <= (5 * 2.0 ** -18 + 2.0 ** -17) * want + 1e-30).all()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("shape", SHAPES[:2])
+def test_a_row_that_is_not_finite(shape, bad):
+    import torch
+    p, q, k, v = _inputs(shape, shape[4] ** -0.5)
+    k[..., 0] = k[..., 0].abs() + 0.5
+    want = _scores(p, q, k, v)
+    at = p.seq_len - shape[2] // 2
+    if bad < 0:  # (every product -inf)
+        q[:, :, at, 0] = bad
+    else:
+        q[:, :, at] = bad
+    got = _scores(p, q, k, v)
+    assert not torch.isfinite(got[..., :at + 1]).any()
+    assert got[..., at + 1:].equal(want[..., at + 1:])
+
+
+@pytest.mark.parametrize("shape", SHAPES[:2])
+def test_a_scale_of_zero(shape):
+    import torch
+    p, q, k, v = _inputs(shape, 0.0)
+    q *= 2.0 ** 57   # (products of some 2^118)
+    k *= 2.0 ** 57
+    hkv, group, window, n, d = shape
+    rows = torch.arange(n - window, n, dtype=torch.float64)
+    seen = (rows[:, None] >= torch.arange(n)[None]).double()
+    want = (group * seen / (rows[:, None] + 1)).sum(0)
+    got = _scores(p, q, k, v).double().cpu()
+    # a normaliser of log2 n with 19 bits behind the point, sums of up to 60 equal terms
+    assert ((got - want).abs() <= 1e-5 * want).all()
