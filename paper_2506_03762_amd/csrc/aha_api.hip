@@ -164,15 +164,31 @@ static void best_ranges(int64_t Z, int64_t n, int64_t step, int64_t resident, in
 // Workgroups of which the chip holds two per CU at once.  A problem never has more ranges than that: those that
 // run would wait for those that cannot start (8 x 300000 x 64 rows, 586 ranges: 56 ms).
 constexpr int64_t kHeldAtOnce = 512;
-// Logits held in several rounds of the whole chip, 33 to 64 rows, d = 128: up to which number of ranges that is the
-// faster one.  The workgroups of a problem that begins at the end of a round wait for the next one, so the fewer
-// problems a round holds the more of it is spent waiting; two launches that leave their own last round
-// nearly empty are slow enough for it up to two problems a round.  us in two launches, in one (with a prior):
-// two even launches: 16 heads x 64 ranges 71.7, 66.5, x 96 101, 105, x 192 204, 258; 64 x 128 565, 562, x 192 867,
-// 1003; uneven: 24 x 64 130, 94, x 256 559, 471, x 320 713, 793.
-static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
-    const bool uneven = (int64_t)pl.Z * pl.nchunks > 512;
-    return pl.Z * parts >= 1024 && parts <= (uneven ? kHeldAtOnce / 2 : pl.Z >= 64 ? 128 : 64);
+constexpr int64_t kSweptSteps = 800;  // steps of 256 keys in all from which 65 to 128 rows, d = 64, are swept twice
+// Exponentials held in several rounds of the whole chip, nb blocks of rows: up to which number of ranges that is the faster
+// one.  The workgroups of a problem that begins at the end of a round wait for the next one, and every range reads
+// all ranges' statistics; two launches leave their own last round nearly empty unless their workgroups are just the
+// chip's 512 (`even`).  us otherwise (two launches; d = 64 and more than 64 rows the two sweeps), held, over 560 shapes of 3 to 390
+// ranges, 4 to 296 heads:
+//  - up to 32 rows: 1.5 times as fast on average (hardly more than one round is not taken);
+//  - d = 128, 33 to 64 rows: uneven up to 256: 77 heads x 9 ranges 66.4, 44.0; 7 x 181 90.5, 90.0; 8 x 233 135, 127; even up to two
+//    problems a round from 64 heads on, eight below: 128 x 32 284, 212;
+//  - d = 128, 65 to 128 rows: uneven up to 100: 80 x 9 55.6, 32.3; 21 x 98 82.6, 75.4; 17 x 174 134, 147; 16 x 234 145, 190; even
+//    16 x 64 50.6, 42.6; 128 x 43 201, 199; 64 x 64 151, 156; 32 x 128 150, 172; without a prior 64 x 64 106, 108, 128 x 64 213, 237;
+//  - d = 64, 33 to 64 rows: uneven up to 160: 15 x 71 56.9, 47.1; 8 x 173 60.4, 68.8; even 64 x 64 145, 141; 32 x 128 144, 149;
+//    without a prior 64 x 32 54.4, 51.1, 128 x 32 93.5, 99.1;
+//  - d = 64, 65 to 128 rows: where the sweeps would not be taken either, 28 x 20 36.6, 21.1; 15 x 51 37.6, 25.3; 13 x 74 28.7,
+//    36.2 (sweeps, held).
+// Held would be the faster one a little further, too, where the two launches are tested: up to 256 ranges of 33 to 64 rows, even
+// (16 x 101 120, 98.6), 150 of 65 to 128, uneven (11 x 103 72.4, 54.7; 37 x 145 274, 245), and one or two heads in at most 128
+// ranges of 65 to 128 rows (1 x 100 22.9, 16.2).
+static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, int64_t parts, int64_t steps) {
+    const bool even = (int64_t)pl.Z * pl.nchunks <= 512, prior = p->value_prior;
+    if (nb == 1) return parts <= 128 && pl.Z * parts >= 600;
+    if (p->head_dim == 128 && nb == 2) return parts <= (!even ? 256 : pl.Z >= 64 ? 128 : 64);
+    if (p->head_dim == 64 && nb > 2) return pl.Z * steps < kSweptSteps && parts <= 150;
+    if (!even) return parts <= (p->head_dim == 128 ? 100 : 160);
+    return (parts <= 64 && pl.Z * parts <= 2048) || (prior && parts <= (nb == 2 ? 64 : 48));
 }
 
 // Windowed bf16 scores in one launch.  Its layout starts where the one of two launches does, but may be longer: a
@@ -180,15 +196,13 @@ static bool held_in_rounds(const PrefillPlan &pl, int64_t parts) {
 // score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV heads, 400 to 65536 keys, d = 64 and 128), 1.30
 // times as fast as two launches on average.  us in two launches, in one:
 //  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
-//    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0.  In
-//    several rounds the exchange is waited for in each: a gain only with enough bytes behind it (64 rows,
-//    d = 128: 64 x 32480 296, 276; 8 x 38147 53.8, 56.7, not taken; 32 rows 32 x 28176 121, 130; 64 rows,
-//    d = 64 16 x 34742 51.2, 60.8; 128 rows 64 x 16164 161, 194) and while a round still holds several problems
-//    whole (held_in_rounds).  Every range reads all ranges'
-//    statistics: above 48 ranges of 96 and more rows that is too much (1 x 25019 x 123 22.9, 27.6).
+//    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0; 96 and 128 rows in up to
+//    512 ranges, but for few workgroups: 1 x 131072 x 128 53.8, 39.5, 6 x 19416 x 96 32.6, 22.4 (52 shapes 1.38 times as fast on
+//    average, 1.18 at least).
+//    In several rounds the exchange is waited for in each (held_in_rounds).
 //  - 65 to 128 rows, d = 64, longer problems, swept twice: 6 x 46683 x 126 52.7, 36.3 (d = 128, bound by its
 //    bytes: 8 x 29221 x 128 48.3, 48.9, not taken).
-//  - 129 to 256 rows, held by eight waves where one workgroup per CU covers the problem (16 x 1117 x 152
+//  - 129 to 256 rows, held by eight waves where one workgroup per CU covers the problem (in several rounds 62 shapes take 1.4 times as long; 16 x 1117 x 152
 //    22.9, 17.1; 32 x 1502 x 256 32.8, 20.4), else swept twice (24 x 32929 x 160 163, 126; 6 x 29092 x
 //    256 68.5, 47.7; held in 32 x 1502 x 256 the sweeps' 37.4 become 22.2).
 //  - 257 to 512 rows, two tiles, swept twice (64 x 940 x 315 46.7, 30.4, d = 64 35.3, 22.2; 8 x 9057 x 504 56.3, 42.6, d = 64
@@ -214,12 +228,15 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
         // the shortest ranges of which two per CU cover the problem, else the longest that can be held
         nb = blocks;
         int per = 1;
-        while (2 * per * nb <= 4 && pl.Z * ((steps + per - 1) / per) > kHeldAtOnce) per *= 2;
+        // (four steps beside value rows take more registers than there are, d = 128: us of four and two, 16 heads x 25716 keys x 16
+        // rows 59.2, 49.0; 173 x 2481 x 32 79.3, 50.0; 22 shapes 1.33 times as fast on average, without a prior 0.97)
+        const int most = nb == 2 || (p->head_dim == 128 && p->value_prior) ? 2 : 4;
+        while (2 * per * nb <= 4 && 2 * per <= most && pl.Z * ((steps + per - 1) / per) > kHeldAtOnce) per *= 2;
         parts = (steps + per - 1) / per;
         keys = per * kP2Keys;
-        hold = pl.Z * parts <= kHeldAtOnce ? nb <= 2 || parts <= 48
-                                           : nb == 2 && p->head_dim == 128 && held_in_rounds(pl, parts);
-        if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < 800)) return;
+        hold = pl.Z * parts <= kHeldAtOnce ? nb <= 2 || parts <= 48 || pl.Z * parts > 128
+                                           : held_in_rounds(p, pl, nb, parts, steps);
+        if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < kSweptSteps)) return;
         if (!hold) nb = 4;
     } else if (blocks <= 8) {
         hold = pl.Z * steps <= 256;
@@ -259,7 +276,8 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
 // 6172 x 32, d = 64 9.5, 10.4; 4 x 60798 x 32 27.2, 29.5; 4 x 31485 x 128 21.6, 22.5), eight blocks of rows in
 // steps of 512 keys for at most half of the CUs (8 x 3600 x 256 18.5, 19.9, 4 x 12000, d = 64 13.7, 15.4; not 8 x
 // 12000 23.9, 22.3), and without a prior,
-// of which a second launch would have to be saved, many steps of the larger tiles (32 x 31856 x 256 79.3, 82.3).
+// of which a second launch would have to be saved, many steps of the largest tile (32 x 31856 x 256 86.3, 90.1, d = 64, 32 x 59762
+// 104, 115; but 192 rows, which two launches pad to 256: 32 x 31856 97.8, 77.4, d = 64 64.5, 52.6).
 static void plan_given(const aha_params *p, PrefillPlan &pl) {
     pl.given_nb = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window;
@@ -270,7 +288,7 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
     best_ranges(pl.Z, p->seq_len, nb <= 4 ? 256 : 512, resident, p->value_prior ? given_keys(p->head_dim, nb) : INT64_MAX / 2,
                 p->value_prior, parts, keys);
     if (pl.Z * parts > 1 << 30 || parts > resident) return;  // (all of a problem's workgroups have to run at once)
-    if (p->value_prior ? nb <= 4 && pl.Z <= 8 && parts > (nb <= 2 ? 24 : 50) : nb > 4 && (int64_t)pl.Z * p->seq_len > 1 << 19) return;
+    if (p->value_prior ? nb <= 4 && pl.Z <= 8 && parts > (nb <= 2 ? 24 : 50) : nb == 8 && (int64_t)pl.Z * p->seq_len > 1 << 19) return;
     if (p->value_prior && blocks == 8 && pl.Z * (((int64_t)p->seq_len + 511) / 512) <= 128) return;
     pl.given_nb = nb;
     pl.given_parts = (int)parts;

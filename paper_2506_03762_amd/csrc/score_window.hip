@@ -21,7 +21,6 @@
 // reads 32 bytes of 32 rows.  Where the last-level cache would not keep them anyway they go past the caches.  us
 // of the score stage before and after: 48 heads x 6846 keys x 64 rows 59.0, 47.3; 12 x 59081 x 64 108, 92.8; 128 x
 // 16384 x 64 259, 252.  110 shapes of 1 to 512 rows 1.027 times as fast on average.
-// With one block of rows and four steps (up to 32 rows) value rows, keys and exponentials take all registers: 40 spilled, once per step.
 // Two tiles share their value rows, 32 each, and load them like keys (as memory lies was slower).
 #include <type_traits>
 
@@ -662,7 +661,8 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 #define AHA_STREAM(NB, NT)                                            \
     if (!pl.win_hold && pl.win_nb == NB && pl.win_tiles == NT) \
         return launch_stream<D, NB, NT, NT == 2 && PRIOR ? kValuesCached : PRIOR>(g, pl, x, w, scores, st);
-    AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(1, 1, 4) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
+    if constexpr (D == 64 || !PRIOR) { AHA_HOLD(1, 1, 4) }
+    AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
     AHA_HOLD(4, 1, 1) AHA_HOLD(3, 2, 1) AHA_HOLD(4, 2, 1)
     if constexpr (D == 64) { AHA_STREAM(4, 1) AHA_STREAM(8, 1) }  // (d = 128: held, or two launches; score_share.hip)
     AHA_STREAM(6, 1) AHA_STREAM(6, 2)

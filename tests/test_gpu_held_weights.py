@@ -68,3 +68,24 @@ def test_a_scale_of_zero(shape):
     got = _scores(p, q, k, v).double().cpu()
     # a normaliser of log2 n with 19 bits behind the point, sums of up to 60 equal terms
     assert ((got - want).abs() <= 1e-5 * want).all()
+
+
+ROUNDS = [
+    # more workgroups than the chip holds at once: KV heads, group, window, n, d
+    (40, 1, 30, 15990, 64), (20, 2, 15, 32100, 128), (50, 1, 96, 3001, 128), (28, 1, 128, 5000, 64), (70, 1, 64, 4100, 64),
+    (3, 1, 128, 16849, 128),  # (one round, many ranges)
+]
+
+
+@pytest.mark.parametrize("shape", ROUNDS)
+def test_several_rounds(shape):
+    p, q, k, v = _inputs(shape, shape[4] ** -0.5)
+    want, got = _exact(p, q, k), _scores(p, q, k, v)
+    assert ((got.double() - want).abs() <= (5 * 2.0 ** -18 + 2.0 ** -17) * want + 1e-30).all()
+    # a workgroup that looks once and does whatever is not there yet
+    assert B.load().aha_exchange_looks(0) == B.AHA_OK
+    try:
+        alone = _scores(p, q, k, v)
+    finally:
+        B.load().aha_exchange_looks(4000)
+    assert alone.equal(got)

@@ -101,3 +101,20 @@ def test_results_in_it(z, group, window, n, d, size):
     # fp32 arithmetic on exact products: logits of a few tens carry 1e-5 absolute, which is the relative error of their
     # exponentials, on either side
     assert ((got[0] - got[1]).abs() <= 4e-4 * got[0] + 2e-7 * got[0].mean()).all()
+
+
+@pytest.mark.parametrize("z,window,n,d,prior,one", [
+    # several rounds of the chip (us: two launches, one)
+    (80, 128, 2304, 128, 1, True),    # 55.6, 32.3
+    (128, 32, 16384, 64, 1, True),    # 142, 110
+    (173, 32, 2481, 64, 1, False),    # hardly more than one round
+    (173, 32, 2481, 128, 1, True),    # (shorter ranges) 79.3, 50.0
+    (64, 128, 16384, 128, 1, False),  # 151, 156
+    (32, 96, 32768, 128, 1, False),   # 147, 162
+    (64, 64, 16384, 64, 0, True),     # 54.4, 51.1
+    (128, 64, 16384, 64, 0, False),   # 93.5, 99.1
+    (8, 64, 88500, 64, 1, False),     # 60.4, 68.8
+    (6, 96, 19416, 128, 1, True),     # one round, many ranges: 32.6, 22.4
+])
+def test_held_in_rounds(z, window, n, d, prior, one):
+    assert _one_launch("aha_prefill_scores", _params(z, 1, window, n, d, value_prior=prior)) == one
