@@ -104,7 +104,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
     set_range(own);
     Count count;
     PriorHalo<D> halo;
-    if (PRIOR && own == 0 && threadIdx.x == 63) count.look(x, z);
+    if (PRIOR && threadIdx.x == 63) {
+        count.look_epoch(x, z);
+        if (own == 0) count.look(x, z);
+    }
     bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block (or value rows) load while one multiplies
     {
         constexpr int NBL = NB / HALVES;  // row blocks that 256 threads load
@@ -130,7 +133,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         if (PRIOR) store_halo(halo, tid);
     }
     __syncthreads();
-    if (PRIOR && threadIdx.x == 63) count.look_epoch(x, z);
 
     // (one base for what a lane reads per block: scale, position, normaliser)
     int at = threadIdx.x & 31;
