@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaha.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["aha_api.hip", "value_prior.hip", "score_f32.hip", "score_bf16.hip", "score_full.hip", "score_window.hip", "score_share.hip", "score_given.hip",
+SOURCES = ["aha_api.hip", "value_prior.hip", "score_f32.hip", "score_hold_f32.hip", "score_bf16.hip", "score_full.hip", "score_window.hip", "score_share.hip", "score_given.hip",
            "attn_window.hip", "topk.hip", "compact.hip", "decode.hip"]
 
 HIPCC_FLAGS = [

@@ -302,6 +302,38 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
     pl.given_bytes = off;
 }
 
+// fp32 scores in one launch (score_hold_f32.hip), where its workgroups are on the chip at once.  Score stage, us in two launches, in one
+// (88 shapes of 8 to 192 rows, 1 to 96 heads, 200 to 5000 keys: 1.25 times as fast on average):
+//  - more than 32 rows: in ranges of 32 keys, up to 64 of them (2 heads x 272 keys x 64 rows, d = 128 15.7, 13.5; 8 x 4
+//    x 32 of 315, d = 64 17.4, 11.9; 1 x 1896 x 128, d = 64 17.5, 16.4, in ranges of 128 keys 19.5), else of 128 (2 x 4131 x 128, d = 64
+//    23.4, 21.6, of 32 keys 25.7; 8 x 3048 x 64, d = 128 37.8, 20.2; 32 x 358 x 119 27.6, 26.4);
+//  - up to 32 rows: in ranges of 128 keys (8 x 1224 x 8, d = 64 11.3, 9.2; 32 x 264 x 8, d = 128 15.3, 15.0; 4 x 2968 x 32, d = 64 18.7,
+//    9.6).  Below some 60 thousand pairs of row and key two launches take as long or less (8 x 329 x 8, d = 64 9.9, 11.2), but the
+//    host enqueues a launch less: the step with selection and compaction 19.5, 17.6, 2 x 512 x 32 18.8, 17.1; not with d = 128
+//    and a prior (8 x 306 x 16 19.2, 20.5; without 1 x 363 x 32 19.3, 16.0).
+static void plan_hold_f32(const aha_params *p, PrefillPlan &pl) {
+    pl.hold32_parts = 0;
+    const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window, blocks = (R + 31) / 32;
+    if (p->dtype != AHA_F32 || blocks > kHoldF32Blocks) return;
+    if (blocks == 1 && p->head_dim == 128 && p->value_prior && (double)pl.Z * R * p->seq_len < 6e4) return;
+    int64_t parts, keys = blocks == 1 ? 128 : 32;
+    for (;; keys = 128) {
+        parts = ((int64_t)p->seq_len + keys - 1) / keys;
+        // workgroups that the chip holds at once (the kernel has up to 18 KB of LDS besides)
+        const int64_t resident = hold_f32_lds(p->head_dim, (int)blocks, (int)keys) + 18 * 1024 <= 80 * 1024 ? 512 : 256;
+        if (pl.Z * parts <= resident && (keys == 128 || parts <= 64)) break;
+        if (keys == 128) return;
+    }
+    pl.hold32_keys = (int)keys;
+    pl.hold32_parts = (int)parts;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
+    pl.off_h32stats = take(16 * (size_t)pl.Z * parts * R);
+    pl.off_h32max = take(16 * (size_t)pl.Z * parts);
+    pl.off_h32words = take(kExchangeBytes * (size_t)pl.Z);
+    pl.hold32_bytes = off;
+}
+
 // Several query tiles (score_full.hip).
 // Places of a query head: whole waves', unless the tiles become many more (their statistics use the room behind, which only
 // the row statistics' output needs, too).  A further tile costs its products with all keys, whole waves save masks for the
@@ -407,6 +439,7 @@ static PrefillPlan plan_prefill(const aha_params *p) {
     pl.bytes = off;
     plan_window(p, pl);
     plan_given(p, pl);
+    plan_hold_f32(p, pl);
     return pl;
 }
 
@@ -615,7 +648,7 @@ int32_t aha_workspace_bytes(const aha_params *p, size_t *out_bytes) {
     int32_t rc = check_prefill(p, false);
     if (rc) return rc;
     const PrefillPlan pl = plan_prefill(p);
-    *out_bytes = std::max({pl.bytes, pl.win_bytes, pl.given_bytes, plan_decode(p).bytes, topk_ws_bytes(p)});
+    *out_bytes = std::max({pl.bytes, pl.win_bytes, pl.given_bytes, pl.hold32_bytes, plan_decode(p).bytes, topk_ws_bytes(p)});
     return AHA_OK;
 }
 
@@ -696,6 +729,14 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
                                           ? launch_score_share(g, pl, workspace, next_tag(), window_patience(pl), scores, st)
                                           : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),
                              "windowed score kernel")) ||
+            (rc = hip_result(stage(2, st), "stage event")))
+            return rc;
+        return hip_result(stage(3, st), "stage event");
+    }
+    if (pl.hold32_parts && !with_lse && !rows && workspace_bytes >= pl.hold32_bytes) {
+        const int looks = patience((int64_t)pl.Z * pl.hold32_parts, 256, 1, 2 * ((g.R + 31) / 32));
+        if ((rc = hip_result(stage(1, st), "stage event")) ||
+            (rc = hip_result(launch_score_hold_f32(g, pl, workspace, next_tag(), looks, scores, st), "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;
         return hip_result(stage(3, st), "stage event");

@@ -69,6 +69,10 @@ struct PrefillPlan {
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
     size_t off_gmax, off_gwords, given_bytes;
+    // fp32 scores in one launch (hold32_parts > 0): ranges per problem; where the rows' pairs, the ranges' largest priors, epochs
+    // and counts live
+    int hold32_parts, hold32_keys;
+    size_t off_h32stats, off_h32max, off_h32words, hold32_bytes;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;  // of the layout of two launches
 };
@@ -91,6 +95,15 @@ hipError_t launch_value_prior(const ScoreGeom &g, const PrefillPlan &pl, void *w
 // are already in the workspace, pass 1 is skipped.
 hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
                             float *scores, hipStream_t st, hipEvent_t mid, bool have_lse);
+// score_hold_f32.hip
+// The same in one launch (pl.hold32_parts > 0): up to kHoldF32Blocks blocks of 32 rows, ranges of 128 or 32 keys.
+constexpr int kHoldF32Blocks = 6;
+// dynamic LDS: a query block (rows padded by 16 bytes) per wave that takes other rows, and a weight per row and key
+constexpr size_t hold_f32_lds(int d, int blocks, int keys) {
+    return (size_t)(128 / keys) * 32 * (d + 4) * 4 + (size_t)blocks * 32 * keys * 4;
+}
+hipError_t launch_score_hold_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,
+                                 hipStream_t st);
 // score_bf16.hip
 // `fold_prior`: pass 1 also forms the value prior of its key range (windowed scores only).
 hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
