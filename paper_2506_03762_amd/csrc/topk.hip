@@ -22,11 +22,12 @@
 // in every pass.
 //
 // Bound by the latency of its chain (launch, first loads, six barriers) and, from 8K tokens on,
-// by the one CU that works on a problem.  In-kernel stamps at 8 x 32768 scores (cycles at
-// 2.4 GHz): loads and range 5.4 K, histogram 5.2 K (the LDS atomics' rate), scan 2.0 K, candidates
-// 5.0 K, rank 1.0 K, output 4.5 K with all comparisons made again there; the masks of the candidates' pass, kept on the scalar
-// unit, leave it those of the steps with keys in the threshold bin (back to back 8 x 32768 13.4 -> 12.5 us, 8 x 16384 8.6 ->
-// 8.2, 128 x 16384 8.95 -> 8.65).  Against lanes that own consecutive positions (scattered
+// by the one CU that works on a problem.  In-kernel stamps at 8 x 32768 scores (us): loads 1.9, range 1.2, histogram 2.2 (the LDS
+// atomics' rate), scan 1.0, candidates 1.9, rank 0.8, output 1.9; a vector instruction per key costs 0.2.  The masks of the
+// candidates' pass are kept on the scalar unit, so that the output compares again only in steps with keys in the threshold
+// bin (back to back 8 x 32768 13.4 -> 12.5 us).  Waves of whole steps skip the padding's instructions, scores that are not
+// negative most of the conversion, and with many steps four share a branch: 8 x 32768 12.9 -> 11.7, 4 x 24000 10.8 -> 9.75, 8 x
+// 16384 8.35 -> 8.15, 8 x 65536 33.0 -> 31.2; up to eight steps as before.  Against lanes that own consecutive positions (scattered
 // loads, per-lane bit masks, a second scan), back to back: 2 x 512 scores 5.9 -> 3.4 us,
 // 32 x 4096 6.6 -> 4.8, 12 x 5003 9.0 -> 5.4, 8 x 16384 10.0 -> 8.4, 128 x 16384 11.2 -> 9.5,
 // 8 x 32768 16.1 -> 13.2, 8 x 65536 34.8 -> 31.8, 8 x 120000 290 -> 67.
@@ -121,8 +122,17 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
             const int off = (t0 + t) * 64 + lane;
             u[t] = __float_as_uint(row[whole ? off : min(off, last)]);
         }
+        // (scores are rarely negative: then a key is the value with its sign bit set, one instruction instead of four)
+        uint32_t any = 0;
 #pragma unroll
-        for (int t = 0; t < N; ++t) u[t] = order_key(__uint_as_float(u[t]));
+        for (int t = 0; t < N; ++t) any |= u[t];
+        if (N >= 12 && __builtin_amdgcn_ballot_w64((int)any < 0) == 0) {
+#pragma unroll
+            for (int t = 0; t < N; ++t) u[t] |= 0x80000000u;
+        } else {
+#pragma unroll
+            for (int t = 0; t < N; ++t) u[t] = order_key(__uint_as_float(u[t]));
+        }
         if (!whole) {
 #pragma unroll
             for (int t = 0; t < N; ++t) {
@@ -155,7 +165,12 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
 
     // 1. range of the keys (padding: 0 - 1 wraps to the top and never is the minimum)
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    for_steps([&](uint32_t u, int) { kmin = min(kmin, u - 1u); kmax = max(kmax, u); });
+    if (!LONG && ITEMS >= 12 && whole) {  // (no padding)
+        for_steps([&](uint32_t u, int) { kmin = min(kmin, u); kmax = max(kmax, u); });
+        kmin -= 1u;
+    } else {
+        for_steps([&](uint32_t u, int) { kmin = min(kmin, u - 1u); kmax = max(kmax, u); });
+    }
     kmin = reduce_lanes<1, 64>(kmin, OpMinU{});
     kmax = reduce_lanes<1, 64>(kmax, OpMaxU{});
     if (lane == 0) { sm.red[0][wave] = kmin; sm.red[1][wave] = kmax; }
@@ -168,9 +183,13 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
     const uint32_t range = kmax - kmin;
     constexpr int kBinBits = 31 - __builtin_clz(BINS);
     const int sh = range ? max(0, 32 - __clz(range) - kBinBits) : 0;  // (range >> sh) < BINS
-    for_steps([&](uint32_t u, int) {
-        if (u >= kmin) atomicAdd(&sm.hist[(u - kmin) >> sh], 1);  // (padding keys are not counted)
-    });
+    if (!LONG && ITEMS >= 12 && whole) {
+        for_steps([&](uint32_t u, int) { atomicAdd(&sm.hist[(u - kmin) >> sh], 1); });
+    } else {
+        for_steps([&](uint32_t u, int) {
+            if (u >= kmin) atomicAdd(&sm.hist[(u - kmin) >> sh], 1);  // (padding keys are not counted)
+        });
+    }
     __syncthreads();
     {
         int cb[BPT], loc = 0;
@@ -212,30 +231,57 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
         if (lane == 0) sm.wcnt[wave] = c;
     };
     const bool ranked = nbin <= kCandMax;  // (uniform)
-    // of a ranked bin, per step: the lanes whose keys are above it, and whether any are inside
+    // of a ranked bin: per step the lanes whose keys are above it, per group of steps whether any are inside
     constexpr bool KEPT = !LONG;
+    constexpr int GROUP = KEPT && ITEMS >= 24 ? 4 : 1;  // steps that share a branch: few have keys inside (16 steps: 8 x 16384 8.05, 8.38 with four)
     unsigned long long over[KEPT ? ITEMS : 1];
     uint32_t inside = 0;
     static_assert(!KEPT || ITEMS <= 32, "a bit per step");
     if (ranked) {
         // 3a. exact rank among the keys of the threshold bin
         int above = 0;  // keys of this wave above the bin
-        for_steps([&](uint32_t u, int t) {
-            const bool gt = u > hi, cand = (u >= lo) & !gt;
-            const unsigned long long gts = ballot(gt);
-            if constexpr (KEPT) over[t] = gts;
-            above += __popcll(gts);
-            const unsigned long long in = ballot(cand);
-            if (in) {
-                if (KEPT) inside |= 1u << t;
-                int slot = 0;
-                if (lane == 0) slot = atomicAdd(&sm.ncand, __popcll(in));
-                slot = __builtin_amdgcn_readfirstlane(slot);
-                if (cand)
-                    sm.cand[mask_rank(in, slot)] =
-                        ((unsigned long long)u << 32) | (uint32_t)(~(base + t * 64 + lane));
+        auto collect = [&](unsigned long long in, bool cand, uint32_t u, int t) {
+            int slot = 0;
+            if (lane == 0) slot = atomicAdd(&sm.ncand, __popcll(in));
+            slot = __builtin_amdgcn_readfirstlane(slot);
+            if (cand) sm.cand[mask_rank(in, slot)] = ((unsigned long long)u << 32) | (uint32_t)(~(base + t * 64 + lane));
+        };
+        if constexpr (GROUP > 1) {
+#pragma unroll
+            for (int t0 = 0; t0 < ITEMS; t0 += GROUP) {
+                unsigned long long in[GROUP], any = 0;
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) {
+                    over[t0 + i] = ballot(key[t0 + i] > hi);
+                    in[i] = ballot(key[t0 + i] >= lo) & ~over[t0 + i];
+                    above += __popcll(over[t0 + i]);
+                    any |= in[i];
+                }
+                if (any) {
+                    inside |= 1u << (t0 / GROUP);
+#pragma unroll
+                    for (int i = 0; i < GROUP; ++i)
+                        if (in[i]) collect(in[i], __builtin_amdgcn_inverse_ballot_w64(in[i]), key[t0 + i], t0 + i);
+                }
             }
-        });
+        } else {
+            for_steps([&](uint32_t u, int t) {
+                if constexpr (LONG) {
+                    const unsigned long long gts = ballot(u > hi), in = ballot(u >= lo) & ~gts;
+                    above += __popcll(gts);
+                    if (in) collect(in, __builtin_amdgcn_inverse_ballot_w64(in), u, t);
+                } else {
+                    const bool gt = u > hi, cand = (u >= lo) & !gt;
+                    over[t] = ballot(gt);
+                    above += __popcll(over[t]);
+                    const unsigned long long in = ballot(cand);
+                    if (in) {
+                        inside |= 1u << t;
+                        collect(in, cand, u, t);
+                    }
+                }
+            });
+        }
         if (lane == 0) sm.wcnt[wave] = above;
         __syncthreads();
         for (int i = tid; i < nbin; i += THREADS) {
@@ -313,11 +359,23 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
     };
     if constexpr (KEPT) {
         if (ranked) {  // (the comparisons have been made, but for keys in the bin)
-            for_steps([&](uint32_t u, int t) {
-                unsigned long long m = over[t];
-                if (inside & (1u << t)) m = ballot(selected(u, t));
-                put(m, __builtin_amdgcn_inverse_ballot_w64(m), t);
-            });
+            if constexpr (GROUP > 1) {
+#pragma unroll
+                for (int t0 = 0; t0 < ITEMS; t0 += GROUP) {
+                    if (inside & (1u << (t0 / GROUP))) {
+#pragma unroll
+                        for (int t = t0; t < t0 + GROUP; ++t) over[t] = ballot(selected(key[t], t));
+                    }
+#pragma unroll
+                    for (int t = t0; t < t0 + GROUP; ++t) put(over[t], __builtin_amdgcn_inverse_ballot_w64(over[t]), t);
+                }
+            } else {
+                for_steps([&](uint32_t u, int t) {
+                    unsigned long long m = over[t];
+                    if (inside & (1u << t)) m = ballot(selected(u, t));
+                    put(m, __builtin_amdgcn_inverse_ballot_w64(m), t);
+                });
+            }
             return;
         }
     }
