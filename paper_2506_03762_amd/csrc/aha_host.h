@@ -110,7 +110,8 @@ hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws
                              float *scores, hipStream_t st, hipEvent_t mid, bool have_lse,
                              bool fold_prior);
 // score_full.hip
-// The same with more rows than one tile (pl.n_qtiles > 1); the prior has been formed, the scores are zero.
+// The same with more rows than one tile (pl.n_qtiles > 1); a prior has been formed and the scores are zero, or the row statistics zero
+// them (no prior, no given normalisers).
 hipError_t launch_score_full(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores, hipStream_t st,
                              hipEvent_t mid, bool have_lse);
 // score_window.hip

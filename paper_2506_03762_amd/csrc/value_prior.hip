@@ -6,7 +6,7 @@
 // The windowed bf16 scores form the prior inside their one launch (score_window.hip,
 // score_given.hip) or, in two, inside the row statistics (score_bf16.hip, up to 128 rows), fp32
 // inputs as extra workgroups of theirs (score_f32.hip); this kernel serves full accumulation
-// (where it also zeroes the scores), pool widths above 17, chosen rows, larger tiles whose workspace
+// (where it also zeroes the scores; without a prior the row statistics do), pool widths above 17, chosen rows, larger tiles whose workspace
 // holds two launches only, and given normalisers in two launches (which it converts for the
 // column-sum pass).
 #include "value_tile.h"
@@ -45,9 +45,9 @@ hipError_t launch_value_prior(const ScoreGeom &g, const PrefillPlan &pl, void *w
     char *w = (char *)ws;
     float *gamma = (float *)(w + pl.off_gamma);
     float *gbm = (float *)(w + pl.off_gblockmax);
-    // bf16 full accumulation (several query tiles) needs zeroed scores
+    if (!prior_here && !lse) return hipSuccess;  // nothing for this launch to do
+    // bf16 full accumulation (several query tiles) needs zeroed scores (without this launch the row statistics zero them)
     float *zero_scores = (g.dtype == AHA_BF16 && pl.n_qtiles > 1) ? scores : nullptr;
-    if (!prior_here && !zero_scores && !lse) return hipSuccess;  // nothing for this launch to do
     ScoreGeom gl = g;
     gl.value_prior = prior_here ? 1 : 0;
     const int vt = (prior_here || zero_scores) ? pl.n_vtiles : 1;
