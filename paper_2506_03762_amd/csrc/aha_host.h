@@ -77,7 +77,7 @@ struct PrefillPlan {
     size_t bytes;  // of the layout of two launches
 };
 
-constexpr int kExchangeBytes = 256;  // per problem: count and epoch of an exchange inside a launch
+constexpr int kExchangeBytes = 128;  // per problem: count and epoch of an exchange inside a launch
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup
 constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)
 constexpr int kFullKeys = 64;     // keys of a step with several query tiles
@@ -123,6 +123,10 @@ hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *
 // The same with pl.win_share.
 hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                               float *scores, hipStream_t st);
+// Keys of a range whose norms and prior the LDS keeps: in the kernels that share the keys (score_share.hip), in the others that
+// sweep twice (score_window.hip).  Longer ranges keep them in the workspace.
+int share_keys_in_lds(int d, int tiles);
+int stream_keys_in_lds(int d, int nb, int tiles);
 // score_given.hip
 // Keys of a range whose norms, prior and column sums (12 bytes) fit beside a tile of nb blocks of query
 // rows (and 1 KB of other values) with two workgroups per CU (up to four blocks) or one.

@@ -10,7 +10,7 @@
 //
 // us of the step (scores, top-k, compaction) against waves that keep 64 keys in registers and read the rows from LDS: 8 heads x
 // 16384 keys x 512 rows 73.1 -> 59.8 (77.3 -> 66.1 on another box), 8 x 32768 x 256 81.7 -> 77.6.  In the latter (stamps, us): first keys 8, first sweep
-// 18, announced to seen 3.5, merged 1.6, second sweep 22, prior and its exchange 4; 537 and 690 ns per 64 x 32 block and
+// 18, exchange and merge 5 (some 3 since its words carry the data), second sweep 22, prior and its exchange 4; 537 and 690 ns per 64 x 32 block and
 // SIMD, where the matrix core and the vector ALU would take 400 together: the sweeps read 200 MB in 40 us besides, a
 // barrier per 64 keys.  Steps on the way: value rows three steps of 64 keys ahead instead of one of 128, 81.6 -> 77.6; value
 // rows beside the first sweep and the wave-private keys, 84.4 instead of 83.5.
@@ -492,6 +492,11 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
                        (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax), (float *)(w + pl.off_wnu),
                        (float *)(w + pl.off_wgamma), scores);
     return hipGetLastError();
+}
+
+int share_keys_in_lds(int d, int tiles) {
+    if (d == 64) return ShareSmem<64, 8, true>::KEYS;
+    return tiles == 2 ? ShareSmem<128, 8, true>::KEYS : ShareSmem<128, 4, true>::KEYS;
 }
 
 hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,

@@ -671,6 +671,12 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     return hipErrorInvalidValue;
 }
 
+int stream_keys_in_lds(int d, int nb, int tiles) {
+    if (d == 128) return tiles == 2 ? StreamSmem<128, 6, 2>::KEYS : StreamSmem<128, 6, 1>::KEYS;
+    if (tiles == 2) return StreamSmem<64, 6, 2>::KEYS;
+    return nb == 4 ? StreamSmem<64, 4, 1>::KEYS : nb == 6 ? StreamSmem<64, 6, 1>::KEYS : StreamSmem<64, 8, 1>::KEYS;
+}
+
 hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
                                float *scores, hipStream_t st) {
     char *w = (char *)ws;
