@@ -15,7 +15,7 @@
 //
 // The tag is a 64-bit number that no other call of the process uses, so the workspace needs no clearing launch
 // (3 us) in front: whatever it holds on entry is not this tag.  A captured graph replays a call with
-// its tag, so a number in the workspace, one per problem and whatever it is on entry, is added to it, and
+// its tag, so a number in the workspace, one per problem and whatever it is on entry, goes into it, and
 // the workgroup that is the last of its problem to have seen all parts moves that number on (everybody has read it by then).  It is
 // found by a counter that starts itself: its upper bits are the call's number, and an arrival that finds other
 // bits there sets them.
@@ -126,6 +126,9 @@ __device__ __forceinline__ int largest_of(const Words &x, int nparts, int own, i
 struct Count {
     uint64_t found, epoch;
     __device__ __forceinline__ void look_epoch(const Exchange &x, int z) { epoch = get(x.epoch(z)); }
+    // of the words.  (Times an odd number of 64 bits: calls' tags lie 2^20 apart, and epochs of different problems
+    // or layouts that differ by that much would meet.)
+    __device__ __forceinline__ uint64_t words_tag(const Exchange &x) const { return x.tag + epoch * 0x9E3779B97F4A7C15u; }
     __device__ __forceinline__ void look(const Exchange &x, int z) { found = get(x.count(z)); }
     __device__ __forceinline__ void start(const Exchange &x, int z) {
         if ((found ^ x.tag) >> kCountBits)

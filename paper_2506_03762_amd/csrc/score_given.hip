@@ -241,7 +241,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
                 gm = sMax[0];
 #pragma unroll
                 for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
-                const uint64_t tag = x.tag + count.epoch;  // (of the last lane)
+                const uint64_t tag = count.words_tag(x);  // (of the last lane)
                 const Words priors(maxima + (int64_t)z * nparts,
                                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(tag >> 32), 63) << 32 |
                                        (uint32_t)__builtin_amdgcn_readlane((int)tag, 63));

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
             if (lane == 0) s_max[wave] = gam;
         }
         if (part == 0 && wave == 3) count.started();
-        if (tid == 255) s_tag = x.tag + count.epoch;
+        if (tid == 255) s_tag = count.words_tag(x);
         __syncthreads();
         const uint64_t tag = s_tag;
         const Words rows(stats + (int64_t)z * nparts * g.R, tag), priors(maxima + (int64_t)z * nparts, tag);

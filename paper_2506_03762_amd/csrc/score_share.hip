@@ -371,7 +371,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
         }
         // the last requests, past the range, write to LDS, where the second sweep begins (and the count is to be there first)
         wait_vm<0>();
-        if (tid == 511) *sTag = x.tag + count.epoch;
+        if (tid == 511) *sTag = count.words_tag(x);
         __syncthreads();
         const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), *sTag);
         if (tid < W::ROWS) {

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                 sNu[halo.pos - max(0, key_begin - (g.pool - 1) / 2)] = hn;
         }
         if (part == 0 && wave == WAVES - 1) count.started();
-        if (tid == THREADS - 1) *sTag = x.tag + count.epoch;
+        if (tid == THREADS - 1) *sTag = count.words_tag(x);
         __syncthreads();
         const uint64_t tag = *sTag;
         const Words rows(stats + (int64_t)z * nparts * (H::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * WAVES, tag);
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             if (lane < 32) sRed[wave * W::TROWS + nb * 32 + lane] = make_float2(m[nb], s[nb]);
         }
         if (part == 0 && wave == 7) count.started();
-        if (tid == 511) *sTag = x.tag + count.epoch;
+        if (tid == 511) *sTag = count.words_tag(x);
         __syncthreads();
         const uint64_t tag = *sTag;
         const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * 8, tag);
