@@ -676,6 +676,14 @@ static uint64_t next_tag() {
 }
 static thread_local int32_t g_looks = kLooks;
 
+// Captured calls are replayed with the same tag (a stream that does not say is taken for capturing).
+static ExchangeCall exchange_call(hipStream_t st, int looks) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(st, &status);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return {next_tag(), looks, e != hipSuccess || status != hipStreamCaptureStatusNone};
+}
+
 // Looks of a call of `workgroups` in all, of which the chip holds `resident` at once and each multiplies nb blocks of
 // 32 rows with each of `steps` key blocks per wave for its part.  All of them at once: a few times what a part takes (set-up
 // and exchange 15 us; a step its loads, 15 us with the whole chip loading, or its products, 2.5 us a
@@ -733,10 +741,10 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     if (with_lse ? pl.given_nb && workspace_bytes >= pl.given_bytes
                  : pl.win_nb && !rows && workspace_bytes >= pl.win_bytes) {
         if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, next_tag(), given_patience(pl), lse, scores, st)
+            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, exchange_call(st, given_patience(pl)), lse, scores, st)
                                       : pl.win_share
-                                          ? launch_score_share(g, pl, workspace, next_tag(), window_patience(pl), scores, st)
-                                          : launch_score_window(g, pl, workspace, next_tag(), window_patience(pl), scores, st),
+                                          ? launch_score_share(g, pl, workspace, exchange_call(st, window_patience(pl)), scores, st)
+                                          : launch_score_window(g, pl, workspace, exchange_call(st, window_patience(pl)), scores, st),
                              "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;
@@ -745,7 +753,7 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     if (pl.hold32_parts && !with_lse && !rows && workspace_bytes >= pl.hold32_bytes) {
         const int looks = patience((int64_t)pl.Z * pl.hold32_parts, 256, 1, 2 * ((g.R + 31) / 32));
         if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(launch_score_hold_f32(g, pl, workspace, next_tag(), looks, scores, st), "windowed score kernel")) ||
+            (rc = hip_result(launch_score_hold_f32(g, pl, workspace, exchange_call(st, looks), scores, st), "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;
         return hip_result(stage(3, st), "stage event");

@@ -62,22 +62,28 @@ struct PrefillPlan {
     bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
     // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
     // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
-    // prior maxima, epochs and counts (exchange.h), the value norms and the prior live
+    // prior maxima and counts (exchange.h), the value norms and the prior live
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold, win_share;  // (share: by the kernel whose waves share the keys)
     size_t off_wstats, off_wmax, off_wwords, off_wnu, off_wgamma, win_bytes;
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
     size_t off_gmax, off_gwords, given_bytes;
-    // fp32 scores in one launch (hold32_parts > 0): ranges per problem; where the rows' pairs, the ranges' largest priors, epochs
-    // and counts live
+    // fp32 scores in one launch (hold32_parts > 0): ranges per problem; where the rows' pairs, the ranges' largest priors and
+    // the counts live
     int hold32_parts, hold32_keys;
     size_t off_h32stats, off_h32max, off_h32words, hold32_bytes;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;  // of the layout of two launches
 };
 
-constexpr int kExchangeBytes = 128;  // per problem: count and epoch of an exchange inside a launch
+constexpr int kExchangeBytes = 128;  // per problem: the count of an exchange inside a launch
+// A call whose workgroups exchange parts of a result inside a launch (exchange.h).
+struct ExchangeCall {
+    uint64_t tag;   // a number that no other call uses, its low 20 bits zero
+    int looks;      // at the other workgroups' parts before missing ones are done in place
+    bool replayed;  // captured into a graph
+};
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup
 constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)
 constexpr int kFullKeys = 64;     // keys of a step with several query tiles
@@ -102,7 +108,7 @@ constexpr int kHoldF32Blocks = 6;
 constexpr size_t hold_f32_lds(int d, int blocks, int keys) {
     return (size_t)(128 / keys) * 32 * (d + 4) * 4 + (size_t)blocks * 32 * keys * 4;
 }
-hipError_t launch_score_hold_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,
+hipError_t launch_score_hold_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call, float *scores,
                                  hipStream_t st);
 // score_bf16.hip
 // `fold_prior`: pass 1 also forms the value prior of its key range (windowed scores only).
@@ -115,13 +121,12 @@ hipError_t launch_score_bf16(const ScoreGeom &g, const PrefillPlan &pl, void *ws
 hipError_t launch_score_full(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores, hipStream_t st,
                              hipEvent_t mid, bool have_lse);
 // score_window.hip
-// Windowed scores in one launch (pl.win_nb > 0).  `tag`: a number no other call uses, its low 20 bits
-// zero; `looks`: at the other workgroups' parts before missing ones are done in place.
-hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+// Windowed scores in one launch (pl.win_nb > 0).
+hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                                float *scores, hipStream_t st);
 // score_share.hip
 // The same with pl.win_share.
-hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                               float *scores, hipStream_t st);
 // Keys of a range whose norms and prior the LDS keeps: in the kernels that share the keys (score_share.hip), in the others that
 // sweep twice (score_window.hip).  Longer ranges keep them in the workspace.
@@ -135,7 +140,7 @@ constexpr int given_keys(int d, int nb) {
     return room / 12 / 512 * 512;
 }
 // The same from the caller's row normalisers `lse` (pl.given_nb > 0).
-hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                               const float *lse, float *scores, hipStream_t st);
 // Row statistics of the observed rows out (pass 1 only): natural-log normaliser and entropy,
 // dense [batch, Hq, window]; either pointer may be null.

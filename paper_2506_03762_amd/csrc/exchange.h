@@ -8,17 +8,19 @@
 // announcements behind the data, which a wave looked at before all fetched the data, it was three.  us of the step before and after:
 // 12 heads x 5003 keys x 120 rows 23.5 -> 21.2, 32 x 4096 x 64 31.6 -> 31.1, 128 x 16384 x 64 338 -> 336, 8 x 16384 x 512 65.6 ->
 // 63.2, 8 x 32768 x 256 79.5 -> 77.0.
-// A line that every wave of a launch reads is slow: with the problems' counts and epochs (below) side by side and the epoch read by
-// each wave 8 x 32768 x 256 took 80.4 and 32 x 4096 x 64 31.8, with a line per problem and one reader per workgroup 78.2 and 30.7.  Taken
-// back: the priors' maxima looked for together with the row statistics (32 x 4096 0.9 slower: they come later), or
+// Taken back: the priors' maxima looked for together with the row statistics (32 x 4096 0.9 slower: they come later), or
 // requested before these are merged (0.3 slower).
 //
 // The tag is a 64-bit number that no other call of the process uses, so the workspace needs no clearing launch
 // (3 us) in front: whatever it holds on entry is not this tag.  A captured graph replays a call with
-// its tag, so a number in the workspace, one per problem and whatever it is on entry, goes into it, and
-// the workgroup that is the last of its problem to have seen all parts moves that number on (everybody has read it by then).  It is
-// found by a counter that starts itself: its upper bits are the call's number, and an arrival that finds other
-// bits there sets them.
+// its tag, and other work may have written to any part of the workspace since, so nothing that lies there can tell two replays
+// apart: no word may outlive a replay.  The workgroup that is the last of its problem to have seen all parts takes
+// the words away; only captured calls do that (the host asks the stream).  It is found by a
+// counter that starts itself: its upper bits are the call's number, and an arrival that finds other
+// bits there sets them.  us of the score stage, eager and replayed: 32 x 4096 x 64 20.4, 21.1; 8 x 16384 x 512 46.2, 47.4; 1 x 131072 x
+// 64, 8192 words 28.0, 33.2.  (Words told apart by a number in the workspace that each call moved on cost
+// a load per workgroup instead, 20.3, 46.8 and 30.6 either way, and were taken for the next replay's once other work
+// had put that number back.)
 //
 // Nobody depends on workgroups that may not be running: after `looks` looks at the others' parts a
 // workgroup does missing parts itself and leaves them too (a part's result is the same bits whoever
@@ -34,11 +36,11 @@
 namespace aha {
 
 struct Exchange {
-    uint64_t *words;  // [problem][kExchangeBytes / 8], in memory lines of its own: a count, a number that is added to the tag
-    uint64_t tag;     // of this call; the low kCountBits are zero, the rest is not
-    int looks;        // at the others' parts before missing ones are done here
-    __device__ __forceinline__ uint64_t *count(int z) const { return words + (int64_t)z * (kExchangeBytes / 8); }
-    __device__ __forceinline__ uint64_t *epoch(int z) const { return count(z) + 1; }
+    uint64_t *counts;  // [problem][kExchangeBytes / 8], a count for each
+    uint64_t tag;      // of this call; the low kCountBits are zero, the rest is not
+    int looks;         // at the others' parts before missing ones are done here
+    bool replayed;     // the call is captured: its words are taken away
+    __device__ __forceinline__ uint64_t *count(int z) const { return counts + (int64_t)z * (kExchangeBytes / 8); }
 };
 constexpr int kCountBits = 20;  // parts of a problem: fewer than 2^20
 
@@ -51,22 +53,31 @@ __device__ __forceinline__ T get(const T *p) {
     return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// What a part leaves goes as words of 16 bytes that carry the tag beside two floats: {value, tag, value, tag}, the
-// tag's lower and upper half, stored and loaded in one piece (each half proves its own float
-// if they ever were not).
+// What a part leaves goes as words of 16 bytes that carry the tag beside two floats: {value, lo, value, hi}, stored and loaded in
+// one piece (each half proves its own float if they ever were not: either of lo and hi differs between any two of 2^32
+// consecutive calls).
 struct Words {
     __amdgpu_buffer_rsrc_t at;
-    uint32_t lo, hi;  // tag halves
+    uint32_t lo, hi;  // both zero for no call
     // (a problem's words lie within 2^31 bytes)
     __device__ __forceinline__ Words(void *base, uint64_t tag)
-        : at(__builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000)),
-          lo(__builtin_amdgcn_readfirstlane((int)(uint32_t)tag)), hi(__builtin_amdgcn_readfirstlane((int)(uint32_t)(tag >> 32))) {}
+        : at(__builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000)), lo((uint32_t)(tag >> kCountBits)),
+          hi((uint32_t)(tag >> (kCountBits + 32)) + lo * 0x9E3779B1u) {}
     static constexpr int kAgent = 16;  // (sc1: past the caches that are not shared)
     __device__ __forceinline__ void put(int word, float a, float b) const {
         __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(a), lo, __float_as_uint(b), hi}, at, word * 16, 0, kAgent);
     }
     __device__ __forceinline__ u32x4 get(int word) const {
         return __builtin_amdgcn_raw_buffer_load_b128(at, word * 16, 0, kAgent);
+    }
+    // The first `words` of them at `base` are none any more, by all threads of a workgroup.  (Through the caches: that has to have
+    // arrived at the launch's end only.  Eight stores to a branch, past the last word dropped: one CU does it.)
+    static __device__ __forceinline__ void take_away(void *base, int words, int tid, int threads) {
+        const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(base, 0, words * 16, 0x00027000);
+        for (int i = tid; i < words; i += 8 * threads)
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, to, (i + t * threads) * 16, 0, 0);
     }
     __device__ __forceinline__ bool there(u32x4 w) const { return w.y == lo && w.w == hi; }
 };
@@ -118,34 +129,39 @@ __device__ __forceinline__ int largest_of(const Words &x, int nparts, int own, i
     return missing;
 }
 
-// The count of a problem's workgroups that have seen all parts, so that the last one can move the epoch on.
+// The count of a problem's workgroups that have seen all parts, so that the last one can take the words away.
 // Whoever does part 0 sets it to the tag (unless somebody else has) before leaving that part's words:
 // nobody counts himself before.  One thread of the workgroup: `look` early, `start` some time
-// before, `started` (its wave) in front of the barrier before the first word.  It also reads the number that is added to the
-// tag, for the workgroup.
+// before, `started` (its wave) in front of the barrier before the first word.  Calls that are not replayed count nothing.
 struct Count {
-    uint64_t found, epoch;
-    __device__ __forceinline__ void look_epoch(const Exchange &x, int z) { epoch = get(x.epoch(z)); }
-    // of the words.  (Times an odd number of 64 bits: calls' tags lie 2^20 apart, and epochs of different problems
-    // or layouts that differ by that much would meet.)
-    __device__ __forceinline__ uint64_t words_tag(const Exchange &x) const { return x.tag + epoch * 0x9E3779B97F4A7C15u; }
-    __device__ __forceinline__ void look(const Exchange &x, int z) { found = get(x.count(z)); }
+    uint64_t found;
+    __device__ __forceinline__ void look(const Exchange &x, int z) {
+        if (x.replayed) found = get(x.count(z));
+    }
     __device__ __forceinline__ void start(const Exchange &x, int z) {
-        if ((found ^ x.tag) >> kCountBits)
+        if (x.replayed && (found ^ x.tag) >> kCountBits)
             (void)__hip_atomic_compare_exchange_strong(x.count(z), &found, x.tag, __ATOMIC_RELAXED,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ __forceinline__ void started() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-    // once per workgroup, when it has seen all parts
+    __device__ __forceinline__ void started(const Exchange &x) { arrived(x); }
+    // The wave's words have arrived: in front of a barrier between the last word and `arrive`.  (Else one of this workgroup's could
+    // come behind the taking away, where another has done its part, too.)
+    static __device__ __forceinline__ void arrived(const Exchange &x) {
+        if (x.replayed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    // once per workgroup, when all its waves have seen all parts
     __device__ __forceinline__ void arrive(const Exchange &x, int z) {
-        found = __hip_atomic_fetch_add(x.count(z), (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (x.replayed) found = __hip_atomic_fetch_add(x.count(z), (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
-// By the thread that arrived, at the end of the workgroup's work.
-__device__ __forceinline__ void leave(const Exchange &x, int z, int nparts, const Count &c) {
-    if (c.found != x.tag + (uint64_t)(nparts - 1)) return;
-    put(x.epoch(z), c.epoch + 1);
-    put(x.count(z), (uint64_t)0);
+// At the end of the workgroup's work, by all its threads; `counted`: the one that arrived; `flag`: in LDS, used by nobody since a
+// barrier.  Whether it is the last of its problem, which takes the words away.
+__device__ __forceinline__ bool leave(const Exchange &x, int z, int nparts, const Count &c, bool counted, int *flag) {
+    if (!x.replayed) return false;
+    if (counted) *flag = c.found == x.tag + (uint64_t)(nparts - 1);
+    __syncthreads();
+    if (*flag != 0 && counted) put(x.count(z), (uint64_t)0);
+    return *flag != 0;
 }
 
 // Row statistics.

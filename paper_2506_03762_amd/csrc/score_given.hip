@@ -104,10 +104,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
     set_range(own);
     Count count;
     PriorHalo<D> halo;
-    if (PRIOR && threadIdx.x == 63) {
-        count.look_epoch(x, z);
-        if (own == 0) count.look(x, z);
-    }
+    if (PRIOR && own == 0 && threadIdx.x == 63) count.look(x, z);
     bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block (or value rows) load while one multiplies
     {
         constexpr int NBL = NB / HALVES;  // row blocks that 256 threads load
@@ -226,6 +223,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63;
+        const Words priors(maxima + (int64_t)z * nparts, x.tag);
         for (int part = own;;) {
             if (part == 0 && tid == 63) {
                 if (own != 0) count.look(x, z);
@@ -235,22 +233,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
             __syncthreads();
             float gm = wave_max(pool_norms(g, key_begin, key_end, sN, sGam, tid, THREADS));
             if (lane == 0) sMax[wave] = gm;
-            if (part == 0 && wave == 0) count.started();
+            if (part == 0 && wave == 0) count.started(x);
             __syncthreads();
             if (wave == 0) {
                 gm = sMax[0];
 #pragma unroll
                 for (int wv = 1; wv < WAVES; ++wv) gm = fmaxf(gm, sMax[wv]);
-                const uint64_t tag = count.words_tag(x);  // (of the last lane)
-                const Words priors(maxima + (int64_t)z * nparts,
-                                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(tag >> 32), 63) << 32 |
-                                       (uint32_t)__builtin_amdgcn_readlane((int)tag, 63));
                 if (lane == 0) priors.put(part, gm, 0.f);
                 const int missing = least_missing(largest_of<1>(priors, nparts, own, x.looks, lane, 64, gm));
                 if (lane == 0) {
                     *sMissing = missing;
                     sMax[0] = gm;
                 }
+                count.arrived(x);
             }
             __syncthreads();
             const int missing = *sMissing;
@@ -273,7 +268,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void window_given_kernel(ScoreGeom g
         float *out = scores + (int64_t)z * g.n;
         for (int j = key_begin + tid; j < key_end; j += THREADS)
             out[j] = sSum[j - key_begin] * prior_factor(sGam[j - key_begin], ginv);
-        if (tid == 63) leave(x, z, nparts, count);
+        if (leave(x, z, nparts, count, tid == 63, sMissing + 1)) Words::take_away(maxima + (int64_t)z * nparts, nparts, tid, THREADS);
     }
 }
 
@@ -308,10 +303,10 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+hipError_t launch_score_given(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                               const float *lse, float *scores, hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_gwords), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_gwords), call.tag, call.looks, call.replayed};
     u32x4 *maxima = (u32x4 *)(w + pl.off_gmax);
     auto launch = [&](auto prior) {
         constexpr int PRIOR = decltype(prior)::value;

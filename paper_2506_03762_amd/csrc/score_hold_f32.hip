@@ -35,7 +35,6 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
     __shared__ float s_ref[kHoldF32Blocks][KW * 64], s_lam[ROWS], s_M[ROWS], s_inv[ROWS];
     __shared__ float s_nu[KEYS + 256], s_gam[KEYS], s_max[4], s_all[4], s_acc[RW][KEYS];
     __shared__ int s_missing[4];
-    __shared__ uint64_t s_tag;
     const int nblocks = (g.R + 31) / 32, rp = nblocks * 32;
     float *sw = dyn + RW * QB;
 
@@ -49,6 +48,7 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
     const int half = (g.pool - 1) / 2;
 
     Count count;
+    const Words rows(stats + (int64_t)z * nparts * g.R, x.tag), priors(maxima + (int64_t)z * nparts, x.tag);
     int kbeg;
     for (int part = own;;) {
         int tid = threadIdx.x;
@@ -56,10 +56,7 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
         const int lane = tid & 63;
         kbeg = part * KEYS;
         const int kb = kbeg + kw * 32, gt = tid % GT;
-        if (tid == 255) {
-            count.look_epoch(x, z);
-            if (part == 0) count.look(x, z);
-        }
+        if (part == 0 && tid == 255) count.look(x, z);
         F32QueryBlock<D, GT> qb;
         qb.request(g, rm, b, h, rw * 32, gt);
         f32x4 a[D / 8];
@@ -118,11 +115,8 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
             gam = wave_max(gam);
             if (lane == 0) s_max[wave] = gam;
         }
-        if (part == 0 && wave == 3) count.started();
-        if (tid == 255) s_tag = count.words_tag(x);
+        if (part == 0 && wave == 3) count.started(x);
         __syncthreads();
-        const uint64_t tag = s_tag;
-        const Words rows(stats + (int64_t)z * nparts * g.R, tag), priors(maxima + (int64_t)z * nparts, tag);
         if (g.value_prior && tid == 255) priors.put(part, fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])), 0.f);
         if (tid < g.R) {
             float m = s_row[0][tid].x, s = s_row[0][tid].y;
@@ -157,6 +151,7 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
         }
         missing = least_missing(missing);
         if (lane == 0) s_missing[wave] = missing;
+        count.arrived(x);
         __syncthreads();
 #pragma unroll
         for (int wv = 0; wv < 4; ++wv) missing = min(missing, s_missing[wv]);
@@ -202,7 +197,10 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
         }
         scores[(int64_t)z * g.n + j] = out;
     }
-    if (tid == 255) leave(x, z, nparts, count);
+    if (leave(x, z, nparts, count, tid == 255, &s_missing[1])) {
+        Words::take_away(stats + (int64_t)z * nparts * g.R, nparts * g.R, tid, 256);
+        if (g.value_prior) Words::take_away(maxima + (int64_t)z * nparts, nparts, tid, 256);
+    }
 }
 
 template <int D, int KW>
@@ -219,10 +217,10 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     return hipGetLastError();
 }
 
-hipError_t launch_score_hold_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,
+hipError_t launch_score_hold_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call, float *scores,
                                  hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_h32words), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_h32words), call.tag, call.looks, call.replayed};
     if (pl.hold32_keys == 32) return g.d == 64 ? launch_t<64, 1>(g, pl, x, w, scores, st) : launch_t<128, 1>(g, pl, x, w, scores, st);
     return g.d == 64 ? launch_t<64, 4>(g, pl, x, w, scores, st) : launch_t<128, 4>(g, pl, x, w, scores, st);
 }

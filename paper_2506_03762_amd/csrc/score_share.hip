@@ -36,8 +36,8 @@ struct ShareSmem {
     static constexpr int off_row = off_col + 4 * 8 * 64 * 4;  // normaliser, scale, position
     static constexpr int off_misc = off_row + 3 * ROWS * 4;
     // between the sweeps: float2 [8][256], in the fourth stage if it is large enough
-    static constexpr int red_bytes = 8 * 256 * 8, off_red = red_bytes <= stage2 ? 3 * stage2 : off_misc + 20 * 4;
-    static constexpr int off_nu = off_misc + 20 * 4 + (red_bytes <= stage2 ? 0 : red_bytes);
+    static constexpr int red_bytes = 8 * 256 * 8, off_red = red_bytes <= stage2 ? 3 * stage2 : off_misc + 16 * 4;
+    static constexpr int off_nu = off_misc + 16 * 4 + (red_bytes <= stage2 ? 0 : red_bytes);
     // ranges of up to KEYS keys keep their norms, prior and sums in LDS, longer ones in the workspace and the scores
     static constexpr int room = 160 * 1024 - off_nu - kPriorMaxHalo * 4;
     static constexpr int KEYS = !PRIOR ? 0 : room >= 2048 * 12 ? 2048 : room / 12 / 256 * 256;
@@ -62,7 +62,6 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     int *sPos = (int *)(sLam + W::ROWS);
     float *sMax = (float *)(smem + W::off_misc);
     int *sMissing = (int *)sMax + 8;
-    uint64_t *sTag = (uint64_t *)(sMax + 16);
     float *sN = (float *)(smem + W::off_nu), *sGam = (float *)(smem + W::off_gam), *sSum = (float *)(smem + W::off_sum);
     const bool in_lds = W::KEYS && part_keys <= W::KEYS;
 
@@ -336,7 +335,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     };
 
     Count count;
-    if (threadIdx.x == 511) count.look_epoch(x, z);
+    const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), x.tag), priors(maxima + (int64_t)z * nparts, x.tag);
     load_rows_of_wave<D, NQ>(g, rm, b, h, w0, (int)threadIdx.x & 63, qf);
     {
         const int tid = threadIdx.x, lane = tid & 63;
@@ -371,9 +370,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
         }
         // the last requests, past the range, write to LDS, where the second sweep begins (and the count is to be there first)
         wait_vm<0>();
-        if (tid == 511) *sTag = count.words_tag(x);
         __syncthreads();
-        const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), *sTag);
         if (tid < W::ROWS) {
             float M = sRed[tid].x, total = sRed[tid].y;
             if constexpr (W::KG == 2) merge_stats(M, total, sRed[W::ROWS + tid].x, sRed[W::ROWS + tid].y);
@@ -423,7 +420,6 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
     second_sweep();
     if constexpr (PRIOR != 0) {
         asm volatile("" : "+v"(tid));
-        const Words priors(maxima + (int64_t)z * nparts, *sTag);
         PriorHalo<D> halo;
         halo.request(g, vbase, key_begin, key_end, tid);
         for (int part = own, looks = x.looks;;) {
@@ -449,6 +445,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
                     *sMissing = missing;
                     sMax[0] = all;
                 }
+                count.arrived(x);
             }
             __syncthreads();
             const int missing = *sMissing;
@@ -475,7 +472,10 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
                             : out[j] * prior_factor(gamma[(int64_t)z * g.n + j], ginv);
     }
     if (tid == 511) count.arrive(x, z);
-    if (tid == 511) leave(x, z, nparts, count);
+    if (leave(x, z, nparts, count, tid == 511, sMissing + 1)) {
+        Words::take_away(stats + (int64_t)z * nparts * (W::ROWS / 2), nparts * (W::ROWS / 2), tid, 512);
+        if (PRIOR) Words::take_away(maxima + (int64_t)z * nparts, nparts, tid, 512);
+    }
 }
 
 // ---------------------------------------------------------------- launch --
@@ -499,10 +499,10 @@ int share_keys_in_lds(int d, int tiles) {
     return tiles == 2 ? ShareSmem<128, 8, true>::KEYS : ShareSmem<128, 4, true>::KEYS;
 }
 
-hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks, float *scores,
+hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call, float *scores,
                               hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_wwords), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_wwords), call.tag, call.looks, call.replayed};
     auto scaled = [&](auto d, auto rg, auto prior) {
         constexpr int D = decltype(d)::value, RG = decltype(rg)::value, PRIOR = decltype(prior)::value;
         return g.scale_mode == AHA_SCALE_FIXED ? launch_t<D, RG, true, PRIOR>(g, pl, x, w, scores, st)

@@ -36,7 +36,7 @@ struct HoldSmem {
     static constexpr size_t off_nu = off_red + 4 * ROWS * sizeof(float2);
     static constexpr size_t off_gam = off_nu + (PRIOR ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
     static constexpr size_t off_misc = off_gam + (PRIOR ? KEYS * sizeof(float) : 0);
-    static constexpr size_t bytes = off_misc + 20 * sizeof(float);
+    static constexpr size_t bytes = off_misc + 16 * sizeof(float);
     static_assert(KEYS * sizeof(float) <= 4 * ROWS * sizeof(float2) || NT == 1, "column sums of the second tile");
     static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
 };
@@ -62,7 +62,6 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     float *sNu = (float *)(smem + H::off_nu), *sGam = (float *)(smem + H::off_gam);
     float *sMax = (float *)(smem + H::off_misc);
     int *sMissing = (int *)sMax + 8;
-    uint64_t *sTag = (uint64_t *)(sMax + 16);
 
     const int own = (int)blockIdx.x % nparts, z = (int)blockIdx.x / nparts;
     const int b = z / g.Hkv, h = z % g.Hkv;
@@ -71,6 +70,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
     const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
 
     Count count;
+    const Words rows(stats + (int64_t)z * nparts * (H::ROWS / 2), x.tag), priors(maxima + (int64_t)z * nparts * WAVES, x.tag);
     f32x16 acc[STEPS][NB][kMB];
     float ref[STEPS][NB];
     int pos[NB], bmin[NB];
@@ -126,10 +126,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                 if (st + 1 < STEPS) load_values(st + 1);
             }
             // (keys at or past n, in the last range, lie behind every row's position)
-            if (st == STEPS - 1) {  // (used behind the products)
-                if (tid == THREADS - 1) count.look_epoch(x, z);
-                if (part == 0 && tid == THREADS - 1) count.start(x, z);
-            }
+            if (st == STEPS - 1 && part == 0 && tid == THREADS - 1) count.start(x, z);
             bf16x8 qf = query_fragment<D, NB>(sQ, 0, 0, lane);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
@@ -154,11 +151,8 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
             if (halo.valid && tid % PriorHalo<D>::CPR == 0)
                 sNu[halo.pos - max(0, key_begin - (g.pool - 1) / 2)] = hn;
         }
-        if (part == 0 && wave == WAVES - 1) count.started();
-        if (tid == THREADS - 1) *sTag = count.words_tag(x);
+        if (part == 0 && wave == WAVES - 1) count.started(x);
         __syncthreads();
-        const uint64_t tag = *sTag;
-        const Words rows(stats + (int64_t)z * nparts * (H::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * WAVES, tag);
         if (tid < H::ROWS) {
             float M = -INFINITY, sum = 0.f;
             const float2 *src = sRed + (NT == 2 ? tid / H::TROWS * 4 * H::TROWS : 0) + tid % H::TROWS;
@@ -180,6 +174,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         }
         missing = least_missing(missing);
         if (lane == 0) sMissing[wave] = missing;
+        count.arrived(x);
         __syncthreads();
 #pragma unroll
         for (int wv = 0; wv < WAVES; ++wv) missing = min(missing, sMissing[wv]);
@@ -257,7 +252,10 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
                 scores[(int64_t)z * g.n + j] = PRIOR ? tot[mb] * prior_factor(sGam[j - key_begin], ginv) : tot[mb];
         }
     }
-    if (tid == THREADS - 1) leave(x, z, nparts, count);
+    if (leave(x, z, nparts, count, tid == THREADS - 1, sMissing + 1)) {
+        Words::take_away(stats + (int64_t)z * nparts * (H::ROWS / 2), nparts * (H::ROWS / 2), tid, THREADS);
+        if (PRIOR) Words::take_away(maxima + (int64_t)z * nparts * WAVES, nparts * WAVES, tid, THREADS);
+    }
 }
 
 // ---- the logits formed twice --------------------------------------------------------------------
@@ -274,7 +272,7 @@ struct StreamSmem {
                                             ? 8 * TROWS * sizeof(float2)
                                             : (kPriorPiece + kPriorMaxHalo) * sizeof(float);
     static constexpr size_t off_misc = (off_red + red_bytes + 15) / 16 * 16;
-    static constexpr size_t off_nu = off_misc + 20 * sizeof(float);
+    static constexpr size_t off_nu = off_misc + 16 * sizeof(float);
     // ranges of up to KEYS keys keep their norms and prior in LDS, longer ones go through the workspace
     static constexpr size_t room = 160 * 1024 - off_nu - kPriorMaxHalo * sizeof(float);
     static constexpr int KEYS = room >= 2048 * 8 ? 2048 : (int)(room / 8) / 256 * 256;
@@ -305,7 +303,6 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     float *sCol = (float *)sRed, *sNu = (float *)sRed;
     float *sMax = (float *)(smem + W::off_misc);
     int *sMissing = (int *)sMax + 8;
-    uint64_t *sTag = (uint64_t *)(sMax + 16);
     float *sN = (float *)(smem + W::off_nu), *sGam = (float *)(smem + W::off_gam);
     const bool in_lds = W::KEYS && part_keys <= W::KEYS;
 
@@ -317,6 +314,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     const int tile_min = rm.min_pos(tile * W::TROWS, (tile + 1) * W::TROWS);
 
     Count count;
+    const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), x.tag), priors(maxima + (int64_t)z * nparts * 8, x.tag);
     bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block loads while one multiplies
     int key_begin, key_end, nsteps;
     auto kb_of = [&](int i) { return i >= 0 && i < nsteps ? key_begin + i * W::STEP + kw * kWaveKeys : key_end; };
@@ -552,7 +550,6 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             if (i + 1 >= nsteps) break;
             sweep_step(std::bool_constant<PRIOR != 0>{}, blocks, a1, a0, kb_of(i + 1), kb_of(i + 2), false, i + 2 == nsteps);
         }
-        if (tid == 511) count.look_epoch(x, z);
         if (part == 0 && tid == 511) count.start(x, z);
         PriorHalo<D> halo;
         if (PRIOR) halo.request(g, vbase, key_begin, key_end, tid);  // travels while the statistics are reduced
@@ -563,11 +560,8 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             merge_stats(m[nb], s[nb], m2, s2);
             if (lane < 32) sRed[wave * W::TROWS + nb * 32 + lane] = make_float2(m[nb], s[nb]);
         }
-        if (part == 0 && wave == 7) count.started();
-        if (tid == 511) *sTag = count.words_tag(x);
+        if (part == 0 && wave == 7) count.started(x);
         __syncthreads();
-        const uint64_t tag = *sTag;
-        const Words rows(stats + (int64_t)z * nparts * (W::ROWS / 2), tag), priors(maxima + (int64_t)z * nparts * 8, tag);
         if (tid < W::ROWS) {
             float M = -INFINITY, sum = 0.f;
             const float2 *src = sRed + (NT == 2 ? tid / W::TROWS * 4 * W::TROWS : 0) + tid % W::TROWS;
@@ -589,6 +583,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
         }
         missing = least_missing(missing);
         if (lane == 0) sMissing[wave] = missing;
+        count.arrived(x);
         __syncthreads();
 #pragma unroll
         for (int wv = 0; wv < 8; ++wv) missing = min(missing, sMissing[wv]);
@@ -614,7 +609,10 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
     }
     __syncthreads();
     second_sweep(PRIOR ? prior_inverse(largest()) : 1.f);
-    if (tid == 511) leave(x, z, nparts, count);
+    if (leave(x, z, nparts, count, tid == 511, sMissing + 1)) {
+        Words::take_away(stats + (int64_t)z * nparts * (W::ROWS / 2), nparts * (W::ROWS / 2), tid, 512);
+        if (PRIOR) Words::take_away(maxima + (int64_t)z * nparts * 8, nparts * 8, tid, 512);
+    }
 }
 
 // ---------------------------------------------------------------- launch --
@@ -677,10 +675,10 @@ int stream_keys_in_lds(int d, int nb, int tiles) {
     return nb == 4 ? StreamSmem<64, 4, 1>::KEYS : nb == 6 ? StreamSmem<64, 6, 1>::KEYS : StreamSmem<64, 8, 1>::KEYS;
 }
 
-hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, uint64_t tag, int looks,
+hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                                float *scores, hipStream_t st) {
     char *w = (char *)ws;
-    const Exchange x{(uint64_t *)(w + pl.off_wwords), tag, looks};
+    const Exchange x{(uint64_t *)(w + pl.off_wwords), call.tag, call.looks, call.replayed};
     auto launch = [&](auto prior) {
         constexpr int PRIOR = decltype(prior)::value;
         return g.d == 64 ? launch_d<64, PRIOR>(g, pl, x, w, scores, st) : launch_d<128, PRIOR>(g, pl, x, w, scores, st);
