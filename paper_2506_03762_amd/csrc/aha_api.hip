@@ -259,22 +259,13 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
     pl.off_wstats = take(8 * (size_t)pl.Z * parts * tiles * nb * 32);  // (words of 16 bytes: two values and the tag)
-    pl.off_wmax = take((pl.win_share ? 16 : 8 * 16) * (size_t)pl.Z * parts);  // per wave
+    // (a word per wave, or per range where the waves share the keys)
+    if (p->value_prior) pl.off_wmax = take(16 * (pl.win_share ? 1 : hold ? 4 * tiles : 8) * (size_t)pl.Z * parts);
     pl.off_wwords = take(kExchangeBytes * (size_t)pl.Z);
-    const size_t norms = align_up(sizeof(float) * (size_t)pl.Z * p->seq_len, 256);  // or priors
     if (!hold && p->value_prior &&
-        keys > (pl.win_share ? share_keys_in_lds(p->head_dim, tiles) : stream_keys_in_lds(p->head_dim, nb, tiles))) {
-        pl.off_wnu = take(norms);
-        pl.off_wgamma = take(norms);
-    }
+        keys > (pl.win_share ? share_keys_in_lds(p->head_dim, tiles) : stream_keys_in_lds(p->head_dim, nb, tiles)))
+        pl.off_wnu = take(sizeof(float) * (size_t)pl.Z * p->seq_len);
     pl.win_bytes = off;
-    // Two sweeps with a prior ask for what they took when a value of the statistics had 4 bytes and the norms were always
-    // there: callers who keep that size are served in one launch, those with less in two, as they were.
-    if (!hold && p->value_prior) {
-        off = align_up(4 * (size_t)pl.Z * parts * tiles * nb * 32, 256) + align_up(32 * (size_t)pl.Z * parts, 256) +
-              align_up(8 * (size_t)pl.Z * parts, 256) + align_up(8 * (size_t)pl.Z, 256) + 2 * norms;
-        pl.win_bytes = std::max(off, pl.win_bytes);
-    }
 }
 
 // Windowed bf16 scores from given normalisers in one launch (score_given.hip), likewise: one query

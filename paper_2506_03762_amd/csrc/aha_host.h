@@ -62,10 +62,10 @@ struct PrefillPlan {
     bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
     // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
     // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
-    // prior maxima and counts (exchange.h), the value norms and the prior live
+    // prior maxima and counts (exchange.h) and the value norms live
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold, win_share;  // (share: by the kernel whose waves share the keys)
-    size_t off_wstats, off_wmax, off_wwords, off_wnu, off_wgamma, win_bytes;
+    size_t off_wstats, off_wmax, off_wwords, off_wnu, win_bytes;
     // windowed bf16 scores from given normalisers in one launch (given_nb > 0), likewise
     int given_nb, given_parts, given_keys;
     size_t off_gmax, off_gwords, given_bytes;
@@ -77,7 +77,7 @@ struct PrefillPlan {
     size_t bytes;  // of the layout of two launches
 };
 
-constexpr int kExchangeBytes = 128;  // per problem: the count of an exchange inside a launch
+constexpr int kExchangeBytes = 64;  // per problem: the count of an exchange inside a launch
 // A call whose workgroups exchange parts of a result inside a launch (exchange.h).
 struct ExchangeCall {
     uint64_t tag;   // a number that no other call uses, its low 20 bits zero
@@ -129,7 +129,7 @@ hipError_t launch_score_window(const ScoreGeom &g, const PrefillPlan &pl, void *
 hipError_t launch_score_share(const ScoreGeom &g, const PrefillPlan &pl, void *ws, const ExchangeCall &call,
                               float *scores, hipStream_t st);
 // Keys of a range whose norms and prior the LDS keeps: in the kernels that share the keys (score_share.hip), in the others that
-// sweep twice (score_window.hip).  Longer ranges keep them in the workspace.
+// sweep twice (score_window.hip).  Longer ranges keep the norms in the workspace.
 int share_keys_in_lds(int d, int tiles);
 int stream_keys_in_lds(int d, int nb, int tiles);
 // score_given.hip

@@ -235,7 +235,7 @@ __device__ __forceinline__ float loaded_row_norm(const bf16x8 (&w)[kMB][D / 16],
     return nu;
 }
 
-constexpr int kPriorPiece = 512;   // keys whose norms are staged for pooling at a time
+constexpr int kPriorPiece = 512;   // keys whose norms are staged for pooling at a time (unless there is more LDS)
 constexpr int kPriorMaxHalo = 32;  // rows on both sides together
 // Pooling halo of a key range [kbeg, kend): the (pool - 1) / 2 value rows below and above it,
 // one per group of d / 8 lanes (at most 256 / (d / 8) rows: the host checks the pool width).
@@ -286,17 +286,17 @@ __device__ __forceinline__ float pool_norms(const ScoreGeom &g, int kbeg, int ke
 }
 
 // gamma of the keys [kbeg, kend) from the norms the workgroup's waves left in nu_g, in pieces staged in
-// s_nu, to `gamma`; returns this thread's largest.  The caller has passed a barrier since the last norm
+// s_nu, to use(key, gamma); returns this thread's largest.  The caller has passed a barrier since the last norm
 // was written, and nobody uses s_nu any more.
-template <int D, int THREADS>
+template <int D, int THREADS, int PIECE = kPriorPiece, class Use>
 __device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, int kbeg, int kend,
                                                      const float *nu_g, const PriorHalo<D> &halo,
-                                                     float *s_nu, float *gamma, int tid) {
+                                                     float *s_nu, int tid, Use &&use) {
     const int half = (g.pool - 1) / 2;
     const float hn = halo.norm();
     float gmax = 0.f;
-    for (int t0 = kbeg; t0 < kend; t0 += kPriorPiece) {
-        const int t1 = min(kend, t0 + kPriorPiece);
+    for (int t0 = kbeg; t0 < kend; t0 += PIECE) {
+        const int t1 = min(kend, t0 + PIECE);
         const int lo = max(0, t0 - half), hi = min(g.n, t1 + half);  // hi exclusive
         for (int t = max(lo, kbeg) + tid; t < min(hi, kend); t += THREADS) s_nu[t - lo] = nu_g[(int64_t)z * g.n + t];
         // the halo rows that touch this piece (the first piece below, the last one above)
@@ -308,7 +308,7 @@ __device__ __forceinline__ float pool_norms_of_range(const ScoreGeom &g, int z, 
             float s = 0.f;
             for (int t = a; t <= e; ++t) s += s_nu[t - lo];
             const float gam = s / (float)(e - a + 1);
-            gamma[(int64_t)z * g.n + j] = gam;
+            use(j, gam);
             gmax = fmaxf(gmax, gam);
         }
         __syncthreads();

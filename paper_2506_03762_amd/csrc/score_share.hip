@@ -38,18 +38,22 @@ struct ShareSmem {
     // between the sweeps: float2 [8][256], in the fourth stage if it is large enough
     static constexpr int red_bytes = 8 * 256 * 8, off_red = red_bytes <= stage2 ? 3 * stage2 : off_misc + 16 * 4;
     static constexpr int off_nu = off_misc + 16 * 4 + (red_bytes <= stage2 ? 0 : red_bytes);
-    // ranges of up to KEYS keys keep their norms, prior and sums in LDS, longer ones in the workspace and the scores
+    // ranges of up to KEYS keys keep their norms, prior and sums in LDS, longer ones the norms in the workspace and the sums in the scores
     static constexpr int room = 160 * 1024 - off_nu - kPriorMaxHalo * 4;
     static constexpr int KEYS = !PRIOR ? 0 : room >= 2048 * 12 ? 2048 : room / 12 / 256 * 256;
     static constexpr int off_gam = off_nu + (KEYS + kPriorMaxHalo) * 4, off_sum = off_gam + KEYS * 4;
     static constexpr int bytes = off_sum + KEYS * 4;
+    // keys whose norms are pooled at a time, in the stages' place (us of the score stage in pieces of 512 and so: 64 heads x 32768
+    // keys x 256 rows 381, 374)
+    static constexpr int PIECE = 4096;
+    static_assert((PIECE + kPriorMaxHalo) * 4 <= off_col, "the stages");
     static_assert(bytes <= 160 * 1024, "LDS of a CU");
     static_assert(KG * ROWS * 8 <= 4 * 8 * 64 * 4, "the key groups' statistics");
 };
 
 template <int D, int RG, bool FIXED, int PRIOR>
 __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x, u32x4 *stats,
-                                                              u32x4 *maxima, float *nu_g, float *gamma, float *scores) {
+                                                              u32x4 *maxima, float *nu_g, float *scores) {
     using W = ShareSmem<D, RG, PRIOR != 0>;
     using R = KeyRows<D>;
     using Request = KeyRequest<D, W::STEP, 8>;
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
                 gm = pool_norms(g, key_begin, key_end, sN, sGam, tid, 512);
             } else {
                 __syncthreads();  // (the stages become the norms' LDS)
-                gm = pool_norms_of_range<D, 512>(g, z, key_begin, key_end, nu_g, halo, (float *)smem, gamma, tid);
+                gm = pool_norms_of_range<D, 512, W::PIECE>(g, z, key_begin, key_end, nu_g, halo, (float *)smem, tid, [](int, float) {});
             }
             gm = wave_max(gm);
             if (lane == 0) sMax[wave] = gm;
@@ -467,9 +471,12 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
         }
         const float ginv = prior_inverse(sMax[0]);
         float *out = scores + (int64_t)z * g.n;
-        for (int j = key_begin + tid; j < key_end; j += 512)
-            out[j] = in_lds ? sSum[j - key_begin] * prior_factor(sGam[j - key_begin], ginv)
-                            : out[j] * prior_factor(gamma[(int64_t)z * g.n + j], ginv);
+        if (in_lds) {
+            for (int j = key_begin + tid; j < key_end; j += 512) out[j] = sSum[j - key_begin] * prior_factor(sGam[j - key_begin], ginv);
+        } else {  // (formed once more: no place to keep it)
+            pool_norms_of_range<D, 512, W::PIECE>(g, z, key_begin, key_end, nu_g, halo, (float *)smem, tid,
+                                        [&](int j, float gam) { out[j] *= prior_factor(gam, ginv); });
+        }
     }
     if (tid == 511) count.arrive(x, z);
     if (leave(x, z, nparts, count, tid == 511, sMissing + 1)) {
@@ -490,7 +497,7 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, const Exch
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(512), W::bytes, st, g, pl.win_parts, pl.win_keys, x,
                        (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax), (float *)(w + pl.off_wnu),
-                       (float *)(w + pl.off_wgamma), scores);
+                       scores);
     return hipGetLastError();
 }
 

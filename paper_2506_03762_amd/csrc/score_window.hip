@@ -273,7 +273,7 @@ struct StreamSmem {
                                             : (kPriorPiece + kPriorMaxHalo) * sizeof(float);
     static constexpr size_t off_misc = (off_red + red_bytes + 15) / 16 * 16;
     static constexpr size_t off_nu = off_misc + 16 * sizeof(float);
-    // ranges of up to KEYS keys keep their norms and prior in LDS, longer ones go through the workspace
+    // ranges of up to KEYS keys keep their norms and prior in LDS, longer ones the norms in the workspace and the prior in the scores
     static constexpr size_t room = 160 * 1024 - off_nu - kPriorMaxHalo * sizeof(float);
     static constexpr int KEYS = room >= 2048 * 8 ? 2048 : (int)(room / 8) / 256 * 256;
     static constexpr size_t off_gam = off_nu + (KEYS ? (KEYS + kPriorMaxHalo) * sizeof(float) : 0);
@@ -285,8 +285,7 @@ struct StreamSmem {
 
 template <int D, int NB, int NT, int PRIOR>
 __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int nparts, int part_keys, Exchange x,
-                                                               u32x4 *stats, u32x4 *maxima, float *nu_g,
-                                                               float *gamma, float *scores) {
+                                                               u32x4 *stats, u32x4 *maxima, float *nu_g, float *scores) {
     using S = TileSmem<D, NB>;
     using W = StreamSmem<D, NB, NT>;
     // with two tiles a wave takes 32 of the 64 value rows it shares
@@ -413,10 +412,10 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             asm volatile("" : "+v"(ln));
             const int my_v = ((ln >> 4) & 1) * 8 + ((ln >> 3) & 1) * 4 + ((ln >> 2) & 1) * 2 + ((ln >> 1) & 1);
             float gam[kMB];
-            if (PRIOR && !in_lds) {
+            if (PRIOR && !in_lds) {  // (in the scores' places, which nobody else writes or reads)
 #pragma unroll
                 for (int mb = 0; mb < kMB; ++mb)
-                    gam[mb] = gamma[(int64_t)z * g.n + min(acc_key(kb, mb, my_v, ln), key_end - 1)];
+                    gam[mb] = scores[(int64_t)z * g.n + min(acc_key(kb, mb, my_v, ln), key_end - 1)];
             }
             f32x16 col[kMB];
 #pragma unroll
@@ -483,8 +482,8 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             step(a1, a0, i - 1);
         }
     };
-    // the prior of the range from its norms; the wave's largest gamma
-    auto pool_range = [&](const PriorHalo<D> &halo, int tid) {
+    // the prior of the range from its norms (kept: of the own one); the wave's largest gamma
+    auto pool_range = [&](const PriorHalo<D> &halo, int tid, bool kept) {
         float gm;
         if (in_lds) {
             const float hn = halo.norm();
@@ -493,7 +492,9 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             gm = pool_norms(g, key_begin, key_end, sN, sGam, tid, 512);
         } else {
             __syncthreads();  // (the statistics' LDS becomes the norms')
-            gm = pool_norms_of_range<D, 512>(g, z, key_begin, key_end, nu_g, halo, sNu, gamma, tid);
+            gm = pool_norms_of_range<D, 512>(g, z, key_begin, key_end, nu_g, halo, sNu, tid, [&](int j, float gam) {
+                if (kept) scores[(int64_t)z * g.n + j] = gam;  // (another's range may have its scores already)
+            });
         }
         return wave_max(gm);
     };
@@ -570,7 +571,7 @@ __global__ __launch_bounds__(512, 2) void window_stream_kernel(ScoreGeom g, int 
             put_rows(rows, part * (W::ROWS / 2), tid, M + log2f(sum));
         }
         if (PRIOR) {
-            const float gm = pool_range(halo, tid);
+            const float gm = pool_range(halo, tid, part == own);
             if (lane == 0) priors.put(part * 8 + wave, gm, 0.f);
         }
         __syncthreads();
@@ -645,7 +646,7 @@ static hipError_t launch_stream(const ScoreGeom &g, const PrefillPlan &pl, const
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.Z * pl.win_parts)), dim3(512), W::bytes, st, g, pl.win_parts,
                        pl.win_keys, x, (u32x4 *)(w + pl.off_wstats), (u32x4 *)(w + pl.off_wmax),
-                       (float *)(w + pl.off_wnu), (float *)(w + pl.off_wgamma), scores);
+                       (float *)(w + pl.off_wnu), scores);
     return hipGetLastError();
 }
 

@@ -66,9 +66,10 @@ def test_few_steps_of_large_tiles(z, n, d, prior, one):
     assert _one_launch("aha_prefill_scores_lse", _params(z, 4, 56, n, d, value_prior=prior))
 
 
-# KV heads, group, window, keys, d, and a workspace that holds two launches; one launch needs up to twice as much
-SMALLER = [(64, 7, 32, 3170, 64, 1863424), (64, 5, 77, 7257, 64, 3962368), (64, 7, 64, 6233, 128, 3699200),
-           (128, 3, 128, 77252, 64, 41804800), (89, 4, 100, 14177, 128, 7254272)]
+# KV heads, group, window, keys, d, and a workspace that holds two launches; one launch, swept twice by more ranges than the
+# chip holds at once, needs up to a sixth more
+SMALLER = [(183, 4, 29, 13938, 64, 10805248), (89, 4, 100, 14177, 128, 7254272), (141, 2, 173, 22503, 64, 15051520),
+           (43, 4, 114, 25641, 128, 6541312), (94, 4, 103, 36264, 64, 15998976)]
 
 
 @pytest.mark.parametrize("z,group,window,n,d,size", SMALLER)
@@ -83,6 +84,23 @@ def test_workspace_of_two_launches_is_served(z, group, window, n, d, size):
     assert _call("aha_prefill_scores_rows", p, size) != B.AHA_ERR_WORKSPACE
     for name in ("aha_prefill_scores", "aha_prefill_scores_lse", "aha_prefill_row_stats"):
         assert _call(name, p, size // 4) == B.AHA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("z,group,window,n,d,prior,size", [
+    # sizes that were asked for when statistics took four bytes a value and norms and prior always lay in the workspace
+    (64, 7, 32, 6233, 128, 1, 3726336), (8, 8, 64, 131072, 128, 1, 8923392), (22, 3, 57, 196890, 128, 1, 34848768),
+    (42, 1, 398, 14322, 64, 1, 5339136), (11, 1, 73, 111119, 64, 1, 9912832), (256, 3, 41, 9749, 64, 1, 20109312),
+    (171, 1, 271, 45870, 64, 1, 65446912), (89, 4, 100, 14177, 128, 1, 11581696),
+    # held: short prompts, with a prior and without
+    (61, 3, 1, 50, 64, 0, 28416), (212, 7, 2, 41, 128, 0, 91136), (253, 8, 1, 46, 64, 1, 112640), (44, 5, 49, 50, 128, 1, 99328),
+    # two launches' sizes, which hold one launch as well
+    (64, 7, 32, 3170, 64, 1, 1863424), (64, 5, 77, 7257, 64, 1, 3962368), (64, 7, 64, 6233, 128, 1, 3699200),
+    (128, 3, 128, 77252, 64, 1, 41804800),
+])
+def test_one_launch_at_former_sizes(z, group, window, n, d, prior, size):
+    p = _params(z, group, window, n, d, value_prior=prior)
+    assert B.workspace_bytes(p) <= size
+    assert _one_launch("aha_prefill_scores", p, size)
 
 
 @pytest.mark.gpu
