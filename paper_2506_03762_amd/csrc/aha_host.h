@@ -77,7 +77,7 @@ struct PrefillPlan {
     size_t bytes;  // of the layout of two launches
 };
 
-constexpr int kExchangeBytes = 64;  // per problem: the count of an exchange inside a launch
+constexpr int kExchangeBytes = 32;  // per problem: the count of an exchange inside a launch
 // A call whose workgroups exchange parts of a result inside a launch (exchange.h).
 struct ExchangeCall {
     uint64_t tag;   // a number that no other call uses, its low 20 bits zero

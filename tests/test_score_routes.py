@@ -93,6 +93,7 @@ def test_workspace_of_two_launches_is_served(z, group, window, n, d, size):
     (171, 1, 271, 45870, 64, 1, 65446912), (89, 4, 100, 14177, 128, 1, 11581696),
     # held: short prompts, with a prior and without
     (61, 3, 1, 50, 64, 0, 28416), (212, 7, 2, 41, 128, 0, 91136), (253, 8, 1, 46, 64, 1, 112640), (44, 5, 49, 50, 128, 1, 99328),
+    (50, 8, 31, 46, 128, 1, 111872),
     # two launches' sizes, which hold one launch as well
     (64, 7, 32, 3170, 64, 1, 1863424), (64, 5, 77, 7257, 64, 1, 3962368), (64, 7, 64, 6233, 128, 1, 3699200),
     (128, 3, 128, 77252, 64, 1, 41804800),
