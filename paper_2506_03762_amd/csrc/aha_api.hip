@@ -170,7 +170,9 @@ constexpr int64_t kSweptSteps = 800;  // steps of 256 keys in all from which 65 
 // all ranges' statistics; two launches leave their own last round nearly empty unless their workgroups are just the
 // chip's 512 (`even`).  us otherwise (two launches; d = 64 and more than 64 rows the two sweeps), held, over 560 shapes of 3 to 390
 // ranges, 4 to 296 heads:
-//  - up to 32 rows: 1.5 times as fast on average (hardly more than one round is not taken);
+//  - up to 32 rows: 1.5 times as fast on average (hardly more than one round is not taken, but in ranges of two steps, d = 128 with a
+//    prior, up to 256 of them, at any number of rounds: 33 x 18 62.5, 38.0; 5 x 202 85.3, 68.7; 8 x 256 139, 109; 64 x 256 1172, 836; 3 x
+//    330 72, 73; 16 x 400 447, 463);
 //  - d = 128, 33 to 64 rows: uneven up to 256: 77 heads x 9 ranges 66.4, 44.0; 7 x 181 90.5, 90.0; 8 x 233 135, 127; even up to two
 //    problems a round from 64 heads on, eight below: 128 x 32 284, 212;
 //  - d = 128, 65 to 128 rows: uneven up to 100: 80 x 9 55.6, 32.3; 21 x 98 82.6, 75.4; 17 x 174 134, 147; 16 x 234 145, 190; even
@@ -182,9 +184,9 @@ constexpr int64_t kSweptSteps = 800;  // steps of 256 keys in all from which 65 
 // Held would be the faster one a little further, too, where the two launches are tested: up to 256 ranges of 33 to 64 rows, even
 // (16 x 101 120, 98.6), 150 of 65 to 128, uneven (11 x 103 72.4, 54.7; 37 x 145 274, 245), and one or two heads in at most 128
 // ranges of 65 to 128 rows (1 x 100 22.9, 16.2).
-static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, int64_t parts, int64_t steps) {
+static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, int per, int64_t parts, int64_t steps) {
     const bool even = (int64_t)pl.Z * pl.nchunks <= 512, prior = p->value_prior;
-    if (nb == 1) return parts <= 128 && pl.Z * parts >= 600;
+    if (nb == 1) return per == 2 || (parts <= 128 && pl.Z * parts >= 600);
     if (p->head_dim == 128 && nb == 2) return parts <= (!even ? 256 : pl.Z >= 64 ? 128 : 64);
     if (p->head_dim == 64 && nb > 2) return pl.Z * steps < kSweptSteps && parts <= 150;
     if (!even) return parts <= (p->head_dim == 128 ? 100 : 160);
@@ -229,13 +231,14 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
         nb = blocks;
         int per = 1;
         // (four steps beside value rows take more registers than there are, d = 128: us of four and two, 16 heads x 25716 keys x 16
-        // rows 59.2, 49.0; 173 x 2481 x 32 79.3, 50.0; 22 shapes 1.33 times as fast on average, without a prior 0.97)
-        const int most = nb == 2 || (p->head_dim == 128 && p->value_prior) ? 2 : 4;
+        // rows 59.2, 49.0; 173 x 2481 x 32 79.3, 50.0; 22 shapes 1.33 times as fast on average, without a prior 0.97; but longer problems,
+        // in one round or in two of two steps: 3 x 168740 x 32 68.7, 73.2; 1 x 500000 71.0, two launches 91.7)
+        const int most = nb == 2 || (p->head_dim == 128 && p->value_prior && (steps + 1) / 2 <= 256) ? 2 : 4;
         while (2 * per * nb <= 4 && 2 * per <= most && pl.Z * ((steps + per - 1) / per) > kHeldAtOnce) per *= 2;
         parts = (steps + per - 1) / per;
         keys = per * kP2Keys;
         hold = pl.Z * parts <= kHeldAtOnce ? nb <= 2 || parts <= 48 || pl.Z * parts > 128
-                                           : held_in_rounds(p, pl, nb, parts, steps);
+                                           : held_in_rounds(p, pl, nb, per, parts, steps);
         if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < kSweptSteps)) return;
         if (!hold) nb = 4;
     } else if (blocks <= 8) {

@@ -660,8 +660,7 @@ static hipError_t launch_d(const ScoreGeom &g, const PrefillPlan &pl, const Exch
 #define AHA_STREAM(NB, NT)                                            \
     if (!pl.win_hold && pl.win_nb == NB && pl.win_tiles == NT) \
         return launch_stream<D, NB, NT, NT == 2 && PRIOR ? kValuesCached : PRIOR>(g, pl, x, w, scores, st);
-    if constexpr (D == 64 || !PRIOR) { AHA_HOLD(1, 1, 4) }
-    AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
+    AHA_HOLD(1, 1, 4) AHA_HOLD(1, 1, 1) AHA_HOLD(1, 1, 2) AHA_HOLD(2, 1, 1) AHA_HOLD(2, 1, 2) AHA_HOLD(3, 1, 1)
     AHA_HOLD(4, 1, 1) AHA_HOLD(3, 2, 1) AHA_HOLD(4, 2, 1)
     if constexpr (D == 64) { AHA_STREAM(4, 1) AHA_STREAM(8, 1) }  // (d = 128: held, or two launches; score_share.hip)
     AHA_STREAM(6, 1) AHA_STREAM(6, 2)

@@ -89,3 +89,32 @@ def test_several_rounds(shape):
     finally:
         B.load().aha_exchange_looks(4000)
     assert alone.equal(got)
+
+
+BESIDE_VALUES = [
+    # up to 32 rows beside value rows, d = 128: ranges of four steps, ranges of two in several rounds
+    (2, 1, 32, 140001, 128), (9, 1, 2, 32848, 128), (33, 8, 1, 8848, 128), (5, 1, 5, 103215, 128),
+]
+
+
+@pytest.mark.parametrize("shape", BESIDE_VALUES)
+def test_beside_value_rows(shape):
+    import torch
+    p, q, k, v = _inputs(shape, shape[4] ** -0.5)
+    want = _exact(p, q, k)
+    p.value_prior, n = 1, p.seq_len
+    half = (p.pool_kernel - 1) // 2
+    past = torch.nn.functional.pad((v.double() ** 2).sum(-1).cumsum(-1), (1, 0))
+    first, last = (torch.arange(n, device="cuda") - half).clamp(min=0), (torch.arange(n, device="cuda") + half + 1).clamp(max=n)
+    gamma = (past[..., last] - past[..., first]) / (last - first)
+    want *= gamma / gamma.amax(-1, keepdim=True)
+    got = _scores(p, q, k, v)
+    # (as above, and twice, for the key's own prior and the largest: sums of 128 squares, of the pool's seven and two more roundings)
+    assert ((got.double() - want).abs() <= (5 * 2.0 ** -18 + 2.0 ** -17 + 2 * (2.0 ** -17 + 9 * 2.0 ** -24)) * want + 1e-30).all()
+    # a workgroup that looks once and does whatever is not there yet
+    assert B.load().aha_exchange_looks(0) == B.AHA_OK
+    try:
+        alone = _scores(p, q, k, v)
+    finally:
+        B.load().aha_exchange_looks(4000)
+    assert alone.equal(got)

@@ -137,3 +137,20 @@ def test_results_in_it(z, group, window, n, d, size):
 ])
 def test_held_in_rounds(z, window, n, d, prior, one):
     assert _one_launch("aha_prefill_scores", _params(z, 1, window, n, d, value_prior=prior)) == one
+
+
+@pytest.mark.parametrize("z,group,window,n,one", [
+    # up to 32 rows with a prior, d = 128, in ranges of two steps (us: two launches, one): hardly more than one round
+    (33, 8, 1, 8848, True),    # 62.5, 38.0
+    (53, 4, 4, 4736, True),    # 52.4, 36.4
+    (257, 1, 15, 537, True),   # 44.2, 32.9
+    # many ranges to a problem
+    (5, 1, 5, 103215, True),   # 85.3, 68.7
+    (8, 1, 32, 131072, True),  # 139, 109
+    (64, 1, 8, 131073, False), (8, 1, 32, 204550, False),
+    # more of them than that: of four steps, in one round
+    (2, 5, 1, 199437, True), (3, 1, 32, 168740, True), (1, 1, 32, 500000, True),
+    (2, 1, 32, 270000, False),
+])
+def test_ranges_beside_value_rows(z, group, window, n, one):
+    assert _one_launch("aha_prefill_scores", _params(z, group, window, n)) == one
