@@ -322,8 +322,8 @@ static void plan_hold_f32(const aha_params *p, PrefillPlan &pl) {
     int64_t parts, keys = blocks == 1 ? 128 : 32;
     for (;; keys = 128) {
         parts = ((int64_t)p->seq_len + keys - 1) / keys;
-        // workgroups that the chip holds at once (the kernel has up to 18 KB of LDS besides)
-        const int64_t resident = hold_f32_lds(p->head_dim, (int)blocks, (int)keys) + 18 * 1024 <= 80 * 1024 ? 512 : 256;
+        // workgroups that the chip holds at once
+        const int64_t resident = hold_f32_lds(p->head_dim, (int)blocks, (int)keys) + kHoldF32Static <= 80 * 1024 ? 512 : 256;
         if (pl.Z * parts <= resident && (keys == 128 || parts <= 64)) break;
         if (keys == 128) return;
     }

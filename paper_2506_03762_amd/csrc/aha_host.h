@@ -104,6 +104,7 @@ hipError_t launch_score_f32(const ScoreGeom &g, const PrefillPlan &pl, void *ws,
 // score_hold_f32.hip
 // The same in one launch (pl.hold32_parts > 0): up to kHoldF32Blocks blocks of 32 rows, ranges of 128 or 32 keys.
 constexpr int kHoldF32Blocks = 6;
+constexpr size_t kHoldF32Static = 19 * 1024;  // LDS that the kernel has besides, at most
 // dynamic LDS: a query block (rows padded by 16 bytes) per wave that takes other rows, and a weight per row and key
 constexpr size_t hold_f32_lds(int d, int blocks, int keys) {
     return (size_t)(128 / keys) * 32 * (d + 4) * 4 + (size_t)blocks * 32 * keys * 4;

@@ -25,16 +25,23 @@ __device__ __forceinline__ void merge_pair(float &m, float &s, float m2, float s
     m = M;
 }
 
-// KW: waves over the keys, of four; the others over the row blocks
+// Static LDS. KW: waves over the keys, of four; the others over the row blocks
+template <int KW>
+struct HoldF32Smem {
+    static constexpr int KEYS = KW * 32, ROWS = kHoldF32Blocks * 32;
+    float2 row[KW][ROWS], mrg[256];
+    float ref[kHoldF32Blocks][KW * 64], lam[ROWS], M[ROWS], inv[ROWS];
+    float nu[KEYS + 256], gam[KEYS], max[4], all[4], acc[4 / KW][KEYS];
+    int missing[4];
+};
+static_assert(sizeof(HoldF32Smem<1>) <= kHoldF32Static && sizeof(HoldF32Smem<4>) <= kHoldF32Static, "what the plan reckons with");
+
 template <int D, int KW>
 __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int nparts, Exchange x, u32x4 *stats, u32x4 *maxima,
                                                           float *scores) {
-    constexpr int RW = 4 / KW, KEYS = KW * 32, GT = KW * 64, ROWS = kHoldF32Blocks * 32, QB = 32 * f32_ld(D);
+    constexpr int RW = 4 / KW, KEYS = KW * 32, GT = KW * 64, QB = 32 * f32_ld(D);
     extern __shared__ __attribute__((aligned(16))) float dyn[];  // a query block per RW; weights [block][key wave][element][lane]
-    __shared__ float2 s_row[KW][ROWS], s_mrg[256];
-    __shared__ float s_ref[kHoldF32Blocks][KW * 64], s_lam[ROWS], s_M[ROWS], s_inv[ROWS];
-    __shared__ float s_nu[KEYS + 256], s_gam[KEYS], s_max[4], s_all[4], s_acc[RW][KEYS];
-    __shared__ int s_missing[4];
+    __shared__ HoldF32Smem<KW> sm;
     const int nblocks = (g.R + 31) / 32, rp = nblocks * 32;
     float *sw = dyn + RW * QB;
 
@@ -62,16 +69,16 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
         f32x4 a[D / 8];
         f32_load_keys<D>(kbase, g.ks[2], kb, g.n - 1, lane, a);
         if (tid < rp)  // (while the loads travel)
-            s_lam[tid] = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, max(rm.pos(tid), 0) + 1, g.budget, g.d);
+            sm.lam[tid] = row_scale_log2(g.scale_mode, g.fixed_scale, g.lambda_floor, max(rm.pos(tid), 0) + 1, g.budget, g.d);
         if (g.value_prior)
-            value_norms_to_lds<4>(vbase, g.vs[2], D, max(0, kbeg - half), min(g.n, kbeg + KEYS + half), s_nu, tid);
+            value_norms_to_lds<4>(vbase, g.vs[2], D, max(0, kbeg - half), min(g.n, kbeg + KEYS + half), sm.nu, tid);
         if (part == 0 && tid == 255) count.start(x, z);
         qb.commit(gt, sq);
         __syncthreads();
         for (int nb0 = 0;;) {
             const int nb = nb0 + rw;  // (past the last block: nothing is left of it)
             const int pos = rm.pos(nb * 32 + (lane & 31));  // -1 past the last row
-            const float lam = s_lam[min(nb * 32, rp - 32) + (lane & 31)];
+            const float lam = sm.lam[min(nb * 32, rp - 32) + (lane & 31)];
             f32x16 t = f32_block_dots<D>(a, sq + (lane & 31) * f32_ld(D) + 4 * (lane >> 5));
             float mx = -INFINITY;
 #pragma unroll
@@ -86,14 +93,14 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
                     t[v] = acc_key(kb, 0, v, lane) <= pos ? exp2f(fmaf(t[v], lam, -mref)) : 0.f;
                     w[v * 64] = t[v];
                 }
-                s_ref[nb][gt] = m;
+                sm.ref[nb][gt] = m;
 #pragma unroll
                 for (int o = 8; o; o >>= 1)
 #pragma unroll
                     for (int v = 0; v < o; ++v) t[v] += t[v + o];
                 float s = t[0];
                 merge_pair(m, s, __shfl_xor(m, 32), __shfl_xor(s, 32));
-                if (lane < 32) s_row[kw][nb * 32 + lane] = make_float2(m, s);
+                if (lane < 32) sm.row[kw][nb * 32 + lane] = make_float2(m, s);
             }
             nb0 += RW;
             if (nb0 >= nblocks) break;
@@ -108,20 +115,20 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
             if (tid < KEYS && j < g.n) {
                 const int lo = max(0, kbeg - half), first = max(0, j - half), last = min(g.n - 1, j + half);
                 float s = 0.f;
-                for (int t = first; t <= last; ++t) s += s_nu[t - lo];
+                for (int t = first; t <= last; ++t) s += sm.nu[t - lo];
                 gam = s / (float)(last - first + 1);
-                s_gam[tid] = gam;
+                sm.gam[tid] = gam;
             }
             gam = wave_max(gam);
-            if (lane == 0) s_max[wave] = gam;
+            if (lane == 0) sm.max[wave] = gam;
         }
         if (part == 0 && wave == 3) count.started(x);
         __syncthreads();
-        if (g.value_prior && tid == 255) priors.put(part, fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])), 0.f);
+        if (g.value_prior && tid == 255) priors.put(part, fmaxf(fmaxf(sm.max[0], sm.max[1]), fmaxf(sm.max[2], sm.max[3])), 0.f);
         if (tid < g.R) {
-            float m = s_row[0][tid].x, s = s_row[0][tid].y;
+            float m = sm.row[0][tid].x, s = sm.row[0][tid].y;
 #pragma unroll
-            for (int wv = 1; wv < KW; ++wv) merge_pair(m, s, s_row[wv][tid].x, s_row[wv][tid].y);
+            for (int wv = 1; wv < KW; ++wv) merge_pair(m, s, sm.row[wv][tid].x, sm.row[wv][tid].y);
             rows.put(part * g.R + tid, m, s);
         }
         // the rows' pairs over all parts: a thread takes a row of every subs-th part; the priors of up to 256 parts travel with them
@@ -140,21 +147,21 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
             for (int t = 0; t < 4; ++t)
                 if (at(t) < nparts) merge_pair(m, s, __uint_as_float(w[t].x), __uint_as_float(w[t].z));
         }
-        s_mrg[tid] = make_float2(m, s);
+        sm.mrg[tid] = make_float2(m, s);
         if (g.value_prior && __builtin_amdgcn_ballot_w64(missing != INT32_MAX) == 0) {
             float gm;
             if (nparts <= 256 && __builtin_amdgcn_ballot_w64(tid < nparts && !priors.there(prior)) == 0)
                 gm = wave_max(tid < nparts ? __uint_as_float(prior.x) : 0.f);
             else
                 missing = largest_of<1>(priors, nparts, own, x.looks, tid, 256, gm);
-            if (lane == 0) s_all[wave] = gm;
+            if (lane == 0) sm.all[wave] = gm;
         }
         missing = least_missing(missing);
-        if (lane == 0) s_missing[wave] = missing;
+        if (lane == 0) sm.missing[wave] = missing;
         count.arrived(x);
         __syncthreads();
 #pragma unroll
-        for (int wv = 0; wv < 4; ++wv) missing = min(missing, s_missing[wv]);
+        for (int wv = 0; wv < 4; ++wv) missing = min(missing, sm.missing[wv]);
         missing = uniform(missing);
         if (missing == INT32_MAX && part == own) break;
         // somebody is not there: done here (and no more waiting); in the end the own part again, whose weights LDS has to hold
@@ -166,9 +173,9 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
     if (tid == 255) count.arrive(x, z);
     if (tid < rp) {
         float m = -INFINITY, s = 0.f;
-        for (int sub = 0; sub < min(256 / rp, nparts); ++sub) merge_pair(m, s, s_mrg[sub * rp + tid].x, s_mrg[sub * rp + tid].y);
-        s_M[tid] = m;
-        s_inv[tid] = 1.f / s;
+        for (int sub = 0; sub < min(256 / rp, nparts); ++sub) merge_pair(m, s, sm.mrg[sub * rp + tid].x, sm.mrg[sub * rp + tid].y);
+        sm.M[tid] = m;
+        sm.inv[tid] = 1.f / s;
     }
     __syncthreads();
     f32x16 col;
@@ -176,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
     for (int v = 0; v < 16; ++v) col[v] = 0.f;
     for (int nb = rw; nb < nblocks; nb += RW) {
         const int row = nb * 32 + (lane & 31), pos = rm.pos(row);
-        const float f = exp2f(s_ref[nb][tid % GT] - s_M[row]) * s_inv[row];
+        const float f = exp2f(sm.ref[nb][tid % GT] - sm.M[row]) * sm.inv[row];
         const float *w = sw + ((nb * KW + kw) * 16) * 64 + lane;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -186,18 +193,18 @@ __global__ __launch_bounds__(256, 2) void f32_hold_kernel(ScoreGeom g, int npart
     }
     const float tot = fold16_over32(col, lane);
     const int my_v = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
-    if ((lane & 1) == 0) s_acc[rw][acc_key(kw * 32, 0, my_v, lane)] = tot;
+    if ((lane & 1) == 0) sm.acc[rw][acc_key(kw * 32, 0, my_v, lane)] = tot;
     __syncthreads();
     const int j = kbeg + tid;
     if (tid < KEYS && j < g.n) {
-        float out = RW == 1 ? s_acc[0][tid] : (s_acc[0][tid] + s_acc[RW > 1 ? 1 : 0][tid]) + (s_acc[RW > 2 ? 2 : 0][tid] + s_acc[RW > 2 ? 3 : 0][tid]);
+        float out = RW == 1 ? sm.acc[0][tid] : (sm.acc[0][tid] + sm.acc[RW > 1 ? 1 : 0][tid]) + (sm.acc[RW > 2 ? 2 : 0][tid] + sm.acc[RW > 2 ? 3 : 0][tid]);
         if (g.value_prior) {
-            const float gm = fmaxf(fmaxf(s_all[0], s_all[1]), fmaxf(s_all[2], s_all[3]));
-            out = gm > 0.f ? out * (s_gam[tid] / gm) : out;  // all-zero values: no prior
+            const float gm = fmaxf(fmaxf(sm.all[0], sm.all[1]), fmaxf(sm.all[2], sm.all[3]));
+            out = gm > 0.f ? out * (sm.gam[tid] / gm) : out;  // all-zero values: no prior
         }
         scores[(int64_t)z * g.n + j] = out;
     }
-    if (leave(x, z, nparts, count, tid == 255, &s_missing[1])) {
+    if (leave(x, z, nparts, count, tid == 255, &sm.missing[1])) {
         Words::take_away(stats + (int64_t)z * nparts * g.R, nparts * g.R, tid, 256);
         if (g.value_prior) Words::take_away(maxima + (int64_t)z * nparts, nparts, tid, 256);
     }
