@@ -25,9 +25,10 @@
 // by the one CU that works on a problem.  In-kernel stamps at 8 x 32768 scores (us): loads 1.9, range 1.2, histogram 2.2 (the LDS
 // atomics' rate), scan 1.0, candidates 1.9, rank 0.8, output 1.9; a vector instruction per key costs 0.2.  The masks of the
 // candidates' pass are kept on the scalar unit, so that the output compares again only in steps with keys in the threshold
-// bin (back to back 8 x 32768 13.4 -> 12.5 us).  Waves of whole steps skip the padding's instructions, scores that are not
-// negative most of the conversion, and with many steps four share a branch: 8 x 32768 12.9 -> 11.7, 4 x 24000 10.8 -> 9.75, 8 x
-// 16384 8.35 -> 8.15, 8 x 65536 33.0 -> 31.2; up to eight steps as before.  Against lanes that own consecutive positions (scattered
+// bin (back to back 8 x 32768 13.4 -> 12.5 us).  From 12
+// steps on scores that are not negative skip most of the conversion, from 24 on waves of whole steps skip the padding's
+// instructions and four steps share a branch: 8 x 12000 7.41 -> 7.12, 8 x 16384 8.57 -> 8.21, 8 x 20000 10.7 -> 9.8, 8 x 32768 13.3 ->
+// 12.2, 8 x 65536 34.2 -> 32.2 (with negative ones among them 8.49, 8.58; 9.93, 9.99; 12.7, 13.0; 16.8, 16.4; 38.3, 36.4).  Against lanes that own consecutive positions (scattered
 // loads, per-lane bit masks, a second scan), back to back: 2 x 512 scores 5.9 -> 3.4 us,
 // 32 x 4096 6.6 -> 4.8, 12 x 5003 9.0 -> 5.4, 8 x 16384 10.0 -> 8.4, 128 x 16384 11.2 -> 9.5,
 // 8 x 32768 16.1 -> 13.2, 8 x 65536 34.8 -> 31.8, 8 x 120000 290 -> 67.
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
 
     // 1. range of the keys (padding: 0 - 1 wraps to the top and never is the minimum)
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    if (!LONG && ITEMS >= 12 && whole) {  // (no padding)
+    if (!LONG && ITEMS >= 24 && whole) {  // (no padding; with 16 steps the path costs more than it saves: 8 x 16384 8.21, 8.29 with it)
         for_steps([&](uint32_t u, int) { kmin = min(kmin, u); kmax = max(kmax, u); });
         kmin -= 1u;
     } else {
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(WAVES * 64) void topk_kernel(const float *__restric
     const uint32_t range = kmax - kmin;
     constexpr int kBinBits = 31 - __builtin_clz(BINS);
     const int sh = range ? max(0, 32 - __clz(range) - kBinBits) : 0;  // (range >> sh) < BINS
-    if (!LONG && ITEMS >= 12 && whole) {
+    if (!LONG && ITEMS >= 24 && whole) {
         for_steps([&](uint32_t u, int) { atomicAdd(&sm.hist[(u - kmin) >> sh], 1); });
     } else {
         for_steps([&](uint32_t u, int) {
