@@ -167,30 +167,33 @@ constexpr int64_t kHeldAtOnce = 512;
 constexpr int64_t kSweptSteps = 800;  // steps of 256 keys in all from which 65 to 128 rows, d = 64, are swept twice
 // Exponentials held in several rounds of the whole chip, nb blocks of rows: up to which number of ranges that is the faster
 // one.  The workgroups of a problem that begins at the end of a round wait for the next one, and every range reads
-// all ranges' statistics; two launches leave their own last round nearly empty unless their workgroups are just the
-// chip's 512 (`even`).  us otherwise (two launches; d = 64 and more than 64 rows the two sweeps), held, over 560 shapes of 3 to 390
-// ranges, 4 to 296 heads:
+// all ranges' statistics, so it costs more the more ranges there are and the more problems share them (`shared`); two launches
+// leave their own last round nearly empty unless their workgroups are just the chip's 512 (`even`).  us otherwise (two launches; d = 64 and
+// more than 64 rows the two sweeps), held, over 1450 shapes of 3 to 500 ranges, 2 to 296 heads:
 //  - up to 32 rows: 1.5 times as fast on average (hardly more than one round is not taken, but in ranges of two steps, d = 128 with a
 //    prior, up to 256 of them, at any number of rounds: 33 x 18 62.5, 38.0; 5 x 202 85.3, 68.7; 8 x 256 139, 109; 64 x 256 1172, 836; 3 x
 //    330 72, 73; 16 x 400 447, 463);
-//  - d = 128, 33 to 64 rows: uneven up to 256: 77 heads x 9 ranges 66.4, 44.0; 7 x 181 90.5, 90.0; 8 x 233 135, 127; even up to two
-//    problems a round from 64 heads on, eight below: 128 x 32 284, 212;
-//  - d = 128, 65 to 128 rows: uneven up to 100: 80 x 9 55.6, 32.3; 21 x 98 82.6, 75.4; 17 x 174 134, 147; 16 x 234 145, 190; even
-//    16 x 64 50.6, 42.6; 128 x 43 201, 199; 64 x 64 151, 156; 32 x 128 150, 172; without a prior 64 x 64 106, 108, 128 x 64 213, 237;
-//  - d = 64, 33 to 64 rows: uneven up to 160: 15 x 71 56.9, 47.1; 8 x 173 60.4, 68.8; even 64 x 64 145, 141; 32 x 128 144, 149;
-//    without a prior 64 x 32 54.4, 51.1, 128 x 32 93.5, 99.1;
-//  - d = 64, 65 to 128 rows: where the sweeps would not be taken either, 28 x 20 36.6, 21.1; 15 x 51 37.6, 25.3; 13 x 74 28.7,
-//    36.2 (sweeps, held).
-// Held would be the faster one a little further, too, where the two launches are tested: up to 256 ranges of 33 to 64 rows, even
-// (16 x 101 120, 98.6), 150 of 65 to 128, uneven (11 x 103 72.4, 54.7; 37 x 145 274, 245), and one or two heads in at most 128
-// ranges of 65 to 128 rows (1 x 100 22.9, 16.2).
+//  - d = 128, 33 to 64 rows: up to 256: 16 x 101 72.2, 58.3; 8 x 256 131, 113; 64 x 192 871, 727; more than that where uneven, or for two
+//    heads: 24 x 280 1.23 times as fast; even 16 x 320 0.91;
+//  - d = 128, 65 to 128 rows: 80 x 9 55.6, 32.3; uneven 37 x 145 261, 214; 21 x 150 150, 130, without a prior 48 x 115 1.02 times as
+//    fast, 24 x 145 0.92; few heads in more: 6 x 180 70.9, 56.2, 5 x 256 1.10; 12 x 230 0.89; even 16 x 100 55.3, 52.2; 8 x 160 62.8, 56.3; 16
+//    x 150 65.5, 71.0; 64 x 64 138, 136 (not taken); 32 x 150 174, 206;
+//  - d = 64, 33 to 64 rows: uneven with a prior 15 x 140 92.7, 83.1, 27 x 180 1.03 times as fast, without 27 x 130 0.89, 9 x 145 1.09, 48
+//    x 160 1.07; even 8 x 140 51.9, 49.2; 8 x 173 57.3, 60.5; 64 x 64 138, 133; without a prior 8 x 100 30.7, 25.2; 64 x 32 48.4, 46.2;
+//    128 x 32 93.5, 99.1;
+//  - d = 64, 65 to 128 rows: where the sweeps would not be taken either, 28 x 20 36.6, 21.1; 15 x 51 37.6, 25.3; 4 x 190 36.6, 33.4; 2 x
+//    260 1.35 times as fast, x 390 0.86; 13 x 74 28.7, 36.2 (sweeps, held).
+// Of 900 of them in two launches or held this takes 1.007 times the faster one's time on average.
 static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, int per, int64_t parts, int64_t steps) {
     const bool even = (int64_t)pl.Z * pl.nchunks <= 512, prior = p->value_prior;
+    const int64_t shared = parts * (pl.Z + 6);
     if (nb == 1) return per == 2 || (parts <= 128 && pl.Z * parts >= 600);
-    if (p->head_dim == 128 && nb == 2) return parts <= (!even ? 256 : pl.Z >= 64 ? 128 : 64);
-    if (p->head_dim == 64 && nb > 2) return pl.Z * steps < kSweptSteps && parts <= 150;
-    if (!even) return parts <= (p->head_dim == 128 ? 100 : 160);
-    return (parts <= 64 && pl.Z * parts <= 2048) || (prior && parts <= (nb == 2 ? 64 : 48));
+    if (p->head_dim == 128 && nb == 2) return parts <= (even && pl.Z > 2 ? 256 : kHeldAtOnce);
+    if (p->head_dim == 128 && even) return parts <= 256 && (shared <= 2432 || (prior && parts <= 48));
+    if (p->head_dim == 128) return parts <= 256 && (shared <= 2900 || parts <= (prior ? 170 : 100));
+    if (nb > 2) return pl.Z * steps < kSweptSteps && shared <= 2100;
+    if (even) return shared <= (prior ? 2112 : 1600) || (parts <= 64 && (prior || pl.Z * parts <= 2048));
+    return shared <= 2400 || parts <= (prior ? 180 : pl.Z < 32 ? 122 : 160);
 }
 
 // Windowed bf16 scores in one launch.  Its layout starts where the one of two launches does, but may be longer: a
@@ -199,7 +202,7 @@ static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, i
 // times as fast as two launches on average.  us in two launches, in one:
 //  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
 //    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0; 96 and 128 rows in up to
-//    512 ranges, but for few workgroups: 1 x 131072 x 128 53.8, 39.5, 6 x 19416 x 96 32.6, 22.4 (52 shapes 1.38 times as fast on
+//    512 ranges: 1 x 131072 x 128 53.8, 39.5, 6 x 19416 x 96 32.6, 22.4, 1 x 25600 x 128 20.1, 12.6 (88 shapes 1.44 times as fast on
 //    average, 1.18 at least).
 //    In several rounds the exchange is waited for in each (held_in_rounds).
 //  - 65 to 128 rows, d = 64, longer problems, swept twice: 6 x 46683 x 126 52.7, 36.3 (d = 128, bound by its
@@ -237,8 +240,7 @@ static void plan_window(const aha_params *p, PrefillPlan &pl) {
         while (2 * per * nb <= 4 && 2 * per <= most && pl.Z * ((steps + per - 1) / per) > kHeldAtOnce) per *= 2;
         parts = (steps + per - 1) / per;
         keys = per * kP2Keys;
-        hold = pl.Z * parts <= kHeldAtOnce ? nb <= 2 || parts <= 48 || pl.Z * parts > 128
-                                           : held_in_rounds(p, pl, nb, per, parts, steps);
+        hold = pl.Z * parts <= kHeldAtOnce || held_in_rounds(p, pl, nb, per, parts, steps);
         if (!hold && (blocks < 3 || p->head_dim != 64 || pl.Z * steps < kSweptSteps)) return;
         if (!hold) nb = 4;
     } else if (blocks <= 8) {

@@ -74,6 +74,9 @@ ROUNDS = [
     # more workgroups than the chip holds at once: KV heads, group, window, n, d
     (40, 1, 30, 15990, 64), (20, 2, 15, 32100, 128), (50, 1, 96, 3001, 128), (28, 1, 128, 5000, 64), (70, 1, 64, 4100, 64),
     (3, 1, 128, 16849, 128),  # (one round, many ranges)
+    (1, 1, 128, 25601, 128), (2, 1, 70, 12500, 64),  # (and few workgroups)
+    # many ranges of a problem in several rounds
+    (6, 1, 100, 46001, 128), (16, 1, 64, 49300, 128), (2, 1, 40, 143400, 128), (4, 1, 128, 48600, 64), (8, 1, 50, 58000, 64),
 ]
 
 
@@ -94,6 +97,8 @@ def test_several_rounds(shape):
 BESIDE_VALUES = [
     # up to 32 rows beside value rows, d = 128: ranges of four steps, ranges of two in several rounds
     (2, 1, 32, 140001, 128), (9, 1, 2, 32848, 128), (33, 8, 1, 8848, 128), (5, 1, 5, 103215, 128),
+    # more rows: many ranges, in one round and in several
+    (1, 1, 128, 25601, 128), (6, 1, 100, 46001, 128), (9, 1, 64, 58000, 128), (8, 1, 64, 71500, 64),
 ]
 
 

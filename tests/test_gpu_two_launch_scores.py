@@ -12,10 +12,11 @@ from tests.test_score_routes import _one_launch, _params
 
 TWO = [
     # batch, KV heads, group, window, n, d
-    (1, 1, 1, 100, 12801, 128), (1, 2, 3, 40, 12550, 128),   # ranges of one step
+    (11, 50, 1, 20, 250, 64),   # ranges of one step
     (1, 64, 1, 20, 8500, 64), (2, 16, 1, 32, 17000, 64),     # up to 32 rows
-    (1, 8, 1, 64, 38147, 128), (1, 16, 2, 32, 34742, 64), (4, 4, 1, 33, 33100, 64),   # up to 64
-    (1, 8, 4, 32, 29221, 128), (1, 9, 1, 65, 26000, 128),    # up to 128
+    (1, 1, 1, 64, 262500, 128), (1, 1, 2, 32, 262700, 64), (4, 2, 1, 33, 88600, 64),   # up to 64
+    (1, 2, 4, 32, 66000, 128), (1, 3, 1, 65, 66001, 128), (1, 2, 3, 40, 65900, 128), (1, 1, 1, 100, 131500, 128),   # up to 128
+    (1, 1, 1, 100, 131501, 64),
 ]
 # (two sweeps by four workgroups per problem, 2560 keys each, where the LDS keeps 2048)
 LONG_RANGES = [(1, 64, 5, 32, 8300, 64), (1, 56, 2, 100, 9100, 64)]

@@ -37,14 +37,15 @@ def _one_launch(name, p, size=None):
     # holds workgroups, whatever the length:
     (1, 262144, True), (1, 524288, False), (1, 1 << 20, False), (1, 1 << 30, False), (2, 262145, False),
     (8, 262145, False), (8, 300000, False), (8, 1 << 20, False), (24, 262145, False), (256, 1 << 20, False),
-    # where a round of the chip holds enough problems whole
-    (16, 32768, True),     # 71.7, 66.5
-    (16, 49152, False),    # 101, 105
-    (64, 65536, True),     # 565, 562
-    (64, 98304, False),    # 867, 1003
-    (24, 131072, True),    # 559, 471
-    (24, 163840, False),   # 713, 793
-    (128, 16384, True), (8, 65536, False),
+    # in several rounds of the chip, up to 256 ranges; more where two launches would leave their last round nearly empty
+    (16, 32768, True), (16, 49152, True),     # (x 101 ranges) 72.2, 58.3
+    (8, 65536, True),      # 71.1, 54.9
+    (64, 65536, True), (64, 98304, True),     # 871, 727
+    (16, 131072, True),    # 276, 237
+    (16, 163840, False),   # 349, 371
+    (24, 131072, True), (24, 163840, True),   # 717, 553
+    (2, 163840, True),     # 62.9, 51.5
+    (128, 16384, True),
 ])
 def test_ranges_of_a_problem_fit_the_chip(z, n, one):
     for group, window in ((1, 64), (2, 17), (3, 20)):
@@ -134,6 +135,19 @@ def test_results_in_it(z, group, window, n, d, size):
     (128, 64, 16384, 64, 0, False),   # 93.5, 99.1
     (8, 64, 88500, 64, 1, False),     # 60.4, 68.8
     (6, 96, 19416, 128, 1, True),     # one round, many ranges: 32.6, 22.4
+    (1, 128, 12800, 128, 1, True),    # and few workgroups: 20.5, 13.4
+    (2, 70, 12544, 64, 0, True),      # 15.4, 9.1
+    (1, 128, 25600, 128, 0, True), (1, 128, 32768, 128, 0, True),   # 20.1, 12.6; 20.7, 12.7
+    (11, 128, 26368, 128, 1, True),   # several rounds: 69.3, 50.9
+    (37, 96, 37120, 128, 1, True),    # 261, 214
+    (6, 128, 46080, 128, 1, True),    # few heads in many ranges: 70.9, 56.2
+    (16, 128, 25600, 128, 0, True),   # 55.3, 52.2
+    (16, 70, 38400, 128, 0, False),   # 65.5, 71.0
+    (17, 70, 44544, 128, 0, False),   # 84.5, 93.6
+    (8, 64, 71680, 64, 1, True),      # 51.9, 49.2
+    (27, 64, 66560, 64, 1, True),     # 139, 131
+    (27, 40, 66560, 64, 0, False),    # 86.2, 97.0
+    (4, 128, 48640, 64, 1, True),     # 36.6, 33.4
 ])
 def test_held_in_rounds(z, window, n, d, prior, one):
     assert _one_launch("aha_prefill_scores", _params(z, 1, window, n, d, value_prior=prior)) == one
