@@ -25,35 +25,7 @@
 namespace aha {
 
 // ---------------------------------------------------------------- pass 1 --
-constexpr int kNoPrior = 0, kPriorFold = 1, kPriorOneStep = 2;  // value prior inside pass 1 (below)
-
-// gamma = edge-truncated mean of nu over the pool window for the keys [kbeg, kend) of problem
-// z (at most kPriorPiece), whose norms the workgroup's waves left in s_nu, written to `gamma`;
-// returns (in every thread) the largest gamma of the range.
-constexpr size_t kPriorSmem = (kPriorPiece + kPriorMaxHalo + 4) * sizeof(float);
-template <int D>
-__device__ __forceinline__ float pool_norms_in_lds(const ScoreGeom &g, int z, int kbeg, int kend,
-                                                   const PriorHalo<D> &halo, float *s_nu, float *gamma,
-                                                   int tid) {
-    const int half = (g.pool - 1) / 2, lo = max(0, kbeg - half);
-    float *s_max = s_nu + kPriorPiece + kPriorMaxHalo;
-    const float hn = halo.norm();
-    if (halo.valid && tid % PriorHalo<D>::CPR == 0) s_nu[halo.pos - lo] = hn;
-    __syncthreads();
-    float gmax = 0.f;
-    for (int j = kbeg + tid; j < kend; j += 256) {
-        const int a = max(0, j - half), e = min(g.n - 1, j + half);
-        float s = 0.f;
-        for (int t = a; t <= e; ++t) s += s_nu[t - lo];
-        const float gam = s / (float)(e - a + 1);
-        gamma[(int64_t)z * g.n + j] = gam;
-        gmax = fmaxf(gmax, gam);
-    }
-    gmax = wave_max(gmax);
-    if ((tid & 63) == 0) s_max[tid >> 6] = gmax;
-    __syncthreads();
-    return fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-}
+constexpr int kNoPrior = 0, kPriorFold = 1;  // value prior inside pass 1 (below)
 
 // The prior of a key range formed AFTER the main loop (see bf16_pass1_kernel): value rows of the keys [kbeg, kend) of problem z are streamed in a phase
 // of their own: nu = ||V||^2 of the range and its pooling halo into
@@ -97,14 +69,10 @@ __device__ __forceinline__ float value_prior_of_range(const ScoreGeom &g, int b,
 // PRIOR (windowed scores of up to four row blocks with the value prior, the sizes that score_window.hip
 // leaves): the workgroup also forms the prior of its key range and leaves the range's maximum in
 // gblockmax[z * nparts + part]: one launch less than a value-prior kernel of its own.
-//  - kPriorFold: the steps are too short to hide value rows under (the key prefetch would have half a
-//    step to arrive), and the kernel is bound by the key stream: the value rows are streamed
-//    in a phase of their own after the statistics (16K tokens x 128 heads x 64 rows: 183 us
-//    against 215 us interleaved).
-//  - ranges of one step (kPriorOneStep; problems of which every workgroup gets at most 256
-//    keys): the register buffer of the next key block is idle throughout, so the value rows
-//    and the pooling halo are requested in the set-up, right behind the keys, and their norms
-//    never leave LDS.  The kernel waits for memory once: 12 heads x 5003 x 120 rows 13.7 -> 11.6 us.
+// The steps are too short to hide value rows under (the key prefetch would have half a
+// step to arrive), and the kernel is bound by the key stream: the value rows are streamed
+// in a phase of their own after the statistics (16K tokens x 128 heads x 64 rows: 183 us
+// against 215 us interleaved).
 // ENT: the chunk's mean scaled logit under its own probabilities, E_c[t] = m + u / s, is
 // written to `partial_mean` beside the chunk's log2-sum-exp2; row_stats_merge_kernel turns the
 // chunks of a row into its entropy.
@@ -114,14 +82,12 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
                                                             float *partial_mean, float *gamma,
                                                             float *gblockmax) {
     using S = TileSmem<D, NB>;
-    constexpr bool kOneStep = PRIOR == kPriorOneStep;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __bf16 *sQ = (__bf16 *)smem;
     float *sLam = (float *)(smem + S::q_bytes);
     int *sPos = (int *)(sLam + S::ROWS);
     int *sBlk = sPos + 2 * S::ROWS;
     float4 *sRed = (float4 *)smem;  // reuses the query tile after the main loop
-    float *sNu = (float *)(smem + S::bytes);  // kOneStep: kPriorSmem bytes behind the tile
 
     // logical workgroup index -> (part, tile pair, problem)
     const int wg = logical_wg_index(total_wgs, n_qtiles > 1);
@@ -166,8 +132,6 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
         // this wave's key block of step i; past the last step: rows clamped to the range's end
         auto kb_of = [&](int i) { return i < nsteps ? k_at0 + i * kdir : key_end; };
         bf16x8 a0[kMB][D / 16], a1[kMB][D / 16];  // the next key block loads while one multiplies
-        PriorHalo<D> halo;
-        const __bf16 *vbase = (const __bf16 *)g.v + b * g.vs[0] + h * g.vs[1];
         {
             // (the thread index goes through an opaque move: the set-up's addresses are then
             // recomputed per tile instead of being kept across the main loop, where they
@@ -179,10 +143,6 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             const float lam_req = q_tile_scale<D, NB>(g, rm, rho0, tid_s);
             __builtin_amdgcn_sched_barrier(0);  // the key block is requested last
             load_a<D>(kbase, g.ks[2], kb_of(0), key_end, lane, a0);
-            if constexpr (kOneStep) {
-                load_a<D>(vbase, g.vs[2], kb_of(0), key_end, lane, a1);
-                halo.request(g, vbase, key_begin, key_end, tid_s);
-            }
             q_tile_meta<D, NB>(g, rm, rho0, tid_s, lam_req, sLam, sPos, sBlk);
             q_tile_commit<D, NB>(qt_regs, tid_s, sQ);
         }
@@ -236,23 +196,10 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             load_a<D>(kbase, g.ks[2], kb_next, key_end, lane, nx);
             blocks(a, kb, 0, NB);
         };
-        if constexpr (kOneStep) {
-            const int kb = kb_of(0);
-            blocks(a0, kb, 0, NB);
-            __builtin_amdgcn_sched_barrier(0);
-            float nu[kMB];
-            fragment_row_norms<D>(a1, nu);
-#pragma unroll
-            for (int mb = 0; mb < kMB; ++mb) {
-                const int row = kb + mb * 32 + lane;
-                if (lane < 32 && row < key_end) sNu[row - max(0, key_begin - (g.pool - 1) / 2)] = nu[mb];
-            }
-        } else {
-            for (int i = 0; i < nsteps; i += 2) {
-                step(a0, a1, kb_of(i), kb_of(i + 1));
-                if (i + 1 >= nsteps) break;
-                step(a1, a0, kb_of(i + 1), kb_of(i + 2));
-            }
+        for (int i = 0; i < nsteps; i += 2) {
+            step(a0, a1, kb_of(i), kb_of(i + 1));
+            if (i + 1 >= nsteps) break;
+            step(a1, a0, kb_of(i + 1), kb_of(i + 2));
         }
         // fold the two half-waves (same query column, different key rows); a statistic
         // (m, s, u) re-referenced to a maximum M >= m is (M, s f, (u + (m - M) s) f), f = 2^(m - M)
@@ -298,11 +245,7 @@ __global__ __launch_bounds__(256, 2) void bf16_pass1_kernel(ScoreGeom g, int n_q
             my_partial[tid] = M + log2f(sum);  // -inf for a row that saw no key
             if (ENT) partial_mean[my_off + tid] = sum > 0.f ? mref + mom / sum : 0.f;
         }
-        if constexpr (kOneStep) {
-            // (every wave's norms were written before the barriers of the reduction above)
-            const float gm = pool_norms_in_lds<D>(g, z, key_begin, key_end, halo, sNu, gamma, tid);
-            if (tid == 0) gblockmax[z * nparts + part] = gm;
-        } else if constexpr (PRIOR == kPriorFold) {
+        if constexpr (PRIOR == kPriorFold) {
             __syncthreads();  // the reduction buffer is done with
             const float gm = value_prior_of_range(g, b, h, z, key_begin, key_end, (float *)smem,
                                                   gamma, tid);
@@ -501,27 +444,23 @@ template <int D, int NB>
 static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, float *scores,
                            hipStream_t st, hipEvent_t mid, bool have_lse, bool fold_prior) {
     using S = TileSmem<D, NB>;
-    static_assert(2 * (S::bytes + kPriorSmem) <= 160 * 1024, "two workgroups per CU");
+    static_assert(2 * S::bytes <= 160 * 1024, "two workgroups per CU");
     static_assert(S::bytes >= kPriorTailSmem, "the prior's own phase borrows the query tile's LDS");
     char *w = (char *)ws;
     float *partial = (float *)(w + pl.off_partial);
     float *gamma = (float *)(w + pl.off_gamma);
     float *gbm = (float *)(w + pl.off_gblockmax);
-    // (the prior is formed here for tiles of up to four blocks, in ranges of one step for four: the
-    // other sizes are score_window.hip's)
-    constexpr int kFold = NB <= 4 ? kPriorFold : kNoPrior, kOneStep = NB == 4 ? kPriorOneStep : kFold;
+    constexpr int kFold = NB <= 4 ? kPriorFold : kNoPrior;  // (larger tiles: value_prior.hip)
     static DeviceOnce once;
     const hipError_t ea = device_once(once, [] {
-        const void *kernels[7] = {(const void *)bf16_pass1_kernel<D, NB, false>,
+        const void *kernels[6] = {(const void *)bf16_pass1_kernel<D, NB, false>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, false, kFold>,
-                                  (const void *)bf16_pass1_kernel<D, NB, false, false, kOneStep>,
                                   (const void *)bf16_pass1_kernel<D, NB, true>,
                                   (const void *)bf16_pass1_kernel<D, NB, false, true>,
                                   (const void *)bf16_pass2_kernel<D, NB>,
                                   (const void *)bf16_pass2_kernel<D, NB, true>};
         for (const void *kf : kernels) {
-            const hipError_t e = hipFuncSetAttribute(
-                kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(S::bytes + kPriorSmem));
+            const hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::bytes);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -537,13 +476,9 @@ static hipError_t launch_t(const ScoreGeom &g, const PrefillPlan &pl, void *ws, 
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, true>), xcd_grid(wgs1), dim3(256),
                                S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1, partial,
                                (float *)nullptr, (float *)nullptr, (float *)nullptr);
-        else if (fold_prior && pl.nchunks == (g.n + kWgKeys - 1) / kWgKeys)  // ranges of one step
-            hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kOneStep>), xcd_grid(wgs1),
-                               dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
-                               partial, (float *)nullptr, gamma, gbm);
         else if (fold_prior)
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false, false, kFold>), xcd_grid(wgs1),
-                               dim3(256), S::bytes + kPriorSmem, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
+                               dim3(256), S::bytes, st, g, pl.n_qtiles, pl.nchunks, (int)wgs1,
                                partial, (float *)nullptr, gamma, gbm);
         else
             hipLaunchKernelGGL((bf16_pass1_kernel<D, NB, false>), xcd_grid(wgs1), dim3(256),

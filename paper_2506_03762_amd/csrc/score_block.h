@@ -144,7 +144,7 @@ __device__ __forceinline__ void colsum_update(const f32x16 (&acc)[kMB], float la
 
 // Value prior (Sec. 4.3).  The value rows of the keys a wave multiplies in a step pass through the
 // register buffer that the next key block does not need yet.  Loaded with the addressing of the key
-// fragments (two tiles of the two-sweep kernel, ranges of one step in two launches), a lane holds one half (the
+// fragments (two tiles of the two-sweep kernel), a lane holds one half (the
 // channels of its half-wave) of a value row per group of 32.
 
 // nu = ||V_row||^2 of those rows: squares summed in-lane, one exchange between the half-waves.
