@@ -309,18 +309,32 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
 
 // fp32 scores in one launch (score_hold_f32.hip), where its workgroups are on the chip at once.  Score stage, us in two launches, in one
 // (88 shapes of 8 to 192 rows, 1 to 96 heads, 200 to 5000 keys: 1.25 times as fast on average):
-//  - more than 32 rows: in ranges of 32 keys, up to 64 of them (2 heads x 272 keys x 64 rows, d = 128 15.7, 13.5; 8 x 4
+//  - more than 32 rows: in ranges of 32 keys, up to 64 of them (4 heads x 1070 keys x 64 rows, d = 64 14.9, 10.5; 8 x 4
 //    x 32 of 315, d = 64 17.4, 11.9; 1 x 1896 x 128, d = 64 17.5, 16.4, in ranges of 128 keys 19.5), else of 128 (2 x 4131 x 128, d = 64
 //    23.4, 21.6, of 32 keys 25.7; 8 x 3048 x 64, d = 128 37.8, 20.2; 32 x 358 x 119 27.6, 26.4);
-//  - up to 32 rows: in ranges of 128 keys (8 x 1224 x 8, d = 64 11.3, 9.2; 32 x 264 x 8, d = 128 15.3, 15.0; 4 x 2968 x 32, d = 64 18.7,
-//    9.6).  Below some 60 thousand pairs of row and key two launches take as long or less (8 x 329 x 8, d = 64 9.9, 11.2), but the
-//    host enqueues a launch less: the step with selection and compaction 19.5, 17.6, 2 x 512 x 32 18.8, 17.1; not with d = 128
-//    and a prior (8 x 306 x 16 19.2, 20.5; without 1 x 363 x 32 19.3, 16.0).
+//  - up to 32 rows: in ranges of 128 keys (8 x 1224 x 8, d = 64 11.5, 10.8; 4 x 2968 x 32, d = 64 20.3, 11.1; 2 x 512 x 32 10.1, 10.3).
+// Two launches give each row a workgroup, one launch each 128 keys all rows: with few rows, fewer of them than CUs and short prompts
+// two take less time, unless on the matrix core (of 1700 shapes 470 such ones 1.12 times as long in one launch, the others 0.8; 8 x
+// 1541 x 24, d = 128, 63 wide, matrix core, 0.7): 8 x 329 x 8, d = 64 9.1, 10.5; 4 x 500 x 16 9.5, 10.4; 1 x 300 x 8 9.0, 9.9; d = 128 with a
+// prior 4 x 700 x 32 13.3, 13.9; pool widths above 17 (each range squares the halo's rows) 2 x 842 x 32, d = 64, 63 wide 1.05 times
+// as long, 4 x 1273 x 8 1.13.
+// But up to pool widths of 17, unless d = 128 with a prior, the host's launch is longer than the difference: us of the step with selection and
+// compaction, 8 x 329 x 8 17.4, 16.9, 1 x 300 x 8 17.3, 15.6; in a captured graph 14.9, 16.9 and 14.3, 15.7.  So there
+// captured calls take two launches.  (What is left of the difference in graphs comes from the words that a captured call takes
+// away, exchange.h: 0.7 us.)
 static void plan_hold_f32(const aha_params *p, PrefillPlan &pl) {
     pl.hold32_parts = 0;
     const int64_t R = (int64_t)(p->n_q_heads / p->n_kv_heads) * p->window, blocks = (R + 31) / 32;
     if (p->dtype != AHA_F32 || blocks > kHoldF32Blocks) return;
-    if (blocks == 1 && p->head_dim == 128 && p->value_prior && (double)pl.Z * R * p->seq_len < 6e4) return;
+    const bool d64 = p->head_dim == 64, prior = p->value_prior, wide = prior && p->pool_kernel > 17;
+    // below how many keys of few problems and rows two launches take less time
+    int64_t least = d64 ? (prior ? 1500 - 35 * R : 0) : prior ? std::max<int64_t>(1000, 2000 - 35 * R) : 1350 - 35 * R;
+    if (wide) least = 8 * std::max<int64_t>(least, 800) / 5;
+    const bool few = pl.Z * R < (d64 || R > 8 ? 256 : 300) && ((int64_t)pl.Z * p->seq_len < 14000 || (R < 4 && prior));
+    const bool longer = !pl.f32_mfma && ((few && p->seq_len < least && R <= (prior && (!d64 || wide) ? 64 : 32)) ||
+                                         (!d64 && prior && blocks == 1 && (double)pl.Z * R * p->seq_len < 6e4));
+    if (longer && (wide || (!d64 && prior))) return;
+    pl.hold32_eager = longer;
     int64_t parts, keys = blocks == 1 ? 128 : 32;
     for (;; keys = 128) {
         parts = ((int64_t)p->seq_len + keys - 1) / keys;
@@ -672,13 +686,15 @@ static uint64_t next_tag() {
 }
 static thread_local int32_t g_looks = kLooks;
 
-// Captured calls are replayed with the same tag (a stream that does not say is taken for capturing).
-static ExchangeCall exchange_call(hipStream_t st, int looks) {
+// `unknown`: for a stream that does not say.
+static bool captured(hipStream_t st, bool unknown) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     const hipError_t e = hipStreamIsCapturing(st, &status);
     if (e != hipSuccess) (void)hipGetLastError();
-    return {next_tag(), looks, e != hipSuccess || status != hipStreamCaptureStatusNone};
+    return e == hipSuccess ? status != hipStreamCaptureStatusNone : unknown;
 }
+// Captured calls are replayed with the same tag.
+static ExchangeCall exchange_call(hipStream_t st, int looks) { return {next_tag(), looks, captured(st, true)}; }
 
 // Looks of a call of `workgroups` in all, of which the chip holds `resident` at once and each multiplies nb blocks of
 // 32 rows with each of `steps` key blocks per wave for its part.  All of them at once: a few times what a part takes (set-up
@@ -746,7 +762,7 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
             return rc;
         return hip_result(stage(3, st), "stage event");
     }
-    if (pl.hold32_parts && !with_lse && !rows && workspace_bytes >= pl.hold32_bytes) {
+    if (pl.hold32_parts && !with_lse && !rows && workspace_bytes >= pl.hold32_bytes && !(pl.hold32_eager && captured(st, false))) {
         const int looks = patience((int64_t)pl.Z * pl.hold32_parts, 256, 1, 2 * ((g.R + 31) / 32));
         if ((rc = hip_result(stage(1, st), "stage event")) ||
             (rc = hip_result(launch_score_hold_f32(g, pl, workspace, exchange_call(st, looks), scores, st), "windowed score kernel")) ||

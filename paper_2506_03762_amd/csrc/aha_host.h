@@ -72,6 +72,7 @@ struct PrefillPlan {
     // fp32 scores in one launch (hold32_parts > 0): ranges per problem; where the rows' pairs, the ranges' largest priors and
     // the counts live
     int hold32_parts, hold32_keys;
+    bool hold32_eager;  // (unless the call is captured: two launches take less time, but cost the host more)
     size_t off_h32stats, off_h32max, off_h32words, hold32_bytes;
     size_t off_rowL, off_partial, off_partial_mean, off_gamma, off_gblockmax;
     size_t bytes;  // of the layout of two launches

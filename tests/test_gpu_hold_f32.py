@@ -21,12 +21,24 @@ SHAPES = [
     (128, 1, 32, 512, 128, True), (129, 1, 32, 512, 128, False),   # two workgroups per CU
     (128, 3, 32, 256, 128, True), (128, 3, 32, 257, 128, False),   # one
     (8, 1, 16, 306, 128, False), (8, 1, 16, 306, 64, True),        # two launches 19.2 us, one 20.5
+    # few problems and rows, short prompts, d = 128 with a prior (score stage in two launches, one)
+    (4, 1, 32, 700, 128, False), (8, 1, 32, 700, 128, True),       # 13.3, 13.9
+    (2, 1, 64, 900, 128, False), (2, 1, 64, 1400, 128, True), (1, 1, 8, 1500, 128, False), (4, 1, 32, 1100, 128, True),
 ])
 def test_route(z, group, window, n, d, one):
     p = _params(z, group, window, n, d, dtype=B.AHA_F32)
     assert _one_launch("aha_prefill_scores", p) == one
     assert not _one_launch("aha_prefill_scores_rows", p)
     assert not _one_launch("aha_prefill_scores_lse", p)
+
+
+@pytest.mark.parametrize("z,window,n,pool,one", [
+    # each range squares the rows of its pools' halo (step in two launches, one)
+    (2, 32, 512, 17, True), (2, 32, 512, 63, False),    # 18.5, 19.1
+    (4, 8, 1300, 63, False), (2, 32, 1400, 255, True), (8, 128, 315, 255, True),
+])
+def test_route_of_wide_pools(z, window, n, pool, one):
+    assert _one_launch("aha_prefill_scores", _params(z, 1, window, n, 64, dtype=B.AHA_F32, pool_kernel=pool)) == one
 
 
 def test_workspace_of_two_launches_is_served():
@@ -112,3 +124,26 @@ def test_a_row_that_is_not_finite(shape, bad):
     B.aha_prefill_scores(p, q, k, v, scores, ws)
     assert not torch.isfinite(scores[..., :at + 1]).any()
     assert scores[..., at + 1:].equal(want[..., at + 1:])
+
+
+@pytest.mark.gpu
+def test_captured_where_two_launches_are_shorter():
+    """Few rows of a short prompt: one launch, two in a graph (those of chosen rows)."""
+    import torch
+    p, q, k, v, ws, scores = _random((1, 4, 1, 16, 500, 128))
+    p.value_prior = 0
+    rows = torch.arange(p.seq_len - p.window, p.seq_len, dtype=torch.int32, device="cuda").expand(1, 4, p.window).contiguous()
+    chosen, eager = torch.empty_like(scores), torch.empty_like(scores)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.aha_prefill_scores(p, q, k, v, scores, ws)
+    for s in ((q.clone(), k.clone()), (q.flip(2), k.roll(5, 2)), (q.clone(), k.clone())):
+        q.copy_(s[0]), k.copy_(s[1])
+        B.aha_prefill_scores_rows(p, q, k, v, rows, chosen, ws)
+        B.aha_prefill_scores(p, q, k, v, eager, ws)
+        scores.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert scores.equal(chosen) and not eager.equal(chosen)
+        # (what fp32 scores are held to)
+        assert ((eager - scores).abs() <= 1e-5 * scores).all()
