@@ -200,7 +200,7 @@ static bool held_in_rounds(const aha_params *p, const PrefillPlan &pl, int nb, i
 // call whose workspace does not hold it takes two launches.  Where, and which kernel, follows from the times of the
 // score stage both ways over 400 shapes (1 to 512 rows, 1 to 256 KV heads, 400 to 65536 keys, d = 64 and 128), 1.30
 // times as fast as two launches on average.  us in two launches, in one:
-//  - up to 128 rows, logits held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
+//  - up to 128 rows, exponentials held, where the ranges fit the chip at once (two workgroups per CU): 32 heads x
 //    4113 keys x 32 rows 33.6, 25.6; 16 x 4823 x 63 26.2, 19.2; 2 x 631 x 63 (d = 64) 13.7, 10.0; 96 and 128 rows in up to
 //    512 ranges: 1 x 131072 x 128 53.8, 39.5, 6 x 19416 x 96 32.6, 22.4, 1 x 25600 x 128 20.1, 12.6 (88 shapes 1.44 times as fast on
 //    average, 1.18 at least).

@@ -61,7 +61,7 @@ struct PrefillPlan {
     bool f32_mfma;   // fp32 scores on the matrix core (pass 1 in nchunks key ranges)
     bool can_fold;   // windowed bf16 scores in two launches: pass 1 can form the value prior per key chunk
     // windowed bf16 scores in one launch (win_nb > 0): row blocks of a query tile, the tiles of a workgroup,
-    // whether their logits are held; ranges per problem and their keys; where the ranges' statistics,
+    // whether their exponentials are held; ranges per problem and their keys; where the ranges' statistics,
     // prior maxima and counts (exchange.h) and the value norms live
     int win_nb, win_tiles, win_parts, win_keys;
     bool win_hold, win_share;  // (share: by the kernel whose waves share the keys)

@@ -454,7 +454,7 @@ __global__ __launch_bounds__(512, 2) void window_share_kernel(ScoreGeom g, int n
             __syncthreads();
             const int missing = *sMissing;
             if (missing == INT32_MAX && part == own) break;
-        // somebody is not there: its norms are formed here (and no more waiting); in the end the own
+            // somebody is not there: its norms are formed here (and no more waiting); in the end the own
             // ones again
             part = missing != INT32_MAX ? missing ^ own : own;
             looks = 0;

@@ -41,14 +41,14 @@ struct HoldSmem {
     static_assert(off_red / NT % 16 == 0, "a tile's rows are read and written 16 bytes at a time");
 };
 
-// STEPS: 256-key steps of a workgroup's range, all of whose logits are held: NB * STEPS <= 4.
+// STEPS: 256-key steps of a workgroup's range, all of whose exponentials are held: NB * STEPS <= 4.
 // NT = 2: two tiles of rows, eight waves; waves w and w + 4 take the same keys, one tile each.
 template <int D, int NB, int NT, int STEPS, int PRIOR>
 __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, int nparts, Exchange x, u32x4 *stats,
                                                                   u32x4 *maxima, float *scores) {
     using S = TileSmem<D, NB>;
     using H = HoldSmem<D, NB, NT, STEPS * kWgKeys, PRIOR != 0>;
-    static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "logits in registers");
+    static_assert(NB * STEPS <= 4 && (NT == 1 || STEPS == 1), "exponentials in registers");
     constexpr int THREADS = 256 * NT, WAVES = 4 * NT, VM = NT == 2 ? 1 : kMB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wave = uniform((int)threadIdx.x >> 6), tile = NT == 2 ? wave >> 2 : 0, kw = wave & 3;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             const int kb = kb_of(st);
-            if constexpr (PRIOR) {  // (first: the value rows' registers are then free for the logits)
+            if constexpr (PRIOR) {  // (first: the value rows' registers are then free for the products)
                 int row;
                 const float nu = loaded_row_norm<D, VM>(w, lane, row);
                 row += kb + (NT == 2 ? tile * 32 : 0);
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
         missing = uniform(missing);
         if (missing == INT32_MAX && part == own) break;
         // somebody is not there: done here (and no more waiting); in the end the own part again, whose
-        // logits the accumulators have to hold
+        // exponentials the accumulators have to hold
         part = missing != INT32_MAX ? missing ^ own : own;
         x.looks = 0;
         __syncthreads();
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256 * NT, 2) void window_hold_kernel(ScoreGeom g, i
 }
 
 // ---- the logits formed twice --------------------------------------------------------------------
-// window_stream_kernel: more rows than whose logits a wave can hold, or longer ranges.  A workgroup of
+// window_stream_kernel: more rows than whose exponentials a wave can hold, or longer ranges.  A workgroup of
 // eight waves owns a CU and a range of keys; the first sweep over the range leaves the rows' statistics, the
 // second, from the last step to the first, starts on keys that are in the caches still and sums columns.
 // NT = 1: one tile of up to 256 rows, the waves take 64 keys each.  NT = 2: two tiles, of up to 512 rows;

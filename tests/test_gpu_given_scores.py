@@ -66,7 +66,7 @@ def test_scores_and_missing_parts(shape, prior):
 
 @pytest.mark.parametrize("shape", [(1, 4, 2, 32, 3000, 128), (1, 3, 8, 32, 900, 128), (4, 128, 1, 8, 2305, 64)])
 def test_graph_replays(shape):
-    """A replay reuses the call's tag: the announcements of the one before must be gone."""
+    """A replay reuses the call's tag: the words of the one before must be gone."""
     import torch
     w, opts = _case(shape)
     sets = [tuple(H.to_device(a, w.dtype) for a in synth.make_prefill(w, layer=i)) for i in range(2)]

@@ -72,7 +72,7 @@ def test_token_major(shape):
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[3], SHAPES[4], SHAPES[6]])
 def test_graph_replays(shape):
-    """A replay reuses the call's tag: both kinds of announcements of the one before must be gone."""
+    """A replay reuses the call's tag: both kinds of words of the one before must be gone."""
     import torch
     p, q, k, v = _random(*shape)
     p = p.with_strides(q, k, v)

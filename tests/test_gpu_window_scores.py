@@ -60,7 +60,7 @@ def test_scores_and_missing_parts(shape, prior):
 @pytest.mark.parametrize("shape", [(1, 4, 2, 32, 3000, 128), (1, 3, 8, 32, 900, 128), (1, 2, 8, 64, 2100, 64),
                                    (2, 16, 3, 43, 2100, 128)])
 def test_graph_replays(shape):
-    """A replay reuses the call's tag: the announcements of the one before must be gone."""
+    """A replay reuses the call's tag: the words of the one before must be gone."""
     import torch
     w, opts = _workload(*shape), Opts()
     sets = [_on_gpu(w, opts, synth.make_prefill(w, layer=i)) for i in range(3)]
