@@ -314,7 +314,7 @@ static void plan_given(const aha_params *p, PrefillPlan &pl) {
 //    23.4, 21.6, of 32 keys 25.7; 8 x 3048 x 64, d = 128 37.8, 20.2; 32 x 358 x 119 27.6, 26.4);
 //  - up to 32 rows: in ranges of 128 keys (8 x 1224 x 8, d = 64 11.5, 10.8; 4 x 2968 x 32, d = 64 20.3, 11.1; 2 x 512 x 32 10.1, 10.3).
 // Two launches give each row a workgroup, one launch each 128 keys all rows: with few rows, fewer of them than CUs and short prompts
-// two take less time, unless on the matrix core (of 1700 shapes 470 such ones 1.12 times as long in one launch, the others 0.8; 8 x
+// two take less time, unless on the matrix core (of 1725 shapes 584 such ones 1.11 times as long in one launch, the others 0.79; 8 x
 // 1541 x 24, d = 128, 63 wide, matrix core, 0.7): 8 x 329 x 8, d = 64 9.1, 10.5; 4 x 500 x 16 9.5, 10.4; 1 x 300 x 8 9.0, 9.9; d = 128 with a
 // prior 4 x 700 x 32 13.3, 13.9; pool widths above 17 (each range squares the halo's rows) 2 x 842 x 32, d = 64, 63 wide 1.05 times
 // as long, 4 x 1273 x 8 1.13.
