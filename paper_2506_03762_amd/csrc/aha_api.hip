@@ -693,8 +693,27 @@ static bool captured(hipStream_t st, bool unknown) {
     if (e != hipSuccess) (void)hipGetLastError();
     return e == hipSuccess ? status != hipStreamCaptureStatusNone : unknown;
 }
-// Captured calls are replayed with the same tag.
-static ExchangeCall exchange_call(hipStream_t st, int looks) { return {next_tag(), looks, captured(st, true)}; }
+__global__ __launch_bounds__(256) void no_words_kernel(uint4 *words, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) words[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+// A call of Z problems and `workgroups` in all, of which the chip holds `resident` at once, that exchanges words in the workspace's first
+// `bytes`.  Captured calls are replayed with the same tag, and no word may outlive a replay.  A problem's last workgroup takes its
+// words away, which it finds out by a count that all wait for at their end, and does alone: a launch that does it in front is shorter
+// from some 6000 words on and in several rounds of the chip.  us of the score stage eager, replayed either way: 2 x 512 x 32, d = 64 8.5, 8.9,
+// 10.5; 32 x 4096 x 64 18.9, 19.9, 21.1; 4 x 19793 x 224, d = 64, 5000 words 27.6, 30.3, 30.3; 1 x 131072 x 64 26.8, 32.1, 29.0; 1 x 60757 x
+// 448, d = 64, 30000 words 37.7, 48.1, 40.2; 5 x 107065 x 48, d = 64, two rounds 37.8, 45.4, 40.4; 128 x 16384 x 64 203, 209, 207.
+static hipError_t exchange_call(hipStream_t st, int looks, int64_t Z, int64_t workgroups, int64_t resident, void *workspace, size_t bytes,
+                                ExchangeCall &call) {
+    call = {0, looks, false};
+    if (bytes == 0) return hipSuccess;  // (nothing to exchange)
+    call.tag = next_tag();
+    call.replayed = captured(st, true);
+    const int64_t words = (int64_t)(bytes / 16);
+    if (!call.replayed || (workgroups <= resident && words <= 6000 * Z)) return hipSuccess;
+    call.replayed = false;
+    hipLaunchKernelGGL(no_words_kernel, dim3((unsigned)std::min<int64_t>((words + 1023) / 1024, 512)), dim3(256), 0, st, (uint4 *)workspace, words);
+    return hipGetLastError();
+}
 
 // Looks of a call of `workgroups` in all, of which the chip holds `resident` at once and each multiplies nb blocks of
 // 32 rows with each of `steps` key blocks per wave for its part.  All of them at once: a few times what a part takes (set-up
@@ -752,11 +771,15 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     if ((rc = hip_result(stage(0, st), "stage event"))) return rc;
     if (with_lse ? pl.given_nb && workspace_bytes >= pl.given_bytes
                  : pl.win_nb && !rows && workspace_bytes >= pl.win_bytes) {
-        if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, exchange_call(st, given_patience(pl)), lse, scores, st)
-                                      : pl.win_share
-                                          ? launch_score_share(g, pl, workspace, exchange_call(st, window_patience(pl)), scores, st)
-                                          : launch_score_window(g, pl, workspace, exchange_call(st, window_patience(pl)), scores, st),
+        ExchangeCall call;
+        const hipError_t e = with_lse ? exchange_call(st, given_patience(pl), pl.Z, (int64_t)pl.Z * pl.given_parts, pl.given_nb <= 4 ? 512 : 256,
+                                                      workspace, pl.off_gwords, call)
+                                      : exchange_call(st, window_patience(pl), pl.Z, (int64_t)pl.Z * pl.win_parts,
+                                                      pl.win_hold && pl.win_tiles == 1 ? kHeldAtOnce : 256, workspace, pl.off_wwords, call);
+        if ((rc = hip_result(e, "windowed score kernel")) || (rc = hip_result(stage(1, st), "stage event")) ||
+            (rc = hip_result(with_lse ? launch_score_given(g, pl, workspace, call, lse, scores, st)
+                                      : pl.win_share ? launch_score_share(g, pl, workspace, call, scores, st)
+                                                     : launch_score_window(g, pl, workspace, call, scores, st),
                              "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;
@@ -764,8 +787,10 @@ static int32_t prefill_scores_impl(const aha_params *p, const void *q, const voi
     }
     if (pl.hold32_parts && !with_lse && !rows && workspace_bytes >= pl.hold32_bytes && !(pl.hold32_eager && captured(st, false))) {
         const int looks = patience((int64_t)pl.Z * pl.hold32_parts, 256, 1, 2 * ((g.R + 31) / 32));
-        if ((rc = hip_result(stage(1, st), "stage event")) ||
-            (rc = hip_result(launch_score_hold_f32(g, pl, workspace, exchange_call(st, looks), scores, st), "windowed score kernel")) ||
+        ExchangeCall call;
+        const hipError_t e = exchange_call(st, looks, pl.Z, 1, 1, workspace, pl.off_h32words, call);  // (all at once)
+        if ((rc = hip_result(e, "windowed score kernel")) || (rc = hip_result(stage(1, st), "stage event")) ||
+            (rc = hip_result(launch_score_hold_f32(g, pl, workspace, call, scores, st), "windowed score kernel")) ||
             (rc = hip_result(stage(2, st), "stage event")))
             return rc;
         return hip_result(stage(3, st), "stage event");

@@ -83,7 +83,7 @@ constexpr int kExchangeBytes = 32;  // per problem: the count of an exchange ins
 struct ExchangeCall {
     uint64_t tag;   // a number that no other call uses, its low 20 bits zero
     int looks;      // at the other workgroups' parts before missing ones are done in place
-    bool replayed;  // captured into a graph
+    bool replayed;  // captured into a graph, and nothing takes its words away in front
 };
 constexpr int kVTileRows = 256;   // rows per value-prior workgroup
 constexpr int kP2Keys = 256;      // keys per pass-2 workgroup (4 waves x 64)

@@ -15,12 +15,12 @@
 // (3 us) in front: whatever it holds on entry is not this tag.  A captured graph replays a call with
 // its tag, and other work may have written to any part of the workspace since, so nothing that lies there can tell two replays
 // apart: no word may outlive a replay.  The workgroup that is the last of its problem to have seen all parts takes
-// the words away; only captured calls do that (the host asks the stream).  It is found by a
-// counter that starts itself: its upper bits are the call's number, and an arrival that finds other
-// bits there sets them.  us of the score stage, eager and replayed: 32 x 4096 x 64 20.4, 21.1; 8 x 16384 x 512 46.2, 47.4; 1 x 131072 x
-// 64, 8192 words 28.0, 33.2.  (Words told apart by a number in the workspace that each call moved on cost
-// a load per workgroup instead, 20.3, 46.8 and 30.6 either way, and were taken for the next replay's once other work
-// had put that number back.)
+// the words away, or, where these are many, a launch in front does (exchange_call in aha_api.hip); only captured calls do that (the host
+// asks the stream).  The last workgroup is found by a counter that starts itself: its upper bits are the call's number, and
+// an arrival that finds other bits there sets them.  us of the score stage, eager and replayed: 32 x 4096 x 64 20.4, 21.1; 8 x 16384 x
+// 512 46.2, 47.4.  (Words told apart by a number in the workspace that each call moved on cost a load per workgroup instead, 20.3
+// and 46.8 either way, and were taken for the next replay's once other work had put that number back.  Each workgroup its own part's
+// words, told by a second count at its end: 1 x 60757 x 448 48.1 -> 42.6, 40.2 with the launch, but 1 x 131072 x 64 32.1 -> 38.0.)
 //
 // Nobody depends on workgroups that may not be running: after `looks` looks at the others' parts a
 // workgroup does missing parts itself and leaves them too (a part's result is the same bits whoever
@@ -39,7 +39,7 @@ struct Exchange {
     uint64_t *counts;  // [problem][kExchangeBytes / 8], a count for each
     uint64_t tag;      // of this call; the low kCountBits are zero, the rest is not
     int looks;         // at the others' parts before missing ones are done here
-    bool replayed;     // the call is captured: its words are taken away
+    bool replayed;     // the call is captured, and nothing takes its words away in front
     __device__ __forceinline__ uint64_t *count(int z) const { return counts + (int64_t)z * (kExchangeBytes / 8); }
 };
 constexpr int kCountBits = 20;  // parts of a problem: fewer than 2^20

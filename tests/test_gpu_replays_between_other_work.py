@@ -12,6 +12,9 @@ SHAPES = {
     "share": (1, 8, 4, 64, 6000, 128), "share_two_tiles": (1, 2, 8, 64, 2100, 64), "share_workspace": (2, 64, 8, 64, 1300, 128),
     "given": (1, 4, 2, 32, 3000, 128), "given_large_tile": (1, 32, 8, 32, 2300, 128),
     "fp32": (1, 2, 2, 32, 512, 64), "fp32_short_ranges": (2, 3, 3, 21, 700, 128),
+    # more words to a problem than its last workgroup takes away
+    "held_many_words": (1, 1, 1, 64, 100000, 128), "stream_many_words": (2, 1, 3, 128, 17000, 64), "share_many_words": (1, 1, 7, 64, 20000, 64),
+    "fp32_many_words": (1, 2, 2, 64, 6000, 64),
 }
 
 
